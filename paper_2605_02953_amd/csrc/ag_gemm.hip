@@ -24,6 +24,10 @@ struct AgGemmParams {
   int32_t* status;
   int32_t* schedule;   // or null
   int timing;          // schedule records hold time stamps instead
+  const float* a_scales;   // fp8: one per shard, or null
+  const float* b_scales;   // fp8: one per output column, or null
+  int32_t* epoch_word;     // fp8, if set: the call's epoch is 1 + this word, which the last work-group to finish advances
+  int32_t* finished;       // ... counting the work-groups that are done
   int m_per_rank, m, n, k, world, rank, nnodes;
   int32_t epoch;
   int num_producers, teams;
@@ -32,13 +36,25 @@ struct AgGemmParams {
   TileOrder tiling;
 };
 
+// Scales of an fp8 tile: one per shard (rows), one per column.
+struct ShardScales {
+  const AgGemmParams& p;
+  int m0, n0;
+  __device__ __forceinline__ float row(int r) const { return p.a_scales ? p.a_scales[min(m0 + r, p.m - 1) / p.m_per_rank] : 1.f; }
+  __device__ __forceinline__ f32x4_t cols(int c) const {   // n is a multiple of 8: the four columns are inside or none is
+    if (!p.b_scales || n0 + c >= p.n) return f32x4_t{1.f, 1.f, 1.f, 1.f};
+    const float* s = p.b_scales + n0 + c;
+    return f32x4_t{s[0], s[1], s[2], s[3]};
+  }
+};
+
 template <class T>
-__global__ __launch_bounds__(T::THREADS) void ag_gemm_kernel(const AgGemmParams p) {
-  extern __shared__ __attribute__((aligned(1024))) char lds[];
+__device__ __forceinline__ void ag_gemm_work_group(const AgGemmParams& p, const int32_t epoch, char* lds) {
+  constexpr int kElement = T::F8 ? 1 : 2;
   if ((int)blockIdx.x < p.num_producers) {
-    const size_t shard_bytes = (size_t)p.m_per_rank * p.k * 2;
+    const size_t shard_bytes = (size_t)p.m_per_rank * p.k * kElement;
     produce_chunks<T::THREADS>(
-        p.world, shard_bytes, blockIdx.x, p.num_producers, p.teams, p.epoch,
+        p.world, shard_bytes, blockIdx.x, p.num_producers, p.teams, epoch,
         [&](int i) { return (void*)(p.workspace + (size_t)p.order[i] * shard_bytes); },
         [&](int i) { return p.shard[p.order[i]]; }, [&](int i) { return p.flags + p.order[i]; },
         [&](int i) { return p.arrivals + p.order[i]; });
@@ -52,10 +68,10 @@ __global__ __launch_bounds__(T::THREADS) void ag_gemm_kernel(const AgGemmParams 
     int32_t* rec = p.schedule + 4 * (size_t)wg;
     rec[0] = t.pid_m; rec[1] = t.pid_n; rec[2] = t.first; rec[3] = t.last;
   }
-  if (p.wait) flag_wait_block(p.flags, t.first, t.last - t.first + 1, p.epoch, p.spin_limit, p.status);
+  if (p.wait) flag_wait_block(p.flags, t.first, t.last - t.first + 1, epoch, p.spin_limit, p.status);
   const unsigned long long ts_ready = p.timing ? wall_clock64() : 0;
 
-  const uint32_t row_bytes = (uint32_t)p.k * 2u;
+  const uint32_t row_bytes = (uint32_t)p.k * kElement;
   const int M = p.m, N = p.n;
   auto a_row = [=](int r) { return (uint32_t)min(m0 + r, M - 1) * row_bytes; };
   typename T::Acc acc;
@@ -63,13 +79,28 @@ __global__ __launch_bounds__(T::THREADS) void ag_gemm_kernel(const AgGemmParams 
     gemm_mainloop<T>(acc, p.workspace, a_row, p.b, BColumns{(uint32_t)N * 2u, n0, N}, p.k, lds);
   } else {
     auto b_row = [=](int r) { return (uint32_t)min(n0 + r, N - 1) * row_bytes; };
-    gemm_mainloop<T>(acc, p.workspace, a_row, p.b, b_row, p.k, lds);
+    gemm_mainloop<T>(acc, p.workspace, a_row, p.b, b_row, T::F8 ? p.k / 2 : p.k, lds);
   }
-  store_tile_bf16<T>(acc, p.c, (size_t)p.n, m0, n0, M, N, lds);
+  if constexpr (T::F8) park_tile_bf16<T>(acc, lds, ShardScales{p, m0, n0});
+  else park_tile_bf16<T>(acc, lds);
+  store_parked_bf16<T>(p.c, (size_t)p.n, m0, n0, m0, M, N, lds);
   if (p.timing && threadIdx.x == 0) {
     int32_t* rec = p.schedule + 4 * (size_t)wg;
     rec[0] = (int32_t)(ts_start & 0x7fffffff); rec[1] = rec[0];
     rec[2] = (int32_t)(ts_ready & 0x7fffffff); rec[3] = (int32_t)(wall_clock64() & 0x7fffffff);
+  }
+}
+
+template <class T>
+__global__ __launch_bounds__(T::THREADS) void ag_gemm_kernel(const AgGemmParams p) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  if constexpr (T::F8) {
+    // (the fp8 operator can be recorded and replayed at every size: see ag_gemm_splitk_kernel)
+    const int32_t epoch = call_epoch(p.epoch, p.epoch_word);
+    ag_gemm_work_group<T>(p, epoch, lds);
+    advance_epoch(epoch, p.epoch_word, p.finished);
+  } else {
+    ag_gemm_work_group<T>(p, p.epoch, lds);
   }
 }
 
@@ -112,13 +143,16 @@ extern "C" ditron_status_t ditron_ag_gemm(const void* const* a_shards, const voi
       if (!a_shards[s] || !aligned16(a_shards[s])) return DITRON_ERR_INVALID_ARG;
     if (arrival_order && !is_permutation(arrival_order, world)) return DITRON_ERR_INVALID_ARG;
   }
-  const bool decode_shaped = dtype == DITRON_FP8_E4M3 || (b_layout == DITRON_B_NK && bf16_ag_is_decode_shaped(m_per_rank * world, n));
-  if ((flags & DITRON_EPOCH_IN_MEMORY) && !decode_shaped) return DITRON_ERR_UNSUPPORTED;
+  const bool fp8 = dtype == DITRON_FP8_E4M3;
+  const bool decode_shaped = ag_takes_decode_kernel(m_per_rank * world, n, k, dtype, b_layout, tune.decode_variant);
+  if ((flags & DITRON_EPOCH_IN_MEMORY) && !decode_shaped && !fp8) return DITRON_ERR_UNSUPPORTED;
   if (decode_shaped)
     return ditron_ag_gemm_decode(a_shards, b, b_layout, c, a_scales, b_scales, workspace, signals, status, schedule_out,
                                  arrival_order, m_per_rank, n, k, world, rank, dtype, epoch, flags, tuning, stream);
-  if (k % 8 != 0 || n % 8 != 0) return DITRON_ERR_UNSUPPORTED;
-  if (!fits_32bit((size_t)m_per_rank * world, k, 2) || !fits_32bit(n, k, 2)) return DITRON_ERR_UNSUPPORTED;
+  if (fp8 && b_layout != DITRON_B_NK) return DITRON_ERR_UNSUPPORTED;
+  if (k % (fp8 ? 16 : 8) != 0 || n % 8 != 0) return DITRON_ERR_UNSUPPORTED;
+  const int esize = fp8 ? 1 : 2;
+  if (!fits_32bit((size_t)m_per_rank * world, k, esize) || !fits_32bit(n, k, esize)) return DITRON_ERR_UNSUPPORTED;
 
   AgGemmParams p{};
   for (int i = 0; i < world; ++i) {
@@ -141,6 +175,15 @@ extern "C" ditron_status_t ditron_ag_gemm(const void* const* a_shards, const voi
   p.rank = rank;
   p.nnodes = tune.num_nodes;
   p.epoch = epoch;
+  if (fp8) {
+    p.a_scales = a_scales;
+    p.b_scales = b_scales;
+    if (flags & DITRON_EPOCH_IN_MEMORY) {
+      const size_t words = ditron_signal_words(world, 1);
+      p.epoch_word = signals + words - 1;
+      p.finished = signals + words - 2;
+    }
+  }
   p.spin_limit = tune.spin_limit;
   p.wait = mode != Mode::kPreset;
   TileChoice tc = choose_tile(p.m, n, k, b_layout == DITRON_B_NK);
@@ -149,12 +192,17 @@ extern "C" ditron_status_t ditron_ag_gemm(const void* const* a_shards, const voi
   p.tiling.group_m = tc.group_m;
   p.tiling.num_xcd = tc.num_xcd;
   p.tiling.per_xcd = tc.per_xcd;
-  const ProducerPlan pl = plan_producers((size_t)p.m * k * 2, world);
+  const ProducerPlan pl = plan_producers((size_t)p.m * k * esize, world);
   p.num_producers = emulate ? pl.producers : 0;
   p.teams = pl.teams;
   if (b_layout == DITRON_B_KN) {
     if (tc.big) return launch_ag<TileBigKN>(p, (hipStream_t)stream);
     return launch_ag<TileSmallKN>(p, (hipStream_t)stream);
+  }
+  if (fp8) {
+    if (tc.block_n == 224) return launch_ag<TileBigF8_224>(p, (hipStream_t)stream);
+    if (tc.block_n == 192) return launch_ag<TileBigF8_192>(p, (hipStream_t)stream);
+    return launch_ag<TileBigF8>(p, (hipStream_t)stream);
   }
   if (tc.big) {
     if (tc.block_n == 224) return launch_ag<TileBigDirect224>(p, (hipStream_t)stream);

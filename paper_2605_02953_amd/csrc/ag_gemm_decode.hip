@@ -27,8 +27,6 @@ struct DecodeTile {
   static constexpr int PENDING_A = (NA - 2) * A_LOADS, PENDING_B = NB - 2;
 };
 
-typedef int i32x8_t __attribute__((ext_vector_type(8)));
-
 struct AgGemmDecodeParams {
   const void* shard[DITRON_MAX_WORLD];
   int order[DITRON_MAX_WORLD];
@@ -539,26 +537,12 @@ __device__ __forceinline__ void splitk_work_group(const AgGemmDecodeParams& p, c
   }
 }
 
-// The epoch of a call is a launch argument, or, for callers that record the launch once and replay it (a HIP
-// graph), one more than a word in memory: every work-group reads the word when it starts, and the last one to
-// finish (they count themselves) writes the new epoch there, after every other work-group has read the old one.
 template <bool BF16, class T>
 __global__ __launch_bounds__(T::THREADS) void ag_gemm_splitk_kernel(const AgGemmDecodeParams p) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
-  int32_t epoch = p.epoch;
-  if (p.epoch_word)
-    epoch = __builtin_amdgcn_readfirstlane(__hip_atomic_load(p.epoch_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) + 1;
+  const int32_t epoch = call_epoch(p.epoch, p.epoch_word);
   splitk_work_group<BF16, T>(p, epoch, lds);
-  if (p.epoch_word) {
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      const int old = __hip_atomic_fetch_add(p.finished, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (old == (int)gridDim.x - 1) {
-        __hip_atomic_store(p.finished, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(p.epoch_word, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
-  }
+  advance_epoch(epoch, p.epoch_word, p.finished);
 }
 
 }  // namespace ditron

@@ -46,7 +46,7 @@ extern "C" ditron_status_t ditron_tile_config(int op, int m, int n, int k, int d
   if (dtype == DITRON_FP8_E4M3 && op != 0) return DITRON_ERR_UNSUPPORTED;
   const Tuning tune = resolve_tuning(tuning, 1);
   if (!tune.valid) return DITRON_ERR_INVALID_ARG;
-  const bool decode = dtype == DITRON_FP8_E4M3 || (op == 0 && bf16_ag_is_decode_shaped(m, n));
+  const bool decode = op == 0 && ag_takes_decode_kernel(m, n, k, dtype, DITRON_B_NK, tune.decode_variant);
   TileChoice t = decode ? choose_tile_decode(m, n, k) : choose_tile(m, n, k, op == 0);
   int splits = 1;
   if (decode) {
@@ -86,7 +86,7 @@ extern "C" size_t ditron_ag_gemm_workspace_bytes(int m_per_rank, int n, int k, i
   const int esize = dtype == DITRON_BF16 ? 2 : 1;
   const int m = world * m_per_rank;
   const size_t gathered = (size_t)m * k * esize;
-  const bool decode = dtype == DITRON_FP8_E4M3 || (b_layout == DITRON_B_NK && bf16_ag_is_decode_shaped(m, n));
+  const bool decode = ag_takes_decode_kernel(m, n, k, dtype, b_layout, tune.decode_variant);
   if (!decode) return gathered;
   // decode-shaped problems: the partial tiles of the split contraction follow the gathered operand
   const DecodePlan plan = plan_decode(m, n, k * esize, tune.decode_variant);
@@ -109,7 +109,7 @@ extern "C" ditron_status_t ditron_schedule_dump(int op, int m, int n, int k, int
   if (dtype == DITRON_FP8_E4M3 && (op != 0 || b_layout != DITRON_B_NK)) return DITRON_ERR_UNSUPPORTED;
   const Tuning tune = resolve_tuning(tuning, op == 3 ? 1 : world);
   if (!tune.valid) return DITRON_ERR_INVALID_ARG;
-  const bool decode = op == 0 && (dtype == DITRON_FP8_E4M3 || (b_layout == DITRON_B_NK && bf16_ag_is_decode_shaped(m, n)));
+  const bool decode = op == 0 && ag_takes_decode_kernel(m, n, k, dtype, b_layout, tune.decode_variant);
   TileChoice tc = decode ? choose_tile_decode(m, n, k) : choose_tile(m, n, k, op == 0 && b_layout == DITRON_B_NK);
   int splits = 1;
   if (decode) {

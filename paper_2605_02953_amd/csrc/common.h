@@ -71,6 +71,25 @@ __device__ inline void flag_wait_block(const int32_t* flags, int first, int coun
   __syncthreads();
 }
 
+// The epoch of a call is a launch argument, or, for callers that record the launch once and replay it (a HIP
+// graph), one more than a word in memory: every work-group reads the word when it starts, and the last one to
+// finish (they count themselves) writes the new epoch there, after every other work-group has read the old one.
+__device__ inline int32_t call_epoch(int32_t epoch, const int32_t* epoch_word) {
+  if (!epoch_word) return epoch;
+  return __builtin_amdgcn_readfirstlane(__hip_atomic_load(epoch_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) + 1;
+}
+__device__ inline void advance_epoch(int32_t epoch, int32_t* epoch_word, int32_t* finished) {
+  if (!epoch_word) return;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int old = __hip_atomic_fetch_add(finished, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (old == (int)gridDim.x - 1) {
+      __hip_atomic_store(finished, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(epoch_word, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+}
+
 // ------------------------------------------------------------------ chunk copy
 // Copy `bytes` (multiple of 16) from src to dst with 128-bit accesses, the calling
 // work-group being part `part` of `nparts` cooperating work-groups.

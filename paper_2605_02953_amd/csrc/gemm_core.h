@@ -80,16 +80,22 @@ __device__ __forceinline__ void barrier_no_drain() {
 // is 16 rows x 32 k: the 16-byte chunk (lane / 16) of the 32-deep step of row (lane % 16)); written for the
 // direct-to-LDS staging.  The accumulator of a block is four registers instead of sixteen, so the instruction
 // moves a quarter of the accumulator registers per unit of matrix work.
-template <int BM_, int BN_, bool B_KN_ = false, bool DIRECT_ = false, bool X16_ = false>
+//
+// F8: both operands are OCP e4m3 (a 128-byte row of a K tile is 128 elements), fed to v_mfma_f32_16x16x128_f8f6f4 by a
+// loop of its own (gemm_mainloop_f8); everything that counts in bytes is as for X16.  `K` is then passed in units of
+// two bytes.
+template <int BM_, int BN_, bool B_KN_ = false, bool DIRECT_ = false, bool X16_ = false, bool F8_ = false>
 struct GemmTile4W {
   static_assert((BM_ == 256 || BM_ == 128) && (BN_ == 256 || BN_ == 192 || BN_ == 128 || (X16_ && BN_ == 224)), "supported tile sides");
   static_assert(!B_KN_ || BN_ != 192, "a [K, N] row of 192 elements does not split evenly over the loading lanes");
   static_assert(!DIRECT_ || !B_KN_, "the direct-to-LDS staging is written for [N, K] operands");
   static_assert(!X16_ || DIRECT_, "the 16 x 16 x 32 loop is written for the direct-to-LDS staging");
+  static_assert(!F8_ || (X16_ && BM_ == 256 && BN_ >= 192), "the fp8 loop is written for 256-row tiles and direct-to-LDS staging");
   static_assert(!X16_ || (BN_ <= BM_ && BN_ % 32 == 0), "the 16 x 16 x 32 loop keeps A and B parts in one ring of pieces the size of the A part");
   static constexpr bool B_KN = B_KN_;
   static constexpr bool DIRECT = DIRECT_;   // operands go from global memory straight into LDS (no staging registers)
   static constexpr bool X16 = X16_;
+  static constexpr bool F8 = F8_;
   static constexpr int BM = BM_, BN = BN_, BK = 64, NSTAGE = 2;
   static constexpr int WAVES_M = 2, WAVES_N = 2, NWAVES = 4, THREADS = 256;
   static constexpr int WTM = BM / 2, WTN = BN / 2, MI = WTM / 32, NI = WTN / 32;
@@ -416,6 +422,147 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
   wait_vmcnt0();   // the last iteration's requests (the last K tile once more) are not left in flight
 }
 
+// ------------------------------------------------------------------ fp8 form
+// K loop for e4m3 operands on v_mfma_f32_16x16x128_f8f6f4 (32 cycles, twice the flops per cycle and per byte of the
+// bf16 instruction): a 128-byte K tile is one instruction deep, 8 x NB of them per wave.  LDS, loads, piece ring
+// and the mid-tile barrier are those of gemm_mainloop_x16: the loop moves the same bytes per cycle of matrix work.
+// A lane's 32 bytes of a fragment are the chunks lq and 4 + lq of its row (which k they are does not matter as long as
+// both operands agree), so the reads are the conflict-free ones of the 16 x 16 x 32 form.
+//
+// A whole K tile of fragments is 128 registers, and holding two of them does not fit beside 256 accumulators.  The
+// wave's quarter is therefore walked in four quadrants whose operand halves change one at a time:
+//   Q0: a_lo x b_lo   reads b_hi            Q1: a_lo x b_hi   reads a_hi           (this K tile)
+//   barrier: tile kt+1 has landed, nobody reads tile kt any more
+//   Q2: a_hi x b_hi   reads a_lo of kt+1    Q3: a_hi x b_lo   reads b_lo of kt+1
+// Every half is read one quadrant before its first use into registers that were last used the quadrant before; b_lo of
+// the next tile lands in the registers of b_hi, so the two B halves change places from tile to tile (the loop body
+// exists twice) and 128 fragment registers suffice with the reads spread evenly.
+typedef int i32x8_t __attribute__((ext_vector_type(8)));
+
+template <class T>
+struct Frags8 {
+  static constexpr int AH = T::MB / 2, BL = (T::NB + 1) / 2, BH = T::NB / 2;
+  u32x4_t a[2][AH][2];   // [lo / hi rows][block][chunk lq, chunk 4 + lq]
+  u32x4_t b[2][BL][2];   // [register set]: b_lo of the tiles of parity P is set P, b_hi set 1 - P
+};
+
+__device__ __forceinline__ i32x8_t join_f8(const u32x4_t lo, const u32x4_t hi) {
+  return __builtin_bit_cast(i32x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// which of the `n` events spread over the first `slots` slots belongs to slot s (-1: none)
+constexpr int event_in_slot(int s, int n, int slots) {
+  for (int i = 0; i < n; ++i)
+    if (i * slots / n == s) return i;
+  return -1;
+}
+
+// On entry the LDS must be idle; on exit no load is in flight.
+template <class T, bool WHOLE, class ARow, class BRow>
+__device__ __forceinline__ void gemm_mainloop_f8(typename T::Acc16& acc, const char* a_base, ARow a_row,
+                                                    const char* b_base, BRow b_row, int K, char* lds) {
+  typedef Frags8<T> F;
+  constexpr int AL = T::A_LOADS, BLD = T::B_LOADS, PIECE = T::A_BYTES;
+  constexpr int AH = F::AH, NL = F::BL, NH = F::BH;
+  constexpr int HALF_MMAS = AH * T::NB;   // matrix instructions between two events of the barrier
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int wm = wave / 2, wn = wave % 2;
+  const int lr = lane & 15, lq = lane >> 4;
+  const int a_off = (wm * T::WTM + lr) * T::ROW_BYTES;
+  const int b_off = (wn * T::WTN + lr) * T::ROW_BYTES;
+  int koff[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) koff[ks] = ((ks * 4 + lq) ^ swz128_x16(lr)) * 16;
+#pragma unroll
+  for (int nb = 0; nb < T::NB; ++nb)
+#pragma unroll
+    for (int mb = 0; mb < T::MB; ++mb) acc[nb][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  const int kt_all = (K + 63) / 64;
+  const int kt_last = kt_all - 1;
+  Stager4W<T> st;
+  st.init(a_base, a_row, b_base, b_row);
+  auto wrap = [](int x) { return x >= 5 ? x - 5 : x; };
+  auto load_a = [&](auto i, int kt, char* piece) { st.template issue_one<decltype(i)::value, WHOLE>(kt, K, piece); };
+  auto load_b = [&](auto i, int kt, char* piece) { st.template issue_one<AL + decltype(i)::value, WHOLE>(kt, K, piece - T::A_BYTES); };
+  static_for<0, AL>([&](auto i) { load_a(i, 0, lds); });
+  static_for<0, BLD>([&](auto i) { load_b(i, 0, lds + PIECE); });
+  static_for<0, AL>([&](auto i) { load_a(i, min(1, kt_last), lds + 2 * PIECE); });
+  static_for<0, BLD>([&](auto i) { load_b(i, min(1, kt_last), lds + 3 * PIECE); });
+  wait_vmcnt<AL + BLD>();
+  barrier_no_drain();
+
+  F f;
+  // read J of a half: block J / 2, chunk J % 2
+  auto read_a = [&](auto j, auto half, const char* piece) {
+    constexpr int J = decltype(j)::value, H = decltype(half)::value;
+    f.a[H][J / 2][J % 2] = *(const u32x4_t*)(piece + a_off + (H * AH + J / 2) * 16 * 128 + koff[J % 2]);
+  };
+  auto read_b = [&](auto j, auto set, auto first, const char* piece) {
+    constexpr int J = decltype(j)::value, S = decltype(set)::value, FIRST = decltype(first)::value;
+    f.b[S][J / 2][J % 2] = *(const u32x4_t*)(piece + b_off + (FIRST + J / 2) * 16 * 128 + koff[J % 2]);
+  };
+  using std::integral_constant;
+  typedef integral_constant<int, 0> I0;
+  typedef integral_constant<int, 1> I1;
+  static_for<0, 2 * AH>([&](auto j) { read_a(j, I0{}, lds); });
+  static_for<0, 2 * NL>([&](auto j) { read_b(j, I0{}, I0{}, lds + PIECE); });
+
+  int ia = 0;   // piece of A(kt)
+  auto tile = [&](auto parity, int kt) {
+    constexpr int P = decltype(parity)::value;
+    const char* cur_a = lds + ia * PIECE;
+    const char* cur_b = lds + wrap(ia + 1) * PIECE;
+    const char* nxt_a = lds + wrap(ia + 2) * PIECE;
+    const char* nxt_b = lds + wrap(ia + 3) * PIECE;
+    char* free_a = lds + wrap(ia + 4) * PIECE;   // held B(kt-1): nobody has read it since the last barrier
+    char* free_b = lds + ia * PIECE;             // A(kt): free after this iteration's barrier
+    const int kf = min(kt + 2, kt_last);         // past the end the last K tile is requested again, into pieces nobody reads
+    // one quadrant: rows of half AHALF, columns of half BHALF; ROWS_OUTER: the A half is the newer one, its last block
+    // is used last.  BASE: matrix instructions of this barrier interval before the quadrant (which loads are due).
+    auto quadrant = [&](auto ahalf, auto bhalf, auto rows_outer, auto reads, auto window, auto base, auto read, auto nloads, auto load) {
+      constexpr int A = decltype(ahalf)::value, BH_ = decltype(bhalf)::value;
+      constexpr bool RO = decltype(rows_outer)::value != 0;
+      constexpr int NBQ = BH_ ? NH : NL, N = AH * NBQ, R = decltype(reads)::value, W = decltype(window)::value + N;
+      constexpr int SET = BH_ ? 1 - P : P;
+      static_for<0, N>([&](auto sl) {
+        constexpr int S = decltype(sl)::value;
+        constexpr int mb = RO ? S / NBQ : S % AH, nb = RO ? S % NBQ : S / AH;
+        f32x4_t& c = acc[BH_ * NL + nb][A * AH + mb];
+        c = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(join_f8(f.b[SET][nb][0], f.b[SET][nb][1]),
+                                                             join_f8(f.a[A][mb][0], f.a[A][mb][1]), c, 0, 0, 0, 0, 0, 0);
+        constexpr int rd = event_in_slot(S, R, W);
+        if constexpr (rd >= 0) read(integral_constant<int, (rd >= 0 ? rd : 0)>{});
+        constexpr int ld = event_in_slot(decltype(base)::value + S - 1, decltype(nloads)::value, HALF_MMAS);   // not behind the same instruction as a read
+        if constexpr (ld >= 0) load(integral_constant<int, (ld >= 0 ? ld : 0)>{});
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    typedef integral_constant<int, -4> Early;    // reads done four instructions before the quadrant ends: the barrier waits for them
+    quadrant(I0{}, I0{}, I0{}, integral_constant<int, 2 * NH>{}, I0{}, I0{},
+             [&](auto j) { read_b(j, integral_constant<int, 1 - P>{}, integral_constant<int, NL>{}, cur_b); },
+             integral_constant<int, AL>{}, [&](auto i) { load_a(i, kf, free_a); });
+    quadrant(I0{}, I1{}, I0{}, integral_constant<int, 2 * AH>{}, Early{}, integral_constant<int, AH * NL>{},
+             [&](auto j) { read_a(j, I1{}, cur_a); },
+             integral_constant<int, AL>{}, [&](auto i) { load_a(i, kf, free_a); });
+    wait_vmcnt<AL>();   // this wave's part of tile kt+1 has landed (loads return in order); A(kt+2) may be in flight
+    wait_lgkmcnt0();    // every read of tile kt has returned
+    barrier_no_drain();
+    quadrant(I1{}, I1{}, I1{}, integral_constant<int, 2 * AH>{}, I0{}, I0{},
+             [&](auto j) { read_a(j, I0{}, nxt_a); },
+             integral_constant<int, BLD>{}, [&](auto i) { load_b(i, kf, free_b); });
+    quadrant(I1{}, I0{}, I1{}, integral_constant<int, 2 * NL>{}, I0{}, integral_constant<int, AH * NH>{},
+             [&](auto j) { read_b(j, integral_constant<int, 1 - P>{}, I0{}, nxt_b); },
+             integral_constant<int, BLD>{}, [&](auto i) { load_b(i, kf, free_b); });
+    ia = wrap(ia + 2);
+  };
+  for (int kt = 0; kt < kt_all; kt += 2) {
+    tile(I0{}, kt);
+    if (kt + 1 < kt_all) tile(I1{}, kt + 1);
+  }
+  wait_vmcnt0();   // the last iteration's requests (the last K tile once more) are not left in flight
+}
+
 // One barrier per 64-deep K tile.  A single wave per SIMD has to keep the matrix pipe fed
 // while it also issues every memory instruction, so the loop body is written as slots of two
 // MFMAs plus a few memory instructions, each slot fenced so that the compiler keeps the
@@ -433,7 +580,11 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
 template <class T, class ARow, class BRow>
 __device__ __forceinline__ void gemm_mainloop(typename T::Acc& acc, const char* a_base, ARow a_row,
                                                  const char* b_base, BRow b_row, int K, char* lds) {
-  if constexpr (T::X16) {
+  if constexpr (T::F8) {
+    if (K % 64 == 0) gemm_mainloop_f8<T, true>(acc, a_base, a_row, b_base, b_row, K, lds);
+    else gemm_mainloop_f8<T, false>(acc, a_base, a_row, b_base, b_row, K, lds);
+    return;
+  } else if constexpr (T::X16) {
     // two copies of the loop: the per-load range test of a ragged last K tile costs the others 0.8 %
     if (K % 64 == 0) gemm_mainloop_x16<T, true>(acc, a_base, a_row, b_base, b_row, K, lds);
     else gemm_mainloop_x16<T, false>(acc, a_base, a_row, b_base, b_row, K, lds);
@@ -672,9 +823,14 @@ struct ParkedTile {
   __device__ static __forceinline__ int key(int m) { return SLP == 16 ? (m & 15) : ((m >> 1) & 7); }
 };
 
-// First half of the epilogue: accumulators -> bf16 -> the wave's piece of the operand stages.
-template <class T>
-__device__ __forceinline__ void park_tile_bf16(const typename T::Acc& acc, char* lds) {
+// No scales: every factor is one.
+struct Unscaled {};
+
+// First half of the epilogue: accumulators -> bf16 -> the wave's piece of the operand stages.  `scales` (16 x 16 blocks
+// only): row(r) and cols(c) give the factors of the tile's row r and of its columns c .. c + 3; a value becomes
+// (value * row) * column before it is rounded.
+template <class T, class Scales = Unscaled>
+__device__ __forceinline__ void park_tile_bf16(const typename T::Acc& acc, char* lds, Scales scales = Scales{}) {
   typedef ParkedTile<T> P;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   __syncthreads();   // every wave is done reading the operand stages
@@ -682,14 +838,27 @@ __device__ __forceinline__ void park_tile_bf16(const typename T::Acc& acc, char*
   if constexpr (T::X16) {
     // a lane holds, per block, row (lane % 16) and the four columns 4 (lane / 16) .. + 3: half a 16-byte slot
     const int lr = lane & 15, lq = lane >> 4;
+    auto park_block = [&](int mb, int nb, const f32x4_t x) {
+      const int m = mb * 16 + lr, g = nb * 2 + (lq >> 1);
+      bf16x4_t v = {(__bf16)x[0], (__bf16)x[1], (__bf16)x[2], (__bf16)x[3]};
+      *(bf16x4_t*)(park + m * P::ROW + ((g ^ P::key(m)) * 16) + (lq & 1) * 8) = v;
+    };
+    if constexpr (std::is_same_v<Scales, Unscaled>) {
 #pragma unroll
-    for (int mb = 0; mb < T::MB; ++mb) {
-      const int m = mb * 16 + lr;
+      for (int mb = 0; mb < T::MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < T::NB; ++nb) park_block(mb, nb, acc[nb][mb]);
+    } else {
+      const int wm = wave / T::WAVES_N, wn = wave % T::WAVES_N;
+      float rs[T::MB];
+#pragma unroll
+      for (int mb = 0; mb < T::MB; ++mb) rs[mb] = scales.row(wm * T::WTM + mb * 16 + lr);
 #pragma unroll
       for (int nb = 0; nb < T::NB; ++nb) {
-        const int g = nb * 2 + (lq >> 1);
-        bf16x4_t v = {(__bf16)acc[nb][mb][0], (__bf16)acc[nb][mb][1], (__bf16)acc[nb][mb][2], (__bf16)acc[nb][mb][3]};
-        *(bf16x4_t*)(park + m * P::ROW + ((g ^ P::key(m)) * 16) + (lq & 1) * 8) = v;
+        const f32x4_t cs = scales.cols(wn * T::WTN + nb * 16 + lq * 4);
+#pragma unroll
+        for (int mb = 0; mb < T::MB; ++mb) park_block(mb, nb, acc[nb][mb] * rs[mb] * cs);
+        __builtin_amdgcn_sched_barrier(0);   // a column block at a time: its values, not the whole tile's, are in registers
       }
     }
     wait_lgkmcnt0();

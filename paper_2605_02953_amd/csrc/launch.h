@@ -19,6 +19,11 @@ typedef GemmTile4W<256, 256, false, true, true> TileBigDirect;
 // of 256 units partly empty (choose_tile).
 typedef GemmTile4W<256, 224, false, true, true> TileBigDirect224;
 typedef GemmTile4W<256, 192, false, true, true> TileBigDirect192;
+// The same three for fp8 operands (256-row tiles are taken by fp8 problems large enough for them, see
+// ag_takes_decode_kernel).
+typedef GemmTile4W<256, 256, false, true, true, true> TileBigF8;
+typedef GemmTile4W<256, 224, false, true, true, true> TileBigF8_224;
+typedef GemmTile4W<256, 192, false, true, true, true> TileBigF8_192;
 // 128x128 output tile: 64x64 per wave, 64 KiB of LDS; for problems with too few 256x256 tiles
 // to fill the chip.
 typedef GemmTile4W<128, 128> TileSmall;
@@ -110,10 +115,21 @@ inline TileChoice choose_tile(int m, int n, int /*k*/, bool narrow_ok = false) {
   return t;
 }
 
-// Decode-shaped AllGather-GEMM (fp8 always; bf16 when the 128 x 128 tiles of the tile engine would not
+// Decode-shaped AllGather-GEMM (fp8 with few 256 x 256 tiles; bf16 when the 128 x 128 tiles of the tile engine would not
 // cover half the chip and B is stored [n, k]): one tile shape, 128 rows x 32 columns, 4 computing waves +
 // 4 loading waves.
 inline bool bf16_ag_is_decode_shaped(int m, int n) { return (long)cdiv(m, 128) * cdiv(n, 128) <= 128; }
+// The tile loaders address an operand with 32-bit byte offsets, and the buffer-addressed
+// loaders reserve offsets from 0x7ffffff0 up as "out of range, reads zero".
+inline bool fits_32bit(size_t rows, size_t cols, size_t esize) { return rows * cols * esize < 0x7ffffff0ull; }
+
+// fp8 takes the 256-row tiles of the tile engine where they fill three quarters of the chip (the bf16 rule), unless the
+// caller asks for a decode variant or an operand is too large for the engine's 32-bit offsets.
+inline bool ag_takes_decode_kernel(int m, int n, int k, int dtype, int b_layout, int decode_variant) {
+  if (dtype == DITRON_FP8_E4M3)
+    return decode_variant != 0 || (long)cdiv(m, 256) * cdiv(n, 256) < 192 || !fits_32bit(m, k, 1) || !fits_32bit(n, k, 1);
+  return b_layout == DITRON_B_NK && bf16_ag_is_decode_shaped(m, n);
+}
 inline TileChoice choose_tile_decode(int /*m*/, int /*n*/, int /*k*/) {
   TileChoice t{};
   t.big = false;
@@ -170,10 +186,6 @@ inline ProducerPlan plan_producers(size_t total_bytes, int nchunks) {
 }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
-// The tile loaders address an operand with 32-bit byte offsets, and the buffer-addressed
-// loaders reserve offsets from 0x7ffffff0 up as "out of range, reads zero".
-inline bool fits_32bit(size_t rows, size_t cols, size_t esize) { return rows * cols * esize < 0x7ffffff0ull; }
 
 // With more than one node the tile-row order comes from the paper's multi-node listings; a shape
 // for which they do not visit every tile row exactly once is refused.
