@@ -255,7 +255,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_ar_kernel(const GemmArParams 
     if ((int)threadIdx.x < p.world && (!p.peers_resident || (int)threadIdx.x == p.rank))
       flag_wait_lane(p.tile_flags + (size_t)threadIdx.x * ntiles, pid_m * p.npn + pid_n, 1, p.epoch, p.spin_limit, p.status);
     __syncthreads();
-    ar_reduce_tile<T, WORLD, (T::BM * T::BN / 8 / T::THREADS >= 32 ? 4 : 2), TWO>(p, pid_m * T::BM, pid_n * T::BN);
+    ar_reduce_tile<T, WORLD, WORLD == 2 || WORLD == 4 ? 8 : 4, TWO>(p, pid_m * T::BM, pid_n * T::BN);
   }
   // the last consumer to leave puts the queue back to zero for the next call
   if (threadIdx.x == 0) {
@@ -303,9 +303,13 @@ static ditron_status_t launch_ar(GemmArParams& p, int units, bool two_shot, hipS
     hipLaunchKernelGGL(kern, dim3(grid), dim3(T::THREADS), T::LDS_BYTES, stream, p);
     return hipGetLastError() == hipSuccess ? DITRON_OK : DITRON_ERR_HIP;
   };
-  if (two_shot)
-    return p.world == 8 ? launch(KernelConstant<gemm_ar_kernel<T, 8, true>>{}) : launch(KernelConstant<gemm_ar_kernel<T, 0, true>>{});
-  return p.world == 8 ? launch(KernelConstant<gemm_ar_kernel<T, 8, false>>{}) : launch(KernelConstant<gemm_ar_kernel<T, 0, false>>{});
+  // a fixed number of ranks lets the consumer have the vectors of every rank in flight together
+  switch (p.world) {
+    case 2: return two_shot ? launch(KernelConstant<gemm_ar_kernel<T, 2, true>>{}) : launch(KernelConstant<gemm_ar_kernel<T, 2, false>>{});
+    case 4: return two_shot ? launch(KernelConstant<gemm_ar_kernel<T, 4, true>>{}) : launch(KernelConstant<gemm_ar_kernel<T, 4, false>>{});
+    case 8: return two_shot ? launch(KernelConstant<gemm_ar_kernel<T, 8, true>>{}) : launch(KernelConstant<gemm_ar_kernel<T, 8, false>>{});
+    default: return two_shot ? launch(KernelConstant<gemm_ar_kernel<T, 0, true>>{}) : launch(KernelConstant<gemm_ar_kernel<T, 0, false>>{});
+  }
 }
 
 }  // namespace ditron

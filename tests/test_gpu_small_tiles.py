@@ -1,0 +1,70 @@
+"""The 128 x 128 tile of the tile engine at the lengths of its operand ring, and the all-reduce consumer at the rank
+counts that have an instance of their own, against the CPU oracle through the C ABI.  Inputs are small integers: every
+sum is exact in fp32, so the only rounding is the one to bf16 and the bits must be the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import ag_gemm as oag, formats, gemm_ar as oar
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2605_02953_amd import binding
+    assert torch.cuda.is_available()
+    return binding
+
+
+from gpu_util import to_dev, bits, nk, AgGemmRun, GemmArRun  # noqa: E402
+
+
+def _ok(B, st, run):
+    assert st == B.OK, B.status_string(st)
+    torch.cuda.synchronize()
+    assert run.status.cpu().tolist()[0] == 0
+
+
+# less than a K tile, up to the three that the ring requests ahead, one more, two turns of the ring's seven pieces; whole
+# and ragged last K tiles.  2000 x 2056: 272 tiles, the last row and the last column of tiles ragged
+@pytest.mark.parametrize("k", [8, 64, 128, 136, 192, 200, 256, 448, 520])
+def test_128_row_tiles_are_bit_exact(B, k):
+    cfg = synth.CONFIGS[2].scaled(world=8, m_per_rank=250, n=2056, k=k, rank=5)
+    st, tc = B.tile_config(0, cfg.m, cfg.n, k)
+    assert (st, tc["block_m"], tc["block_n"], tc["splits"]) == (B.OK, 128, 128, 1)
+    shards, b = synth.ag_gemm_inputs(cfg, integer=True)
+    run = AgGemmRun(B, 8, cfg.m_per_rank, cfg.n, k)
+    st = run([to_dev(s) for s in shards], to_dev(nk(b)), cfg.rank)
+    _ok(B, st, run)
+    assert np.array_equal(bits(run.workspace), oag.gather(shards))
+    assert np.array_equal(bits(run.c), formats.encode_bf16_rne(oag.ag_gemm(shards, b).astype(np.float32)))
+
+
+# 2, 4 and 8 ranks: every one has its own number of vectors in flight; 5: the loop over any number of ranks.
+# 264 columns: a last tile of one vector; 3080 x ~4040: 256-row tiles
+@pytest.mark.parametrize("world", [2, 4, 5, 8])
+@pytest.mark.parametrize("rows,n,k", [(120, 264, 72), (1000, 1288, 64), (4040, 3080, 64)])
+def test_all_reduce_consumer_by_rank_count(B, world, rows, n, k):
+    cfg = synth.CONFIGS[3].scaled(world=world, m_per_rank=rows // world, n=n, k=k)
+    a_list, b_list = synth.gemm_rs_inputs(cfg, integer=True)
+    parts = [oar.partial_bits(a, b) for a, b in zip(a_list, b_list)]
+    full = oar.allreduce_partials_f32_ordered(parts)
+    d = world - 1
+    peers = [None if s == d else to_dev(parts[s]) for s in range(world)]
+    a_dev, b_dev = to_dev(a_list[d]), to_dev(nk(b_list[d]))
+    run = GemmArRun(B, world, cfg.m, n, k)
+    run.out.fill_(0x7FC0)
+    _ok(B, run(a_dev, b_dev, peers, d), run)
+    assert np.array_equal(bits(run.gemm_out), parts[d])
+    assert np.array_equal(bits(run.out), full)
+    outs = [torch.full((cfg.m, n), 0x7FC0, dtype=torch.int16, device="cuda") for _ in range(world)]
+    reduced = [None if s == d else to_dev(full) for s in range(world)]
+    run.epoch += 1
+    st = B.gemm_ar_two_shot(a_dev, b_dev, B.B_NK, run.gemm_out, peers, outs, reduced, run.signals, run.status, None, cfg.m, n, k,
+                            world, d, run.epoch, B.EMULATE_PRODUCER)
+    _ok(B, st, run)
+    assert np.array_equal(bits(outs[d]), full)
+    mine = bits(outs[0]) if d else full
+    assert ((mine == full) | (mine == 0x7FC0)).all()
