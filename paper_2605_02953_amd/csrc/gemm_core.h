@@ -103,8 +103,13 @@ struct GemmTile4W {
   static constexpr int PB = BN * 2 + 64;                      // B_KN: bytes between two k rows of the staged B tile
   static constexpr int A_BYTES = BM * ROW_BYTES, B_BYTES = B_KN ? BK * PB : BN * ROW_BYTES;
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-  // X16: a ring of five operand pieces (the A part and the B part of a K tile are pieces of their own), all of the LDS
-  static constexpr int LDS_BYTES = X16_ ? 5 * A_BYTES : NSTAGE * STAGE_BYTES;
+  // X16: a ring of 2 DEPTH + 1 operand pieces (the A part and the B part of a K tile are pieces of their own): DEPTH K
+  // tiles are requested ahead.  256 rows: five pieces are all of the LDS.  128 rows: seven of ten (2 / 3 / 4 tiles ahead,
+  // [1024 x 8192] x [8192 x 3696], operands resident: 66 / 57 / 57 us; 464 tiles of [2048 x 3696]: 123 / 109 / 111 us, so a
+  // second work-group on the unit, which 2 would leave room for, is worth less than the third tile in flight).
+  static constexpr int DEPTH = BM_ == 128 ? 3 : 2;
+  static constexpr int PIECES = 2 * DEPTH + 1;
+  static constexpr int LDS_BYTES = X16_ ? PIECES * A_BYTES : NSTAGE * STAGE_BYTES;
   static constexpr int ROWS_PER_PASS = THREADS / 8;           // 32 rows per pass of 16-byte loads
   static constexpr int A_LOADS = BM / ROWS_PER_PASS, B_LOADS = BN / ROWS_PER_PASS, LOADS = A_LOADS + B_LOADS;
   // The K loop is written as slots of two MFMAs (one B fragment, two A fragments).
@@ -323,11 +328,12 @@ constexpr int load_in_slot(int s, int n, int slots) {
 // as zeros (their offsets are pushed out of the buffer's range).  A K tile is two 32-deep steps of MB x NB MFMAs each, written as slots of
 // four MFMAs plus one fragment read and at most one load.  All fragments of a step are read during the step
 // before it, so a K tile's operands are no longer read once its second step starts: the barrier sits between
-// the two steps.  LDS is a ring of five pieces of 32 KiB; the A part of K tile j lives in piece 2j mod 5 and
-// its B part in piece (2j + 1) mod 5, so two and a half K tiles are resident:
-//   step 0 of tile kt : fragment reads of step 1; loads of A(kt+2) into the piece idle since the last barrier
+// the two steps.  LDS is a ring of P = 2D + 1 pieces (D = 2: five of 32 KiB; D = 3, 128-row tiles: seven of
+// 16 KiB); the A part of K tile j lives in piece 2j mod P and its B part in piece (2j + 1) mod P, so D and a
+// half K tiles are resident:
+//   step 0 of tile kt : fragment reads of step 1; loads of A(kt+D) into the piece idle since the last barrier
 //   barrier           : every wave's part of tile kt+1 has landed, nobody reads tile kt any more
-//   step 1 of tile kt : fragment reads of step 0 of tile kt+1; loads of B(kt+2) into the piece of A(kt)
+//   step 1 of tile kt : fragment reads of step 0 of tile kt+1; loads of B(kt+D) into the piece of A(kt)
 // The loads go out one per two slots over the whole K tile and have one to three steps to land (with two
 // whole-tile stages all of them went out during step 1 and had one to two: at operands that are not in the
 // caches, cfg 2 and cfg 3 shapes beside the vendor GEMM, the ring takes 8-10 % less time; with operands that
@@ -343,7 +349,7 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
                                                      const char* b_base, BRow b_row, int K, char* lds) {
   constexpr int MB = T::MB, NB = T::NB, READS = MB + NB, AL = T::A_LOADS, BL = T::B_LOADS;
   constexpr int SLOTS = MB * NB / 4;   // per step
-  constexpr int PIECE = T::A_BYTES;
+  constexpr int PIECE = T::A_BYTES, D = T::DEPTH;
   static_assert(MB % 4 == 0 && READS <= 2 * SLOTS && AL <= SLOTS && BL <= SLOTS && T::B_BYTES <= T::A_BYTES,
                 "at most two reads and one load per slot; a B part fits in a piece");
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -365,15 +371,16 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
   const int kt_last = kt_all - 1;
   Stager4W<T> st;
   st.init(a_base, a_row, b_base, b_row);
-  auto wrap = [](int x) { return x >= 5 ? x - 5 : x; };
+  auto wrap = [](int x) { return x >= T::PIECES ? x - T::PIECES : x; };
   // load I of K tile kt into the piece at `piece` (the stager puts B loads T::A_BYTES behind the address it is given)
   auto load_a = [&](auto i, int kt, char* piece) { st.template issue_one<decltype(i)::value, WHOLE>(kt, K, piece); };
   auto load_b = [&](auto i, int kt, char* piece) { st.template issue_one<AL + decltype(i)::value, WHOLE>(kt, K, piece - T::A_BYTES); };
-  static_for<0, AL>([&](auto i) { load_a(i, 0, lds); });
-  static_for<0, BL>([&](auto i) { load_b(i, 0, lds + PIECE); });
-  static_for<0, AL>([&](auto i) { load_a(i, min(1, kt_last), lds + 2 * PIECE); });
-  static_for<0, BL>([&](auto i) { load_b(i, min(1, kt_last), lds + 3 * PIECE); });
-  wait_vmcnt<AL + BL>();
+  static_for<0, D>([&](auto j) {
+    constexpr int J = decltype(j)::value;
+    static_for<0, AL>([&](auto i) { load_a(i, min(J, kt_last), lds + 2 * J * PIECE); });
+    static_for<0, BL>([&](auto i) { load_b(i, min(J, kt_last), lds + (2 * J + 1) * PIECE); });
+  });
+  wait_vmcnt<(D - 1) * (AL + BL)>();
   barrier_no_drain();
   Frags16<T> f0, f1;
   static_for<0, READS>([&](auto j) { read_one16<T, 0, decltype(j)::value>(f0, lds, lds + PIECE, a_off, b_off, koff); });
@@ -383,9 +390,9 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
     const char* cur_b = lds + wrap(ia + 1) * PIECE;
     const char* nxt_a = lds + wrap(ia + 2) * PIECE;
     const char* nxt_b = lds + wrap(ia + 3) * PIECE;
-    char* free_a = lds + wrap(ia + 4) * PIECE;   // held B(kt-1): nobody has read it since the last barrier
+    char* free_a = lds + wrap(ia + 2 * D) * PIECE;   // held B(kt-1): nobody has read it since the last barrier
     char* free_b = lds + ia * PIECE;             // A(kt): free after this iteration's barrier
-    const int kf = min(kt + 2, kt_last);   // past the end the last K tile is requested again, into pieces nobody reads
+    const int kf = min(kt + D, kt_last);   // past the end the last K tile is requested again, into pieces nobody reads
     static_for<0, SLOTS>([&](auto sl) {
       constexpr int S = decltype(sl)::value;
       mma_one16<T, S, 0>(acc, f0);
@@ -400,7 +407,7 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
       mma_one16<T, S, 3>(acc, f0);
       __builtin_amdgcn_sched_barrier(0);
     });
-    wait_vmcnt<AL>();   // this wave's part of tile kt+1 has landed (loads return in order); A(kt+2) may be in flight
+    wait_vmcnt<(D - 2) * (AL + BL) + AL>();   // this wave's part of tile kt+1 has landed (loads return in order); the younger ones may be in flight
     wait_lgkmcnt0();    // every read of tile kt has returned
     barrier_no_drain();
     static_for<0, SLOTS>([&](auto sl) {

@@ -24,10 +24,12 @@ typedef GemmTile4W<256, 192, false, true, true> TileBigDirect192;
 typedef GemmTile4W<256, 256, false, true, true, true> TileBigF8;
 typedef GemmTile4W<256, 224, false, true, true, true> TileBigF8_224;
 typedef GemmTile4W<256, 192, false, true, true, true> TileBigF8_192;
-// 128x128 output tile: 64x64 per wave, 64 KiB of LDS; for problems with too few 256x256 tiles
-// to fill the chip.
-typedef GemmTile4W<128, 128> TileSmall;
-// The same two sizes for B stored [K, N] (register staging, two LDS stages, 32 x 32 x 16 MFMA, as the 128x128 tile).
+// 128x128 output tile on the same loop with three K tiles in flight (112 KiB of LDS): 64x64 per wave; for problems with
+// too few 256x256 tiles to fill the chip.  (The register-staged 32 x 32 x 16 loop with two LDS stages that it replaced
+// requests one K tile ahead, which is less than the L2 takes under load: [1024 x 8192] x [8192 x 3696], operands resident,
+// 73 -> 57 us; 0.53 -> 0.38 us per K tile of a work-group, of which 0.34 are the 768 cycles of its LDS traffic.)
+typedef GemmTile4W<128, 128, false, true, true> TileSmall;
+// The same two sizes for B stored [K, N] (register staging, two LDS stages, 32 x 32 x 16 MFMA).
 typedef GemmTile4W<256, 256, true> TileBigKN;
 typedef GemmTile4W<128, 128, true> TileSmallKN;
 // The MoE grouped GEMM: 4 waves as 2 x 2.  An expert's rows are padded to whole row tiles, so the row
