@@ -27,6 +27,17 @@ __device__ __forceinline__ int swz128(int r) { return (r & 7) ^ ((r >> 3) & 1); 
 // times as long under swz128 as under this one (and the 32-row read above 1.64 times as long under this one).
 __device__ __forceinline__ int swz128_x16(int r) { return r & 7; }
 
+// The same for a B tile staged as k rows of BN elements: the pair of 16-byte chunks p (16 columns) of k row r is stored at
+// pair position p ^ swz_kn<BN>(r).  A transposing read takes four rows (r .. r + 3, r a multiple of 4) of one pair per group
+// of 16 lanes, two groups (rows 8 apart) per cycle: eight pairs that fall on the eight 32-byte windows of the 256-byte bank
+// row.  Rows of 256 and 128 elements all start at window 0; rows of 192 at window 4 r mod 8 (and the exclusive or stays below
+// their 12 pairs).
+template <int BN>
+__device__ __forceinline__ int swz_kn(int r) {
+  static_assert(BN == 256 || BN == 192 || BN == 128, "bank windows worked out for these");
+  return BN == 192 ? (r & 2) | ((r >> 3) & 1) : (r & 3) | ((r >> 1) & 4);
+}
+
 // The explicit waits are pinned in place: the scheduler must not move matrix instructions
 // behind them (a wave blocked in a wait issues nothing).
 __device__ __forceinline__ void wait_vmcnt0() {
@@ -60,26 +71,24 @@ __device__ __forceinline__ void barrier_no_drain() {
 }
 
 // ------------------------------------------------------------------ the tile
-// BM x BN output tile (BM 256 or 128, BN 256, 192 or 128) computed by four waves, one per SIMD,
+// BM x BN output tile (BM 256 or 128, BN 256, 224, 192 or 128) computed by four waves, one per SIMD,
 // each owning BM/2 x BN/2 (256 x 256: 128 x 128 per wave, 256 accumulator registers, every
-// fragment read from LDS feeds four MFMAs).  Operands are staged global -> registers -> LDS, or,
-// with DIRECT, global -> LDS (`buffer_load ... lds`; measured faster on 256 x 256 tiles whose
-// contraction is a whole number of K tiles, slower for a ragged last K tile and on 128-row tiles,
-// so the launch code picks per problem).  LDS holds two stages of one 64-deep K tile each (the
-// 16 x 16 x 32 form: a ring of five half stages), rows of 128 bytes (measured free of bank
-// conflicts for both the fragment reads and the staging stores).
+// fragment read from LDS feeds four MFMAs).
 //
-// B_KN: B is stored [K, N] (N contiguous) instead of [N, K].  Its K tile is then staged as it
-// lies in memory, 64 rows of BN elements with a pitch of 2 BN + 64 bytes, and the MFMA
-// operand (eight consecutive k of one column per lane) is assembled by two transposing LDS
-// reads (ds_read_b64_tr_b16: inside each group of 16 lanes, lane i receives element i % 4 of
-// the 8-byte chunks addressed by lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4; measured).  The pitch
-// makes the four rows a group touches, and the two groups that share a cycle, hit distinct banks.
+// X16: operands go global -> LDS (DIRECT: `buffer_load ... lds`) into a ring of operand pieces and feed
+// v_mfma_f32_16x16x32_bf16 (a wave's quarter is cut into 16 x 16 blocks, a fragment is 16 rows x 32 k: the 16-byte chunk
+// (lane / 16) of the 32-deep step of row (lane % 16)).  The accumulator of a block is four registers instead of sixteen, so
+// the instruction moves a quarter of the accumulator registers per unit of matrix work.  LDS rows of 128 bytes (measured
+// free of bank conflicts for the fragment reads).
+// Otherwise: operands go global -> registers -> LDS (or, DIRECT, through gemm_mainloop_ring_split) in two stages of one
+// 64-deep K tile each and feed v_mfma_f32_32x32x16_bf16: the MoE tiles for which that measured faster.
 //
-// X16: the same tile fed to v_mfma_f32_16x16x32_bf16 (a wave's quarter is cut into 16 x 16 blocks, a fragment
-// is 16 rows x 32 k: the 16-byte chunk (lane / 16) of the 32-deep step of row (lane % 16)); written for the
-// direct-to-LDS staging.  The accumulator of a block is four registers instead of sixteen, so the instruction
-// moves a quarter of the accumulator registers per unit of matrix work.
+// B_KN (X16): B is stored [K, N] (N contiguous) instead of [N, K].  Its K tile is staged as it lies in memory, 64 rows of
+// BN elements, the pairs of chunks swizzled by the row (swz_kn), and the MFMA operand (eight consecutive k of one column per
+// lane) is assembled by two transposing LDS reads (ds_read_b64_tr_b16: inside each group of 16 lanes, lane i receives
+// element i % 4 of the 8-byte chunks addressed by lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4; measured).  Everything that counts
+// in bytes is as for [N, K].  (It replaced a register-staged 32 x 32 x 16 loop: [7976 x 8192] x [8192 x 3584] fused 446 ->
+// 388 us at 256 x 256 tiles, 128 x 128 tiles 20 to 30 % less, MoE 2 to 23 % less.)
 //
 // F8: both operands are OCP e4m3 (a 128-byte row of a K tile is 128 elements), fed to v_mfma_f32_16x16x128_f8f6f4 by a
 // loop of its own (gemm_mainloop_f8); everything that counts in bytes is as for X16.  `K` is then passed in units of
@@ -87,11 +96,10 @@ __device__ __forceinline__ void barrier_no_drain() {
 template <int BM_, int BN_, bool B_KN_ = false, bool DIRECT_ = false, bool X16_ = false, bool F8_ = false>
 struct GemmTile4W {
   static_assert((BM_ == 256 || BM_ == 128) && (BN_ == 256 || BN_ == 192 || BN_ == 128 || (X16_ && BN_ == 224)), "supported tile sides");
-  static_assert(!B_KN_ || BN_ != 192, "a [K, N] row of 192 elements does not split evenly over the loading lanes");
-  static_assert(!DIRECT_ || !B_KN_, "the direct-to-LDS staging is written for [N, K] operands");
+  static_assert(!B_KN_ || X16_, "the 32 x 32 x 16 loop is written for [N, K] operands");
   static_assert(!X16_ || DIRECT_, "the 16 x 16 x 32 loop is written for the direct-to-LDS staging");
-  static_assert(!F8_ || (X16_ && BM_ == 256 && BN_ >= 192), "the fp8 loop is written for 256-row tiles and direct-to-LDS staging");
-  static_assert(!X16_ || (BN_ <= BM_ && BN_ % 32 == 0), "the 16 x 16 x 32 loop keeps A and B parts in one ring of pieces the size of the A part");
+  static_assert(!F8_ || (X16_ && !B_KN_ && BM_ == 256 && BN_ >= 192), "the fp8 loop is written for 256-row tiles and direct-to-LDS staging");
+  static_assert(!X16_ || BN_ % 32 == 0, "whole 16 x 16 blocks per wave");
   static constexpr bool B_KN = B_KN_;
   static constexpr bool DIRECT = DIRECT_;   // operands go from global memory straight into LDS (no staging registers)
   static constexpr bool X16 = X16_;
@@ -100,23 +108,24 @@ struct GemmTile4W {
   static constexpr int WAVES_M = 2, WAVES_N = 2, NWAVES = 4, THREADS = 256;
   static constexpr int WTM = BM / 2, WTN = BN / 2, MI = WTM / 32, NI = WTN / 32;
   static constexpr int ROW_BYTES = 128;
-  static constexpr int PB = BN * 2 + 64;                      // B_KN: bytes between two k rows of the staged B tile
-  static constexpr int A_BYTES = BM * ROW_BYTES, B_BYTES = B_KN ? BK * PB : BN * ROW_BYTES;
+  static constexpr int PB = BN * 2;                           // B_KN: bytes of a k row of the staged B tile
+  static constexpr int A_BYTES = BM * ROW_BYTES, B_BYTES = BN * ROW_BYTES;
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
   // X16: a ring of 2 DEPTH + 1 operand pieces (the A part and the B part of a K tile are pieces of their own): DEPTH K
   // tiles are requested ahead.  256 rows: five pieces are all of the LDS.  128 rows: seven of ten (2 / 3 / 4 tiles ahead,
   // [1024 x 8192] x [8192 x 3696], operands resident: 66 / 57 / 57 us; 464 tiles of [2048 x 3696]: 123 / 109 / 111 us, so a
   // second work-group on the unit, which 2 would leave room for, is worth less than the third tile in flight).
-  static constexpr int DEPTH = BM_ == 128 ? 3 : 2;
+  static constexpr int PIECE_BYTES = A_BYTES > B_BYTES ? A_BYTES : B_BYTES;
+  static constexpr int DEPTH = PIECE_BYTES <= 16 * 1024 ? 3 : 2;
   static constexpr int PIECES = 2 * DEPTH + 1;
-  static constexpr int LDS_BYTES = X16_ ? PIECES * A_BYTES : NSTAGE * STAGE_BYTES;
+  static constexpr int LDS_BYTES = X16_ ? PIECES * PIECE_BYTES : NSTAGE * STAGE_BYTES;
   static constexpr int ROWS_PER_PASS = THREADS / 8;           // 32 rows per pass of 16-byte loads
   static constexpr int A_LOADS = BM / ROWS_PER_PASS, B_LOADS = BN / ROWS_PER_PASS, LOADS = A_LOADS + B_LOADS;
   // The K loop is written as slots of two MFMAs (one B fragment, two A fragments).
   static constexpr int PAIRS = MI * NI / 2;                   // slots per 16-deep step
   static constexpr int SLOTS = 4 * PAIRS;                     // slots per 64-deep K tile
-  static constexpr int B_READS = B_KN ? 2 : 1;                // LDS reads per B fragment
-  static constexpr int READS = MI + B_READS * NI;             // fragment reads per step
+  static constexpr int B_READS = B_KN ? 2 : 1;                // X16: LDS reads per B fragment
+  static constexpr int READS = MI + NI;                       // fragment reads per step (32 x 32 x 16 loop)
   static constexpr int HALF = (PAIRS + 1) / 2;                // slots of a step that take its reads when they must be early
   static constexpr int MB = WTM / 16, NB = WTN / 16;          // X16: 16 x 16 blocks of a wave's quarter
   // the accumulators of one wave: [column block][row block]
@@ -127,8 +136,7 @@ struct GemmTile4W {
 
 template <class T>
 struct Frags4W {
-  bf16x8_t a[T::MI];
-  bf16x4_t b[T::NI][2];   // low and high four k of the fragment ([N, K] storage fills both with one read)
+  bf16x8_t a[T::MI], b[T::NI];
 };
 
 template <int I, int N, class F>
@@ -141,31 +149,14 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
-// B fragment NI_ of step KS: READ 0 (and, for [K, N] storage, READ 1 for the upper four k).
-// b_off is the lane's base inside the stage: for [N, K] storage the row of its column, for
-// [K, N] storage the chunk it addresses in the transposing read.
-template <class T, int KS, int NI_, int READ>
-__device__ __forceinline__ void read_b(Frags4W<T>& f, const char* st, int b_off, const int (&koff)[4]) {
-  if constexpr (T::B_KN) {
-    const char* src = st + b_off + NI_ * 64 + (KS * 16 + READ * 4) * T::PB;
-    const s16x4_t v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)DITRON_LDS(src));
-    f.b[NI_][READ] = __builtin_bit_cast(bf16x4_t, v);
-  } else {
-    const bf16x8_t v = *(const bf16x8_t*)(st + b_off + NI_ * 32 * 128 + koff[KS]);
-    f.b[NI_][0] = __builtin_shufflevector(v, v, 0, 1, 2, 3);
-    f.b[NI_][1] = __builtin_shufflevector(v, v, 4, 5, 6, 7);
-  }
-}
-
 // Fragment read J of step KS (0..3) of the K tile staged at `st`.  koff[KS] is the lane's
 // swizzled chunk offset for that step.  The order (b0, a0..a[MI-1], b1..b[NI-1]) is the order
 // in which mma_pair consumes them.
 template <class T, int KS, int J>
 __device__ __forceinline__ void read_one(Frags4W<T>& f, const char* st, int a_off, int b_off, const int (&koff)[4]) {
-  constexpr int BR = T::B_READS;
-  if constexpr (J < BR) read_b<T, KS, 0, J>(f, st, b_off, koff);
-  else if constexpr (J < BR + T::MI) f.a[J - BR] = *(const bf16x8_t*)(st + a_off + (J - BR) * 32 * 128 + koff[KS]);
-  else read_b<T, KS, 1 + (J - BR - T::MI) / BR, (J - BR - T::MI) % BR>(f, st, b_off, koff);
+  if constexpr (J == 0) f.b[0] = *(const bf16x8_t*)(st + b_off + koff[KS]);
+  else if constexpr (J <= T::MI) f.a[J - 1] = *(const bf16x8_t*)(st + a_off + (J - 1) * 32 * 128 + koff[KS]);
+  else f.b[J - T::MI] = *(const bf16x8_t*)(st + b_off + (J - T::MI) * 32 * 128 + koff[KS]);
 }
 // reads [LO, HI) of a step
 template <class T, int KS, int LO, int HI>
@@ -176,9 +167,8 @@ __device__ __forceinline__ void read_range(Frags4W<T>& f, const char* st, int a_
 template <class T, int P>
 __device__ __forceinline__ void mma_pair(typename T::Acc32& acc, const Frags4W<T>& f) {
   constexpr int ni = P / (T::MI / 2), mi = (P % (T::MI / 2)) * 2;
-  const bf16x8_t b = __builtin_shufflevector(f.b[ni][0], f.b[ni][1], 0, 1, 2, 3, 4, 5, 6, 7);
-  acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, f.a[mi], acc[ni][mi], 0, 0, 0);
-  acc[ni][mi + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, f.a[mi + 1], acc[ni][mi + 1], 0, 0, 0);
+  acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[ni], f.a[mi], acc[ni][mi], 0, 0, 0);
+  acc[ni][mi + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[ni], f.a[mi + 1], acc[ni][mi + 1], 0, 0, 0);
 }
 
 // Where the columns of a B stored [K, N] are: the mainloop's `b_row` argument for B_KN tiles.
@@ -191,15 +181,17 @@ template <class T>
 struct Stager4W {
   static constexpr int kOutOfRange = 0x7ffffff0;
   static constexpr int KN_LANES = T::BN / 8;              // B_KN: lanes that cover one k row of the tile
-  static constexpr int KN_ROWS = T::THREADS / KN_LANES;   // B_KN: k rows per pass
-  static constexpr bool kDirect = T::DIRECT;
+    static constexpr bool kDirect = T::DIRECT;
   __amdgpu_buffer_rsrc_t a_rsrc, b_rsrc;
   int off[T::LOADS];
   u32x4_t reg[T::LOADS];
   int lds_off;    // byte offset inside an operand area of a stage, pass 0
   int kc;
-  int kn_row, kn_lds_off, kn_tile_bytes;   // B_KN: the lane's k row in pass 0, its LDS offset, bytes per K tile of B
+  int kn_tid, kn_tile_bytes;   // B_KN: the lane's place among the loading threads, bytes per K tile of B
   int wave_lds;   // direct-to-LDS form: where the wave's 8 rows of a pass start
+
+  // B_KN: the k row that the lane's load of pass `pass` belongs to
+  __device__ __forceinline__ int kn_row(int pass) const { return (pass * T::THREADS + kn_tid) / KN_LANES; }
 
   template <class ARow, class BRow>
   __device__ __forceinline__ void init(const char* a_base, ARow a_row, const char* b_base, BRow b_row) {
@@ -219,16 +211,16 @@ struct Stager4W {
 #pragma unroll
     for (int i = 0; i < T::A_LOADS; ++i) off[i] = (int)(a_row(r + i * T::ROWS_PER_PASS) + (uint32_t)(c * 16));
     if constexpr (T::B_KN) {
-      // lane (k row, group of 8 columns): 16 bytes = 8 columns of one k; a wave covers whole rows of the tile
-      kn_row = tid / KN_LANES;
-      const int n8 = tid % KN_LANES;
-      const int col = b_row.n0 + n8 * 8;
-      kn_lds_off = kn_row * T::PB + n8 * 16;
+      // the staged rows follow each other without gaps: pass i and thread tid fill 16-byte chunk i THREADS + tid of them
+      kn_tid = tid;
       kn_tile_bytes = (int)(b_row.ld_bytes * 64u);
 #pragma unroll
-      for (int i = 0; i < T::B_LOADS; ++i)
-        off[T::A_LOADS + i] = col < b_row.n ? (int)((uint32_t)(kn_row + i * KN_ROWS) * b_row.ld_bytes + (uint32_t)col * 2u)
+      for (int i = 0; i < T::B_LOADS; ++i) {
+        const int row = kn_row(i), n8 = i * T::THREADS + tid - row * KN_LANES;
+        const int col = b_row.n0 + (n8 ^ (2 * swz_kn<T::BN>(row))) * 8;   // position n8 holds global chunk n8 ^ 2 swz_kn
+        off[T::A_LOADS + i] = col < b_row.n ? (int)((uint32_t)row * b_row.ld_bytes + (uint32_t)col * 2u)
                                             : kOutOfRange;   // columns past N read as zero
+      }
     } else {
 #pragma unroll
       for (int i = 0; i < T::B_LOADS; ++i)
@@ -239,28 +231,24 @@ struct Stager4W {
   // `kt` must be a valid K tile; a chunk past K reads as zero (lane offset pushed out of range)
   template <int I>
   __device__ __forceinline__ u32x4_t load_one(int kt, int K) const {
-    if constexpr (T::B_KN && I >= T::A_LOADS) {
-      const bool dead = kt * 64 + kn_row + (I - T::A_LOADS) * KN_ROWS >= K;
-      return __builtin_amdgcn_raw_buffer_load_b128(b_rsrc, dead ? kOutOfRange : off[I], kt * kn_tile_bytes, 0);
-    } else {
-      const bool dead = kt * 64 + kc >= K;
-      const int v = dead ? kOutOfRange : off[I];
-      return __builtin_amdgcn_raw_buffer_load_b128(I < T::A_LOADS ? a_rsrc : b_rsrc, v, kt * 128, 0);
-    }
+    const bool dead = kt * 64 + kc >= K;
+    const int v = dead ? kOutOfRange : off[I];
+    return __builtin_amdgcn_raw_buffer_load_b128(I < T::A_LOADS ? a_rsrc : b_rsrc, v, kt * 128, 0);
   }
-  // Direct-to-LDS form of load I ([N, K] operands): the wave's 64 lanes fill 8 rows x 128 bytes that are
+  // Direct-to-LDS form of load I (B stored [K, N]: below; else): the wave's 64 lanes fill 8 rows x 128 bytes that are
   // contiguous in the stage (lane l lands at byte 16 l), so the swizzle is applied on the global side: `off`
   // was built for the chunk that belongs at the lane's LDS position.  A chunk past K is pushed out of the
-  // buffer's range, for which zeros are written.
+  // buffer's range, for which zeros are written.  B stored [K, N]: the 64 lanes fill 1 KiB of k rows of BN elements.
   template <int I, bool WHOLE = false>
   __device__ __forceinline__ void issue_one(int kt, int K, char* stage) const {
     constexpr int area = I < T::A_LOADS ? 0 : T::A_BYTES;
     constexpr int pass = I < T::A_LOADS ? I : I - T::A_LOADS;
-    const bool dead = !WHOLE && kt * 64 + kc >= K;   // WHOLE: K is a whole number of K tiles, no chunk lies past it
+    constexpr bool kn = T::B_KN && I >= T::A_LOADS;   // rows of k, not chunks of k
+    const bool dead = !WHOLE && kt * 64 + (kn ? kn_row(pass) : kc) >= K;   // WHOLE: K is a whole number of K tiles, nothing lies past it
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass does not know this builtin
     __builtin_amdgcn_raw_ptr_buffer_load_lds(I < T::A_LOADS ? a_rsrc : b_rsrc,
                                              DITRON_LDS(stage + area + pass * T::ROWS_PER_PASS * T::ROW_BYTES + wave_lds), 16,
-                                             dead ? kOutOfRange : off[I], kt * 128, 0, 0);
+                                             dead ? kOutOfRange : off[I], kt * (kn ? kn_tile_bytes : 128), 0, 0);
 #else
     (void)dead; (void)stage;
 #endif
@@ -281,8 +269,7 @@ struct Stager4W {
   __device__ __forceinline__ void commit_one(char* stage) const {
     constexpr int area = I < T::A_LOADS ? 0 : T::A_BYTES;
     constexpr int pass = I < T::A_LOADS ? I : I - T::A_LOADS;
-    if constexpr (T::B_KN && I >= T::A_LOADS) *(u32x4_t*)(stage + area + kn_lds_off + pass * KN_ROWS * T::PB) = reg[I];
-    else *(u32x4_t*)(stage + area + lds_off + pass * T::ROWS_PER_PASS * T::ROW_BYTES) = reg[I];
+    *(u32x4_t*)(stage + area + lds_off + pass * T::ROWS_PER_PASS * T::ROW_BYTES) = reg[I];
   }
   template <int LO, int HI>
   __device__ __forceinline__ void commit_range(char* stage) const {
@@ -291,28 +278,53 @@ struct Stager4W {
 };
 
 // ------------------------------------------------------------------ 16 x 16 x 32 form
+// The transposing read beside direct-to-LDS loads.  A bare builtin call carries no alias information, and the compiler then
+// waits for every load in flight (vmcnt(0)) before it, as if it might read what they write: the loop below took three times
+// as long.  The restrict-qualified parameter gives it some; which loads have landed is the loop's own affair, as it is for
+// the ordinary reads.
+__device__ __forceinline__ bf16x4_t read_tr16(__attribute__((address_space(3))) s16x4_t* __restrict__ src) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_bit_cast(bf16x4_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(src));
+#else
+  return bf16x4_t{};
+#endif
+}
+
 template <class T>
 struct Frags16 {
   bf16x8_t a[T::MB];
-  bf16x8_t b[T::NB];
+  bf16x4_t b[T::NB][2];   // low and high four k of the fragment ([N, K] storage fills both with one read)
 };
 
 // Fragment read J of the 32-deep step KS (0 or 1) of the K tile whose A part is staged at `pa` and whose B part
-// at `pb`, in the order the slots below consume them: b0, a0 .. a[MB-1], b1 .. b[NB-1].  koff[KS]: the lane's
-// swizzled chunk offset.
+// at `pb`, in the order the slots below consume them: b0, a0 .. a[MB-1], b1 .. b[NB-1] (B stored [K, N]: two reads
+// per B fragment).  koff[KS]: the lane's swizzled chunk offset; b_off: the row of its column or, B stored [K, N], per
+// column block the 8 bytes it addresses in the transposing read.
 template <class T, int KS, int J>
-__device__ __forceinline__ void read_one16(Frags16<T>& f, const char* pa, const char* pb, int a_off, int b_off,
+__device__ __forceinline__ void read_one16(Frags16<T>& f, const char* pa, const char* pb, int a_off, const int* b_off,
                                             const int (&koff)[2]) {
-  if constexpr (J == 0) f.b[0] = *(const bf16x8_t*)(pb + b_off + koff[KS]);
-  else if constexpr (J <= T::MB) f.a[J - 1] = *(const bf16x8_t*)(pa + a_off + (J - 1) * 16 * 128 + koff[KS]);
-  else f.b[J - T::MB] = *(const bf16x8_t*)(pb + b_off + (J - T::MB) * 16 * 128 + koff[KS]);
+  constexpr int BR = T::B_READS;
+  if constexpr (J >= BR && J < BR + T::MB) {
+    f.a[J - BR] = *(const bf16x8_t*)(pa + a_off + (J - BR) * 16 * 128 + koff[KS]);
+  } else {
+    constexpr int JB = J < BR ? J : J - T::MB, NB_ = JB / BR;
+    if constexpr (T::B_KN) {
+      const char* src = pb + b_off[NB_] + (KS * 32 + (JB % BR) * 4) * T::PB;
+      f.b[NB_][JB % BR] = read_tr16((__attribute__((address_space(3))) s16x4_t*)DITRON_LDS(src));
+    } else {
+      const bf16x8_t v = *(const bf16x8_t*)(pb + b_off[0] + NB_ * 16 * 128 + koff[KS]);
+      f.b[NB_][0] = __builtin_shufflevector(v, v, 0, 1, 2, 3);
+      f.b[NB_][1] = __builtin_shufflevector(v, v, 4, 5, 6, 7);
+    }
+  }
 }
 
 // MFMA I (0..3) of slot S of a step: column block S / (MB / 4), row block 4 (S % (MB / 4)) + I.
 template <class T, int S, int I>
 __device__ __forceinline__ void mma_one16(typename T::Acc16& acc, const Frags16<T>& f) {
   constexpr int nb = S / (T::MB / 4), mb = (S % (T::MB / 4)) * 4 + I;
-  acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.b[nb], f.a[mb], acc[nb][mb], 0, 0, 0);
+  const bf16x8_t b = __builtin_shufflevector(f.b[nb][0], f.b[nb][1], 0, 1, 2, 3, 4, 5, 6, 7);
+  acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, f.a[mb], acc[nb][mb], 0, 0, 0);
 }
 
 // The `n` loads of a step are spread evenly over its `slots` slots: load i goes into slot i * slots / n.  Which load
@@ -347,16 +359,25 @@ constexpr int load_in_slot(int s, int n, int slots) {
 template <class T, bool WHOLE, class ARow, class BRow>
 __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const char* a_base, ARow a_row,
                                                      const char* b_base, BRow b_row, int K, char* lds) {
-  constexpr int MB = T::MB, NB = T::NB, READS = MB + NB, AL = T::A_LOADS, BL = T::B_LOADS;
+  constexpr int MB = T::MB, NB = T::NB, READS = MB + T::B_READS * NB, AL = T::A_LOADS, BL = T::B_LOADS;
   constexpr int SLOTS = MB * NB / 4;   // per step
-  constexpr int PIECE = T::A_BYTES, D = T::DEPTH;
-  static_assert(MB % 4 == 0 && READS <= 2 * SLOTS && AL <= SLOTS && BL <= SLOTS && T::B_BYTES <= T::A_BYTES,
-                "at most two reads and one load per slot; a B part fits in a piece");
+  constexpr int PIECE = T::PIECE_BYTES, D = T::DEPTH;
+  static_assert(MB % 4 == 0 && READS <= (T::B_KN ? 3 : 2) * SLOTS && AL <= SLOTS && BL <= SLOTS,
+                "at most two reads (B stored [K, N]: three) and one load per slot");
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wm = wave / 2, wn = wave % 2;
   const int lr = lane & 15, lq = lane >> 4;
   const int a_off = (wm * T::WTM + lr) * T::ROW_BYTES;
-  const int b_off = (wn * T::WTN + lr) * T::ROW_BYTES;
+  int b_off[T::B_KN ? NB : 1];
+  if constexpr (T::B_KN) {
+    // inside its group of 16 lanes (k rows 8 lq .. + 3, + 4 with the second read), lane r points at k row r / 4, columns
+    // 4 (r % 4) .. + 3 of the 16
+    const int row = lq * 8 + (lr >> 2);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) b_off[nb] = row * T::PB + ((wn * NB + nb) ^ swz_kn<T::BN>(row)) * 32 + (lr & 3) * 8;
+  } else {
+    b_off[0] = (wn * T::WTN + lr) * T::ROW_BYTES;
+  }
   int koff[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) koff[ks] = ((ks * 4 + lq) ^ swz128_x16(lr)) * 16;
@@ -405,6 +426,7 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
       if constexpr (load_in_slot(S, AL, SLOTS) >= 0) load_a(std::integral_constant<int, load_in_slot(S, AL, SLOTS)>{}, kf, free_a);
       __builtin_amdgcn_sched_barrier(0);
       mma_one16<T, S, 3>(acc, f0);
+      if constexpr (2 * SLOTS + S < READS) read_one16<T, 1, 2 * SLOTS + S>(f1, cur_a, cur_b, a_off, b_off, koff);
       __builtin_amdgcn_sched_barrier(0);
     });
     wait_vmcnt<(D - 2) * (AL + BL) + AL>();   // this wave's part of tile kt+1 has landed (loads return in order); the younger ones may be in flight
@@ -422,6 +444,7 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
       if constexpr (load_in_slot(S, BL, SLOTS) >= 0) load_b(std::integral_constant<int, load_in_slot(S, BL, SLOTS)>{}, kf, free_b);
       __builtin_amdgcn_sched_barrier(0);
       mma_one16<T, S, 3>(acc, f1);
+      if constexpr (2 * SLOTS + S < READS) read_one16<T, 0, 2 * SLOTS + S>(f0, nxt_a, nxt_b, a_off, b_off, koff);
       __builtin_amdgcn_sched_barrier(0);
     });
     ia = wrap(ia + 2);
@@ -581,8 +604,8 @@ __device__ __forceinline__ void gemm_mainloop_f8(typename T::Acc16& acc, const c
 //   every other slot         : global loads of tile kt+2, each after the LDS store that frees
 //                               its register
 // The body is branch-free (past the end the last tile is staged again into a free stage).
-// On entry the LDS stages must be idle (every wave of the work-group past its last access to them): the
-// direct-to-LDS staging starts writing them with its first instruction.  On exit none of the wave's loads
+// On entry the LDS stages must be idle (every wave of the work-group past its last access to them): they are written
+// from the first instruction on.  On exit none of the wave's loads
 // is in flight; other waves may still be reading fragments, so a barrier precedes any reuse of the stages.
 template <class T, class ARow, class BRow>
 __device__ __forceinline__ void gemm_mainloop(typename T::Acc& acc, const char* a_base, ARow a_row,
@@ -602,12 +625,7 @@ __device__ __forceinline__ void gemm_mainloop(typename T::Acc& acc, const char* 
   const int wm = wave / 2, wn = wave % 2;
   const int lr = lane & 31, lh = lane >> 5;
   const int a_off = (wm * T::WTM + lr) * T::ROW_BYTES;
-  // [N, K] storage: the row of the lane's column.  [K, N] storage: the 8-byte chunk the lane
-  // addresses in the transposing read: inside its group of 16 lanes, lane r points at k row r/4,
-  // columns 4 (r % 4) .. +3; the group serves 16 columns, the two halves of the wave 8 k each.
-  const int b_off = T::B_KN ? T::A_BYTES + (((lane & 15) >> 2) + lh * 8) * T::PB +
-                                  (wn * T::WTN + ((lane >> 4) & 1) * 16 + (lane & 3) * 4) * 2
-                            : T::A_BYTES + (wn * T::WTN + lr) * T::ROW_BYTES;
+  const int b_off = T::A_BYTES + (wn * T::WTN + lr) * T::ROW_BYTES;
   int koff[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) koff[ks] = ((ks * 2 + lh) ^ swz128(lr)) * 16;
@@ -622,47 +640,6 @@ __device__ __forceinline__ void gemm_mainloop(typename T::Acc& acc, const char* 
   const int kt_last = kt_all - 1;
   Stager4W<T> st;
   st.init(a_base, a_row, b_base, b_row);
-  if constexpr (Stager4W<T>::kDirect) {
-    // Operands go from global memory straight into the LDS stages.  K tiles 0 and 1 are requested together;
-    // inside the loop the loads of a K tile are issued over the 2 PAIRS slots that follow the barrier which
-    // frees its stage (the last step of iteration kt: tile kt+2 into the stage of tile kt; the first step of
-    // the next iteration: the rest of that tile), and have to be there at the next barrier.
-    st.template issue_range<0, LOADS>(0, K, lds);
-    st.template issue_range<0, LOADS>(min(1, kt_last), K, lds + T::STAGE_BYTES);
-    wait_vmcnt<LOADS>();
-    barrier_no_drain();
-    Frags4W<T> f0, f1;
-    read_range<T, 0, 0, READS>(f0, lds, a_off, b_off, koff);
-    for (int kt = 0; kt < kt_all; ++kt) {
-      char* cur = lds + (kt & 1) * T::STAGE_BYTES;
-      char* nxt = lds + ((kt + 1) & 1) * T::STAGE_BYTES;
-      const int kf = min(kt + 2, kt_last), kg = min(kt + 1, kt_last);
-      static_for<0, SLOTS>([&](auto sl) {
-        constexpr int S = decltype(sl)::value, PART = S / PAIRS, J = S % PAIRS;
-        if constexpr (S == 3 * PAIRS) {
-          wait_vmcnt0();     // this wave's part of tile kt+1 has landed
-          wait_lgkmcnt0();   // every read of tile kt has returned
-          barrier_no_drain();
-        }
-        mma_pair<T, J>(acc, (PART & 1) ? f1 : f0);
-        if constexpr (PART == 0) read_range<T, 1, J * READS / PAIRS, (J + 1) * READS / PAIRS>(f1, cur, a_off, b_off, koff);
-        if constexpr (PART == 1) read_range<T, 2, J * READS / PAIRS, (J + 1) * READS / PAIRS>(f0, cur, a_off, b_off, koff);
-        if constexpr (PART == 2 && J < T::HALF)
-          read_range<T, 3, J * READS / T::HALF, (J + 1) * READS / T::HALF>(f1, cur, a_off, b_off, koff);
-        if constexpr (PART == 3 && J < T::HALF)
-          read_range<T, 0, J * READS / T::HALF, (J + 1) * READS / T::HALF>(f0, nxt, a_off, b_off, koff);
-        constexpr int W = S >= 3 * PAIRS ? S - 3 * PAIRS : S + PAIRS;   // position in the issue window
-        if constexpr (W < 2 * PAIRS) {
-          constexpr int LO = W * LOADS / (2 * PAIRS), HI = (W + 1) * LOADS / (2 * PAIRS);
-          if constexpr (S >= 3 * PAIRS) st.template issue_range<LO, HI>(kf, K, cur);
-          else st.template issue_range<LO, HI>(kg, K, nxt);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      });
-    }
-    wait_vmcnt0();   // the last iteration's requests (the last K tile once more) are not left in flight
-    return;
-  }
   // the first two K tiles are requested together (the second into registers that are free until the
   // loop starts), so the tile pays for one cold round trip to memory, not two in a row
   st.template fetch_range<0, LOADS>(0, K);
@@ -704,61 +681,11 @@ __device__ __forceinline__ void gemm_mainloop(typename T::Acc& acc, const char* 
   }
 }
 
-// Mainloop for tiles whose operands stream from HBM rather than from the L2 (the grouped GEMM's expert
-// weights): what bounds such a tile is the bytes a compute unit has in flight, so the two stages above
-// (one K tile requested ahead: 32 KiB at the 128 x 128 tile, about 32 GB/s per unit at 2 us of memory
-// latency) become a ring of NST stages filled by direct-to-LDS loads, NST - 1 K tiles ahead, one barrier
-// per K tile; the matrix work of a K tile (512 cycles at 128 x 128) is short against its loads.
-// Requests past the last K tile are out of the buffers' range: zeros are written, memory is not asked.
-template <class T, int NST, class ARow, class BRow>
-__device__ __forceinline__ void gemm_mainloop_ring(typename T::Acc32& acc, const char* a_base, ARow a_row,
-                                                      const char* b_base, BRow b_row, int K, char* lds) {
-  static_assert(T::DIRECT && !T::B_KN, "ring staging is written for [N, K] operands loaded straight into LDS");
-  constexpr int PAIRS = T::PAIRS, READS = T::READS, LOADS = T::LOADS;
-  static_assert((NST - 2) * LOADS <= 63 && NST >= 3, "wait-count immediate");
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int wm = wave / 2, wn = wave % 2;
-  const int lr = lane & 31, lh = lane >> 5;
-  const int a_off = (wm * T::WTM + lr) * T::ROW_BYTES;
-  const int b_off = T::A_BYTES + (wn * T::WTN + lr) * T::ROW_BYTES;
-  int koff[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) koff[ks] = ((ks * 2 + lh) ^ swz128(lr)) * 16;
-#pragma unroll
-  for (int ni = 0; ni < T::NI; ++ni)
-#pragma unroll
-    for (int mi = 0; mi < T::MI; ++mi)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[ni][mi][v] = 0.f;
-  const int kt_all = (K + 63) / 64;
-  Stager4W<T> st;
-  st.init(a_base, a_row, b_base, b_row);
-#pragma unroll
-  for (int j = 0; j < NST - 1; ++j) st.template issue_range<0, LOADS>(j, K, lds + j * T::STAGE_BYTES);
-#pragma unroll 1
-  for (int kt = 0; kt < kt_all; ++kt) {
-    wait_vmcnt<(NST - 2) * LOADS>();   // this wave's part of tile kt has landed (loads return in order)
-    barrier_no_drain();                // ... everybody's, and every wave is past its reads of tile kt - 1
-    st.template issue_range<0, LOADS>(kt + NST - 1, K, lds + ((kt + NST - 1) % NST) * T::STAGE_BYTES);
-    const char* cur = lds + (kt % NST) * T::STAGE_BYTES;
-    Frags4W<T> f0, f1;
-    read_range<T, 0, 0, READS>(f0, cur, a_off, b_off, koff);
-    read_range<T, 1, 0, READS>(f1, cur, a_off, b_off, koff);
-    static_for<0, PAIRS>([&](auto j) { mma_pair<T, decltype(j)::value>(acc, f0); });
-    read_range<T, 2, 0, READS>(f0, cur, a_off, b_off, koff);
-    static_for<0, PAIRS>([&](auto j) { mma_pair<T, decltype(j)::value>(acc, f1); });
-    read_range<T, 3, 0, READS>(f1, cur, a_off, b_off, koff);
-    static_for<0, PAIRS>([&](auto j) { mma_pair<T, decltype(j)::value>(acc, f0); });
-    static_for<0, PAIRS>([&](auto j) { mma_pair<T, decltype(j)::value>(acc, f1); });
-  }
-  wait_vmcnt0();   // the requests past the end have completed before the stages are used for anything else
-}
-
-// The same ring with the two jobs given to different waves: a work-group of eight waves, waves 0-3 (one per
-// SIMD) only read fragments and issue MFMAs, waves 4-7 only issue the loads.  A wave issues in order, so in
-// the form above the eight load instructions of a K tile (512 cycles of address-unit time per compute unit)
-// and its 512 cycles of matrix work follow one another; here they overlap.  Returns true in the computing
-// waves (which hold the accumulators) and false in the loading waves, whose requests have all completed.
+// Mainloop over a ring of NST stages filled by direct-to-LDS loads, NST - 1 K tiles ahead, one barrier per K tile, for a
+// work-group of eight waves: waves 0-3 (one per SIMD) only read fragments and issue MFMAs, waves 4-7 only issue the loads.
+// A wave issues in order, so the load instructions of a K tile and its matrix work would otherwise follow one another.
+// Requests past the last K tile are out of the buffers' range: zeros are written, memory is not asked.  Returns true in the
+// computing waves (which hold the accumulators) and false in the loading waves, whose requests have all completed.
 template <class T, int NST, class ARow, class BRow>
 __device__ __forceinline__ bool gemm_mainloop_ring_split(typename T::Acc32& acc, const char* a_base, ARow a_row,
                                                             const char* b_base, BRow b_row, int K, char* lds) {

@@ -29,9 +29,9 @@ typedef GemmTile4W<256, 192, false, true, true, true> TileBigF8_192;
 // requests one K tile ahead, which is less than the L2 takes under load: [1024 x 8192] x [8192 x 3696], operands resident,
 // 73 -> 57 us; 0.53 -> 0.38 us per K tile of a work-group, of which 0.34 are the 768 cycles of its LDS traffic.)
 typedef GemmTile4W<128, 128, false, true, true> TileSmall;
-// The same two sizes for B stored [K, N] (register staging, two LDS stages, 32 x 32 x 16 MFMA).
-typedef GemmTile4W<256, 256, true> TileBigKN;
-typedef GemmTile4W<128, 128, true> TileSmallKN;
+// The same for B stored [K, N].
+typedef GemmTile4W<256, 256, true, true, true> TileBigKN;
+typedef GemmTile4W<128, 128, true, true, true> TileSmallKN;
 // The MoE grouped GEMM: 4 waves as 2 x 2.  An expert's rows are padded to whole row tiles, so the row
 // tile is 128 unless the experts are large or the 128-row tiles would need more rounds (choose_moe_tile).
 constexpr int kMoeBlockM = 128;   // the smallest row tile: what the upper bound on the tile count assumes
@@ -96,7 +96,7 @@ inline double tiling_cost(long tiles, int block_n) {
   return work * ((double)full + (rest ? 0.55 + 0.45 * (double)rest / 256.0 : 0.0));
 }
 
-// narrow_ok: the caller has the 224-column tile (AllGather-GEMM with B stored [N, K]; the column counts of the
+// narrow_ok: the caller has the 224-column and 192-column tiles (AllGather-GEMM with B stored [N, K]; the column counts of the
 // GEMM-ReduceScatter and GEMM + AllReduce shapes of the paper's tables are whole rounds of 256-column tiles)
 inline TileChoice choose_tile(int m, int n, int /*k*/, bool narrow_ok = false) {
   TileChoice t{};

@@ -568,10 +568,11 @@ extern "C" ditron_status_t ditron_moe_ag_grouped_gemm(
   g.epoch = epoch;
   g.spin_limit = tune.spin_limit;
   g.wait = mode != Mode::kPreset;
-  if (w_layout == DITRON_B_KN) {   // [hidden, inter] weights: the column block is 128 or 256 (a 192-column row does not split over the loading lanes)
+  if (w_layout == DITRON_B_KN) {   // weights stored [hidden, inter]
     const bool wide = mt.block_n > 128;
-    if (mt.block_m == 256) return wide ? launch_moe_gemm<GemmTile4W<256, 256, true>>(g, max_tiles, s) : launch_moe_gemm<GemmTile4W<256, 128, true>>(g, max_tiles, s);
-    return wide ? launch_moe_gemm<GemmTile4W<128, 256, true>>(g, max_tiles, s) : launch_moe_gemm<GemmTile4W<128, 128, true>>(g, max_tiles, s);
+    if (mt.block_m == 256) return wide ? launch_moe_gemm<GemmTile4W<256, 256, true, true, true>>(g, max_tiles, s) : launch_moe_gemm<GemmTile4W<256, 128, true, true, true>>(g, max_tiles, s);
+    if (mt.block_n == 192) return launch_moe_gemm<GemmTile4W<128, 192, true, true, true>>(g, max_tiles, s);
+    return wide ? launch_moe_gemm<GemmTile4W<128, 256, true, true, true>>(g, max_tiles, s) : launch_moe_gemm<GemmTile4W<128, 128, true, true, true>>(g, max_tiles, s);
   }
   if (mt.block_m == 256) {
     if (mt.block_n == 128) return launch_moe_gemm<GemmTile4W<256, 128>>(g, max_tiles, s);
@@ -580,9 +581,9 @@ extern "C" ditron_status_t ditron_moe_ag_grouped_gemm(
   // 128-row tiles: their operands are streamed (an expert's weights are read by one or two row tiles), so
   // they go through as deep a ring of LDS stages as fits
   switch (mt.block_n) {
-    case 128: return launch_moe_gemm<GemmTile4W<128, 128, false, true>, 5>(g, max_tiles, s);
+    case 128: return launch_moe_gemm<GemmTile4W<128, 128, false, true, true>>(g, max_tiles, s);
     case 192: return launch_moe_gemm<GemmTile4W<128, 192, false, true>, 4>(g, max_tiles, s);
-    default: return launch_moe_gemm<GemmTile4W<128, 256, false, true>, 3>(g, max_tiles, s);
+    default: return launch_moe_gemm<GemmTile4W<128, 256, false, true, true>>(g, max_tiles, s);
   }
 }
 
@@ -819,8 +820,9 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
   ditron_status_t st;
   if (w_layout == DITRON_B_KN) {
     const bool wide = mt.block_n > 128;
-    if (mt.block_m == 256) st = wide ? launch_moe_gemm<GemmTile4W<256, 256, true>>(g, max_tiles, s) : launch_moe_gemm<GemmTile4W<256, 128, true>>(g, max_tiles, s);
-    else st = wide ? launch_moe_gemm<GemmTile4W<128, 256, true>>(g, max_tiles, s) : launch_moe_gemm<GemmTile4W<128, 128, true>>(g, max_tiles, s);
+    if (mt.block_m == 256) st = wide ? launch_moe_gemm<GemmTile4W<256, 256, true, true, true>>(g, max_tiles, s) : launch_moe_gemm<GemmTile4W<256, 128, true, true, true>>(g, max_tiles, s);
+    else if (mt.block_n == 192) st = launch_moe_gemm<GemmTile4W<128, 192, true, true, true>>(g, max_tiles, s);
+    else st = wide ? launch_moe_gemm<GemmTile4W<128, 256, true, true, true>>(g, max_tiles, s) : launch_moe_gemm<GemmTile4W<128, 128, true, true, true>>(g, max_tiles, s);
   } else if (mt.block_m == 256) {
     st = mt.block_n == 128 ? launch_moe_gemm<GemmTile4W<256, 128>>(g, max_tiles, s) : launch_moe_gemm<TileBigDirect>(g, max_tiles, s);
   } else {
@@ -831,9 +833,9 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
     // work-groups, 113.6 with 768; 256 x 256 tiles 108-118).
     if (inter <= 256) st = launch_moe_gemm_walk<GemmTile4W<128, 128>>(g, max_tiles, 512, s); else
     switch (mt.block_n) {
-      case 128: st = launch_moe_gemm<GemmTile4W<128, 128, false, true>, 5>(g, max_tiles, s); break;
+      case 128: st = launch_moe_gemm<GemmTile4W<128, 128, false, true, true>>(g, max_tiles, s); break;
       case 192: st = launch_moe_gemm<GemmTile4W<128, 192, false, true>, 4>(g, max_tiles, s); break;
-      default: st = launch_moe_gemm<GemmTile4W<128, 256, false, true>, 3>(g, max_tiles, s); break;
+      default: st = launch_moe_gemm<GemmTile4W<128, 256, false, true, true>>(g, max_tiles, s); break;
     }
   }
   if (st != DITRON_OK) return st;

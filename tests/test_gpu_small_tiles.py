@@ -19,6 +19,7 @@ def B():
 
 
 from gpu_util import to_dev, bits, nk, AgGemmRun, GemmArRun  # noqa: E402
+from test_gpu_moe import _run_and_check  # noqa: E402
 
 
 def _ok(B, st, run):
@@ -30,16 +31,40 @@ def _ok(B, st, run):
 # less than a K tile, up to the three that the ring requests ahead, one more, two turns of the ring's seven pieces; whole
 # and ragged last K tiles.  2000 x 2056: 272 tiles, the last row and the last column of tiles ragged
 @pytest.mark.parametrize("k", [8, 64, 128, 136, 192, 200, 256, 448, 520])
-def test_128_row_tiles_are_bit_exact(B, k):
+@pytest.mark.parametrize("kn", [False, True], ids=["b_nk", "b_kn"])
+def test_128_row_tiles_are_bit_exact(B, k, kn):
     cfg = synth.CONFIGS[2].scaled(world=8, m_per_rank=250, n=2056, k=k, rank=5)
-    st, tc = B.tile_config(0, cfg.m, cfg.n, k)
+    st, tc = B.tile_config(4 if kn else 0, cfg.m, cfg.n, k)
     assert (st, tc["block_m"], tc["block_n"], tc["splits"]) == (B.OK, 128, 128, 1)
     shards, b = synth.ag_gemm_inputs(cfg, integer=True)
     run = AgGemmRun(B, 8, cfg.m_per_rank, cfg.n, k)
-    st = run([to_dev(s) for s in shards], to_dev(nk(b)), cfg.rank)
+    st = run([to_dev(s) for s in shards], to_dev(b if kn else nk(b)), cfg.rank, b_layout=B.B_KN if kn else B.B_NK)
     _ok(B, st, run)
     assert np.array_equal(bits(run.workspace), oag.gather(shards))
     assert np.array_equal(bits(run.c), formats.encode_bf16_rne(oag.ag_gemm(shards, b).astype(np.float32)))
+
+
+# 256-row tiles of B stored [k, n] over the same lengths (its ring has five pieces)
+@pytest.mark.parametrize("k", [56, 72, 128, 192, 320, 328])
+def test_256_row_tiles_of_a_kn_weight_are_bit_exact(B, k):
+    cfg = synth.CONFIGS[2].scaled(world=8, m_per_rank=505, n=3080, k=k, rank=2)
+    st, tc = B.tile_config(4, cfg.m, cfg.n, k)
+    assert (st, tc["block_m"], tc["block_n"]) == (B.OK, 256, 256)
+    shards, b = synth.ag_gemm_inputs(cfg, integer=True)
+    run = AgGemmRun(B, 8, cfg.m_per_rank, cfg.n, k)
+    _ok(B, run([to_dev(s) for s in shards], to_dev(b), cfg.rank, b_layout=B.B_KN), run)
+    assert np.array_equal(bits(run.c), formats.encode_bf16_rne(oag.ag_gemm(shards, b).astype(np.float32)))
+
+
+# the grouped GEMM's column blocks (128, 192, 256) with several K tiles, the last one ragged
+@pytest.mark.parametrize("t_r,inter,experts", [(128, 264, 64), (128, 1400, 16), (256, 1544, 8)])
+@pytest.mark.parametrize("hidden", [200, 456])
+@pytest.mark.parametrize("kn", [False, True], ids=["w_nk", "w_kn"])
+def test_moe_column_blocks_are_bit_exact(B, t_r, inter, experts, hidden, kn):
+    cfg = synth.CONFIGS[4].scaled(world=8, tokens_per_rank=t_r, k=hidden, n=inter, num_experts=experts, top_k=2,
+                                  num_local_experts=8, rank=0)
+    xs, ids, w = synth.moe_inputs(cfg, integer=True)
+    _run_and_check(B, cfg, xs, ids, w, 8 * t_r * 2, integer=True, kn=kn)
 
 
 # 2, 4 and 8 ranks: every one has its own number of vectors in flight; 5: the loop over any number of ranks.
