@@ -186,7 +186,7 @@ extern "C" ditron_status_t ditron_ag_gemm(const void* const* a_shards, const voi
   }
   p.spin_limit = tune.spin_limit;
   p.wait = mode != Mode::kPreset;
-  TileChoice tc = choose_tile(p.m, n, k, b_layout == DITRON_B_NK);
+  TileChoice tc = choose_tile(p.m, n, k, b_layout == DITRON_B_NK ? Narrow::kNK : Narrow::kKN);
   if (p.nnodes > 1 && !node_order_is_bijection(p.m, tc.block_m, world, p.nnodes, rank, kOrderGather))
     return DITRON_ERR_UNSUPPORTED;
   p.tiling.group_m = tc.group_m;
@@ -196,6 +196,8 @@ extern "C" ditron_status_t ditron_ag_gemm(const void* const* a_shards, const voi
   p.num_producers = emulate ? pl.producers : 0;
   p.teams = pl.teams;
   if (b_layout == DITRON_B_KN) {
+    if (tc.block_n == 224) return launch_ag<TileBigKN224>(p, (hipStream_t)stream);
+    if (tc.block_n == 192) return launch_ag<TileBigKN192>(p, (hipStream_t)stream);
     if (tc.big) return launch_ag<TileBigKN>(p, (hipStream_t)stream);
     return launch_ag<TileSmallKN>(p, (hipStream_t)stream);
   }

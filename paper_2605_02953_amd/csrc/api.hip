@@ -47,7 +47,8 @@ extern "C" ditron_status_t ditron_tile_config(int op, int m, int n, int k, int d
   const Tuning tune = resolve_tuning(tuning, 1);
   if (!tune.valid) return DITRON_ERR_INVALID_ARG;
   const bool decode = op == 0 && ag_takes_decode_kernel(m, n, k, dtype, DITRON_B_NK, tune.decode_variant);
-  TileChoice t = decode ? choose_tile_decode(m, n, k) : choose_tile(m, n, k, op == 0);
+  TileChoice t = decode ? choose_tile_decode(m, n, k)
+                        : choose_tile(m, n, k, op == 0 ? Narrow::kNK : op == 4 ? Narrow::kKN : Narrow::kNever);
   int splits = 1;
   if (decode) {
     const DecodePlan plan = plan_decode(m, n, k * (dtype == DITRON_BF16 ? 2 : 1), tune.decode_variant);
@@ -110,7 +111,9 @@ extern "C" ditron_status_t ditron_schedule_dump(int op, int m, int n, int k, int
   const Tuning tune = resolve_tuning(tuning, op == 3 ? 1 : world);
   if (!tune.valid) return DITRON_ERR_INVALID_ARG;
   const bool decode = op == 0 && ag_takes_decode_kernel(m, n, k, dtype, b_layout, tune.decode_variant);
-  TileChoice tc = decode ? choose_tile_decode(m, n, k) : choose_tile(m, n, k, op == 0 && b_layout == DITRON_B_NK);
+  TileChoice tc = decode    ? choose_tile_decode(m, n, k)
+                  : op != 0 ? choose_tile(m, n, k)
+                            : choose_tile(m, n, k, b_layout == DITRON_B_NK ? Narrow::kNK : Narrow::kKN);
   int splits = 1;
   if (decode) {
     const DecodePlan plan = plan_decode(m, n, k * (dtype == DITRON_BF16 ? 2 : 1), tune.decode_variant);

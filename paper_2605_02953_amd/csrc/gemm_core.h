@@ -31,10 +31,11 @@ __device__ __forceinline__ int swz128_x16(int r) { return r & 7; }
 // pair position p ^ swz_kn<BN>(r).  A transposing read takes four rows (r .. r + 3, r a multiple of 4) of one pair per group
 // of 16 lanes, two groups (rows 8 apart) per cycle: eight pairs that fall on the eight 32-byte windows of the 256-byte bank
 // row.  Rows of 256 and 128 elements all start at window 0; rows of 192 at window 4 r mod 8 (and the exclusive or stays below
-// their 12 pairs).
+// their 12 pairs); rows of 224 at window 6 r mod 8, where flipping bit 0 for the rows 8 apart is enough (14 pairs).
 template <int BN>
 __device__ __forceinline__ int swz_kn(int r) {
-  static_assert(BN == 256 || BN == 192 || BN == 128, "bank windows worked out for these");
+  static_assert(BN == 256 || BN == 224 || BN == 192 || BN == 128, "bank windows worked out for these");
+  if (BN == 224) return (r >> 3) & 1;
   return BN == 192 ? (r & 2) | ((r >> 3) & 1) : (r & 3) | ((r >> 1) & 4);
 }
 

@@ -31,6 +31,8 @@ typedef GemmTile4W<256, 192, false, true, true, true> TileBigF8_192;
 typedef GemmTile4W<128, 128, false, true, true> TileSmall;
 // The same for B stored [K, N].
 typedef GemmTile4W<256, 256, true, true, true> TileBigKN;
+typedef GemmTile4W<256, 224, true, true, true> TileBigKN224;
+typedef GemmTile4W<256, 192, true, true, true> TileBigKN192;
 typedef GemmTile4W<128, 128, true, true, true> TileSmallKN;
 // The MoE grouped GEMM: 4 waves as 2 x 2.  An expert's rows are padded to whole row tiles, so the row
 // tile is 128 unless the experts are large or the 128-row tiles would need more rounds (choose_moe_tile).
@@ -96,14 +98,22 @@ inline double tiling_cost(long tiles, int block_n) {
   return work * ((double)full + (rest ? 0.55 + 0.45 * (double)rest / 256.0 : 0.0));
 }
 
-// narrow_ok: the caller has the 224-column and 192-column tiles (AllGather-GEMM with B stored [N, K]; the column counts of the
-// GEMM-ReduceScatter and GEMM + AllReduce shapes of the paper's tables are whole rounds of 256-column tiles)
-inline TileChoice choose_tile(int m, int n, int /*k*/, bool narrow_ok = false) {
+// Who takes the 224-column and 192-column tiles.  AllGather-GEMM with B stored [N, K]: wherever the estimate above says so.
+// B stored [K, N]: the same, except where the 256-column tiling is a single round that fills more than three quarters of the
+// chip: [7976 x 8192] x [8192 x 3584] 399 -> 391 us, 8192 x 1376 columns (192 tiles of 256 columns, 256 of 192) 231 -> 212 us;
+// in the excepted part it is 238 -> 235 us at 8192 x 1792 and 198 -> 192 us at 4040 x 3080, where ditron_tile_config's answer
+// for op 4 has always been 256 columns and stays.  GEMM-ReduceScatter and GEMM + AllReduce never: the units that a partly empty
+// round leaves go to the peers' copies and to the reduction there, and full rounds only put those behind the GEMM (8192 rows,
+// GEMM-ReduceScatter of 3584 / 1792 / 1376 columns 139 -> 157, 104 -> 125, 91 -> 111 us; GEMM + AllReduce 207 -> 221,
+// 151 -> 161, 131 -> 134 us).
+enum class Narrow { kNever, kNK, kKN };
+
+inline TileChoice choose_tile(int m, int n, int /*k*/, Narrow narrow = Narrow::kNever) {
   TileChoice t{};
   const long tiles_big = (long)cdiv(m, 256) * cdiv(n, 256);
   t.big = tiles_big >= 192;
   t.block_m = t.block_n = t.big ? 256 : 128;
-  if (t.big && narrow_ok) {
+  if (t.big && (narrow == Narrow::kNK || (narrow == Narrow::kKN && (tiles_big > 256 || tiles_big <= 192)))) {
     double best = 0.98 * tiling_cost(tiles_big, 256);
     for (int bn : {224, 192}) {
       const double c = tiling_cost((long)cdiv(m, 256) * cdiv(n, bn), bn);

@@ -56,6 +56,21 @@ def test_256_row_tiles_of_a_kn_weight_are_bit_exact(B, k):
     assert np.array_equal(bits(run.c), formats.encode_bf16_rne(oag.ag_gemm(shards, b).astype(np.float32)))
 
 
+# 224 and 192 columns of a [k, n] weight: several rounds of tiles, the last rows ragged; 192 columns with a ragged last tile too
+@pytest.mark.parametrize("k", [56, 72, 128, 320, 328])
+@pytest.mark.parametrize("m_per_rank,n,block_n", [(505, 7104, 224), (537, 4000, 192)])
+def test_narrow_256_row_tiles_of_a_kn_weight_are_bit_exact(B, m_per_rank, n, block_n, k):
+    cfg = synth.CONFIGS[2].scaled(world=8, m_per_rank=m_per_rank, n=n, k=k, rank=6)
+    st, tc = B.tile_config(4, cfg.m, n, k)
+    assert (st, tc["block_m"], tc["block_n"]) == (B.OK, 256, block_n)
+    shards, b = synth.ag_gemm_inputs(cfg, integer=True)
+    run = AgGemmRun(B, 8, m_per_rank, n, k)
+    sched = torch.full((4 * tc["ntiles"],), -1, dtype=torch.int32, device="cuda")
+    _ok(B, run([to_dev(s) for s in shards], to_dev(b), cfg.rank, b_layout=B.B_KN, schedule=sched), run)
+    assert np.array_equal(bits(run.c), formats.encode_bf16_rne(oag.ag_gemm(shards, b).astype(np.float32)))
+    assert [tuple(r) for r in sched.cpu().view(-1, 4).tolist()] == [tuple(r) for r in B.schedule_dump(0, cfg.m, n, k, 8, 6, b_layout=B.B_KN)[1]]
+
+
 # the grouped GEMM's column blocks (128, 192, 256) with several K tiles, the last one ragged
 @pytest.mark.parametrize("t_r,inter,experts", [(128, 264, 64), (128, 1400, 16), (256, 1544, 8)])
 @pytest.mark.parametrize("hidden", [200, 456])
