@@ -150,8 +150,8 @@ ditron_status_t ditron_tile_row_order(int op, int m, int block_m, int world, int
  * [n, k] use the 128 x 32 tile of the decode kernel, which the [k, n] layout does not).
  * out[0]=BLOCK_M out[1]=BLOCK_N out[2]=GROUP_SIZE_M out[3]=chiplets used by the work-group
  * remap (0 = no remap) out[4]=tiles per chiplet per block out[5]=number of tiles
- * (ag_gemm / gemm_rs) out[6]=threads per work-group out[7]=operand staging of the tile engine (0 = through
- * registers, 1 = global memory straight into LDS; op 1 and 3 report the choice for B stored [n, k])
+ * (ag_gemm / gemm_rs) out[6]=threads per work-group out[7]=1 for a 256-row tile of
+ * op 0, 1 and 3, else 0 (a value kept for callers: every dense tile's operands go straight into LDS)
  * out[8]=work-groups that share the contraction of one output tile (decode-shaped ag_gemm; else 1): a
  * schedule dump then holds that many identical records per tile, tile after tile.  out[9]=0.
  * `tuning`: only decode_variant matters. */

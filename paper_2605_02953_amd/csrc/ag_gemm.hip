@@ -199,6 +199,7 @@ extern "C" ditron_status_t ditron_ag_gemm(const void* const* a_shards, const voi
     if (tc.block_n == 224) return launch_ag<TileBigKN224>(p, (hipStream_t)stream);
     if (tc.block_n == 192) return launch_ag<TileBigKN192>(p, (hipStream_t)stream);
     if (tc.big) return launch_ag<TileBigKN>(p, (hipStream_t)stream);
+    if (tc.block_n == 64) return launch_ag<TileSmallKN64>(p, (hipStream_t)stream);
     return launch_ag<TileSmallKN>(p, (hipStream_t)stream);
   }
   if (fp8) {

@@ -393,9 +393,10 @@ static ditron_status_t gemm_ar_impl(const void* a, const void* b, int b_layout, 
   p.num_xcd = tc.num_xcd;
   p.per_xcd = tc.per_xcd;
   const hipStream_t s = (hipStream_t)stream;
-  if (b_layout == DITRON_B_KN) return tc.big ? launch_ar<TileBigKN>(p, units, two_shot, s) : launch_ar<TileSmallKN>(p, units, two_shot, s);
-  if (!tc.big) return launch_ar<TileSmall>(p, units, two_shot, s);
-  return launch_ar<TileBigDirect>(p, units, two_shot, s);
+  const bool kn = b_layout == DITRON_B_KN;
+  if (tc.block_n == 64) return kn ? launch_ar<TileSmallKN64>(p, units, two_shot, s) : launch_ar<TileSmall64>(p, units, two_shot, s);
+  if (!tc.big) return kn ? launch_ar<TileSmallKN>(p, units, two_shot, s) : launch_ar<TileSmall>(p, units, two_shot, s);
+  return kn ? launch_ar<TileBigKN>(p, units, two_shot, s) : launch_ar<TileBigDirect>(p, units, two_shot, s);
 }
 
 extern "C" ditron_status_t ditron_gemm_ar(const void* a, const void* b, int b_layout, void* gemm_out,

@@ -31,10 +31,12 @@ __device__ __forceinline__ int swz128_x16(int r) { return r & 7; }
 // pair position p ^ swz_kn<BN>(r).  A transposing read takes four rows (r .. r + 3, r a multiple of 4) of one pair per group
 // of 16 lanes, two groups (rows 8 apart) per cycle: eight pairs that fall on the eight 32-byte windows of the 256-byte bank
 // row.  Rows of 256 and 128 elements all start at window 0; rows of 192 at window 4 r mod 8 (and the exclusive or stays below
-// their 12 pairs); rows of 224 at window 6 r mod 8, where flipping bit 0 for the rows 8 apart is enough (14 pairs).
+// their 12 pairs); rows of 224 at window 6 r mod 8, where flipping bit 0 for the rows 8 apart is enough (14 pairs);
+// rows of 64 at window 4 r mod 8, so bit 0 tells the rows 2 apart from each other and bit 1 those 8 apart (four pairs).
 template <int BN>
 __device__ __forceinline__ int swz_kn(int r) {
-  static_assert(BN == 256 || BN == 224 || BN == 192 || BN == 128, "bank windows worked out for these");
+  static_assert(BN == 256 || BN == 224 || BN == 192 || BN == 128 || BN == 64, "bank windows worked out for these");
+  if (BN == 64) return ((r >> 1) & 1) | ((r >> 2) & 2);
   if (BN == 224) return (r >> 3) & 1;
   return BN == 192 ? (r & 2) | ((r >> 3) & 1) : (r & 3) | ((r >> 1) & 4);
 }
@@ -96,7 +98,7 @@ __device__ __forceinline__ void barrier_no_drain() {
 // two bytes.
 template <int BM_, int BN_, bool B_KN_ = false, bool DIRECT_ = false, bool X16_ = false, bool F8_ = false>
 struct GemmTile4W {
-  static_assert((BM_ == 256 || BM_ == 128) && (BN_ == 256 || BN_ == 192 || BN_ == 128 || (X16_ && BN_ == 224)), "supported tile sides");
+  static_assert((BM_ == 256 || BM_ == 128) && (BN_ == 256 || BN_ == 192 || BN_ == 128 || (X16_ && BN_ == 224) || (X16_ && BM_ == 128 && BN_ == 64)), "supported tile sides");
   static_assert(!B_KN_ || X16_, "the 32 x 32 x 16 loop is written for [N, K] operands");
   static_assert(!X16_ || DIRECT_, "the 16 x 16 x 32 loop is written for the direct-to-LDS staging");
   static_assert(!F8_ || (X16_ && !B_KN_ && BM_ == 256 && BN_ >= 192), "the fp8 loop is written for 256-row tiles and direct-to-LDS staging");
@@ -115,9 +117,10 @@ struct GemmTile4W {
   // X16: a ring of 2 DEPTH + 1 operand pieces (the A part and the B part of a K tile are pieces of their own): DEPTH K
   // tiles are requested ahead.  256 rows: five pieces are all of the LDS.  128 rows: seven of ten (2 / 3 / 4 tiles ahead,
   // [1024 x 8192] x [8192 x 3696], operands resident: 66 / 57 / 57 us; 464 tiles of [2048 x 3696]: 123 / 109 / 111 us, so a
-  // second work-group on the unit, which 2 would leave room for, is worth less than the third tile in flight).
+  // second work-group on the unit, which 2 would leave room for, is worth less than the third tile in flight).  64 columns:
+  // nine, their calls stream the weight from memory.
   static constexpr int PIECE_BYTES = A_BYTES > B_BYTES ? A_BYTES : B_BYTES;
-  static constexpr int DEPTH = PIECE_BYTES <= 16 * 1024 ? 3 : 2;
+  static constexpr int DEPTH = BN == 64 ? 4 : PIECE_BYTES <= 16 * 1024 ? 3 : 2;
   static constexpr int PIECES = 2 * DEPTH + 1;
   static constexpr int LDS_BYTES = X16_ ? PIECES * PIECE_BYTES : NSTAGE * STAGE_BYTES;
   static constexpr int ROWS_PER_PASS = THREADS / 8;           // 32 rows per pass of 16-byte loads
@@ -328,21 +331,23 @@ __device__ __forceinline__ void mma_one16(typename T::Acc16& acc, const Frags16<
   acc[nb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, f.a[mb], acc[nb][mb], 0, 0, 0);
 }
 
-// The `n` loads of a step are spread evenly over its `slots` slots: load i goes into slot i * slots / n.  Which load
-// (or none, -1) belongs to slot s.
-constexpr int load_in_slot(int s, int n, int slots) {
-  for (int i = 0; i < n; ++i)
-    if (i * slots / n == s) return i;
-  return -1;
+// The N loads of a step are spread evenly over its SLOTS slots: load i goes into slot i * SLOTS / N.  Calls `load` for those
+// of slot S.
+template <int S, int N, int SLOTS, class F>
+__device__ __forceinline__ void loads_of_slot(F&& load) {
+  static_for<0, N>([&](auto i) {
+    if constexpr (decltype(i)::value * SLOTS / N == S) load(i);
+  });
 }
 
 // K loop of the 16 x 16 x 32 form, operands loaded straight into LDS.  WHOLE: K is a whole number of 64-deep K
 // tiles and the loads carry no range test; otherwise the chunks of the last K tile that lie past K are written
 // as zeros (their offsets are pushed out of the buffer's range).  A K tile is two 32-deep steps of MB x NB MFMAs each, written as slots of
-// four MFMAs plus one fragment read and at most one load.  All fragments of a step are read during the step
+// four MFMAs plus one fragment read and at most one load (64-column tiles, whose K tile is bound by the bytes it waits
+// for and not by issue: up to four reads and two loads).  All fragments of a step are read during the step
 // before it, so a K tile's operands are no longer read once its second step starts: the barrier sits between
-// the two steps.  LDS is a ring of P = 2D + 1 pieces (D = 2: five of 32 KiB; D = 3, 128-row tiles: seven of
-// 16 KiB); the A part of K tile j lives in piece 2j mod P and its B part in piece (2j + 1) mod P, so D and a
+// the two steps.  LDS is a ring of P = 2D + 1 pieces (D = 2: five of 32 KiB; D = 3 and 4, 128-row tiles: seven
+// and nine of 16 KiB); the A part of K tile j lives in piece 2j mod P and its B part in piece (2j + 1) mod P, so D and a
 // half K tiles are resident:
 //   step 0 of tile kt : fragment reads of step 1; loads of A(kt+D) into the piece idle since the last barrier
 //   barrier           : every wave's part of tile kt+1 has landed, nobody reads tile kt any more
@@ -363,8 +368,8 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
   constexpr int MB = T::MB, NB = T::NB, READS = MB + T::B_READS * NB, AL = T::A_LOADS, BL = T::B_LOADS;
   constexpr int SLOTS = MB * NB / 4;   // per step
   constexpr int PIECE = T::PIECE_BYTES, D = T::DEPTH;
-  static_assert(MB % 4 == 0 && READS <= (T::B_KN ? 3 : 2) * SLOTS && AL <= SLOTS && BL <= SLOTS,
-                "at most two reads (B stored [K, N]: three) and one load per slot");
+  static_assert(MB % 4 == 0 && READS <= 4 * SLOTS && (T::BN == 64 || (READS <= (T::B_KN ? 3 : 2) * SLOTS && AL <= SLOTS && BL <= SLOTS)),
+                "at most two reads (B stored [K, N]: three) and one load per slot; 64 columns, whose K tile waits for its bytes: four and two");
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wm = wave / 2, wn = wave % 2;
   const int lr = lane & 15, lq = lane >> 4;
@@ -424,7 +429,8 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
       if constexpr (SLOTS + S < READS) read_one16<T, 1, SLOTS + S>(f1, cur_a, cur_b, a_off, b_off, koff);
       __builtin_amdgcn_sched_barrier(0);
       mma_one16<T, S, 2>(acc, f0);
-      if constexpr (load_in_slot(S, AL, SLOTS) >= 0) load_a(std::integral_constant<int, load_in_slot(S, AL, SLOTS)>{}, kf, free_a);
+      if constexpr (3 * SLOTS + S < READS) read_one16<T, 1, 3 * SLOTS + S>(f1, cur_a, cur_b, a_off, b_off, koff);
+      loads_of_slot<S, AL, SLOTS>([&](auto i) { load_a(i, kf, free_a); });
       __builtin_amdgcn_sched_barrier(0);
       mma_one16<T, S, 3>(acc, f0);
       if constexpr (2 * SLOTS + S < READS) read_one16<T, 1, 2 * SLOTS + S>(f1, cur_a, cur_b, a_off, b_off, koff);
@@ -442,7 +448,8 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
       if constexpr (SLOTS + S < READS) read_one16<T, 0, SLOTS + S>(f0, nxt_a, nxt_b, a_off, b_off, koff);
       __builtin_amdgcn_sched_barrier(0);
       mma_one16<T, S, 2>(acc, f1);
-      if constexpr (load_in_slot(S, BL, SLOTS) >= 0) load_b(std::integral_constant<int, load_in_slot(S, BL, SLOTS)>{}, kf, free_b);
+      if constexpr (3 * SLOTS + S < READS) read_one16<T, 0, 3 * SLOTS + S>(f0, nxt_a, nxt_b, a_off, b_off, koff);
+      loads_of_slot<S, BL, SLOTS>([&](auto i) { load_b(i, kf, free_b); });
       __builtin_amdgcn_sched_barrier(0);
       mma_one16<T, S, 3>(acc, f1);
       if constexpr (2 * SLOTS + S < READS) read_one16<T, 0, 2 * SLOTS + S>(f0, nxt_a, nxt_b, a_off, b_off, koff);

@@ -334,9 +334,13 @@ static ditron_status_t gemm_rs_impl(const void* a, const void* b, int b_layout, 
   p.teams = pl.teams;
   ditron_status_t st;
   if (b_layout == DITRON_B_KN) {
-    st = tc.big ? launch_rs<TileBigKN>(p, (hipStream_t)stream) : launch_rs<TileSmallKN>(p, (hipStream_t)stream);
+    st = tc.big               ? launch_rs<TileBigKN>(p, (hipStream_t)stream)
+         : tc.block_n == 64 ? launch_rs<TileSmallKN64>(p, (hipStream_t)stream)
+                            : launch_rs<TileSmallKN>(p, (hipStream_t)stream);
   } else {
-    st = tc.big ? launch_rs<TileBigDirect>(p, (hipStream_t)stream) : launch_rs<TileSmall>(p, (hipStream_t)stream);
+    st = tc.big               ? launch_rs<TileBigDirect>(p, (hipStream_t)stream)
+         : tc.block_n == 64 ? launch_rs<TileSmall64>(p, (hipStream_t)stream)
+                            : launch_rs<TileSmall>(p, (hipStream_t)stream);
   }
   if (st != DITRON_OK) return st;
 

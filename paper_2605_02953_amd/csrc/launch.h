@@ -34,6 +34,10 @@ typedef GemmTile4W<256, 256, true, true, true> TileBigKN;
 typedef GemmTile4W<256, 224, true, true, true> TileBigKN224;
 typedef GemmTile4W<256, 192, true, true, true> TileBigKN192;
 typedef GemmTile4W<128, 128, true, true, true> TileSmallKN;
+// 128 x 64, four K tiles in flight (144 KiB), for problems of few 128 x 128 tiles: a unit's K tile is 24 KiB instead of 32, and
+// twice as many units share the weight (choose_tile).
+typedef GemmTile4W<128, 64, false, true, true> TileSmall64;
+typedef GemmTile4W<128, 64, true, true, true> TileSmallKN64;
 // The MoE grouped GEMM: 4 waves as 2 x 2.  An expert's rows are padded to whole row tiles, so the row
 // tile is 128 unless the experts are large or the 128-row tiles would need more rounds (choose_moe_tile).
 constexpr int kMoeBlockM = 128;   // the smallest row tile: what the upper bound on the tile count assumes
@@ -108,11 +112,18 @@ inline double tiling_cost(long tiles, int block_n) {
 // 151 -> 161, 131 -> 134 us).
 enum class Narrow { kNever, kNK, kKN };
 
-inline TileChoice choose_tile(int m, int n, int /*k*/, Narrow narrow = Narrow::kNever) {
+inline TileChoice choose_tile(int m, int n, int k, Narrow narrow = Narrow::kNever) {
   TileChoice t{};
   const long tiles_big = (long)cdiv(m, 256) * cdiv(n, 256);
   t.big = tiles_big >= 192;
   t.block_m = t.block_n = t.big ? 256 : 128;
+  // Half as wide where that many tiles still fit the chip in one round and the K loop is what the call spends its time on.
+  // AllGather-GEMM, B stored [K, N] ([N, K]: the decode kernel): 64 x 3584, K 8192 56.3 -> 41.1 us; 1024 x 2048, K 4096 (256 of
+  // these tiles) 48.5 -> 43.7.  GEMM-ReduceScatter and GEMM + AllReduce need units for the peers' copies and the reduction
+  // beside the tiles, so only up to 128 of them, and long contractions: 128 x 8192, K 3584 31.0 -> 27.1 us and 36.0 -> 33.2;
+  // not so 128 x 8192, K 512 (19.7 -> 21.2), 128 x 16384, K 1024 and 512 x 4096, K 2048 (256 tiles; 30.3 -> 37.5, 28.8 -> 40.4).
+  const long tiles_small = (long)cdiv(m, 128) * cdiv(n, 128);
+  if (narrow == Narrow::kNever ? tiles_small <= 64 && k >= 1536 : tiles_small <= 128 && k >= 512) t.block_n = 64;
   if (t.big && (narrow == Narrow::kNK || (narrow == Narrow::kKN && (tiles_big > 256 || tiles_big <= 192)))) {
     double best = 0.98 * tiling_cost(tiles_big, 256);
     for (int bn : {224, 192}) {

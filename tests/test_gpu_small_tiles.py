@@ -71,6 +71,60 @@ def test_narrow_256_row_tiles_of_a_kn_weight_are_bit_exact(B, m_per_rank, n, blo
     assert [tuple(r) for r in sched.cpu().view(-1, 4).tolist()] == [tuple(r) for r in B.schedule_dump(0, cfg.m, n, k, 8, 6, b_layout=B.B_KN)[1]]
 
 
+# 128 x 64 tiles, GEMM-ReduceScatter (plain, fused) and GEMM + AllReduce: from the shortest contraction that takes them, whole
+# and ragged last K tiles, at several places of the ring's nine pieces; ragged rows and columns, one tile and 64
+@pytest.mark.parametrize("k", [1536, 1544, 1608, 1728])
+@pytest.mark.parametrize("m_per_rank,n", [(8, 64), (15, 1000), (32, 4096)])
+@pytest.mark.parametrize("kn", [False, True], ids=["b_nk", "b_kn"])
+def test_64_column_tiles_reduce_bit_exact(B, m_per_rank, n, k, kn):
+    world, d = 8, 3
+    cfg = synth.CONFIGS[3].scaled(world=world, m_per_rank=m_per_rank, n=n, k=k)
+    layout = B.B_KN if kn else B.B_NK
+    for op in (1, 3):
+        st, tc = B.tile_config(op, cfg.m, n, k)
+        assert (st, tc["block_m"], tc["block_n"]) == (B.OK, 128, 64)
+    a_list, b_list = synth.gemm_rs_inputs(cfg, integer=True)
+    parts = [oar.partial_bits(a, b) for a, b in zip(a_list, b_list)]
+    full = oar.allreduce_partials_f32_ordered(parts)
+    mine = slice(d * m_per_rank, (d + 1) * m_per_rank)
+    a_dev, b_dev = to_dev(a_list[d]), to_dev(b_list[d] if kn else nk(b_list[d]))
+    ar = GemmArRun(B, world, cfg.m, n, k)
+    peers = [None if s == d else to_dev(parts[s]) for s in range(world)]
+    st = B.gemm_ar(a_dev, b_dev, layout, ar.gemm_out, peers, ar.out, ar.signals, ar.status, None, cfg.m, n, k, world, d, 1,
+                   B.EMULATE_PRODUCER)
+    _ok(B, st, ar)
+    assert np.array_equal(bits(ar.gemm_out), parts[d]) and np.array_equal(bits(ar.out), full)
+    blocks = [None if s == d else to_dev(parts[s][mine]) for s in range(world)]
+    signals = torch.zeros(B.signal_words(world, 1), dtype=torch.int32, device="cuda")
+    zeros = lambda *shape: torch.zeros(shape, dtype=torch.int16, device="cuda")   # noqa: E731
+    gemm_out, scatter, out, status = zeros(cfg.m, n), zeros(world, m_per_rank, n), zeros(m_per_rank, n), ar.status
+    assert B.gemm_rs(a_dev, b_dev, layout, gemm_out, blocks, scatter, out, signals, status, None, None, cfg.m, n, k, world, d, 1, 1,
+                     B.EMULATE_PRODUCER) == B.OK
+    torch.cuda.synchronize()
+    assert np.array_equal(bits(gemm_out), parts[d]) and np.array_equal(bits(out), full[mine])
+    dsts = [zeros(world, m_per_rank, n) for _ in range(world)]
+    assert B.gemm_rs_fuse_scatter(a_dev, b_dev, layout, dsts, blocks, out.fill_(0x7FC0), signals, status, None, None, cfg.m, n, k,
+                                  world, d, 1, 2, B.EMULATE_PRODUCER) == B.OK
+    torch.cuda.synchronize()
+    assert status.cpu().tolist()[0] == 0
+    assert np.array_equal(bits(out), full[mine])
+    for r in range(world):
+        assert np.array_equal(bits(dsts[r][d]), parts[d][r * m_per_rank:(r + 1) * m_per_rank])
+
+
+# the same tile under AllGather-GEMM of a [k, n] weight, where shorter contractions and up to 128 tiles of 128 columns take it
+@pytest.mark.parametrize("k", [512, 520, 584, 640, 1160])
+@pytest.mark.parametrize("m_per_rank,n", [(8, 64), (15, 1000), (128, 2048)])
+def test_64_column_tiles_gather_bit_exact(B, m_per_rank, n, k):
+    cfg = synth.CONFIGS[2].scaled(world=8, m_per_rank=m_per_rank, n=n, k=k, rank=3)
+    st, tc = B.tile_config(4, cfg.m, n, k)
+    assert (st, tc["block_m"], tc["block_n"]) == (B.OK, 128, 64)
+    shards, b = synth.ag_gemm_inputs(cfg, integer=True)
+    run = AgGemmRun(B, 8, m_per_rank, n, k)
+    _ok(B, run([to_dev(s) for s in shards], to_dev(b), cfg.rank, b_layout=B.B_KN), run)
+    assert np.array_equal(bits(run.c), formats.encode_bf16_rne(oag.ag_gemm(shards, b).astype(np.float32)))
+
+
 # the grouped GEMM's column blocks (128, 192, 256) with several K tiles, the last one ragged
 @pytest.mark.parametrize("t_r,inter,experts", [(128, 264, 64), (128, 1400, 16), (256, 1544, 8)])
 @pytest.mark.parametrize("hidden", [200, 456])
