@@ -192,7 +192,7 @@ extern "C" ditron_status_t ditron_ag_gemm(const void* const* a_shards, const voi
   p.tiling.group_m = tc.group_m;
   p.tiling.num_xcd = tc.num_xcd;
   p.tiling.per_xcd = tc.per_xcd;
-  const ProducerPlan pl = plan_producers((size_t)p.m * k * esize, world);
+  const ProducerPlan pl = plan_producers((size_t)p.m * k * esize, world, /*tiles_wait=*/true);
   p.num_producers = emulate ? pl.producers : 0;
   p.teams = pl.teams;
   if (b_layout == DITRON_B_KN) {

@@ -608,7 +608,7 @@ extern "C" ditron_status_t ditron_ag_gemm_decode(const void* const* a_shards, co
   p.group_m = tc.group_m;
   p.num_xcd = tc.num_xcd;
   p.per_xcd = tc.per_xcd;
-  const ProducerPlan pl = plan_producers(a_bytes, world);
+  const ProducerPlan pl = plan_producers(a_bytes, world, /*tiles_wait=*/true);
   p.num_producers = emulate ? pl.producers : 0;
   p.teams = pl.teams;
   p.npm = cdiv(p.m, plan.block_m);

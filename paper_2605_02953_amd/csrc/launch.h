@@ -198,9 +198,15 @@ inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 struct ProducerPlan {
   int producers, teams;
 };
-inline ProducerPlan plan_producers(size_t total_bytes, int nchunks) {
+// tiles_wait: nothing of the launch starts before a chunk is there (AllGather-GEMM), so a small transfer is spread further,
+// 128 KiB each over up to 64 work-groups: [512 x 4096] gathered, 6656 columns 47.0 -> 40.2 us for the call; [256 x 8192], 3584
+// columns 53.0 -> 46 (B stored [k, n] 57.8 -> 51); [512 x 8192] e4m3, 3584 columns 53.5 -> 45.7; [1024 x 8192], 3696 columns
+// 77.6 -> 73.5 (128 work-groups: 1 us more).  Not so beyond 32 MiB, where 512 KiB each are as many already ([2048 x 8192], 64 work-groups 134.5, 128
+// 136.4, 256 139.6 us), and not where the copies run beside the tiles (GEMM-ReduceScatter 128 x 8192: 28.7, 29.7 us).
+inline ProducerPlan plan_producers(size_t total_bytes, int nchunks, bool tiles_wait = false) {
   ProducerPlan pl{};
   size_t want = (total_bytes + (512u << 10) - 1) / (512u << 10);
+  if (tiles_wait) want = std::max(want, std::min<size_t>(64, (total_bytes + (128u << 10) - 1) / (128u << 10)));
   want = (want + 7) / 8 * 8;
   pl.producers = (int)(want < 8 ? 8 : (want > 256 ? 256 : want));
   pl.teams = nchunks < pl.producers ? nchunks : pl.producers;
