@@ -48,7 +48,7 @@ extern "C" ditron_status_t ditron_tile_config(int op, int m, int n, int k, int d
   if (!tune.valid) return DITRON_ERR_INVALID_ARG;
   const bool decode = op == 0 && ag_takes_decode_kernel(m, n, k, dtype, DITRON_B_NK, tune.decode_variant);
   TileChoice t = decode ? choose_tile_decode(m, n, k)
-                        : choose_tile(m, n, k, op == 0 ? Narrow::kNK : op == 4 ? Narrow::kKN : Narrow::kNever);
+                        : choose_tile(m, n, k, op == 0 ? Narrow::kNK : op == 4 ? Narrow::kKN : op == 3 ? Narrow::kAllReduce : Narrow::kNever);
   int splits = 1;
   if (decode) {
     const DecodePlan plan = plan_decode(m, n, k * (dtype == DITRON_BF16 ? 2 : 1), tune.decode_variant);
@@ -112,6 +112,7 @@ extern "C" ditron_status_t ditron_schedule_dump(int op, int m, int n, int k, int
   if (!tune.valid) return DITRON_ERR_INVALID_ARG;
   const bool decode = op == 0 && ag_takes_decode_kernel(m, n, k, dtype, b_layout, tune.decode_variant);
   TileChoice tc = decode    ? choose_tile_decode(m, n, k)
+                  : op == 3 ? choose_tile(m, n, k, Narrow::kAllReduce)
                   : op != 0 ? choose_tile(m, n, k)
                             : choose_tile(m, n, k, b_layout == DITRON_B_NK ? Narrow::kNK : Narrow::kKN);
   int splits = 1;

@@ -360,7 +360,7 @@ static ditron_status_t gemm_ar_impl(const void* a, const void* b, int b_layout, 
       p.part[s] = peer_partials[s];
     }
   }
-  const TileChoice tc = choose_tile(m, n, k_local);
+  const TileChoice tc = choose_tile(m, n, k_local, Narrow::kAllReduce);
   p.npm = cdiv(m, tc.block_m);
   p.npn = cdiv(n, tc.block_n);
   const int ntiles = p.npm * p.npn;
@@ -394,7 +394,6 @@ static ditron_status_t gemm_ar_impl(const void* a, const void* b, int b_layout, 
   p.per_xcd = tc.per_xcd;
   const hipStream_t s = (hipStream_t)stream;
   const bool kn = b_layout == DITRON_B_KN;
-  if (tc.block_n == 64) return kn ? launch_ar<TileSmallKN64>(p, units, two_shot, s) : launch_ar<TileSmall64>(p, units, two_shot, s);
   if (!tc.big) return kn ? launch_ar<TileSmallKN>(p, units, two_shot, s) : launch_ar<TileSmall>(p, units, two_shot, s);
   return kn ? launch_ar<TileBigKN>(p, units, two_shot, s) : launch_ar<TileBigDirect>(p, units, two_shot, s);
 }

@@ -110,7 +110,9 @@ inline double tiling_cost(long tiles, int block_n) {
 // round leaves go to the peers' copies and to the reduction there, and full rounds only put those behind the GEMM (8192 rows,
 // GEMM-ReduceScatter of 3584 / 1792 / 1376 columns 139 -> 157, 104 -> 125, 91 -> 111 us; GEMM + AllReduce 207 -> 221,
 // 151 -> 161, 131 -> 134 us).
-enum class Narrow { kNever, kNK, kKN };
+// kAllReduce: like kNever, and the two shapes (256 x 256, 128 x 128) and their rule are fixed: in the two-shot form a rank owns
+// every world-th tile, reduces it and broadcasts it, so the tiling is part of what the ranks agree on and what a call returns.
+enum class Narrow { kNever, kNK, kKN, kAllReduce };
 
 inline TileChoice choose_tile(int m, int n, int k, Narrow narrow = Narrow::kNever) {
   TileChoice t{};
@@ -119,11 +121,12 @@ inline TileChoice choose_tile(int m, int n, int k, Narrow narrow = Narrow::kNeve
   t.block_m = t.block_n = t.big ? 256 : 128;
   // Half as wide where that many tiles still fit the chip in one round and the K loop is what the call spends its time on.
   // AllGather-GEMM, B stored [K, N] ([N, K]: the decode kernel): 64 x 3584, K 8192 56.3 -> 41.1 us; 1024 x 2048, K 4096 (256 of
-  // these tiles) 48.5 -> 43.7.  GEMM-ReduceScatter and GEMM + AllReduce need units for the peers' copies and the reduction
-  // beside the tiles, so only up to 128 of them, and long contractions: 128 x 8192, K 3584 31.0 -> 27.1 us and 36.0 -> 33.2;
+  // these tiles) 48.5 -> 43.7.  GEMM-ReduceScatter needs units for the peers' copies and the reduction
+  // beside the tiles, so only up to 128 of them, and long contractions: 128 x 8192, K 3584 31.0 -> 27.1 us;
   // not so 128 x 8192, K 512 (19.7 -> 21.2), 128 x 16384, K 1024 and 512 x 4096, K 2048 (256 tiles; 30.3 -> 37.5, 28.8 -> 40.4).
   const long tiles_small = (long)cdiv(m, 128) * cdiv(n, 128);
-  if (narrow == Narrow::kNever ? tiles_small <= 64 && k >= 1536 : tiles_small <= 128 && k >= 512) t.block_n = 64;
+  const bool fits = narrow == Narrow::kNever ? tiles_small <= 64 && k >= 1536 : tiles_small <= 128 && k >= 512;
+  if (fits && narrow != Narrow::kAllReduce) t.block_n = 64;
   if (t.big && (narrow == Narrow::kNK || (narrow == Narrow::kKN && (tiles_big > 256 || tiles_big <= 192)))) {
     double best = 0.98 * tiling_cost(tiles_big, 256);
     for (int bn : {224, 192}) {

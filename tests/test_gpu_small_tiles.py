@@ -71,7 +71,7 @@ def test_narrow_256_row_tiles_of_a_kn_weight_are_bit_exact(B, m_per_rank, n, blo
     assert [tuple(r) for r in sched.cpu().view(-1, 4).tolist()] == [tuple(r) for r in B.schedule_dump(0, cfg.m, n, k, 8, 6, b_layout=B.B_KN)[1]]
 
 
-# 128 x 64 tiles, GEMM-ReduceScatter (plain, fused) and GEMM + AllReduce: from the shortest contraction that takes them, whole
+# 128 x 64 tiles, GEMM-ReduceScatter (plain, fused), beside GEMM + AllReduce, which keeps its tiles: from the shortest contraction that takes them, whole
 # and ragged last K tiles, at several places of the ring's nine pieces; ragged rows and columns, one tile and 64
 @pytest.mark.parametrize("k", [1536, 1544, 1608, 1728])
 @pytest.mark.parametrize("m_per_rank,n", [(8, 64), (15, 1000), (32, 4096)])
@@ -80,9 +80,9 @@ def test_64_column_tiles_reduce_bit_exact(B, m_per_rank, n, k, kn):
     world, d = 8, 3
     cfg = synth.CONFIGS[3].scaled(world=world, m_per_rank=m_per_rank, n=n, k=k)
     layout = B.B_KN if kn else B.B_NK
-    for op in (1, 3):
+    for op, block_n in ((1, 64), (3, 128)):   # a two-shot all-reduce deals tiles to ranks: its tiling is fixed
         st, tc = B.tile_config(op, cfg.m, n, k)
-        assert (st, tc["block_m"], tc["block_n"]) == (B.OK, 128, 64)
+        assert (st, tc["block_m"], tc["block_n"]) == (B.OK, 128, block_n)
     a_list, b_list = synth.gemm_rs_inputs(cfg, integer=True)
     parts = [oar.partial_bits(a, b) for a, b in zip(a_list, b_list)]
     full = oar.allreduce_partials_f32_ordered(parts)
