@@ -103,10 +103,10 @@ inline double tiling_cost(long tiles, int block_n) {
 }
 
 // Who takes the 224-column and 192-column tiles.  AllGather-GEMM with B stored [N, K]: wherever the estimate above says so.
-// B stored [K, N]: the same, except where the 256-column tiling is a single round that fills more than three quarters of the
-// chip: [7976 x 8192] x [8192 x 3584] 399 -> 391 us, 8192 x 1376 columns (192 tiles of 256 columns, 256 of 192) 231 -> 212 us;
-// in the excepted part it is 238 -> 235 us at 8192 x 1792 and 198 -> 192 us at 4040 x 3080, where ditron_tile_config's answer
-// for op 4 has always been 256 columns and stays.  GEMM-ReduceScatter and GEMM + AllReduce never: the units that a partly empty
+// B stored [K, N]: where the 256-column tiling leaves at least a quarter of a single round empty, 8192 x 1376 columns (192 tiles
+// of 256 columns, 256 of 192) 231 -> 212 us.  In the other cases it is 1 to 4 % (8192 x 1792 238 -> 235, 4040 x 3080 198 -> 192,
+// 7976 x 3584 399 -> 391 us) and ditron_tile_config's answer for op 4, 256 columns, stays.
+// GEMM-ReduceScatter and GEMM + AllReduce never: the units that a partly empty
 // round leaves go to the peers' copies and to the reduction there, and full rounds only put those behind the GEMM (8192 rows,
 // GEMM-ReduceScatter of 3584 / 1792 / 1376 columns 139 -> 157, 104 -> 125, 91 -> 111 us; GEMM + AllReduce 207 -> 221,
 // 151 -> 161, 131 -> 134 us).
@@ -127,7 +127,7 @@ inline TileChoice choose_tile(int m, int n, int k, Narrow narrow = Narrow::kNeve
   const long tiles_small = (long)cdiv(m, 128) * cdiv(n, 128);
   const bool fits = narrow == Narrow::kNever ? tiles_small <= 64 && k >= 1536 : tiles_small <= 128 && k >= 512;
   if (fits && narrow != Narrow::kAllReduce) t.block_n = 64;
-  if (t.big && (narrow == Narrow::kNK || (narrow == Narrow::kKN && (tiles_big > 256 || tiles_big <= 192)))) {
+  if (t.big && (narrow == Narrow::kNK || (narrow == Narrow::kKN && tiles_big <= 192))) {
     double best = 0.98 * tiling_cost(tiles_big, 256);
     for (int bn : {224, 192}) {
       const double c = tiling_cost((long)cdiv(m, 256) * cdiv(n, bn), bn);
