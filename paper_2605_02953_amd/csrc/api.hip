@@ -46,9 +46,9 @@ extern "C" ditron_status_t ditron_tile_config(int op, int m, int n, int k, int d
   if (dtype == DITRON_FP8_E4M3 && op != 0) return DITRON_ERR_UNSUPPORTED;
   const Tuning tune = resolve_tuning(tuning, 1);
   if (!tune.valid) return DITRON_ERR_INVALID_ARG;
-  const bool decode = op == 0 && ag_takes_decode_kernel(m, n, k, dtype, DITRON_B_NK, tune.decode_variant);
+  const bool decode = op == 0 && ag_takes_decode_kernel(m, n, k, dtype, DITRON_B_NK, tune.decode_variant, 1);
   TileChoice t = decode ? choose_tile_decode(m, n, k)
-                        : choose_tile(m, n, k, op == 0 ? Narrow::kNK : op == 4 ? Narrow::kKN : op == 3 ? Narrow::kAllReduce : Narrow::kNever);
+                        : choose_tile(m, n, k, op == 0 ? ag_narrow(dtype, DITRON_B_NK) : op == 4 ? Narrow::kKN : op == 3 ? Narrow::kAllReduce : Narrow::kNever, 1);
   int splits = 1;
   if (decode) {
     const DecodePlan plan = plan_decode(m, n, k * (dtype == DITRON_BF16 ? 2 : 1), tune.decode_variant);
@@ -87,7 +87,7 @@ extern "C" size_t ditron_ag_gemm_workspace_bytes(int m_per_rank, int n, int k, i
   const int esize = dtype == DITRON_BF16 ? 2 : 1;
   const int m = world * m_per_rank;
   const size_t gathered = (size_t)m * k * esize;
-  const bool decode = ag_takes_decode_kernel(m, n, k, dtype, b_layout, tune.decode_variant);
+  const bool decode = ag_takes_decode_kernel(m, n, k, dtype, b_layout, tune.decode_variant, tune.num_nodes);
   if (!decode) return gathered;
   // decode-shaped problems: the partial tiles of the split contraction follow the gathered operand
   const DecodePlan plan = plan_decode(m, n, k * esize, tune.decode_variant);
@@ -110,11 +110,9 @@ extern "C" ditron_status_t ditron_schedule_dump(int op, int m, int n, int k, int
   if (dtype == DITRON_FP8_E4M3 && (op != 0 || b_layout != DITRON_B_NK)) return DITRON_ERR_UNSUPPORTED;
   const Tuning tune = resolve_tuning(tuning, op == 3 ? 1 : world);
   if (!tune.valid) return DITRON_ERR_INVALID_ARG;
-  const bool decode = op == 0 && ag_takes_decode_kernel(m, n, k, dtype, b_layout, tune.decode_variant);
-  TileChoice tc = decode    ? choose_tile_decode(m, n, k)
-                  : op == 3 ? choose_tile(m, n, k, Narrow::kAllReduce)
-                  : op != 0 ? choose_tile(m, n, k)
-                            : choose_tile(m, n, k, b_layout == DITRON_B_NK ? Narrow::kNK : Narrow::kKN);
+  const bool decode = op == 0 && ag_takes_decode_kernel(m, n, k, dtype, b_layout, tune.decode_variant, tune.num_nodes);
+  TileChoice tc = decode ? choose_tile_decode(m, n, k)
+                         : choose_tile(m, n, k, op == 0 ? ag_narrow(dtype, b_layout) : op == 3 ? Narrow::kAllReduce : Narrow::kNever, op == 3 ? 1 : tune.num_nodes);
   int splits = 1;
   if (decode) {
     const DecodePlan plan = plan_decode(m, n, k * (dtype == DITRON_BF16 ? 2 : 1), tune.decode_variant);

@@ -323,7 +323,7 @@ static ditron_status_t gemm_rs_impl(const void* a, const void* b, int b_layout, 
   p.m_per_rank = m_r;
   p.chunks = chunks_per_slot;
   p.epoch = epoch;
-  TileChoice tc = choose_tile(m, n, k_local);
+  TileChoice tc = choose_tile(m, n, k_local, Narrow::kNever, p.nnodes);
   if (p.nnodes > 1 && !node_order_is_bijection(m, tc.block_m, world, p.nnodes, rank, kOrderScatter))
     return DITRON_ERR_UNSUPPORTED;
   p.tiling.group_m = tc.group_m;

@@ -112,12 +112,26 @@ inline double tiling_cost(long tiles, int block_n) {
 // 151 -> 161, 131 -> 134 us).
 // kAllReduce: like kNever, and the two shapes (256 x 256, 128 x 128) and their rule are fixed: in the two-shot form a rank owns
 // every world-th tile, reduces it and broadcasts it, so the tiling is part of what the ranks agree on and what a call returns.
-enum class Narrow { kNever, kNK, kKN, kAllReduce };
+enum class Narrow { kNever, kNK, kKN, kF8, kAllReduce };   // kF8: as kNK, e4m3 operands
 
-inline TileChoice choose_tile(int m, int n, int k, Narrow narrow = Narrow::kNever) {
+// 256-row tiles where they fill three quarters of the chip in one round, or where 128 x 128 tiles need so many rounds that a
+// round of larger ones is shorter all the same (a K tile of 256 x 256 takes a unit about 1.1 us, one of 128 x 128 0.38).
+// 952 x 11632 (728 tiles of 128 x 128, 184 of 256 x 256), us before and after: AllGather-GEMM K 4096 111 -> 91, B stored [k, n]
+// 120 -> 93, fp8 110 -> 62; GEMM-ReduceScatter over 4 ranks, K 1616 101 -> 59.
+// 2048 x 3000 (384 and 96 tiles): fp8 78 -> 57, GEMM-ReduceScatter 57 -> 48 (K 256: 44 -> 29),
+// AllGather-GEMM 79.0 -> 79.6, B stored [k, n] 85 -> 82.  2048 x 2176 (272 and 72 tiles): fp8 78 -> 57,
+// GEMM-ReduceScatter 47 -> 45 but 45.9 -> 46.9 with B stored [k, n] (2048 x 2560, 320 and 80 tiles: 50 -> 47), AllGather-GEMM 77.8 -> 79.3.
+// Several nodes keep the first rule alone: the node orders of the paper cover more shapes with 128-row tiles.
+inline bool takes_big_tiles(int m, int n, Narrow narrow, int nnodes) {
+  const long big = (long)cdiv(m, 256) * cdiv(n, 256), small = (long)cdiv(m, 128) * cdiv(n, 128);
+  if (big >= 192) return true;
+  return nnodes == 1 && narrow != Narrow::kAllReduce && small > (narrow == Narrow::kNK ? 512 : narrow == Narrow::kKN ? 383 : narrow == Narrow::kF8 ? 256 : 300);
+}
+
+inline TileChoice choose_tile(int m, int n, int k, Narrow narrow, int nnodes) {
   TileChoice t{};
   const long tiles_big = (long)cdiv(m, 256) * cdiv(n, 256);
-  t.big = tiles_big >= 192;
+  t.big = takes_big_tiles(m, n, narrow, nnodes);
   t.block_m = t.block_n = t.big ? 256 : 128;
   // Half as wide where that many tiles still fit the chip in one round and the K loop is what the call spends its time on.
   // AllGather-GEMM, B stored [K, N] ([N, K]: the decode kernel): 64 x 3584, K 8192 56.3 -> 41.1 us; 1024 x 2048, K 4096 (256 of
@@ -127,7 +141,7 @@ inline TileChoice choose_tile(int m, int n, int k, Narrow narrow = Narrow::kNeve
   const long tiles_small = (long)cdiv(m, 128) * cdiv(n, 128);
   const bool fits = narrow == Narrow::kNever ? tiles_small <= 64 && k >= 1536 : tiles_small <= 128 && k >= 512;
   if (fits && narrow != Narrow::kAllReduce) t.block_n = 64;
-  if (t.big && (narrow == Narrow::kNK || (narrow == Narrow::kKN && tiles_big <= 192))) {
+  if (t.big && (narrow == Narrow::kNK || narrow == Narrow::kF8 || (narrow == Narrow::kKN && tiles_big <= 192))) {
     double best = 0.98 * tiling_cost(tiles_big, 256);
     for (int bn : {224, 192}) {
       const double c = tiling_cost((long)cdiv(m, 256) * cdiv(n, bn), bn);
@@ -149,11 +163,14 @@ inline bool bf16_ag_is_decode_shaped(int m, int n) { return (long)cdiv(m, 128) *
 // loaders reserve offsets from 0x7ffffff0 up as "out of range, reads zero".
 inline bool fits_32bit(size_t rows, size_t cols, size_t esize) { return rows * cols * esize < 0x7ffffff0ull; }
 
-// fp8 takes the 256-row tiles of the tile engine where they fill three quarters of the chip (the bf16 rule), unless the
+// fp8 takes the 256-row tiles of the tile engine where takes_big_tiles says so, unless the
 // caller asks for a decode variant or an operand is too large for the engine's 32-bit offsets.
-inline bool ag_takes_decode_kernel(int m, int n, int k, int dtype, int b_layout, int decode_variant) {
+inline Narrow ag_narrow(int dtype, int b_layout) {
+  return dtype == DITRON_FP8_E4M3 ? Narrow::kF8 : b_layout == DITRON_B_NK ? Narrow::kNK : Narrow::kKN;
+}
+inline bool ag_takes_decode_kernel(int m, int n, int k, int dtype, int b_layout, int decode_variant, int nnodes) {
   if (dtype == DITRON_FP8_E4M3)
-    return decode_variant != 0 || (long)cdiv(m, 256) * cdiv(n, 256) < 192 || !fits_32bit(m, k, 1) || !fits_32bit(n, k, 1);
+    return decode_variant != 0 || !takes_big_tiles(m, n, Narrow::kF8, nnodes) || !fits_32bit(m, k, 1) || !fits_32bit(n, k, 1);
   return b_layout == DITRON_B_NK && bf16_ag_is_decode_shaped(m, n);
 }
 inline TileChoice choose_tile_decode(int /*m*/, int /*n*/, int /*k*/) {
@@ -202,9 +219,9 @@ struct ProducerPlan {
   int producers, teams;
 };
 // tiles_wait: nothing of the launch starts before a chunk is there (AllGather-GEMM), so a small transfer is spread further,
-// 128 KiB each over up to 64 work-groups: [512 x 4096] gathered, 6656 columns 47.0 -> 40.2 us for the call; [256 x 8192], 3584
-// columns 53.0 -> 46 (B stored [k, n] 57.8 -> 51); [512 x 8192] e4m3, 3584 columns 53.5 -> 45.7; [1024 x 8192], 3696 columns
-// 77.6 -> 73.5 (128 work-groups: 1 us more).  Not so beyond 32 MiB, where 512 KiB each are as many already ([2048 x 8192], 64 work-groups 134.5, 128
+// 128 KiB each over up to 64 work-groups: [512 x 4096] gathered, 6656 columns 47.3 -> 40.6 us for the call; [256 x 8192], 3584
+// columns, B stored [k, n] 58.0 -> 50.8; [1400 x 3072], 4096 columns 62.6 -> 58.7; [1024 x 8192], 3696 columns 80 -> 76.4 (128
+// work-groups: 77.4).  Not so beyond 32 MiB, where 512 KiB each are as many already ([2048 x 8192], 64 work-groups 134.5, 128
 // 136.4, 256 139.6 us), and not where the copies run beside the tiles (GEMM-ReduceScatter 128 x 8192: 28.7, 29.7 us).
 inline ProducerPlan plan_producers(size_t total_bytes, int nchunks, bool tiles_wait = false) {
   ProducerPlan pl{};

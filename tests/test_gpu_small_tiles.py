@@ -18,7 +18,7 @@ def B():
     return binding
 
 
-from gpu_util import to_dev, bits, nk, AgGemmRun, GemmArRun  # noqa: E402
+from gpu_util import to_dev, bits, nk, AgGemmRun, GemmArRun, GemmRsRun  # noqa: E402
 from test_gpu_moe import _run_and_check  # noqa: E402
 
 
@@ -123,6 +123,39 @@ def test_64_column_tiles_gather_bit_exact(B, m_per_rank, n, k):
     run = AgGemmRun(B, 8, m_per_rank, n, k)
     _ok(B, run([to_dev(s) for s in shards], to_dev(b), cfg.rank, b_layout=B.B_KN), run)
     assert np.array_equal(bits(run.c), formats.encode_bf16_rne(oag.ag_gemm(shards, b).astype(np.float32)))
+
+
+# the edge between 128 x 128 and 256-row tiles below three quarters of a round of the latter: GEMM-ReduceScatter from 301 tiles
+# of 128 x 128 on, AllGather-GEMM from 384 ([k, n]) and 513 ([n, k]); one to six K tiles; calls over several nodes and GEMM +
+# AllReduce never
+@pytest.mark.parametrize("m_per_rank,n,rows", [(250, 2056, (128, 128, 128)), (250, 2440, (256, 128, 128)), (249, 3000, (256, 256, 128)),
+                                               (125, 8456, (256, 256, 256))])
+@pytest.mark.parametrize("k", [64, 328])
+def test_rounds_of_small_tiles_give_way_to_large_ones(B, m_per_rank, n, rows, k):
+    world, d = 8, 2
+    cfg = synth.CONFIGS[3].scaled(world=world, m_per_rank=m_per_rank, n=n, k=k)
+    assert [B.tile_config(op, cfg.m, n, k)[1]["block_m"] for op in (1, 4, 0, 3)] == list(rows) + [128]
+    small = -(-cfg.m // 128) * -(-n // 128)
+    assert len(B.schedule_dump(1, cfg.m, n, k, world, d, tuning=B.tuning(num_nodes=2))[1]) == small
+    a_list, b_list = synth.gemm_rs_inputs(cfg, integer=True)
+    parts = [oar.partial_bits(a, b) for a, b in zip(a_list, b_list)]
+    full = oar.allreduce_partials_f32_ordered(parts)
+    mine = slice(d * m_per_rank, (d + 1) * m_per_rank)
+    a_dev = to_dev(a_list[d])
+    peers = [None if s == d else to_dev(parts[s]) for s in range(world)]
+    blocks = [None if s == d else to_dev(parts[s][mine]) for s in range(world)]
+    shards = [to_dev(a_list[d][r * m_per_rank:(r + 1) * m_per_rank]) for r in range(world)]
+    for layout, b_dev in ((B.B_NK, to_dev(nk(b_list[d]))), (B.B_KN, to_dev(b_list[d]))):
+        ar = GemmArRun(B, world, cfg.m, n, k)
+        _ok(B, ar(a_dev, b_dev, peers, d, b_layout=layout), ar)
+        assert np.array_equal(bits(ar.gemm_out), parts[d]) and np.array_equal(bits(ar.out), full)
+        for nodes in (1, 2):
+            rs = GemmRsRun(B, world, cfg.m, n, k, 1)
+            _ok(B, rs(a_dev, b_dev, blocks, d, b_layout=layout, tuning=B.tuning(num_nodes=nodes)), rs)
+            assert np.array_equal(bits(rs.gemm_out), parts[d]) and np.array_equal(bits(rs.out), full[mine])
+            ag = AgGemmRun(B, world, m_per_rank, n, k)
+            _ok(B, ag(shards, b_dev, d, b_layout=layout, tuning=B.tuning(num_nodes=nodes)), ag)
+            assert np.array_equal(bits(ag.c), parts[d])
 
 
 # the grouped GEMM's column blocks (128, 192, 256) with several K tiles, the last one ragged
