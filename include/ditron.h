@@ -104,9 +104,13 @@ enum {
 typedef struct {
   int num_nodes;       /* nodes the `world` ranks are spread over (must divide world); 0 = 1.  With
                         * more than one node ditron_ag_gemm / ditron_gemm_rs visit the tile rows in
-                        * the order of the paper's multi-node listings (see ditron_tile_row_order);
-                        * a shape for which that order does not visit every tile row exactly once is
-                        * refused with DITRON_ERR_UNSUPPORTED */
+                        * the order of the paper's multi-node listings (see ditron_tile_row_order).
+                        * A shape whose listing does not visit every tile row exactly once is refused
+                        * with DITRON_ERR_UNSUPPORTED: the listing with 256-row tiles where the problem
+                        * has at least 192 tiles of 256 x 256, with 128-row tiles where it has fewer.
+                        * The tile shape does not depend on the number of nodes; where it has 256 rows,
+                        * the listing is complete with 128 and not with 256, the call uses the one-node
+                        * order */
   unsigned spin_limit; /* flag polls per wait before DITRON_ERR_TIMEOUT; 0 = 1 << 20 (of the order
                         * of a second).  A tiny value lets a test exercise the time-out path without
                         * hanging a kernel */
@@ -154,7 +158,8 @@ ditron_status_t ditron_tile_row_order(int op, int m, int block_m, int world, int
  * op 0, 1 and 3, else 0 (a value kept for callers: every dense tile's operands go straight into LDS)
  * out[8]=work-groups that share the contraction of one output tile (decode-shaped ag_gemm; else 1): a
  * schedule dump then holds that many identical records per tile, tile after tile.  out[9]=0.
- * `tuning`: only decode_variant matters. */
+ * `tuning`: only decode_variant matters; the answer holds for any number of nodes, so out[5] * out[8] records
+ * are what a schedule or timing dump of the call writes. */
 ditron_status_t ditron_tile_config(int op, int m, int n, int k, int dtype, const ditron_tuning_t* tuning,
                                    int out[DITRON_TILE_CONFIG_WORDS]);
 

@@ -144,7 +144,7 @@ extern "C" ditron_status_t ditron_ag_gemm(const void* const* a_shards, const voi
     if (arrival_order && !is_permutation(arrival_order, world)) return DITRON_ERR_INVALID_ARG;
   }
   const bool fp8 = dtype == DITRON_FP8_E4M3;
-  const bool decode_shaped = ag_takes_decode_kernel(m_per_rank * world, n, k, dtype, b_layout, tune.decode_variant, tune.num_nodes);
+  const bool decode_shaped = ag_takes_decode_kernel(m_per_rank * world, n, k, dtype, b_layout, tune.decode_variant);
   if ((flags & DITRON_EPOCH_IN_MEMORY) && !decode_shaped && !fp8) return DITRON_ERR_UNSUPPORTED;
   if (decode_shaped)
     return ditron_ag_gemm_decode(a_shards, b, b_layout, c, a_scales, b_scales, workspace, signals, status, schedule_out,
@@ -173,7 +173,6 @@ extern "C" ditron_status_t ditron_ag_gemm(const void* const* a_shards, const voi
   p.k = k;
   p.world = world;
   p.rank = rank;
-  p.nnodes = tune.num_nodes;
   p.epoch = epoch;
   if (fp8) {
     p.a_scales = a_scales;
@@ -186,9 +185,9 @@ extern "C" ditron_status_t ditron_ag_gemm(const void* const* a_shards, const voi
   }
   p.spin_limit = tune.spin_limit;
   p.wait = mode != Mode::kPreset;
-  TileChoice tc = choose_tile(p.m, n, k, ag_narrow(dtype, b_layout), p.nnodes);
-  if (p.nnodes > 1 && !node_order_is_bijection(p.m, tc.block_m, world, p.nnodes, rank, kOrderGather))
-    return DITRON_ERR_UNSUPPORTED;
+  TileChoice tc = choose_tile(p.m, n, k, ag_narrow(dtype, b_layout));
+  p.nnodes = nodes_of_order(p.m, tc.block_m, node_listing_rows(p.m, n), world, tune.num_nodes, rank, kOrderGather);
+  if (!p.nnodes) return DITRON_ERR_UNSUPPORTED;
   p.tiling.group_m = tc.group_m;
   p.tiling.num_xcd = tc.num_xcd;
   p.tiling.per_xcd = tc.per_xcd;

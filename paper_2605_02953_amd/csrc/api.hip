@@ -46,9 +46,9 @@ extern "C" ditron_status_t ditron_tile_config(int op, int m, int n, int k, int d
   if (dtype == DITRON_FP8_E4M3 && op != 0) return DITRON_ERR_UNSUPPORTED;
   const Tuning tune = resolve_tuning(tuning, 1);
   if (!tune.valid) return DITRON_ERR_INVALID_ARG;
-  const bool decode = op == 0 && ag_takes_decode_kernel(m, n, k, dtype, DITRON_B_NK, tune.decode_variant, 1);
+  const bool decode = op == 0 && ag_takes_decode_kernel(m, n, k, dtype, DITRON_B_NK, tune.decode_variant);
   TileChoice t = decode ? choose_tile_decode(m, n, k)
-                        : choose_tile(m, n, k, op == 0 ? ag_narrow(dtype, DITRON_B_NK) : op == 4 ? Narrow::kKN : op == 3 ? Narrow::kAllReduce : Narrow::kNever, 1);
+                        : choose_tile(m, n, k, op == 0 ? ag_narrow(dtype, DITRON_B_NK) : op == 4 ? Narrow::kKN : op == 3 ? Narrow::kAllReduce : Narrow::kNever);
   int splits = 1;
   if (decode) {
     const DecodePlan plan = plan_decode(m, n, k * (dtype == DITRON_BF16 ? 2 : 1), tune.decode_variant);
@@ -87,7 +87,7 @@ extern "C" size_t ditron_ag_gemm_workspace_bytes(int m_per_rank, int n, int k, i
   const int esize = dtype == DITRON_BF16 ? 2 : 1;
   const int m = world * m_per_rank;
   const size_t gathered = (size_t)m * k * esize;
-  const bool decode = ag_takes_decode_kernel(m, n, k, dtype, b_layout, tune.decode_variant, tune.num_nodes);
+  const bool decode = ag_takes_decode_kernel(m, n, k, dtype, b_layout, tune.decode_variant);
   if (!decode) return gathered;
   // decode-shaped problems: the partial tiles of the split contraction follow the gathered operand
   const DecodePlan plan = plan_decode(m, n, k * esize, tune.decode_variant);
@@ -110,9 +110,9 @@ extern "C" ditron_status_t ditron_schedule_dump(int op, int m, int n, int k, int
   if (dtype == DITRON_FP8_E4M3 && (op != 0 || b_layout != DITRON_B_NK)) return DITRON_ERR_UNSUPPORTED;
   const Tuning tune = resolve_tuning(tuning, op == 3 ? 1 : world);
   if (!tune.valid) return DITRON_ERR_INVALID_ARG;
-  const bool decode = op == 0 && ag_takes_decode_kernel(m, n, k, dtype, b_layout, tune.decode_variant, tune.num_nodes);
+  const bool decode = op == 0 && ag_takes_decode_kernel(m, n, k, dtype, b_layout, tune.decode_variant);
   TileChoice tc = decode ? choose_tile_decode(m, n, k)
-                         : choose_tile(m, n, k, op == 0 ? ag_narrow(dtype, b_layout) : op == 3 ? Narrow::kAllReduce : Narrow::kNever, op == 3 ? 1 : tune.num_nodes);
+                         : choose_tile(m, n, k, op == 0 ? ag_narrow(dtype, b_layout) : op == 3 ? Narrow::kAllReduce : Narrow::kNever);
   int splits = 1;
   if (decode) {
     const DecodePlan plan = plan_decode(m, n, k * (dtype == DITRON_BF16 ? 2 : 1), tune.decode_variant);
@@ -125,9 +125,10 @@ extern "C" ditron_status_t ditron_schedule_dump(int op, int m, int n, int k, int
   const int ntiles = o.npm * o.npn;
   *count = ntiles * splits;
   if (*count > capacity) return DITRON_ERR_WORKSPACE;
-  if (op != 3 && tune.num_nodes > 1 &&
-      !node_order_is_bijection(m, tc.block_m, world, tune.num_nodes, rank, op == 0 ? kOrderGather : kOrderScatter))
-    return DITRON_ERR_UNSUPPORTED;
+  const int mode = op == 0 ? kOrderGather : kOrderScatter;
+  const int listing_rows = decode ? tc.block_m : node_listing_rows(m, n);
+  const int nnodes = op == 3 ? 1 : nodes_of_order(m, tc.block_m, listing_rows, world, tune.num_nodes, rank, mode);
+  if (!nnodes) return DITRON_ERR_UNSUPPORTED;
   for (int wg = 0; wg < ntiles; ++wg) {
     int32_t* rec = out + (size_t)DITRON_SCHEDULE_WORDS * wg * splits;
     if (op == 3) {
@@ -135,8 +136,7 @@ extern "C" ditron_status_t ditron_schedule_dump(int op, int m, int n, int k, int
       grouped_order(xcd_remap(wg, ntiles, o.num_xcd, o.per_xcd), o.npm, o.npn, o.group_m, pid_m, pid_n);
       rec[0] = pid_m; rec[1] = pid_n; rec[2] = 0; rec[3] = 0;
     } else {
-      const TileSpan t = tile_of_workgroup(wg, o, op == 0 ? kOrderGather : kOrderScatter, m, m / world, rank, world,
-                                           tune.num_nodes, tc.block_m);
+      const TileSpan t = tile_of_workgroup(wg, o, mode, m, m / world, rank, world, nnodes, tc.block_m);
       // the splits of a tile share its record
       for (int ks = 0; ks < splits; ++ks) {
         int32_t* r = rec + DITRON_SCHEDULE_WORDS * ks;

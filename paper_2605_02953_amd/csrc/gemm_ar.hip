@@ -360,7 +360,7 @@ static ditron_status_t gemm_ar_impl(const void* a, const void* b, int b_layout, 
       p.part[s] = peer_partials[s];
     }
   }
-  const TileChoice tc = choose_tile(m, n, k_local, Narrow::kAllReduce, 1);
+  const TileChoice tc = choose_tile(m, n, k_local, Narrow::kAllReduce);
   p.npm = cdiv(m, tc.block_m);
   p.npn = cdiv(n, tc.block_n);
   const int ntiles = p.npm * p.npn;

@@ -319,13 +319,12 @@ static ditron_status_t gemm_rs_impl(const void* a, const void* b, int b_layout, 
   p.k = k_local;
   p.world = world;
   p.rank = rank;
-  p.nnodes = tune.num_nodes;
   p.m_per_rank = m_r;
   p.chunks = chunks_per_slot;
   p.epoch = epoch;
-  TileChoice tc = choose_tile(m, n, k_local, Narrow::kNever, p.nnodes);
-  if (p.nnodes > 1 && !node_order_is_bijection(m, tc.block_m, world, p.nnodes, rank, kOrderScatter))
-    return DITRON_ERR_UNSUPPORTED;
+  TileChoice tc = choose_tile(m, n, k_local, Narrow::kNever);
+  p.nnodes = nodes_of_order(m, tc.block_m, node_listing_rows(m, n), world, tune.num_nodes, rank, kOrderScatter);
+  if (!p.nnodes) return DITRON_ERR_UNSUPPORTED;
   p.tiling.group_m = tc.group_m;
   p.tiling.num_xcd = tc.num_xcd;
   p.tiling.per_xcd = tc.per_xcd;

@@ -121,17 +121,17 @@ enum class Narrow { kNever, kNK, kKN, kF8, kAllReduce };   // kF8: as kNK, e4m3 
 // 2048 x 3000 (384 and 96 tiles): fp8 78 -> 57, GEMM-ReduceScatter 57 -> 48 (K 256: 44 -> 29),
 // AllGather-GEMM 79.0 -> 79.6, B stored [k, n] 85 -> 82.  2048 x 2176 (272 and 72 tiles): fp8 78 -> 57,
 // GEMM-ReduceScatter 47 -> 45 but 45.9 -> 46.9 with B stored [k, n] (2048 x 2560, 320 and 80 tiles: 50 -> 47), AllGather-GEMM 77.8 -> 79.3.
-// Several nodes keep the first rule alone: the node orders of the paper cover more shapes with 128-row tiles.
-inline bool takes_big_tiles(int m, int n, Narrow narrow, int nnodes) {
+// The number of nodes is no part of the rule: buffers are sized from ditron_tile_config, which does not know it.
+inline bool takes_big_tiles(int m, int n, Narrow narrow) {
   const long big = (long)cdiv(m, 256) * cdiv(n, 256), small = (long)cdiv(m, 128) * cdiv(n, 128);
   if (big >= 192) return true;
-  return nnodes == 1 && narrow != Narrow::kAllReduce && small > (narrow == Narrow::kNK ? 512 : narrow == Narrow::kKN ? 383 : narrow == Narrow::kF8 ? 256 : 300);
+  return narrow != Narrow::kAllReduce && small > (narrow == Narrow::kNK ? 512 : narrow == Narrow::kKN ? 383 : narrow == Narrow::kF8 ? 256 : 300);
 }
 
-inline TileChoice choose_tile(int m, int n, int k, Narrow narrow, int nnodes) {
+inline TileChoice choose_tile(int m, int n, int k, Narrow narrow) {
   TileChoice t{};
   const long tiles_big = (long)cdiv(m, 256) * cdiv(n, 256);
-  t.big = takes_big_tiles(m, n, narrow, nnodes);
+  t.big = takes_big_tiles(m, n, narrow);
   t.block_m = t.block_n = t.big ? 256 : 128;
   // Half as wide where that many tiles still fit the chip in one round and the K loop is what the call spends its time on.
   // AllGather-GEMM, B stored [K, N] ([N, K]: the decode kernel): 64 x 3584, K 8192 56.3 -> 41.1 us; 1024 x 2048, K 4096 (256 of
@@ -168,9 +168,9 @@ inline bool fits_32bit(size_t rows, size_t cols, size_t esize) { return rows * c
 inline Narrow ag_narrow(int dtype, int b_layout) {
   return dtype == DITRON_FP8_E4M3 ? Narrow::kF8 : b_layout == DITRON_B_NK ? Narrow::kNK : Narrow::kKN;
 }
-inline bool ag_takes_decode_kernel(int m, int n, int k, int dtype, int b_layout, int decode_variant, int nnodes) {
+inline bool ag_takes_decode_kernel(int m, int n, int k, int dtype, int b_layout, int decode_variant) {
   if (dtype == DITRON_FP8_E4M3)
-    return decode_variant != 0 || !takes_big_tiles(m, n, Narrow::kF8, nnodes) || !fits_32bit(m, k, 1) || !fits_32bit(n, k, 1);
+    return decode_variant != 0 || !takes_big_tiles(m, n, Narrow::kF8) || !fits_32bit(m, k, 1) || !fits_32bit(n, k, 1);
   return b_layout == DITRON_B_NK && bf16_ag_is_decode_shaped(m, n);
 }
 inline TileChoice choose_tile_decode(int /*m*/, int /*n*/, int /*k*/) {
@@ -249,6 +249,19 @@ inline bool node_order_is_bijection(int m, int block_m, int world, int nnodes, i
     seen[r >> 6] |= 1ull << (r & 63);
   }
   return true;
+}
+
+// Calls over several nodes are served where the listing with tiles of this many rows visits every tile row once, whatever
+// the tile is that the problem takes.
+inline int node_listing_rows(int m, int n) { return (long)cdiv(m, 256) * cdiv(n, 256) >= 192 ? 256 : 128; }
+
+// The number of nodes whose listing a call with tiles of block_m rows follows, 0 if it is refused.  Where the listing at
+// listing_rows is complete and the one at block_m is not, the tile rows are visited in the one-node order: every tile still
+// waits for, or counts towards, just the ranks whose rows it holds, so the order decides only how long it may wait.
+inline int nodes_of_order(int m, int block_m, int listing_rows, int world, int nnodes, int rank, int mode) {
+  if (nnodes <= 1) return 1;
+  if (!node_order_is_bijection(m, listing_rows, world, nnodes, rank, mode)) return 0;
+  return block_m == listing_rows || node_order_is_bijection(m, block_m, world, nnodes, rank, mode) ? nnodes : 1;
 }
 
 inline bool is_permutation(const int* v, int n) {

@@ -126,7 +126,7 @@ def test_64_column_tiles_gather_bit_exact(B, m_per_rank, n, k):
 
 
 # the edge between 128 x 128 and 256-row tiles below three quarters of a round of the latter: GEMM-ReduceScatter from 301 tiles
-# of 128 x 128 on, AllGather-GEMM from 384 ([k, n]) and 513 ([n, k]); one to six K tiles; calls over several nodes and GEMM +
+# of 128 x 128 on, AllGather-GEMM from 384 ([k, n]) and 513 ([n, k]); one to six K tiles; over one node and two; GEMM +
 # AllReduce never
 @pytest.mark.parametrize("m_per_rank,n,rows", [(250, 2056, (128, 128, 128)), (250, 2440, (256, 128, 128)), (249, 3000, (256, 256, 128)),
                                                (125, 8456, (256, 256, 256))])
@@ -135,8 +135,6 @@ def test_rounds_of_small_tiles_give_way_to_large_ones(B, m_per_rank, n, rows, k)
     world, d = 8, 2
     cfg = synth.CONFIGS[3].scaled(world=world, m_per_rank=m_per_rank, n=n, k=k)
     assert [B.tile_config(op, cfg.m, n, k)[1]["block_m"] for op in (1, 4, 0, 3)] == list(rows) + [128]
-    small = -(-cfg.m // 128) * -(-n // 128)
-    assert len(B.schedule_dump(1, cfg.m, n, k, world, d, tuning=B.tuning(num_nodes=2))[1]) == small
     a_list, b_list = synth.gemm_rs_inputs(cfg, integer=True)
     parts = [oar.partial_bits(a, b) for a, b in zip(a_list, b_list)]
     full = oar.allreduce_partials_f32_ordered(parts)
@@ -156,6 +154,65 @@ def test_rounds_of_small_tiles_give_way_to_large_ones(B, m_per_rank, n, rows, k)
             ag = AgGemmRun(B, world, m_per_rank, n, k)
             _ok(B, ag(shards, b_dev, d, b_layout=layout, tuning=B.tuning(num_nodes=nodes)), ag)
             assert np.array_equal(bits(ag.c), parts[d])
+
+
+# Over several nodes the dumps write what the size query announces, where 256-row tiles take over from 128 x 128 ones.  1720
+# rows as eight nodes of one rank: for rank 6 the listing is complete with tiles of 128 rows and not with 256, so that its
+# tiles are visited in the one-node order
+@pytest.mark.parametrize("nodes,d", [(2, 2), (8, 5), (8, 6)])
+def test_dumps_over_several_nodes_fit_the_size_query(B, nodes, d):
+    world, m_r, n, k = 8, 215, 4744, 72
+    cfg = synth.CONFIGS[3].scaled(world=world, m_per_rank=m_r, n=n, k=k)
+    a_list, b_list = synth.gemm_rs_inputs(cfg, integer=True)
+    parts = [oar.partial_bits(a, b) for a, b in zip(a_list, b_list)]
+    mine = slice(d * m_r, (d + 1) * m_r)
+    want = oar.allreduce_partials_f32_ordered(parts)[mine]
+    a_dev = to_dev(a_list[d])
+    blocks = [None if s == d else to_dev(parts[s][mine]) for s in range(world)]
+    shards = [to_dev(a_list[d][r * m_r:(r + 1) * m_r]) for r in range(world)]
+    tuning = B.tuning(num_nodes=nodes)
+
+    def records(query, dtype=B.BF16):
+        st, tc = B.tile_config(query, cfg.m, n, k, dtype)
+        assert st == B.OK and tc["block_m"] == 256
+        assert sorted(B.tile_row_order(0, cfg.m, 128, world, nodes, d)[1]) == list(range(14))
+        complete = sorted(B.tile_row_order(0, cfg.m, 256, world, nodes, d)[1]) == list(range(7))
+        assert complete == ((nodes, d) != (8, 6))
+        return torch.full((4 * tc["ntiles"] + 4 * 2048,), -1, dtype=torch.int32, device="cuda"), 4 * tc["ntiles"]
+
+    def check_records(rec, words, op, layout, dtype=B.BF16):
+        r = rec.cpu().tolist()
+        assert set(r[words:]) == {-1}
+        assert [tuple(r[i:i + 4]) for i in range(0, words, 4)] == B.schedule_dump(op, cfg.m, n, k, world, d, dtype, layout, tuning)[1]
+
+    for layout, b_dev in ((B.B_NK, to_dev(nk(b_list[d]))), (B.B_KN, to_dev(b_list[d]))):
+        rec, words = records(1)
+        rs = GemmRsRun(B, world, cfg.m, n, k, 1)
+        _ok(B, rs(a_dev, b_dev, blocks, d, b_layout=layout, schedule=rec, tuning=tuning), rs)
+        assert np.array_equal(bits(rs.gemm_out), parts[d]) and np.array_equal(bits(rs.out), want)
+        check_records(rec, words, 1, layout)
+        rec, words = records(0 if layout == B.B_NK else 4)
+        ag = AgGemmRun(B, world, m_r, n, k)
+        _ok(B, ag(shards, b_dev, d, b_layout=layout, schedule=rec, tuning=tuning), ag)
+        assert np.array_equal(bits(ag.c), parts[d])
+        check_records(rec, words, 0, layout)
+    # e4m3 of the same integers; then the time stamps, which go to the same places
+    q = lambda x: synth.quantize_e4m3(formats.decode_bf16(x), 1.0)   # noqa: E731
+    a8, b8 = q(a_list[d]), q(b_list[d])
+    ag = AgGemmRun(B, world, m_r, n, 80, esize=1)
+    pad = lambda x: np.concatenate([x, np.zeros((x.shape[0], 8), x.dtype)], axis=1)   # noqa: E731  (k a multiple of 16)
+    sh8, b8 = [to_dev(pad(a8[r * m_r:(r + 1) * m_r])) for r in range(world)], to_dev(pad(nk(b8)))
+    rec, words = records(0, B.FP8_E4M3)
+    _ok(B, ag(sh8, b8, d, dtype=B.FP8_E4M3, schedule=rec, tuning=tuning), ag)
+    assert np.array_equal(bits(ag.c), parts[d])
+    check_records(rec, words, 0, B.B_NK, B.FP8_E4M3)
+    rec.fill_(-1)
+    ag.epoch += 1
+    st = B.ag_gemm(sh8, b8, B.B_NK, ag.c, None, None, ag.ws_raw, ag.signals, ag.status, rec, None, m_r, n, 80, world, d, B.FP8_E4M3,
+                   ag.epoch, B.EMULATE_PRODUCER | B.DUMP_TIMING, tuning=tuning)
+    _ok(B, st, ag)
+    r = rec.cpu().tolist()
+    assert set(r[words:]) == {-1} and -1 not in r[:words]
 
 
 # the grouped GEMM's column blocks (128, 192, 256) with several K tiles, the last one ragged

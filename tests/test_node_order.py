@@ -59,3 +59,34 @@ def test_argument_checks(B):
     assert B.tile_row_order(0, 1024, 256, 8, 3, 0)[0] == B.ERR_INVALID_ARG       # world not a multiple of nnodes
     assert B.tile_row_order(0, 1000, 256, 8, 2, 8)[0] == B.ERR_INVALID_ARG       # rank out of range
     assert B.tile_row_order(0, 1001, 256, 8, 2, 0)[0] == B.ERR_INVALID_ARG       # rows not a multiple of world
+
+
+# (operator, m_per_rank, n) with world 8, on both sides of every line of the
+# tile rule: 256 / 300 / 383 / 512 tiles of 128 x 128, 192 of 256 x 256, and far between them
+TILINGS = [(op, m_r, n) for op in ("ag_nk", "ag_kn", "ag_fp8", "rs_nk", "rs_kn")
+           for m_r, n in [(16, 512), (128, 4096), (128, 4104), (250, 2048), (250, 2056), (250, 2432), (250, 2440), (249, 3000), (319, 3992), (325, 3472),
+                          (119, 11632), (125, 8456), (606, 2336), (505, 3080), (70, 16200), (130, 9736), (33, 16384), (1024, 3584)]]
+
+
+@pytest.mark.parametrize("nnodes", [1, 2, 4, 8])
+def test_the_size_query_holds_for_any_number_of_nodes(B, nnodes):
+    """A schedule or timing dump writes one record per work-group into a buffer sized with tile_config, which is not told how
+    many nodes there are: tile shape and count must be those of the launch whatever the number of nodes."""
+    world, k = 8, 2048
+    for kind, m_r, n in TILINGS:
+        op, query, dtype, layout = {"ag_nk": (0, 0, B.BF16, B.B_NK), "ag_kn": (0, 4, B.BF16, B.B_KN), "ag_fp8": (0, 0, B.FP8_E4M3, B.B_NK),
+                                    "rs_nk": (1, 1, B.BF16, B.B_NK), "rs_kn": (1, 1, B.BF16, B.B_KN)}[kind]
+        m = world * m_r
+        st, tc = B.tile_config(query, m, n, k, dtype)
+        assert st == B.OK
+        served = 0
+        for rank in range(world):
+            st, got = B.schedule_dump(op, m, n, k, world, rank, dtype, layout, B.tuning(num_nodes=nnodes))
+            if st == B.ERR_UNSUPPORTED:
+                continue
+            served += 1
+            assert st == B.OK and len(got) == tc["ntiles"] * tc["splits"], (kind, m_r, n, rank)
+            # every tile once (its splits after one another), the shards or segments of its rows beside it
+            assert sorted({g[:2] for g in got}) == [(i, j) for i in range(S.cdiv(m, tc["block_m"])) for j in range(S.cdiv(n, tc["block_n"]))]
+            assert all(g[2:] == (g[0] * tc["block_m"] // m_r, (min((g[0] + 1) * tc["block_m"], m) - 1) // m_r) for g in got)
+        assert served or nnodes > 1
