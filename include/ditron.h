@@ -106,8 +106,9 @@ typedef struct {
                         * more than one node ditron_ag_gemm / ditron_gemm_rs visit the tile rows in
                         * the order of the paper's multi-node listings (see ditron_tile_row_order).
                         * A shape whose listing does not visit every tile row exactly once is refused
-                        * with DITRON_ERR_UNSUPPORTED: the listing with 256-row tiles where the problem
-                        * has at least 192 tiles of 256 x 256, with 128-row tiles where it has fewer.
+                        * with DITRON_ERR_UNSUPPORTED: the listing with 256-row tiles where a bf16
+                        * problem has at least 192 tiles of 256 x 256, with 128-row tiles elsewhere
+                        * (decode_variant 4: 16).
                         * The tile shape does not depend on the number of nodes; where it has 256 rows,
                         * the listing is complete with 128 and not with 256, the call uses the one-node
                         * order */

@@ -186,7 +186,7 @@ extern "C" ditron_status_t ditron_ag_gemm(const void* const* a_shards, const voi
   p.spin_limit = tune.spin_limit;
   p.wait = mode != Mode::kPreset;
   TileChoice tc = choose_tile(p.m, n, k, ag_narrow(dtype, b_layout));
-  p.nnodes = nodes_of_order(p.m, tc.block_m, node_listing_rows(p.m, n), world, tune.num_nodes, rank, kOrderGather);
+  p.nnodes = nodes_of_order(p.m, tc.block_m, node_listing_rows(p.m, n, dtype), world, tune.num_nodes, rank, kOrderGather);
   if (!p.nnodes) return DITRON_ERR_UNSUPPORTED;
   p.tiling.group_m = tc.group_m;
   p.tiling.num_xcd = tc.num_xcd;

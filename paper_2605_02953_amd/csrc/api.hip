@@ -126,7 +126,7 @@ extern "C" ditron_status_t ditron_schedule_dump(int op, int m, int n, int k, int
   *count = ntiles * splits;
   if (*count > capacity) return DITRON_ERR_WORKSPACE;
   const int mode = op == 0 ? kOrderGather : kOrderScatter;
-  const int listing_rows = decode ? tc.block_m : node_listing_rows(m, n);
+  const int listing_rows = decode ? tc.block_m : node_listing_rows(m, n, dtype);
   const int nnodes = op == 3 ? 1 : nodes_of_order(m, tc.block_m, listing_rows, world, tune.num_nodes, rank, mode);
   if (!nnodes) return DITRON_ERR_UNSUPPORTED;
   for (int wg = 0; wg < ntiles; ++wg) {

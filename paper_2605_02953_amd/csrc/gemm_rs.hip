@@ -323,7 +323,7 @@ static ditron_status_t gemm_rs_impl(const void* a, const void* b, int b_layout, 
   p.chunks = chunks_per_slot;
   p.epoch = epoch;
   TileChoice tc = choose_tile(m, n, k_local, Narrow::kNever);
-  p.nnodes = nodes_of_order(m, tc.block_m, node_listing_rows(m, n), world, tune.num_nodes, rank, kOrderScatter);
+  p.nnodes = nodes_of_order(m, tc.block_m, node_listing_rows(m, n, DITRON_BF16), world, tune.num_nodes, rank, kOrderScatter);
   if (!p.nnodes) return DITRON_ERR_UNSUPPORTED;
   p.tiling.group_m = tc.group_m;
   p.tiling.num_xcd = tc.num_xcd;

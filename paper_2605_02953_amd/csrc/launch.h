@@ -252,8 +252,10 @@ inline bool node_order_is_bijection(int m, int block_m, int world, int nnodes, i
 }
 
 // Calls over several nodes are served where the listing with tiles of this many rows visits every tile row once, whatever
-// the tile is that the problem takes.
-inline int node_listing_rows(int m, int n) { return (long)cdiv(m, 256) * cdiv(n, 256) >= 192 ? 256 : 128; }
+// the tile is that the problem takes: 128 rows for fp8, whose node orders cover more shapes than those of 256 rows do.
+inline int node_listing_rows(int m, int n, int dtype) {
+  return dtype == DITRON_BF16 && (long)cdiv(m, 256) * cdiv(n, 256) >= 192 ? 256 : 128;
+}
 
 // The number of nodes whose listing a call with tiles of block_m rows follows, 0 if it is refused.  Where the listing at
 // listing_rows is complete and the one at block_m is not, the tile rows are visited in the one-node order: every tile still

@@ -104,3 +104,23 @@ def test_fp8_tile_rule_edge(B, m_r, rows):
         torch.cuda.synchronize()
         assert run.status.cpu().tolist()[0] == 0
         assert np.array_equal(bits(run.c), want)
+
+
+# over several nodes fp8 is served where the 128-row listing is complete, also where the problem has 192 large tiles and more
+# and their own listing is not (ranks 4 and 6); n is ragged
+@pytest.mark.parametrize("m_r,n,nodes,rank", [(70, 16200, 4, 4), (70, 16200, 4, 0), (130, 9736, 8, 6), (130, 9736, 8, 5)])
+def test_fp8_of_many_columns_over_several_nodes(B, m_r, n, nodes, rank):
+    cfg, a, sa, b, sb = _case(m_r, n, 144, 9)
+    run = AgGemmRun(B, 8, m_r, n, cfg.k, esize=1)
+    tuning = B.tuning(num_nodes=nodes)
+    st, tc = B.tile_config(0, cfg.m, n, cfg.k, B.FP8_E4M3)
+    sched = torch.full((4 * tc["ntiles"] * tc["splits"],), -1, dtype=torch.int32, device="cuda")
+    st = run([to_dev(x) for x in a], to_dev(nk(b)), rank, dtype=B.FP8_E4M3, schedule=sched, a_scales=to_dev(sa), b_scales=to_dev(sb),
+             tuning=tuning)
+    assert st == B.OK, B.status_string(st)
+    torch.cuda.synchronize()
+    assert run.status.cpu().tolist()[0] == 0
+    want = formats.encode_bf16_rne(oag.ag_gemm(a, b, dtype="e4m3", a_scales=sa, b_scales=sb).astype(np.float32))
+    assert np.array_equal(bits(run.c), want)
+    host = B.schedule_dump(0, cfg.m, n, cfg.k, 8, rank, B.FP8_E4M3, tuning=tuning)[1]
+    assert [tuple(r) for r in sched.cpu().view(-1, 4).tolist()] == host

@@ -90,3 +90,18 @@ def test_the_size_query_holds_for_any_number_of_nodes(B, nnodes):
             assert sorted({g[:2] for g in got}) == [(i, j) for i in range(S.cdiv(m, tc["block_m"])) for j in range(S.cdiv(n, tc["block_n"]))]
             assert all(g[2:] == (g[0] * tc["block_m"] // m_r, (min((g[0] + 1) * tc["block_m"], m) - 1) // m_r) for g in got)
         assert served or nnodes > 1
+
+
+# (world, nodes, m_per_rank, n): 256-row tiles whose listing is incomplete for some ranks although the one of 128 rows is
+# complete (the first three), incomplete for some ranks at 128 rows, complete everywhere
+@pytest.mark.parametrize("world,nnodes,m_r,n", [(8, 4, 70, 16200), (8, 8, 130, 9736), (32, 8, 17, 23568), (8, 4, 37, 16384), (8, 2, 1024, 3584)])
+def test_which_shapes_several_nodes_are_served_for(B, world, nnodes, m_r, n):
+    """fp8 calls are served where the 128-row listing visits every tile row once, also where they take 256-row tiles; bf16
+    calls where the listing at their rule's rows does (256 from 192 tiles of 256 x 256 on)."""
+    m, tuning = world * m_r, B.tuning(num_nodes=nnodes)
+    large = S.cdiv(m, 256) * S.cdiv(n, 256) >= 192
+    for rank in range(world):
+        complete = lambda op, bm: sorted(B.tile_row_order(op, m, bm, world, nnodes, rank)[1]) == list(range(S.cdiv(m, bm)))   # noqa: E731
+        for op, dtype, layout, bm in ((0, B.FP8_E4M3, B.B_NK, 128), (0, B.BF16, B.B_KN, 256 if large else 128), (1, B.BF16, B.B_NK, 256 if large else 128)):
+            st, got = B.schedule_dump(op, m, n, 2048, world, rank, dtype, layout, tuning)
+            assert st == (B.OK if complete(op, bm) else B.ERR_UNSUPPORTED), (rank, op, dtype)
