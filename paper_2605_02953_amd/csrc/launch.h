@@ -114,24 +114,48 @@ inline double tiling_cost(long tiles, int block_n) {
 // every world-th tile, reduces it and broadcasts it, so the tiling is part of what the ranks agree on and what a call returns.
 enum class Narrow { kNever, kNK, kKN, kF8, kAllReduce };   // kF8: as kNK, e4m3 operands
 
+// The most 128 x 128 tiles with which GEMM-ReduceScatter stays on them.  Every tile ends with a release (the segment counter),
+// which a short contraction does not hide, and 256-row tiles have a quarter as many; in a long one a second round of small
+// tiles is partly empty and its units take the peers' copies, while the large tiles leave half of the chip to nobody.  So the
+// line depends on K.  us with 128 x 128 tiles and with 256-row ones (8 ranks):
+//   256 tiles, 2048 x 2048: K 512 39.3, 31.8; 1024 42.4, 34.5; 2048 49.1, 49.3 (224, 904 x 3584: 1024 33.9, 32.9; 1536 35.0, 40.2)
+//   320 tiles, 2048 x 2560: K 512 41.7, 32.2; 1536 48.2, 42.2; 2048 50.5, 49.8; 3584 65.8, 74.1
+//   416 tiles, 1544 x 4096: K 1024 53.7, 37.9; 2560 63.9, 60.1; 3072 66.1, 68.8; 4096 74.8, 85.5
+//   480 tiles, 2048 x 3840: K 3584 73.0, 79.9; 496, 904 x 7936: 91.1, 79.5 (nothing is left of the second round); 5120 112, 103;
+//   6656 128, 127; 8192 146, 152
+// How many of the rows of the large tiles exist matters less: 306 tiles, 264 x 13056 (half of them): K 1024 42.0, 34.3; 2048 47.5,
+// 49.0; 3584 62.3, 74.7; 516, 264 x 22016: 3584 94.1, 82.7.  One row of tiles is bound by the weight, which large tiles ask for in
+// longer runs, at any K: 128 x 38912 K 512 40.7, 33.3; 4096 116, 107; 6656 167, 155.
+inline int reduce_scatter_small_tiles(int m, int k) {
+  if (k <= 1024) return 255;
+  if (k <= 1536 || m <= 128) return 300;
+  return k <= 2560 ? 352 : k <= 6144 ? 480 : 512;
+}
+
 // 256-row tiles where they fill three quarters of the chip in one round, or where 128 x 128 tiles need so many rounds that a
-// round of larger ones is shorter all the same (a K tile of 256 x 256 takes a unit about 1.1 us, one of 128 x 128 0.38).
-// 952 x 11632 (728 tiles of 128 x 128, 184 of 256 x 256), us before and after: AllGather-GEMM K 4096 111 -> 91, B stored [k, n]
-// 120 -> 93, fp8 110 -> 62; GEMM-ReduceScatter over 4 ranks, K 1616 101 -> 59.
-// 2048 x 3000 (384 and 96 tiles): fp8 78 -> 57, GEMM-ReduceScatter 57 -> 48 (K 256: 44 -> 29),
-// AllGather-GEMM 79.0 -> 79.6, B stored [k, n] 85 -> 82.  2048 x 2176 (272 and 72 tiles): fp8 78 -> 57,
-// GEMM-ReduceScatter 47 -> 45 but 45.9 -> 46.9 with B stored [k, n] (2048 x 2560, 320 and 80 tiles: 50 -> 47), AllGather-GEMM 77.8 -> 79.3.
+// round of larger ones is shorter all the same.  us with 128 x 128 tiles (fp8: the decode kernel's) and with 256-row ones:
+// AllGather-GEMM, [n, k], K 4096: 496 tiles, 904 x 7936, 79.2, 81.9; 520, 1160 x 6656, 102, 82 (a third round).
+// [k, n], K 4096: 384 tiles, 2048 x 3000, 82.0, 81.4; 473, 1288 x 5504, K 8192 141, 139; 512, 512 x 16384, K 8192 167, 146; where half
+// of the rows do not exist 264 x 16384 K 4096 69.9, 71.6, K 16384 243, 259.
+// fp8, at any padding: 320 tiles, 2048 x 2560, K 4096 72.5, 49.9; 306, 264 x 13056, 58.9, 42.5; 257, 128 x 32896, 63.4, 42.5; 320, 16 x 40960
+// 52.4, 42.8; 384, 128 x 49152, 66.3, 50.1; 1002, 128 x 128256, 173, 158 (K 8192: 278, 279).
 // The number of nodes is no part of the rule: buffers are sized from ditron_tile_config, which does not know it.
-inline bool takes_big_tiles(int m, int n, Narrow narrow) {
+inline bool takes_big_tiles(int m, int n, int k, Narrow narrow) {
   const long big = (long)cdiv(m, 256) * cdiv(n, 256), small = (long)cdiv(m, 128) * cdiv(n, 128);
   if (big >= 192) return true;
-  return narrow != Narrow::kAllReduce && small > (narrow == Narrow::kNK ? 512 : narrow == Narrow::kKN ? 383 : narrow == Narrow::kF8 ? 256 : 300);
+  switch (narrow) {
+    case Narrow::kNK: return small > 512;
+    case Narrow::kKN: return small > 383;
+    case Narrow::kF8: return small > 256;
+    case Narrow::kNever: return small > reduce_scatter_small_tiles(m, k);
+    default: return false;
+  }
 }
 
 inline TileChoice choose_tile(int m, int n, int k, Narrow narrow) {
   TileChoice t{};
   const long tiles_big = (long)cdiv(m, 256) * cdiv(n, 256);
-  t.big = takes_big_tiles(m, n, narrow);
+  t.big = takes_big_tiles(m, n, k, narrow);
   t.block_m = t.block_n = t.big ? 256 : 128;
   // Half as wide where that many tiles still fit the chip in one round and the K loop is what the call spends its time on.
   // AllGather-GEMM, B stored [K, N] ([N, K]: the decode kernel): 64 x 3584, K 8192 56.3 -> 41.1 us; 1024 x 2048, K 4096 (256 of
@@ -170,7 +194,7 @@ inline Narrow ag_narrow(int dtype, int b_layout) {
 }
 inline bool ag_takes_decode_kernel(int m, int n, int k, int dtype, int b_layout, int decode_variant) {
   if (dtype == DITRON_FP8_E4M3)
-    return decode_variant != 0 || !takes_big_tiles(m, n, Narrow::kF8) || !fits_32bit(m, k, 1) || !fits_32bit(n, k, 1);
+    return decode_variant != 0 || !takes_big_tiles(m, n, k, Narrow::kF8) || !fits_32bit(m, k, 1) || !fits_32bit(n, k, 1);
   return b_layout == DITRON_B_NK && bf16_ag_is_decode_shaped(m, n);
 }
 inline TileChoice choose_tile_decode(int /*m*/, int /*n*/, int /*k*/) {
