@@ -469,6 +469,21 @@ static ditron_status_t launch_moe_gemm_walk(MoeGemmParams& g, int max_tiles, int
   return hipGetLastError() == hipSuccess ? DITRON_OK : DITRON_ERR_HIP;
 }
 
+// 128-row tiles of [n, k] weights.  Their operands are streamed (an expert's weights are read by one or two row tiles).
+// 128 columns: the 16 x 16 x 32 loop with three K tiles in flight.  192 and 256: a ring of as many LDS stages as fit (four and
+// three), filled by waves of their own: the 16 x 16 x 32 loop has room for two K tiles of these widths only.  us for the whole call,
+// weights not in the caches, with the ring and with that loop, 256 columns: 2048 tokens, hidden 4096, 64 experts top-6, 200 columns
+// 85, 97; 256 columns 91, 100; 6000 tokens, 32 experts top-2, 512 columns 107, 113; hidden 2048, 2048 tokens top-4 75, 77.
+// 128 columns: 8192 tokens, hidden 4096, 8 of 64 experts 91.1, 91.7; 1024 tokens, hidden 8192, 32 experts 121.6, 121.3, the same,
+// and with the weights in the caches 1024 tokens, hidden 4096, 8 of 64 experts 52.4, 50.1.
+static ditron_status_t launch_moe_gemm_128_rows(MoeGemmParams& g, int block_n, int max_tiles, hipStream_t s) {
+  switch (block_n) {
+    case 128: return launch_moe_gemm<GemmTile4W<128, 128, false, true, true>>(g, max_tiles, s);
+    case 192: return launch_moe_gemm<GemmTile4W<128, 192, false, true>, 4>(g, max_tiles, s);
+    default: return launch_moe_gemm<GemmTile4W<128, 256, false, true>, 3>(g, max_tiles, s);
+  }
+}
+
 extern "C" ditron_status_t ditron_moe_ag_grouped_gemm(
     const void* const* x_shards, const int32_t* topk_ids, const void* w, int w_layout, void* y, int32_t* counts,
     int32_t* expert_offsets, int32_t* gather_idx, int32_t* tile_records, void* workspace, int32_t* signals,
@@ -578,13 +593,7 @@ extern "C" ditron_status_t ditron_moe_ag_grouped_gemm(
     if (mt.block_n == 128) return launch_moe_gemm<GemmTile4W<256, 128>>(g, max_tiles, s);
     return launch_moe_gemm<TileBigDirect>(g, max_tiles, s);
   }
-  // 128-row tiles: their operands are streamed (an expert's weights are read by one or two row tiles), so
-  // they go through as deep a ring of LDS stages as fits
-  switch (mt.block_n) {
-    case 128: return launch_moe_gemm<GemmTile4W<128, 128, false, true, true>>(g, max_tiles, s);
-    case 192: return launch_moe_gemm<GemmTile4W<128, 192, false, true>, 4>(g, max_tiles, s);
-    default: return launch_moe_gemm<GemmTile4W<128, 256, false, true, true>>(g, max_tiles, s);
-  }
+  return launch_moe_gemm_128_rows(g, mt.block_n, max_tiles, s);
 }
 
 
@@ -831,12 +840,8 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
     // work-groups as are resident at once, each walking down its share of the items (measured at the paper's
     // MoE+RS shape, whole call: 115 us with the ring tiles, 109 with these tiles, 106.5 with 512 resident
     // work-groups, 113.6 with 768; 256 x 256 tiles 108-118).
-    if (inter <= 256) st = launch_moe_gemm_walk<GemmTile4W<128, 128>>(g, max_tiles, 512, s); else
-    switch (mt.block_n) {
-      case 128: st = launch_moe_gemm<GemmTile4W<128, 128, false, true, true>>(g, max_tiles, s); break;
-      case 192: st = launch_moe_gemm<GemmTile4W<128, 192, false, true>, 4>(g, max_tiles, s); break;
-      default: st = launch_moe_gemm<GemmTile4W<128, 256, false, true, true>>(g, max_tiles, s); break;
-    }
+    st = inter <= 256 ? launch_moe_gemm_walk<GemmTile4W<128, 128>>(g, max_tiles, 512, s)
+                      : launch_moe_gemm_128_rows(g, mt.block_n, max_tiles, s);
   }
   if (st != DITRON_OK) return st;
 
