@@ -119,10 +119,16 @@ struct GemmTile4W {
   // [1024 x 8192] x [8192 x 3696], operands resident: 66 / 57 / 57 us; 464 tiles of [2048 x 3696]: 123 / 109 / 111 us, so a
   // second work-group on the unit, which 2 would leave room for, is worth less than the third tile in flight).  64 columns:
   // nine, their calls stream the weight from memory.
-  static constexpr int PIECE_BYTES = A_BYTES > B_BYTES ? A_BYTES : B_BYTES;
-  static constexpr int DEPTH = BN == 64 ? 4 : PIECE_BYTES <= 16 * 1024 ? 3 : 2;
+  // B parts larger than A parts (128 rows, 192 or 256 columns): a ring of DEPTH + 1 A parts and behind it one of DEPTH B parts,
+  // since in pieces of one size half of the A parts' room would be empty and two K tiles all that fits (MoE, [k, n] weights not in
+  // the caches, whole calls: 60 experts, 4856 tokens top-2, hidden 4096, 512 columns 125 -> 112 us; 16 experts, 5064 tokens,
+  // hidden 2048, 1024 columns 76 -> 70; 42 calls more of K 1024 to 4096: 2 to 16 % less).  The 256-row tiles lose 1 to 2 % with two
+  // rings.
+  static constexpr bool TWO_RINGS = X16_ && B_BYTES > A_BYTES;
+  static constexpr int PIECE_BYTES = A_BYTES;
+  static constexpr int DEPTH = BN == 64 ? 4 : BM == 128 ? 3 : 2;
   static constexpr int PIECES = 2 * DEPTH + 1;
-  static constexpr int LDS_BYTES = X16_ ? PIECES * PIECE_BYTES : NSTAGE * STAGE_BYTES;
+  static constexpr int LDS_BYTES = TWO_RINGS ? (DEPTH + 1) * A_BYTES + DEPTH * B_BYTES : X16_ ? PIECES * PIECE_BYTES : NSTAGE * STAGE_BYTES;
   static constexpr int ROWS_PER_PASS = THREADS / 8;           // 32 rows per pass of 16-byte loads
   static constexpr int A_LOADS = BM / ROWS_PER_PASS, B_LOADS = BN / ROWS_PER_PASS, LOADS = A_LOADS + B_LOADS;
   // The K loop is written as slots of two MFMAs (one B fragment, two A fragments).
@@ -352,6 +358,8 @@ __device__ __forceinline__ void loads_of_slot(F&& load) {
 //   step 0 of tile kt : fragment reads of step 1; loads of A(kt+D) into the piece idle since the last barrier
 //   barrier           : every wave's part of tile kt+1 has landed, nobody reads tile kt any more
 //   step 1 of tile kt : fragment reads of step 0 of tile kt+1; loads of B(kt+D) into the piece of A(kt)
+// (T::TWO_RINGS: slots j mod (D + 1) of the A ring and j mod D of the B ring; A(kt+D) goes into the slot of A(kt-1), which is as
+// idle as the piece of B(kt-1), and B(kt+D) into that of B(kt), as free after the barrier as the piece of A(kt))
 // The loads go out one per two slots over the whole K tile and have one to three steps to land (with two
 // whole-tile stages all of them went out during step 1 and had one to two: at operands that are not in the
 // caches, cfg 2 and cfg 3 shapes beside the vendor GEMM, the ring takes 8-10 % less time; with operands that
@@ -399,26 +407,42 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
   Stager4W<T> st;
   st.init(a_base, a_row, b_base, b_row);
   auto wrap = [](int x) { return x >= T::PIECES ? x - T::PIECES : x; };
+  char* const ring_b = T::TWO_RINGS ? lds + (D + 1) * T::A_BYTES : lds + PIECE;   // where B(0) lives
+  constexpr int NEXT_A = T::TWO_RINGS ? T::A_BYTES : 2 * PIECE, NEXT_B = T::TWO_RINGS ? T::B_BYTES : 2 * PIECE;
   // load I of K tile kt into the piece at `piece` (the stager puts B loads T::A_BYTES behind the address it is given)
   auto load_a = [&](auto i, int kt, char* piece) { st.template issue_one<decltype(i)::value, WHOLE>(kt, K, piece); };
   auto load_b = [&](auto i, int kt, char* piece) { st.template issue_one<AL + decltype(i)::value, WHOLE>(kt, K, piece - T::A_BYTES); };
   static_for<0, D>([&](auto j) {
     constexpr int J = decltype(j)::value;
-    static_for<0, AL>([&](auto i) { load_a(i, min(J, kt_last), lds + 2 * J * PIECE); });
-    static_for<0, BL>([&](auto i) { load_b(i, min(J, kt_last), lds + (2 * J + 1) * PIECE); });
+    static_for<0, AL>([&](auto i) { load_a(i, min(J, kt_last), lds + J * NEXT_A); });
+    static_for<0, BL>([&](auto i) { load_b(i, min(J, kt_last), ring_b + J * NEXT_B); });
   });
   wait_vmcnt<(D - 1) * (AL + BL)>();
   barrier_no_drain();
   Frags16<T> f0, f1;
-  static_for<0, READS>([&](auto j) { read_one16<T, 0, decltype(j)::value>(f0, lds, lds + PIECE, a_off, b_off, koff); });
-  int ia = 0;   // piece of A(kt)
+  static_for<0, READS>([&](auto j) { read_one16<T, 0, decltype(j)::value>(f0, lds, ring_b, a_off, b_off, koff); });
+  int ia = 0;   // piece of A(kt); TWO_RINGS: its slot
+  int ib = 0;   // TWO_RINGS: slot of B(kt)
   for (int kt = 0; kt < kt_all; ++kt) {
-    const char* cur_a = lds + ia * PIECE;
-    const char* cur_b = lds + wrap(ia + 1) * PIECE;
-    const char* nxt_a = lds + wrap(ia + 2) * PIECE;
-    const char* nxt_b = lds + wrap(ia + 3) * PIECE;
-    char* free_a = lds + wrap(ia + 2 * D) * PIECE;   // held B(kt-1): nobody has read it since the last barrier
-    char* free_b = lds + ia * PIECE;             // A(kt): free after this iteration's barrier
+    const char *cur_a, *cur_b, *nxt_a, *nxt_b;
+    char *free_a, *free_b;
+    if constexpr (T::TWO_RINGS) {
+      cur_a = lds + ia * T::A_BYTES;
+      cur_b = ring_b + ib * T::B_BYTES;
+      free_a = lds + (ia == 0 ? D : ia - 1) * T::A_BYTES;   // held A(kt-1): nobody has read it since the last barrier
+      free_b = ring_b + ib * T::B_BYTES;                    // B(kt): free after this iteration's barrier
+      ia = ia == D ? 0 : ia + 1;
+      ib = ib == D - 1 ? 0 : ib + 1;
+      nxt_a = lds + ia * T::A_BYTES;
+      nxt_b = ring_b + ib * T::B_BYTES;
+    } else {
+      cur_a = lds + ia * PIECE;
+      cur_b = lds + wrap(ia + 1) * PIECE;
+      nxt_a = lds + wrap(ia + 2) * PIECE;
+      nxt_b = lds + wrap(ia + 3) * PIECE;
+      free_a = lds + wrap(ia + 2 * D) * PIECE;   // held B(kt-1): nobody has read it since the last barrier
+      free_b = lds + ia * PIECE;             // A(kt): free after this iteration's barrier
+    }
     const int kf = min(kt + D, kt_last);   // past the end the last K tile is requested again, into pieces nobody reads
     static_for<0, SLOTS>([&](auto sl) {
       constexpr int S = decltype(sl)::value;
@@ -455,7 +479,7 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
       if constexpr (2 * SLOTS + S < READS) read_one16<T, 0, 2 * SLOTS + S>(f0, nxt_a, nxt_b, a_off, b_off, koff);
       __builtin_amdgcn_sched_barrier(0);
     });
-    ia = wrap(ia + 2);
+    if constexpr (!T::TWO_RINGS) ia = wrap(ia + 2);
   }
   wait_vmcnt0();   // the last iteration's requests (the last K tile once more) are not left in flight
 }

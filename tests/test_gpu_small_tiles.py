@@ -215,7 +215,7 @@ def test_dumps_over_several_nodes_fit_the_size_query(B, nodes, d):
     assert set(r[words:]) == {-1} and -1 not in r[:words]
 
 
-# the grouped GEMM's column blocks (128, 192, 256) with several K tiles, the last one ragged
+# the grouped GEMM's 128-column block (ragged last block) with several K tiles, the last one ragged
 @pytest.mark.parametrize("t_r,inter,experts", [(128, 264, 64), (128, 1400, 16), (256, 1544, 8)])
 @pytest.mark.parametrize("hidden", [200, 456])
 @pytest.mark.parametrize("kn", [False, True], ids=["w_nk", "w_kn"])
@@ -224,6 +224,18 @@ def test_moe_column_blocks_are_bit_exact(B, t_r, inter, experts, hidden, kn):
                                   num_local_experts=8, rank=0)
     xs, ids, w = synth.moe_inputs(cfg, integer=True)
     _run_and_check(B, cfg, xs, ids, w, 8 * t_r * 2, integer=True, kn=kn)
+
+
+# every column block of the 128-row tiles at the lengths of its ring: less than a K tile, up to the four stages ([n, k], 192
+# columns) or three K tiles it requests ahead, one more, two turns; whole and ragged last K tiles; the last block ragged
+@pytest.mark.parametrize("hidden", [8, 72, 128, 192, 200, 256, 328, 520])
+@pytest.mark.parametrize("inter,block_n", [(1528, 128), (1608, 192), (2312, 256)])
+@pytest.mark.parametrize("kn", [False, True], ids=["w_nk", "w_kn"])
+def test_moe_blocks_at_the_lengths_of_their_rings(B, inter, block_n, hidden, kn):
+    cfg = synth.CONFIGS[4].scaled(world=8, tokens_per_rank=128, k=hidden, n=inter, num_experts=8, top_k=2, num_local_experts=8, rank=0)
+    assert B.moe_tile_choice(1024, 2, 8, 8, inter) == (B.OK, 128, block_n)
+    xs, ids, w = synth.moe_inputs(cfg, integer=True)
+    _run_and_check(B, cfg, xs, ids, w, 2048, integer=True, kn=kn)
 
 
 # 2, 4 and 8 ranks: every one has its own number of vectors in flight; 5: the loop over any number of ranks.
