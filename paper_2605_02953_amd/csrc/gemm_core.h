@@ -96,7 +96,9 @@ __device__ __forceinline__ void barrier_no_drain() {
 // F8: both operands are OCP e4m3 (a 128-byte row of a K tile is 128 elements), fed to v_mfma_f32_16x16x128_f8f6f4 by a
 // loop of its own (gemm_mainloop_f8); everything that counts in bytes is as for X16.  `K` is then passed in units of
 // two bytes.
-template <int BM_, int BN_, bool B_KN_ = false, bool DIRECT_ = false, bool X16_ = false, bool F8_ = false>
+//
+// DEPTH_: K tiles requested ahead by the X16 loop, 0 = as many as the tile does best with on its own unit.
+template <int BM_, int BN_, bool B_KN_ = false, bool DIRECT_ = false, bool X16_ = false, bool F8_ = false, int DEPTH_ = 0>
 struct GemmTile4W {
   static_assert((BM_ == 256 || BM_ == 128) && (BN_ == 256 || BN_ == 192 || BN_ == 128 || (X16_ && BN_ == 224) || (X16_ && BM_ == 128 && BN_ == 64)), "supported tile sides");
   static_assert(!B_KN_ || X16_, "the 32 x 32 x 16 loop is written for [N, K] operands");
@@ -126,7 +128,7 @@ struct GemmTile4W {
   // rings.
   static constexpr bool TWO_RINGS = X16_ && B_BYTES > A_BYTES;
   static constexpr int PIECE_BYTES = A_BYTES;
-  static constexpr int DEPTH = BN == 64 ? 4 : BM == 128 ? 3 : 2;
+  static constexpr int DEPTH = DEPTH_ ? DEPTH_ : BN == 64 ? 4 : BM == 128 ? 3 : 2;
   static constexpr int PIECES = 2 * DEPTH + 1;
   static constexpr int LDS_BYTES = TWO_RINGS ? (DEPTH + 1) * A_BYTES + DEPTH * B_BYTES : X16_ ? PIECES * PIECE_BYTES : NSTAGE * STAGE_BYTES;
   static constexpr int ROWS_PER_PASS = THREADS / 8;           // 32 rows per pass of 16-byte loads

@@ -62,6 +62,18 @@ inline int choose_moe_block_n(long expected_rows, int num_local_experts, int int
     if (cdiv(inter, w) * w < cdiv(inter, best) * best || (cdiv(inter, w) * w == cdiv(inter, best) * best && w > best)) best = w;
   return best;
 }
+// Column block of 128-row tiles for [k, n] weights: the narrowest that gives one tile per unit at most, counting at least one
+// row tile for each expert (choose_moe_block_n counts half a tile for an expert of a few rows, and the round that this
+// hides costs more on a tile that has a unit to itself): 60 experts, 736 tokens top-2, hidden 1024 / 2048 / 4096, 936 columns: 192
+// columns, two rounds, 57, 85, 143 us; 256 columns, one, 46, 69, 113; 256 tokens, 768 columns: 128 columns 47, 64, 99, 192 columns
+// 42, 56, 87.  `several_rounds` where none does.
+inline int moe_block_n_kn(long expected_rows, int num_local_experts, int cols, int several_rounds) {
+  const long rows = std::min<long>(expected_rows, 1 << 30);
+  const long row_tiles = std::max<long>(cdiv((int)rows, kMoeBlockM) + (num_local_experts + 1) / 2, std::min<long>(rows, num_local_experts));
+  for (int w : {128, 192, 256})
+    if ((row_tiles + 1) * cdiv(cols, w) <= 256) return w;
+  return several_rounds;
+}
 // Row tile.  What a tile costs is the bytes its compute unit loads, (rows + columns) * K, times the rounds
 // the launch needs on 256 units; the 256-row tile has two LDS stages instead of a ring fed by loading waves,
 // which makes its loads about 1.3 times slower (measured: 64 experts x 768 rows x 256 columns, 416 tiles of

@@ -484,6 +484,19 @@ static ditron_status_t launch_moe_gemm_128_rows(MoeGemmParams& g, int block_n, i
   }
 }
 
+// The same for [k, n] weights.
+static ditron_status_t launch_moe_gemm_256_rows_kn(MoeGemmParams& g, int block_n, int max_tiles, hipStream_t s) {
+  if (block_n == 128) return launch_moe_gemm<GemmTile4W<256, 128, true, true, true>>(g, max_tiles, s);
+  return launch_moe_gemm<TileBigKN>(g, max_tiles, s);
+}
+static ditron_status_t launch_moe_gemm_128_rows_kn(MoeGemmParams& g, int block_n, int max_tiles, hipStream_t s) {
+  switch (block_n) {
+    case 128: return launch_moe_gemm<TileSmallKN>(g, max_tiles, s);
+    case 192: return launch_moe_gemm<GemmTile4W<128, 192, true, true, true>>(g, max_tiles, s);
+    default: return launch_moe_gemm<GemmTile4W<128, 256, true, true, true>>(g, max_tiles, s);
+  }
+}
+
 extern "C" ditron_status_t ditron_moe_ag_grouped_gemm(
     const void* const* x_shards, const int32_t* topk_ids, const void* w, int w_layout, void* y, int32_t* counts,
     int32_t* expert_offsets, int32_t* gather_idx, int32_t* tile_records, void* workspace, int32_t* signals,
@@ -537,8 +550,8 @@ extern "C" ditron_status_t ditron_moe_ag_grouped_gemm(
   r.max_tiles = max_tiles;
   r.world = world;
   r.rank = rank;
-  const MoeTile mt = choose_moe_tile(moe_expected_rows((long)world * tokens_per_rank, top_k, num_experts, num_local_experts),
-                                     num_local_experts, inter);
+  const long expected_rows = moe_expected_rows((long)world * tokens_per_rank, top_k, num_experts, num_local_experts);
+  const MoeTile mt = choose_moe_tile(expected_rows, num_local_experts, inter);
   r.block_m = mt.block_m;
   for (int i = 0; i < world; ++i) {
     r.shard[i] = emulate ? x_shards[i] : nullptr;
@@ -584,10 +597,8 @@ extern "C" ditron_status_t ditron_moe_ag_grouped_gemm(
   g.spin_limit = tune.spin_limit;
   g.wait = mode != Mode::kPreset;
   if (w_layout == DITRON_B_KN) {   // weights stored [hidden, inter]
-    const bool wide = mt.block_n > 128;
-    if (mt.block_m == 256) return wide ? launch_moe_gemm<GemmTile4W<256, 256, true, true, true>>(g, max_tiles, s) : launch_moe_gemm<GemmTile4W<256, 128, true, true, true>>(g, max_tiles, s);
-    if (mt.block_n == 192) return launch_moe_gemm<GemmTile4W<128, 192, true, true, true>>(g, max_tiles, s);
-    return wide ? launch_moe_gemm<GemmTile4W<128, 256, true, true, true>>(g, max_tiles, s) : launch_moe_gemm<GemmTile4W<128, 128, true, true, true>>(g, max_tiles, s);
+    if (mt.block_m == 256) return launch_moe_gemm_256_rows_kn(g, mt.block_n, max_tiles, s);
+    return launch_moe_gemm_128_rows_kn(g, moe_block_n_kn(expected_rows, num_local_experts, inter, mt.block_n), max_tiles, s);
   }
   if (mt.block_m == 256) {
     if (mt.block_n == 128) return launch_moe_gemm<GemmTile4W<256, 128>>(g, max_tiles, s);
@@ -786,8 +797,8 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
   }
 
   // 1. tile list; the inverse index starts at "not on this rank"
-  const MoeTile mt = choose_moe_tile(moe_expected_rows((long)world * tokens_per_rank, top_k, num_experts, num_local_experts),
-                                     num_local_experts, hidden);
+  const long expected_rows = moe_expected_rows((long)world * tokens_per_rank, top_k, num_experts, num_local_experts);
+  const MoeTile mt = choose_moe_tile(expected_rows, num_local_experts, hidden);
   MoeRsPrepareParams pr{};
   pr.expert_offsets = expert_offsets;
   pr.inverse_idx = inverse_idx;
@@ -828,10 +839,14 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
   g.wait = 0;
   ditron_status_t st;
   if (w_layout == DITRON_B_KN) {
-    const bool wide = mt.block_n > 128;
-    if (mt.block_m == 256) st = wide ? launch_moe_gemm<GemmTile4W<256, 256, true, true, true>>(g, max_tiles, s) : launch_moe_gemm<GemmTile4W<256, 128, true, true, true>>(g, max_tiles, s);
-    else if (mt.block_n == 192) st = launch_moe_gemm<GemmTile4W<128, 192, true, true, true>>(g, max_tiles, s);
-    else st = wide ? launch_moe_gemm<GemmTile4W<128, 256, true, true, true>>(g, max_tiles, s) : launch_moe_gemm<GemmTile4W<128, 128, true, true, true>>(g, max_tiles, s);
+    // Contractions of a few K tiles: 128 x 128 tiles with two K tiles in flight, which leave room for a second work-group on the
+    // unit.  Longer ones: 256 columns where the tiles need several rounds.  us for the whole call, weights not in the caches, with these
+    // tiles / 256 columns / 128 columns and three K tiles in flight: 64 tokens, 64 experts top-4, 6000 columns K 200 73 / 80 / 89, 512
+    // 107 / 110 / 122, 768 137 / 139 / 152; 2048 tokens, 32 experts top-4, 2048 columns 200 73 / 75 / 78, 512 83.2 / 83.6 / 88, 1024
+    // 106 / 103 / 108; 144 tokens, 8 experts top-6, 8064 columns 200 41.7 / 41.9 / 43.7, 512 47.5 / 47.0 / 49.7, 2000 86 / 77 / 87.
+    if (mt.block_m == 256) st = launch_moe_gemm_256_rows_kn(g, mt.block_n, max_tiles, s);
+    else if (inter <= 512) st = launch_moe_gemm<GemmTile4W<128, 128, true, true, true, false, 2>>(g, max_tiles, s);
+    else st = launch_moe_gemm_128_rows_kn(g, moe_block_n_kn(expected_rows, num_local_experts, hidden, 256), max_tiles, s);
   } else if (mt.block_m == 256) {
     st = mt.block_n == 128 ? launch_moe_gemm<GemmTile4W<256, 128>>(g, max_tiles, s) : launch_moe_gemm<TileBigDirect>(g, max_tiles, s);
   } else {

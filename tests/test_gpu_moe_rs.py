@@ -129,6 +129,21 @@ def test_moe_rs_weights_kn_and_flags_preset(B):
     _run(B, ids, hs, ws, e0s, 2, world, t_r, inter_r, hidden, experts, top_k, experts, 2, None, True, flags=B.FLAGS_PRESET)
 
 
+# [k, n] weights: contractions up to 512 take a ring of two K tiles (its five pieces: less than one K tile up to two turns, whole
+# and ragged), longer ones 128, 192 and 256 columns in one round of tiles and 256 in several; the last column block ragged
+@pytest.mark.parametrize("inter_r,hidden", [(8, 1000), (64, 1000), (72, 264), (128, 1000), (192, 1000), (200, 4000), (328, 1000), (512, 264),
+                                            (520, 1000), (520, 4000), (520, 5480), (520, 7208), (648, 5480)])
+def test_moe_rs_weights_kn_by_contraction(B, inter_r, hidden):
+    world, t_r, experts, top_k = 4, 16, 8, 2
+    ids, hs, ws, e0s = _case(world, t_r, inter_r, hidden, experts, top_k, experts, seed=inter_r, integer=True)
+    # inputs in -1 .. 1: a rank's combined partial is a sum of 2 inter_r products of variance 4/9, so at most 256 (from where on bf16
+    # does not hold every integer) within 10 standard deviations at 648 (with -2 .. 2 it would be within 3.6), and the oracle's one rounding is all
+    rng = synth.rng_for(inter_r, 41, hidden)
+    hs, ws = [[synth.integer_bf16(rng, x.shape, -1, 1) for x in xs] for xs in (hs, ws)]
+    assert B.moe_tile_choice(world * t_r, top_k, experts, experts, hidden)[1] == 128
+    _run(B, ids, hs, ws, e0s, 3, world, t_r, inter_r, hidden, experts, top_k, experts, 2, None, True, kn=True)
+
+
 def test_moe_rs_large_experts_and_row_overflow(B):
     # 2048 rows per expert: the 256-row tile
     world, t_r, inter_r, hidden, experts, top_k = 8, 512, 128, 264, 4, 2

@@ -238,6 +238,17 @@ def test_moe_blocks_at_the_lengths_of_their_rings(B, inter, block_n, hidden, kn)
     _run_and_check(B, cfg, xs, ids, w, 2048, integer=True, kn=kn)
 
 
+# many experts of a few rows: [k, n] weights take wider blocks than [n, k] ones (192 and 256 where those take 128), which changes
+# nothing in the tile list
+@pytest.mark.parametrize("inter,block_n", [(600, 128), (936, 128), (1160, 192)])
+@pytest.mark.parametrize("kn", [False, True], ids=["w_nk", "w_kn"])
+def test_moe_blocks_of_small_experts(B, inter, block_n, kn):
+    cfg = synth.CONFIGS[4].scaled(world=8, tokens_per_rank=6, k=200, n=inter, num_experts=60, top_k=2, num_local_experts=60, rank=0)
+    assert B.moe_tile_choice(48, 2, 60, 60, inter) == (B.OK, 128, block_n)
+    xs, ids, w = synth.moe_inputs(cfg, integer=True)
+    _run_and_check(B, cfg, xs, ids, w, 96, integer=True, kn=kn)
+
+
 # 2, 4 and 8 ranks: every one has its own number of vectors in flight; 5: the loop over any number of ranks.
 # 264 columns: a last tile of one vector; 3080 x ~4040: 256-row tiles
 @pytest.mark.parametrize("world", [2, 4, 5, 8])
