@@ -266,12 +266,23 @@ def test_all_reduce_consumer_by_rank_count(B, world, rows, n, k):
     _ok(B, run(a_dev, b_dev, peers, d), run)
     assert np.array_equal(bits(run.gemm_out), parts[d])
     assert np.array_equal(bits(run.out), full)
-    outs = [torch.full((cfg.m, n), 0x7FC0, dtype=torch.int16, device="cuda") for _ in range(world)]
+    # two-shot, both layouts of the weight: the own output is complete, and every peer's holds exactly the tiles this rank owns
     reduced = [None if s == d else to_dev(full) for s in range(world)]
-    run.epoch += 1
-    st = B.gemm_ar_two_shot(a_dev, b_dev, B.B_NK, run.gemm_out, peers, outs, reduced, run.signals, run.status, None, cfg.m, n, k,
-                            world, d, run.epoch, B.EMULATE_PRODUCER)
-    _ok(B, st, run)
-    assert np.array_equal(bits(outs[d]), full)
-    mine = bits(outs[0]) if d else full
-    assert ((mine == full) | (mine == 0x7FC0)).all()
+    bm, bn = run.tc["block_m"], run.tc["block_n"]
+    for layout, w_dev in ((B.B_NK, b_dev), (B.B_KN, to_dev(b_list[d]))):
+        outs = [torch.full((cfg.m, n), 0x7FC0, dtype=torch.int16, device="cuda") for _ in range(world)]
+        sched = torch.full((4 * run.ntiles,), -1, dtype=torch.int32, device="cuda")
+        run.epoch += 1
+        st = B.gemm_ar_two_shot(a_dev, w_dev, layout, run.gemm_out, peers, outs, reduced, run.signals, run.status, sched, cfg.m, n, k,
+                                world, d, run.epoch, B.EMULATE_PRODUCER | B.DUMP_SCHEDULE)
+        _ok(B, st, run)
+        assert np.array_equal(bits(outs[d]), full)
+        want = np.full((cfg.m, n), 0x7FC0, dtype=np.uint16)
+        for q, (pm, pn, _, _) in enumerate(sched.cpu().view(-1, 4).tolist()):
+            if oar.two_shot_owner(q, world) == d:
+                blk = (slice(pm * bm, (pm + 1) * bm), slice(pn * bn, (pn + 1) * bn))
+                want[blk] = full[blk]
+        assert (want != 0x7FC0).any() == (run.ntiles > d) and not (full == 0x7FC0).any()   # position d is the rank's first tile
+        for t in range(world):
+            if t != d:
+                assert np.array_equal(bits(outs[t]), want), (layout, t)
