@@ -35,7 +35,7 @@ MEASURED_TRAFFIC = {
     # workload: (bytes read + bytes written, profile, kernels as of commit)
     "cfg2": (873.0e6 + 193.0e6, "profiles/ag_gemm_kernel_cfg2.md", "6445342"),   # fused launch; GEMM-only launch 739.8e6 + 58.8e6; algorithmic 251.7e6 (+ 268.4e6 emulated gather)
     "cfg3": (822.4e6 + 251.8e6, "profiles/gemm_rs_kernel_reduce_slots_kernel_cfg3.md", "6a80893"),   # gemm_rs_kernel fused; reduce_slots_kernel 134.3e6 + 16.8e6 = its algorithmic 151.0e6
-    "cfg4": (144.8e6 + 6.2e6, "profiles/moe_kernels_cfg4.md", "04f4682"),   # moe_grouped_gemm_kernel (algorithmic 123.2e6); the gather in the routing launch: 67.4e6 + 67.2e6
+    "cfg4": (147.5e6 + 6.2e6, "profiles/moe_kernels_cfg4.md", "e21fbd9"),   # moe_grouped_gemm_kernel (algorithmic 123.2e6); the gather in the routing launch: 67.5e6 + 67.2e6
     "gemm_ar": (1956.3e6 + 269.8e6, "profiles/gemm_ar_kernel_table_shape3.md", "6a80893"),   # fused launch: operand panels ~0.9e9 + eight partials 1.07e9 read; partial + output written
     "moe_rs": (33.1e6 + 67.7e6 + 97.1e6 + 62.9e6 + 33.6e6 + 4.2e6 + 0.1e6, "profiles/moe_rs_kernels_table_shape.md", "04f4682"),   # grouped GEMM + combine (with the peers' copies) + reduction + preparation
     "cfg5": (102.1e6 + 28.5e6, "profiles/ag_gemm_splitk_kernel_cfg5.md", "431892f"),   # ag_gemm_splitk_kernel (fp8) with emulated peers: B 67.1e6 + A + three quarters of the partial tiles out and back; algorithmic 70.3e6

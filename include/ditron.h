@@ -89,7 +89,8 @@ enum {
                                   * flag wait entered, flag wait left, end) in ticks of the GPU's constant
                                   * 100 MHz clock, low 31 bits: where a launch's time goes between waiting
                                   * for shards and computing (decode_variant 1 writes nothing) */
-  DITRON_EPOCH_IN_MEMORY = 32u,  /* decode-shaped ditron_ag_gemm (decode_variant 0, 2, 3, 4): the `epoch`
+  DITRON_EPOCH_IN_MEMORY = 32u,  /* fp8 ditron_ag_gemm of any size, and bf16 of decode shape (decode_variant 0, 2,
+                                  * 3, 4): the `epoch`
                                   * argument is ignored; the call's epoch is 1 + the last word of `signals`,
                                   * and the kernel's last work-group to finish stores it there (the word
                                   * before it counts the finished work-groups and returns to zero).  The
@@ -152,7 +153,7 @@ ditron_status_t ditron_tile_row_order(int op, int m, int block_m, int world, int
  * (m = max_rows; the smallest BLOCK_M is reported and 0 for the column block: both are chosen per
  * call, see ditron_moe_tile_choice),
  * 3 = gemm_ar, 4 = ag_gemm with B stored [k, n] (bf16 problems with few 128 x 128 tiles and B stored
- * [n, k] use the 128 x 32 tile of the decode kernel, which the [k, n] layout does not).
+ * [n, k] use the split tiles of the decode kernel, which the [k, n] layout does not).
  * out[0]=BLOCK_M out[1]=BLOCK_N out[2]=GROUP_SIZE_M out[3]=chiplets used by the work-group
  * remap (0 = no remap) out[4]=tiles per chiplet per block out[5]=number of tiles
  * (ag_gemm / gemm_rs) out[6]=threads per work-group out[7]=1 for a 256-row tile of
@@ -225,7 +226,8 @@ ditron_status_t ditron_schedule_dump(int op, int m, int n, int k, int world, int
  *                shards; NULL = rank, rank+1, ... (mod world) as in the paper's producer
  *  tuning->decode_variant (fp8, and bf16 problems of at most 128 tiles of 128 x 128 with B stored
  *                [n, k]; the latency variants of the paper's Section "Kernel library"): 0 = library's
- *                choice; 1 = 128 x 32 tiles over the whole contraction; 2 = 128 x 128 tiles, the
+ *                choice: variant 2, or for large fp8 problems (more than 256 tiles of 128 x 128) 256-row
+ *                tiles of the tile engine, which any other value keeps them from; 1 = 128 x 32 tiles over the whole contraction; 2 = 128 x 128 tiles, the
  *                contraction split over up to 8 work-groups whose fp32 partials are summed in split
  *                order by the last to finish; 3 = the same with 128 x 64 tiles; 4 = 16-row tiles,
  *                one shard's rows at the decode shape, each waiting for its own shard only

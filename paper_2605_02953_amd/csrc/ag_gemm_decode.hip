@@ -230,11 +230,11 @@ __global__ __launch_bounds__(DecodeTile::THREADS) void ag_gemm_decode_kernel(con
 // it.  Here a work-group owns a BM x BN tile over 1/S of the contraction: per 128-byte K tile it
 // loads BM + BN rows instead of 128 + 32, so with 128 x 128 tiles and S = 4 a unit moves 512 KiB
 // where the form above moves 1.25 MiB.  The S partial tiles (fp32, written in the lanes' own order so
-// that every store and load is a contiguous KiB per wave) meet in memory: each work-group stores its
-// partial, then draws a ticket from the tile's counter; the one that draws the last ticket adds the S
-// partials in split order 0..S-1 (its own from registers, so the order and hence the bits do not depend
-// on who came last), applies the scales and writes C.  No work-group waits for another, so the grid may
-// be of any size.  Waves 0-3 fetch A and compute, waves 4-7 fetch B, one barrier per K tile, as above.
+// that every store and load is a contiguous KiB per wave) meet in memory as words that carry the call's epoch: each
+// work-group stores the parts of its partial that others sum, reads the S - 1 others of the part it sums itself until every word
+// carries this epoch, adds the S partials in split order 0..S-1 (so the bits do not depend on who came last), applies the
+// scales and writes that part of C.  The work-groups of a tile wait for each other (bounded); they are
+// neighbours in a grid of at most 256 beside the producers (plan_decode), which wait for nobody.  Waves 0-3 fetch A and compute, waves 4-7 fetch B, one barrier per K tile, as above.
 // BM = 16 is the per-shard form: a tile is one shard's rows and waits for that shard's flag only.
 template <int BM_, int BN_>
 struct SplitKTile {

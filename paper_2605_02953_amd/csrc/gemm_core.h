@@ -1,10 +1,10 @@
-// bf16 MFMA tile engine for gfx950: C_tile[BM,BN] (fp32) += A_tile[BM,K] . B_tile[BN,K]^T.
+// MFMA tile engine for gfx950, bf16 and OCP e4m3: C_tile[BM,BN] (fp32) += A_tile[BM,K] . B_tile[BN,K]^T.
 //
-// Both operands are read as rows that are contiguous along the contraction dimension.  A
-// K slice of 64 elements of BM + BN rows is staged in LDS as 128-byte rows (one cache line per
+// Both operands are read as rows that are contiguous along the contraction dimension (bf16: B also stored [K, N], see B_KN).  A
+// K slice of 128 bytes of BM + BN rows is staged in LDS as 128-byte rows (one cache line per
 // row) whose eight 16-byte chunks are XOR-swizzled by the row index.  Four waves, one per SIMD,
-// each own a quarter of the tile and feed v_mfma_f32_32x32x16_bf16 (or, in the X16 form of the tile,
-// v_mfma_f32_16x16x32_bf16) from 128-bit LDS reads.  The
+// each own a quarter of the tile and feed v_mfma_f32_16x16x32_bf16, v_mfma_f32_16x16x128_f8f6f4 or, for a few MoE tiles,
+// v_mfma_f32_32x32x16_bf16 from 128-bit LDS reads.  The
 // instruction's row operand is taken from the B rows and its column operand from the A rows,
 // so that a lane ends up with four consecutive output columns of one output row.
 #pragma once
@@ -74,7 +74,7 @@ __device__ __forceinline__ void barrier_no_drain() {
 }
 
 // ------------------------------------------------------------------ the tile
-// BM x BN output tile (BM 256 or 128, BN 256, 224, 192 or 128) computed by four waves, one per SIMD,
+// BM x BN output tile (BM 256 or 128, BN 256, 224, 192, 128 or 64) computed by four waves, one per SIMD,
 // each owning BM/2 x BN/2 (256 x 256: 128 x 128 per wave, 256 accumulator registers, every
 // fragment read from LDS feeds four MFMAs).
 //
@@ -90,8 +90,8 @@ __device__ __forceinline__ void barrier_no_drain() {
 // BN elements, the pairs of chunks swizzled by the row (swz_kn), and the MFMA operand (eight consecutive k of one column per
 // lane) is assembled by two transposing LDS reads (ds_read_b64_tr_b16: inside each group of 16 lanes, lane i receives
 // element i % 4 of the 8-byte chunks addressed by lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4; measured).  Everything that counts
-// in bytes is as for [N, K].  (It replaced a register-staged 32 x 32 x 16 loop: [7976 x 8192] x [8192 x 3584] fused 446 ->
-// 388 us at 256 x 256 tiles, 128 x 128 tiles 20 to 30 % less, MoE 2 to 23 % less.)
+// in bytes is as for [N, K].  (It replaced a register-staged 32 x 32 x 16 loop: [7976 x 8192] x [8192 x 3584] fused 441 ->
+// 394 us at 256 x 256 tiles, 128 x 128 tiles 20 to 30 % less, MoE, with the blocks that it then takes, 0 to 25 % less.)
 //
 // F8: both operands are OCP e4m3 (a 128-byte row of a K tile is 128 elements), fed to v_mfma_f32_16x16x128_f8f6f4 by a
 // loop of its own (gemm_mainloop_f8); everything that counts in bytes is as for X16.  `K` is then passed in units of

@@ -27,7 +27,8 @@ typedef GemmTile4W<256, 192, false, true, true, true> TileBigF8_192;
 // 128x128 output tile on the same loop with three K tiles in flight (112 KiB of LDS): 64x64 per wave; for problems with
 // too few 256x256 tiles to fill the chip.  (The register-staged 32 x 32 x 16 loop with two LDS stages that it replaced
 // requests one K tile ahead, which is less than the L2 takes under load: [1024 x 8192] x [8192 x 3696], operands resident,
-// 73 -> 57 us; 0.53 -> 0.38 us per K tile of a work-group, of which 0.34 are the 768 cycles of its LDS traffic.)
+// 73 -> 57 us; 0.53 -> 0.38 us per K tile of a work-group, about 840 cycles, of which the MFMAs are 512 and the LDS array's reads 260
+// by its counter (profiles/tile_loops.md): neither fills the loop, its start-up and barrier latencies do the rest.)
 typedef GemmTile4W<128, 128, false, true, true> TileSmall;
 // The same for B stored [K, N].
 typedef GemmTile4W<256, 256, true, true, true> TileBigKN;
@@ -75,11 +76,12 @@ inline int moe_block_n_kn(long expected_rows, int num_local_experts, int cols, i
   return several_rounds;
 }
 // Row tile.  What a tile costs is the bytes its compute unit loads, (rows + columns) * K, times the rounds
-// the launch needs on 256 units; the 256-row tile has two LDS stages instead of a ring fed by loading waves,
-// which makes its loads about 1.3 times slower (measured: 64 experts x 768 rows x 256 columns, 416 tiles of
-// 128 rows in two rounds against 224 of 256 rows in one: 100 against 85 us for the whole call; 60 experts x
-// 546 rows x 176 columns: 97 against 94 us).  From 1024 rows per expert on the 256-row tile is also ahead
-// on matrix work (fewer loads per MFMA, little padding).
+// the launch needs on 256 units; the 256-row tile's count 1.3 times (a factor fitted to former loops; with the present ones,
+// [n, k] weights, the best 128-row tile and 256 x 256, us for the whole call: 60 experts x 546 rows x 176 columns 80, 73; 64 x 768 x 256
+// 91, 80; 16 x 512 x 1024 78, 72; 64 x 256 x 512 84, 76, all of which the factor gives to 256 rows; 32 x 128 x 768 50, 65; 32 x 375 x 512 45,
+// 52; 64 x 192 x 200 67, 96, which it leaves to 128; it misses 60 x 273 x 352 with 75, 73).  From 1024 rows per expert on the
+// 256-row tile has fewer loads per MFMA and little padding (8 x 2048 x 1536 276, 226; 60 x 546 x 1408 301, 289; not so 32 x 1024 x 512
+// 115, 120, and one expert x 2048 x 2048 39, 48).
 inline MoeTile choose_moe_tile(long expected_rows, int num_local_experts, int inter) {
   const MoeTile small{kMoeBlockM, choose_moe_block_n(expected_rows, num_local_experts, inter)};
   const MoeTile big{256, inter <= 128 ? 128 : 256};
@@ -107,7 +109,9 @@ struct TileChoice {
 // What a launch of `tiles` tiles of 256 x block_n costs, in units of a full round of 256 x 256 tiles: the work of a
 // tile times the rounds, a last round that fills the fraction x of the chip counting 0.55 + 0.45 x (measured: the
 // 192 tiles of cfg 2's second round take 0.886 of the time of the 256 of its first, the chip being power-limited);
-// a 224-column tile loads 3 % more bytes per flop, a 192-column tile 7 %.
+// a 224-column tile loads 3 % more bytes per flop, a 192-column tile 7 %.  The constants are bf16's; for e4m3 the choice they make
+// was the fastest of the three widths, or within 2 % of it, at all of 24 shapes tried (256 / 224 / 192 columns, K 8192, us: 8192 x 1376
+// 120 / 116 / 115, 8192 x 2560 199 / 186 / 175, 8192 x 3584 213 / 205 / 245, 8192 x 3696 215 / 263 / 245, 8192 x 6656 379 / 357 / 386).
 inline double tiling_cost(long tiles, int block_n) {
   const double work = block_n / 256.0 * (block_n == 256 ? 1.0 : block_n == 224 ? 1.03 : 1.07);
   const long full = tiles / 256, rest = tiles % 256;
@@ -170,10 +174,12 @@ inline TileChoice choose_tile(int m, int n, int k, Narrow narrow) {
   t.big = takes_big_tiles(m, n, k, narrow);
   t.block_m = t.block_n = t.big ? 256 : 128;
   // Half as wide where that many tiles still fit the chip in one round and the K loop is what the call spends its time on.
-  // AllGather-GEMM, B stored [K, N] ([N, K]: the decode kernel): 64 x 3584, K 8192 56.3 -> 41.1 us; 1024 x 2048, K 4096 (256 of
-  // these tiles) 48.5 -> 43.7.  GEMM-ReduceScatter needs units for the peers' copies and the reduction
-  // beside the tiles, so only up to 128 of them, and long contractions: 128 x 8192, K 3584 31.0 -> 27.1 us;
-  // not so 128 x 8192, K 512 (19.7 -> 21.2), 128 x 16384, K 1024 and 512 x 4096, K 2048 (256 tiles; 30.3 -> 37.5, 28.8 -> 40.4).
+  // us with 128 and with 64 columns.  AllGather-GEMM, B stored [K, N] ([N, K]: the decode kernel): 64 x 3584, K 512 12.5, 11.4; 8192
+  // 56.4, 42.2; 1024 x 2048 (256 of these tiles) K 512 14.1, 14.2; 1024 19.4, 18.8; 4096 44.2, 39.5.
+  // GEMM-ReduceScatter needs units for the peers' copies and the reduction beside the tiles, so only up to 128 of them, and long
+  // contractions: 128 x 8192 (128 of them) K 512 18.3, 20.7; 1024 18.8, 19.3; 1536 21.0, 21.9 ([K, N]: 22.2, 21.7); 2048 23.2, 22.8; 2560
+  // 28.2, 27.0; 4096 33.4, 30.5; 128 x 4096 512 15.2, 15.6; 1024 17.0, 16.7; 1536 19.2, 18.2; 256 tiles: 128 x 16384, K 1024 30.3, 37.5,
+  // 512 x 4096, K 2048 28.8, 40.4.
   const long tiles_small = (long)cdiv(m, 128) * cdiv(n, 128);
   const bool fits = narrow == Narrow::kNever ? tiles_small <= 64 && k >= 1536 : tiles_small <= 128 && k >= 512;
   if (fits && narrow != Narrow::kAllReduce) t.block_n = 64;
@@ -191,9 +197,8 @@ inline TileChoice choose_tile(int m, int n, int k, Narrow narrow) {
   return t;
 }
 
-// Decode-shaped AllGather-GEMM (fp8 with few 256 x 256 tiles; bf16 when the 128 x 128 tiles of the tile engine would not
-// cover half the chip and B is stored [n, k]): one tile shape, 128 rows x 32 columns, 4 computing waves +
-// 4 loading waves.
+// Decode-shaped AllGather-GEMM (ag_takes_decode_kernel: fp8 where takes_big_tiles says no, bf16 when the 128 x 128 tiles of the
+// tile engine would not cover half the chip and B is stored [n, k]): the tiles of plan_decode, 4 computing waves + 4 loading waves.
 inline bool bf16_ag_is_decode_shaped(int m, int n) { return (long)cdiv(m, 128) * cdiv(n, 128) <= 128; }
 // The tile loaders address an operand with 32-bit byte offsets, and the buffer-addressed
 // loaders reserve offsets from 0x7ffffff0 up as "out of range, reads zero".

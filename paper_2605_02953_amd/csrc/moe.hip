@@ -850,7 +850,7 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
   } else if (mt.block_m == 256) {
     st = mt.block_n == 128 ? launch_moe_gemm<GemmTile4W<256, 128>>(g, max_tiles, s) : launch_moe_gemm<TileBigDirect>(g, max_tiles, s);
   } else {
-    // A contraction of a few K tiles: a tile is over before the ring of stages is full and costs about what a
+    // [n, k] weights and a contraction of a few K tiles: a tile is over before the ring of stages is full and costs about what a
     // work-group start costs, so 128 x 128 tiles on the two-stage loop (two work-groups fit a unit) and as many
     // work-groups as are resident at once, each walking down its share of the items (measured at the paper's
     // MoE+RS shape, whole call: 115 us with the ring tiles, 109 with these tiles, 106.5 with 512 resident

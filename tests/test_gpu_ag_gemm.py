@@ -224,8 +224,8 @@ def test_multi_node_order_that_skips_rows_is_refused(B):
 @pytest.mark.parametrize("kn", [False, True], ids=["b_nk", "b_kn"])
 def test_long_contraction_on_256_tiles_is_bit_exact(B, k, kn):
     """256 x 256 tiles over long contractions, small-integer inputs, both layouts of B, bit for bit: 8256 = 129 and
-    16384 = 256 whole K tiles, 12360 and 16392 with a ragged last K tile (the loads' range test); [n, k] operands
-    go straight into LDS, [k, n] operands through the register-staged loop."""
+    16384 = 256 whole K tiles, 12360 and 16392 with a ragged last K tile (the loads' range test); both
+    layouts go straight into LDS."""
     cfg = synth.CONFIGS[2].scaled(world=8, m_per_rank=505, n=3080, k=k, rank=3)
     st, tc = B.tile_config(4 if kn else 0, cfg.m, cfg.n, cfg.k)
     assert (tc["block_m"], tc["block_n"], tc["direct_staging"]) == (256, 256, 0) if kn else (256, 224, 1)   # 16 x 14 tiles of 224 columns fill more of the last round than 16 x 13 of 256

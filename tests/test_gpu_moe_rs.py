@@ -112,7 +112,7 @@ def _run(B, ids, hs, ws, e0s, d, world, t_r, inter_r, hidden, experts, top_k, lo
     (8, 128, 192, 256, 32, 2, 32, 4, False),      # the table's expert count and top-k at 1/8 of its tokens
     (4, 96, 64, 264, 8, 2, 2, 3, True),           # experts sharded over the ranks: most assignments are elsewhere
     (1, 300, 64, 64, 3, 1, 3, 1, True),           # one rank: no peers
-    (8, 256, 64, 1544, 8, 2, 8, 2, True),         # 4096 rows x 1544 columns: the 256-column block
+    (8, 256, 64, 1544, 8, 2, 8, 2, True),         # 4096 rows x 1544 columns: several rounds of tiles
 ])
 def test_moe_rs_end_to_end(B, world, t_r, inter_r, hidden, experts, top_k, local, chunks, integer):
     ids, hs, ws, e0s = _case(world, t_r, inter_r, hidden, experts, top_k, local, seed=world, integer=integer)
