@@ -331,14 +331,29 @@ static ditron_status_t gemm_rs_impl(const void* a, const void* b, int b_layout, 
   const ProducerPlan pl = plan_producers((size_t)(world - 1) * m_r * n * 2, (world - 1) * chunks_per_slot);
   p.num_producers = (emulate && world > 1) ? pl.producers : 0;
   p.teams = pl.teams;
+  // 128 x 128 tiles that fill the chip together with the peers' copies: two work-groups to a unit, so that the copies and the tiles
+  // of a last, partly empty round run beside others.  us with one and with two to a unit, weights not in the caches, 8 ranks: 245
+  // tiles + 16 copying work-groups, 640 x 6272, K 1024 41.2, 39.2; 1536 48.6, 44.2; 3584 65.5, 60.0 (2 ranks, 8 of them: all in one
+  // round, 51.8, 59.6); 256 tiles, 2048 x 2048, 2048 47.8, 46.7; 3584 66.1, 57.2 ([k, n] 64.9, 56.8); 320, 2048 x 2560, 70.5, 64.2; 480, 1000 x
+  // 7680, 83.1, 79.6; 240 + 16, 2048 x 1920, K 3584 49.4, 56.1.
+  const int tiles = cdiv(m, 128) * cdiv(n, 128);
+  const bool paired = tiles + p.num_producers > 256;
+  // [n, k] weights, up to eight K tiles and 64 tiles or more: the staged tile.  us with it and with TileSmall: 96 tiles, 288 x 4088, K 256
+  // 24.6, 24.9; 512 24.4, 24.9; 768 25.0, 24.9 (2 ranks 19.6, 19.6; 18.3, 19.5; 19.8, 18.6); 120, 992 x 1872, 29.1, 29.5; 29.1, 29.5; 29.4, 29.8
+  // (21.2, 21.8; 21.5, 21.3; 21.3, 22.0); 40, 520 x 1024, K 512 16.6, 17.8 (13.6, 12.9), 768 18.0, 16.6; against the calls as they were
+  // with it, 128 x 128 tiles on the ring took 21.3 -> 21.7 (512 x 4096 over 2 ranks, K 512), 28.8 -> 29.6 (992 x 1872 fused, K 456).
+  const bool staged = tiles >= 64 && k_local <= 512;
   ditron_status_t st;
   if (b_layout == DITRON_B_KN) {
     st = tc.big               ? launch_rs<TileBigKN>(p, (hipStream_t)stream)
          : tc.block_n == 64 ? launch_rs<TileSmallKN64>(p, (hipStream_t)stream)
+         : paired           ? launch_rs<TileSmallKNPaired>(p, (hipStream_t)stream)
                             : launch_rs<TileSmallKN>(p, (hipStream_t)stream);
   } else {
     st = tc.big               ? launch_rs<TileBigDirect>(p, (hipStream_t)stream)
          : tc.block_n == 64 ? launch_rs<TileSmall64>(p, (hipStream_t)stream)
+         : staged           ? launch_rs<TileSmallStaged>(p, (hipStream_t)stream)
+         : paired           ? launch_rs<TileSmallPaired>(p, (hipStream_t)stream)
                             : launch_rs<TileSmall>(p, (hipStream_t)stream);
   }
   if (st != DITRON_OK) return st;

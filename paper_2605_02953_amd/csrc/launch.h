@@ -35,6 +35,13 @@ typedef GemmTile4W<256, 256, true, true, true> TileBigKN;
 typedef GemmTile4W<256, 224, true, true, true> TileBigKN224;
 typedef GemmTile4W<256, 192, true, true, true> TileBigKN192;
 typedef GemmTile4W<128, 128, true, true, true> TileSmallKN;
+// The first form of that tile: register-staged, two LDS stages (64 KiB), 32 x 32 x 16 MFMA.  Left where a few K tiles are all there is
+// (gemm_rs_impl, the MoE down-projection), by 0 to 3 % there.
+typedef GemmTile4W<128, 128> TileSmallStaged;
+// The same two with two K tiles in flight (80 KiB): two work-groups share a unit.  For launches whose work-groups need several
+// rounds all the same and are bound by more than their K loops (GEMM-ReduceScatter with the peers' copies, short MoE contractions).
+typedef GemmTile4W<128, 128, false, true, true, false, 2> TileSmallPaired;
+typedef GemmTile4W<128, 128, true, true, true, false, 2> TileSmallKNPaired;
 // 128 x 64, four K tiles in flight (144 KiB), for problems of few 128 x 128 tiles: a unit's K tile is 24 KiB instead of 32, and
 // twice as many units share the weight (choose_tile).
 typedef GemmTile4W<128, 64, false, true, true> TileSmall64;

@@ -845,7 +845,7 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
     // 107 / 110 / 122, 768 137 / 139 / 152; 2048 tokens, 32 experts top-4, 2048 columns 200 73 / 75 / 78, 512 83.2 / 83.6 / 88, 1024
     // 106 / 103 / 108; 144 tokens, 8 experts top-6, 8064 columns 200 41.7 / 41.9 / 43.7, 512 47.5 / 47.0 / 49.7, 2000 86 / 77 / 87.
     if (mt.block_m == 256) st = launch_moe_gemm_256_rows_kn(g, mt.block_n, max_tiles, s);
-    else if (inter <= 512) st = launch_moe_gemm<GemmTile4W<128, 128, true, true, true, false, 2>>(g, max_tiles, s);
+    else if (inter <= 512) st = launch_moe_gemm<TileSmallKNPaired>(g, max_tiles, s);
     else st = launch_moe_gemm_128_rows_kn(g, moe_block_n_kn(expected_rows, num_local_experts, hidden, 256), max_tiles, s);
   } else if (mt.block_m == 256) {
     st = mt.block_n == 128 ? launch_moe_gemm<GemmTile4W<256, 128>>(g, max_tiles, s) : launch_moe_gemm<TileBigDirect>(g, max_tiles, s);
@@ -855,7 +855,7 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
     // work-groups as are resident at once, each walking down its share of the items (measured at the paper's
     // MoE+RS shape, whole call: 115 us with the ring tiles, 109 with these tiles, 106.5 with 512 resident
     // work-groups, 113.6 with 768; 256 x 256 tiles 108-118).
-    st = inter <= 256 ? launch_moe_gemm_walk<GemmTile4W<128, 128>>(g, max_tiles, 512, s)
+    st = inter <= 256 ? launch_moe_gemm_walk<TileSmallStaged>(g, max_tiles, 512, s)
                       : launch_moe_gemm_128_rows(g, mt.block_n, max_tiles, s);
   }
   if (st != DITRON_OK) return st;

@@ -112,6 +112,27 @@ def test_64_column_tiles_reduce_bit_exact(B, m_per_rank, n, k, kn):
         assert np.array_equal(bits(dsts[r][d]), parts[d][r * m_per_rank:(r + 1) * m_per_rank])
 
 
+# 255 tiles of 128 x 128 beside the peers' copies: [k, n] weights, and [n, k] ones beyond 512, on tiles that share a unit (a ring of
+# two K tiles in five pieces); [n, k] up to 512 on the register-staged tile; from less than a K tile on, whole and ragged last ones
+@pytest.mark.parametrize("k", [8, 72, 128, 192, 200, 328, 512, 520, 584, 640])
+@pytest.mark.parametrize("kn", [False, True], ids=["b_nk", "b_kn"])
+def test_tiles_that_share_a_unit_reduce_bit_exact(B, k, kn):
+    world, d, m_r, n = 8, 5, 240, 2056
+    cfg = synth.CONFIGS[3].scaled(world=world, m_per_rank=m_r, n=n, k=k)
+    st, tc = B.tile_config(1, cfg.m, n, k)
+    assert (st, tc["block_m"], tc["block_n"], tc["ntiles"]) == (B.OK, 128, 128, 255)
+    a_list, b_list = synth.gemm_rs_inputs(cfg, integer=True)
+    parts = [oar.partial_bits(a, b) for a, b in zip(a_list, b_list)]
+    mine = slice(d * m_r, (d + 1) * m_r)
+    want = oar.allreduce_partials_f32_ordered(parts)[mine]
+    blocks = [None if s == d else to_dev(parts[s][mine]) for s in range(world)]
+    rs = GemmRsRun(B, world, cfg.m, n, k, 2)
+    for _ in range(2):
+        _ok(B, rs(to_dev(a_list[d]), to_dev(b_list[d] if kn else nk(b_list[d])), blocks, d, b_layout=B.B_KN if kn else B.B_NK), rs)
+        assert np.array_equal(bits(rs.gemm_out), parts[d]) and np.array_equal(bits(rs.out), want)
+        rs.gemm_out.zero_()
+
+
 # the same tile under AllGather-GEMM of a [k, n] weight, where shorter contractions and up to 128 tiles of 128 columns take it
 @pytest.mark.parametrize("k", [512, 520, 584, 640, 1160])
 @pytest.mark.parametrize("m_per_rank,n", [(8, 64), (15, 1000), (128, 2048)])
