@@ -140,18 +140,18 @@ enum class Narrow { kNever, kNK, kKN, kF8, kAllReduce };   // kF8: as kNK, e4m3 
 // The most 128 x 128 tiles with which GEMM-ReduceScatter stays on them.  Every tile ends with a release (the segment counter),
 // which a short contraction does not hide, and 256-row tiles have a quarter as many; in a long one a second round of small
 // tiles is partly empty and its units take the peers' copies, while the large tiles leave half of the chip to nobody.  So the
-// line depends on K.  us with 128 x 128 tiles and with 256-row ones (8 ranks):
-//   256 tiles, 2048 x 2048: K 512 39.3, 31.8; 1024 42.4, 34.5; 2048 49.1, 49.3 (224, 904 x 3584: 1024 33.9, 32.9; 1536 35.0, 40.2)
-//   320 tiles, 2048 x 2560: K 512 41.7, 32.2; 1536 48.2, 42.2; 2048 50.5, 49.8; 3584 65.8, 74.1
-//   416 tiles, 1544 x 4096: K 1024 53.7, 37.9; 2560 63.9, 60.1; 3072 66.1, 68.8; 4096 74.8, 85.5
-//   480 tiles, 2048 x 3840: K 3584 73.0, 79.9; 496, 904 x 7936: 91.1, 79.5 (nothing is left of the second round); 5120 112, 103;
-//   6656 128, 127; 8192 146, 152
-// How many of the rows of the large tiles exist matters less: 306 tiles, 264 x 13056 (half of them): K 1024 42.0, 34.3; 2048 47.5,
-// 49.0; 3584 62.3, 74.7; 516, 264 x 22016: 3584 94.1, 82.7.  One row of tiles is bound by the weight, which large tiles ask for in
-// longer runs, at any K: 128 x 38912 K 512 40.7, 33.3; 4096 116, 107; 6656 167, 155.
+// line depends on K.  us with 128 x 128 tiles (as gemm_rs_impl runs them) and with 256-row ones, 8 ranks, weights not in the caches:
+//   240 tiles, 2048 x 1920: K 1024 35.2, 33.2; 1536 37.1, 41.7; 3584 50.5, 75.0
+//   256 tiles, 2048 x 2048: K 512 38.2, 31.2; 1536 45.2, 40.8; 2048 47.5, 48.0; 3584 59.0, 76.3
+//   320 tiles, 2048 x 2560: K 1536 48.4, 41.8 (2 ranks 42.0, 42.4); 2048 49.9, 49.1 (45.2, 50.3); 2560 56.5, 64.2
+//   384 tiles, 2048 x 3000: K 2048 61.5, 51.7; 2560 66.9, 61.4; 3584 74.1, 76.8; 480, 2048 x 3840: 2560 68.0, 64.6; 3584 77.2, 79.0; 5120 101, 107
+//   496 tiles, 904 x 7936: K 3584 94.3, 80.8 (nothing is left of the second round); 6656 139, 131; 512, 4000 x 2048: 6656 130, 134; 8192 150, 158
+// How many of the rows of the large tiles exist matters less: 306 tiles, 264 x 13056 (half of them): K 1024 43.7, 35.5; 2048 50.0,
+// 52.3; 3584 70.8, 78.8; 516, 264 x 22016: 3584 119, 86.  One row of tiles is bound by the weight, which large tiles ask for in longer
+// runs, at any K if most of its rows exist: 304 tiles, 128 x 38912, K 512 44.8, 34.8; 3584 105, 93; 6656 170, 155; 16 x 38912 512 28.2, 26.1;
+// 2048 59.3, 56.5; 2560 65.9, 69.9; 6656 128, 145.
 inline int reduce_scatter_small_tiles(int m, int k) {
-  if (k <= 1024) return 255;
-  if (k <= 1536 || m <= 128) return 300;
+  if (k <= 1536 || (m > 64 && m <= 128)) return 255;
   return k <= 2560 ? 352 : k <= 6144 ? 480 : 512;
 }
 

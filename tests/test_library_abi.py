@@ -74,18 +74,19 @@ def test_tile_config(B):
 
 def test_reduce_scatter_tiles_by_contraction(B):
     """GEMM-ReduceScatter: short contractions give 128 x 128 tiles up from 256 of them on, longer ones later; one row of tiles
-    as the shorter ones do.  Both sides of every line."""
+    whose rows mostly exist as the shorter ones do.  Both sides of every line."""
     def rows(m, n, k):
         return B.tile_config(1, m, n, k)[1]["block_m"]
-    for last, k_from, k_to in [(255, 8, 1024), (300, 1032, 1536), (352, 1544, 2560), (480, 2568, 6144), (512, 6152, 16384)]:
+    for last, k_from, k_to in [(255, 8, 1536), (352, 1544, 2560), (480, 2568, 6144), (512, 6152, 16384)]:
         for k in (k_from, k_to):
             for tile_rows in (2, 3, 5, 8):
                 cols = last // tile_rows
                 m = tile_rows * 128 - 8
                 assert rows(m, cols * 128, k) == 128 and rows(m, (last // tile_rows + 1) * 128 - 8, k) == 256, (last, k, tile_rows)
-    assert rows(128, 300 * 128, 4096) == 128 and rows(16, 301 * 128, 4096) == 256 and rows(128, 256 * 128, 1024) == 256
+    assert rows(128, 255 * 128, 4096) == 128 and rows(128, 256 * 128, 4096) == 256 and rows(72, 256 * 128, 8192) == 256
+    assert rows(64, 256 * 128, 4096) == 128 and rows(16, 256 * 128, 1536) == 256      # a row of which half or less exists
     assert rows(2048, 2560, 3584) == rows(264, 13056, 3584) == 128      # 320 and 306 tiles, a long contraction
-    assert rows(2048, 2048, 512) == 256 and rows(2048, 2048, 1032) == 128
+    assert rows(2048, 2048, 512) == 256 and rows(2048, 2048, 2048) == 128
 
 
 def test_operand_staging_choice(B):
