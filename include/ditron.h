@@ -486,7 +486,7 @@ ditron_status_t ditron_moe_grouped_gemm_rs(const void* h, const void* w, int w_l
 
 /* Tile of the grouped GEMM for a call with these sizes (total_tokens = world * tokens_per_rank):
  * out[0] = BLOCK_M (128, or 256 when the experts are large), out[1] = BLOCK_N for [n, k] weights ([k, n]
- * weights and the down-projection may take another with 128 rows).  The tile schedule in tile_records is cut
+ * weights and the down-projection may take another).  The tile schedule in tile_records is cut
  * with this BLOCK_M. */
 ditron_status_t ditron_moe_tile_choice(int total_tokens, int top_k, int num_experts,
                                        int num_local_experts, int inter, int out[2]);

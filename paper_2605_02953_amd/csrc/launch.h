@@ -82,6 +82,14 @@ inline int moe_block_n_kn(long expected_rows, int num_local_experts, int cols, i
     if ((row_tiles + 1) * cdiv(cols, w) <= 256) return w;
   return several_rounds;
 }
+// Column block of 256-row tiles for [k, n] weights: 128 where that is one tile per unit at most, else what choose_moe_tile says.  us for
+// the whole call with 128 and with 256 columns, weights not in the caches: 8 experts x 1590 rows, hidden 4472, 304 columns (162 of the
+// narrower tiles) 113, 128; one expert x 2048, hidden 1024, 2048 columns (144) 54, 60; 4 x 2048, hidden 2048, 512 columns (140) 66, 76;
+// not so 16 x 2048 rows, 200 columns (274) 97, 82.
+inline int moe_block_n_kn_256(long expected_rows, int num_local_experts, int cols, int block_n) {
+  const long row_tiles = (std::min<long>(expected_rows, 1 << 30) + 255) / 256 + (num_local_experts + 1) / 2;
+  return (row_tiles + 1) * cdiv(cols, 128) <= 256 ? 128 : block_n;
+}
 // Row tile.  What a tile costs is the bytes its compute unit loads, (rows + columns) * K, times the rounds
 // the launch needs on 256 units; the 256-row tile's count 1.3 times (a factor fitted to former loops; with the present ones,
 // [n, k] weights, the best 128-row tile and 256 x 256, us for the whole call: 60 experts x 546 rows x 176 columns 80, 73; 64 x 768 x 256

@@ -597,7 +597,8 @@ extern "C" ditron_status_t ditron_moe_ag_grouped_gemm(
   g.spin_limit = tune.spin_limit;
   g.wait = mode != Mode::kPreset;
   if (w_layout == DITRON_B_KN) {   // weights stored [hidden, inter]
-    if (mt.block_m == 256) return launch_moe_gemm_256_rows_kn(g, mt.block_n, max_tiles, s);
+    if (mt.block_m == 256)
+      return launch_moe_gemm_256_rows_kn(g, moe_block_n_kn_256(expected_rows, num_local_experts, inter, mt.block_n), max_tiles, s);
     return launch_moe_gemm_128_rows_kn(g, moe_block_n_kn(expected_rows, num_local_experts, inter, mt.block_n), max_tiles, s);
   }
   if (mt.block_m == 256) {
@@ -844,7 +845,8 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
     // tiles / 256 columns / 128 columns and three K tiles in flight: 64 tokens, 64 experts top-4, 6000 columns K 200 73 / 80 / 89, 512
     // 107 / 110 / 122, 768 137 / 139 / 152; 2048 tokens, 32 experts top-4, 2048 columns 200 73 / 75 / 78, 512 83.2 / 83.6 / 88, 1024
     // 106 / 103 / 108; 144 tokens, 8 experts top-6, 8064 columns 200 41.7 / 41.9 / 43.7, 512 47.5 / 47.0 / 49.7, 2000 86 / 77 / 87.
-    if (mt.block_m == 256) st = launch_moe_gemm_256_rows_kn(g, mt.block_n, max_tiles, s);
+    if (mt.block_m == 256)
+      st = launch_moe_gemm_256_rows_kn(g, moe_block_n_kn_256(expected_rows, num_local_experts, hidden, mt.block_n), max_tiles, s);
     else if (inter <= 512) st = launch_moe_gemm<TileSmallKNPaired>(g, max_tiles, s);
     else st = launch_moe_gemm_128_rows_kn(g, moe_block_n_kn(expected_rows, num_local_experts, hidden, 256), max_tiles, s);
   } else if (mt.block_m == 256) {

@@ -270,6 +270,16 @@ def test_moe_blocks_of_small_experts(B, inter, block_n, kn):
     _run_and_check(B, cfg, xs, ids, w, 96, integer=True, kn=kn)
 
 
+# large experts, [k, n] weights: 256-row tiles of 128 columns where they are one round, of 256 where they are not
+@pytest.mark.parametrize("inter", [264, 1032])
+@pytest.mark.parametrize("hidden", [72, 128, 328])
+def test_moe_large_experts_of_kn_weights(B, inter, hidden):
+    cfg = synth.CONFIGS[4].scaled(world=8, tokens_per_rank=512, k=hidden, n=inter, num_experts=8, top_k=2, num_local_experts=8, rank=0)
+    assert B.moe_tile_choice(4096, 2, 8, 8, inter) == (B.OK, 256, 256)
+    xs, ids, w = synth.moe_inputs(cfg, integer=True)
+    _run_and_check(B, cfg, xs, ids, w, 8192, integer=True, block_m=256, kn=True)
+
+
 # 2, 4 and 8 ranks: every one has its own number of vectors in flight; 5: the loop over any number of ranks.
 # 264 columns: a last tile of one vector; 3080 x ~4040: 256-row tiles
 @pytest.mark.parametrize("world", [2, 4, 5, 8])
