@@ -112,9 +112,9 @@ def test_64_column_tiles_reduce_bit_exact(B, m_per_rank, n, k, kn):
         assert np.array_equal(bits(dsts[r][d]), parts[d][r * m_per_rank:(r + 1) * m_per_rank])
 
 
-# 255 tiles of 128 x 128 beside the peers' copies: [k, n] weights, and [n, k] ones beyond 512, on tiles that share a unit (a ring of
-# two K tiles in five pieces); [n, k] up to 512 on the register-staged tile; from less than a K tile on, whole and ragged last ones
-@pytest.mark.parametrize("k", [8, 72, 128, 192, 200, 328, 512, 520, 584, 640])
+# 255 tiles of 128 x 128 beside the peers' copies: [k, n] weights, and [n, k] ones beyond 1024, on tiles that share a unit (a ring of
+# two K tiles in five pieces); [n, k] up to 1024 on the register-staged tile; from less than a K tile on, whole and ragged last ones
+@pytest.mark.parametrize("k", [8, 72, 128, 192, 200, 328, 512, 584, 1024, 1032, 1096])
 @pytest.mark.parametrize("kn", [False, True], ids=["b_nk", "b_kn"])
 def test_tiles_that_share_a_unit_reduce_bit_exact(B, k, kn):
     world, d, m_r, n = 8, 5, 240, 2056
