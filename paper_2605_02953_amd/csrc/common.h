@@ -21,7 +21,7 @@ __host__ __device__ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 // observed with an acquire load at agent scope before the data is read (the paper's
 // `wait` + `consume_token` pair and its release `st`).  The eight chiplets have separate
 // L2 caches, so nothing weaker than agent scope orders a producer on one chiplet with a
-// consumer on another.
+// consumer on another.  (Where the data itself is stored written through, the release is left out: see stores_done.)
 __device__ inline void flag_raise(int32_t* flag, int32_t value) {
   __hip_atomic_store(flag, value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -90,52 +90,54 @@ __device__ inline void advance_epoch(int32_t epoch, int32_t* epoch_word, int32_t
   }
 }
 
+// ------------------------------------------------------------------ stores that need no release
+// An agent-scope release makes the wave walk its chiplet's L2 and write every dirty line back, whoever wrote it: with 100 work-groups
+// that release beside others that store, that is what a launch waits for.  Data that a flag announces is therefore stored written
+// through to memory (sc0 sc1, what the compiler emits for a system-scope atomic store); a wave's stores are at the place where every
+// chiplet looks for them once they no longer count as outstanding, so after stores_done() in every storing wave and a barrier a plain
+// (relaxed, agent-scope) flag store or counter increment is enough.  Nothing else of the work-group's is announced by such a flag.
+constexpr int kThrough = 17;   // sc0 | sc1 in the builtins' cache-policy operand
+constexpr int kStreaming = 2;  // nt
+__device__ __forceinline__ void stores_done() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+  asm volatile("" ::: "memory");
+}
+// The flag of data that was stored written through, raised after stores_done() and a barrier.
+__device__ __forceinline__ void flag_raise_stored(int32_t* flag, int32_t value) {
+  __hip_atomic_store(flag, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ------------------------------------------------------------------ chunk copy
 // Copy `bytes` (multiple of 16) from src to dst with 128-bit accesses, the calling
 // work-group being part `part` of `nparts` cooperating work-groups.
 // U = independent 16-byte loads in flight per lane; all loads of a round are issued before the first store.
+// The stores are written through, so that publish_after_all needs no release.  us for whole calls with ordinary stores (MoE: streaming ones)
+// and releases, and like this: [8192 x 8192] gathered, 3584 columns, 383 -> 365 (e4m3 208 -> 199); 1024 rows 76.2 -> 73.3; GEMM-ReduceScatter 8192 x
+// 8192 433 -> 425; MoE gather of 67 MB 91.5 -> 81.2.  (Written through with the streaming hint: 376, 202, 82.1, 435, 81.2.)
 // Two forms, each measured against the other where it is used:
 //  * STREAM (nothing on the chip reads the copy soon; the MoE gather, consumed by a later launch): a
-//    work-group takes contiguous blocks of U * blockDim vectors, dealt to the work-groups in turn, reads them
-//    with ordinary loads and stores past the chiplet's L2, so that the flag's release has no dirty lines to
-//    write back.  134 MB gather: 5.0 TB/s read + write, what a plain device-to-device copy reaches on the
-//    chip; with the streaming hint on the loads, or with the other form, 3.5.
+//    work-group takes contiguous blocks of U * blockDim vectors, dealt to the work-groups in turn, and reads them
+//    with ordinary loads.
 //  * otherwise (GEMM tiles of the same launch are waiting for the data: AllGather-GEMM, GEMM-ReduceScatter):
 //    vectors interleaved over the work-groups, loads with the streaming hint (the source is read once and
-//    should not displace the operand panels in the L2), ordinary stores.  cfg 2 fused launch: 417 us against
-//    455 us with the first form.
+//    should not displace the operand panels in the L2).
 template <int U, bool STREAM = false>
 __device__ inline void copy_slice_u(void* __restrict__ dst, const void* __restrict__ src, size_t bytes,
                                     int part, int nparts) {
   const size_t n16 = bytes >> 4;
-  const u32x4_t* s = (const u32x4_t*)src;
-  u32x4_t* d = (u32x4_t*)dst;
-  if constexpr (STREAM) {
-    const size_t block = (size_t)U * blockDim.x;
-    for (size_t b0 = (size_t)part * block; b0 < n16; b0 += (size_t)nparts * block) {
-      u32x4_t v[U];
+  const size_t block = (size_t)U * blockDim.x;   // vectors a work-group copies per round
+  const int step = (STREAM ? 1 : nparts) * (int)blockDim.x, first = (STREAM ? 0 : part * (int)blockDim.x) + (int)threadIdx.x;
+  for (size_t b0 = STREAM ? (size_t)part * block : 0; b0 < n16; b0 += (size_t)nparts * block) {
+    const int left = (int)min((n16 - b0) * 16, (size_t)0x7ffffff0);
+    const __amdgpu_buffer_rsrc_t s = __builtin_amdgcn_make_buffer_rsrc((char*)src + b0 * 16, 0, left, 0x00020000);
+    const __amdgpu_buffer_rsrc_t d = __builtin_amdgcn_make_buffer_rsrc((char*)dst + b0 * 16, 0, left, 0x00020000);
+    // (past the end of the slice nothing is read or written)
+    u32x4_t v[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const size_t i = b0 + u * blockDim.x + threadIdx.x;
-        if (i < n16) v[u] = s[i];
-      }
+    for (int u = 0; u < U; ++u) v[u] = __builtin_amdgcn_raw_buffer_load_b128(s, (first + u * step) * 16, 0, STREAM ? 0 : kStreaming);
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const size_t i = b0 + u * blockDim.x + threadIdx.x;
-        if (i < n16) __builtin_nontemporal_store(v[u], d + i);
-      }
-    }
-  } else {
-    const size_t stride = (size_t)nparts * blockDim.x;
-    for (size_t i = (size_t)part * blockDim.x + threadIdx.x; i < n16; i += U * stride) {
-      u32x4_t v[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (i + u * stride < n16) v[u] = __builtin_nontemporal_load(s + i + u * stride);
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (i + u * stride < n16) d[i + u * stride] = v[u];
-    }
+    for (int u = 0; u < U; ++u) __builtin_amdgcn_raw_buffer_store_b128(v[u], d, (first + u * step) * 16, 0, kThrough);
   }
 }
 
@@ -146,24 +148,18 @@ __device__ inline void copy_slice(void* __restrict__ dst, const void* __restrict
   copy_slice_u<(THREADS <= 256 ? 32 : 16), STREAM>(dst, src, bytes, part, nparts);
 }
 
-// After every cooperating work-group has finished its slice of a chunk, the last one to
+// After every cooperating work-group has finished its slice of a chunk (copy_slice: written through), the last one to
 // arrive raises the chunk's flag and leaves the arrival counter at zero for the next call.
-// Arrivals are release-only; just the last arrival pays for an acquire (on this chip an
-// agent-scope acquire invalidates the chiplet's L2, which the GEMM tiles next door live on).
 __device__ inline void publish_after_all(int32_t* counter, int nparts, int32_t* flag, int32_t value) {
+  stores_done();
   __syncthreads();
-  if (nparts == 1) {   // nobody to wait for: the flag's release covers the work-group's stores
-    if (threadIdx.x == 0) flag_raise(flag, value);
-    return;
+  if (threadIdx.x != 0) return;
+  if (nparts > 1) {
+    const int old = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (old != nparts - 1) return;
+    __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  if (threadIdx.x == 0) {
-    int old = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    if (old == nparts - 1) {
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      flag_raise(flag, value);
-    }
-  }
+  flag_raise_stored(flag, value);
 }
 
 // The emulated peers.  `nchunks` chunks of `chunk_bytes` are delivered by the `nparts` producer
