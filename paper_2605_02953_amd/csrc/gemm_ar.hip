@@ -183,7 +183,7 @@ __global__ __launch_bounds__(T::THREADS) void gemm_ar_kernel(const GemmArParams 
       if (s >= p.rank) ++s;
       int pid_m, pid_n;
       ar_tile_at(p, i / peers, ntiles, pid_m, pid_n);
-      flag_raise(p.tile_flags + (size_t)s * ntiles + pid_m * p.npn + pid_n, p.epoch);
+      flag_raise_stored(p.tile_flags + (size_t)s * ntiles + pid_m * p.npn + pid_n, p.epoch);   // (the partials were there before the launch)
     }
     if constexpr (TWO) {
       // the peers' broadcasts: the i-th tile that is not ours is position (i / (W-1)) W + s, s the
@@ -236,9 +236,10 @@ __global__ __launch_bounds__(T::THREADS) void gemm_ar_kernel(const GemmArParams 
       auto b_row = [=](int r) { return (uint32_t)min(n0 + r, N - 1) * row_bytes; };
       gemm_mainloop<T>(acc, p.a, a_row, p.b, b_row, p.k, lds);
     }
-    store_tile_bf16<T>(acc, p.gemm_out, (size_t)p.n, m0, n0, M, N, lds);
-    __syncthreads();   // every wave's stores are issued: notify
-    if (threadIdx.x == 0) flag_raise(p.tile_flags + (size_t)p.rank * ntiles + pid_m * p.npn + pid_n, p.epoch);
+    store_tile_bf16<T, true>(acc, p.gemm_out, (size_t)p.n, m0, n0, M, N, lds);
+    stores_done();
+    __syncthreads();   // every wave's part of the tile is in memory: notify
+    if (threadIdx.x == 0) flag_raise_stored(p.tile_flags + (size_t)p.rank * ntiles + pid_m * p.npn + pid_n, p.epoch);
     return;
   }
 

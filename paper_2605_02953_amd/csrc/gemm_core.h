@@ -779,8 +779,8 @@ __device__ __forceinline__ bool gemm_mainloop_ring_split(typename T::Acc32& acc,
 // SL lanes; written straight from the MFMA layout, a store instruction would scatter 8-byte
 // pieces over 32 rows).  A parked row has SLP >= SL slots (a power of two); the 16-byte slot g
 // of row m lives at slot g ^ key(m), which keeps the 8-byte writes (2-way at worst) and the
-// 16-byte reads away from bank conflicts.  STREAM: global stores with the streaming hint (for a tile
-// that is followed by a release and read much later: nothing dirty is left for the release to write back).
+// 16-byte reads away from bank conflicts.  THROUGH: the global stores are written through (for a tile that a flag or
+// counter announces: see stores_done).
 template <class T>
 struct ParkedTile {
   static constexpr int SL = T::WTN / 8;            // 16-byte slots of data per row: 16, 12 or 8
@@ -855,7 +855,7 @@ __device__ __forceinline__ void park_tile_bf16(const typename T::Acc& acc, char*
 // Second half: the rows m_lo <= m < m_hi of the parked tile (global row numbers; the tile starts at row
 // m0, column n0) go to c[m, n] with leading dimension ldc.  May be called several times with different
 // windows and destinations.
-template <class T, bool STREAM = false>
+template <class T, bool THROUGH = false>
 __device__ __forceinline__ void store_parked_bf16(__bf16* c, size_t ldc, int m0, int n0, int m_lo, int m_hi, int N,
                                                       const char* lds) {
   typedef ParkedTile<T> P;
@@ -865,22 +865,25 @@ __device__ __forceinline__ void store_parked_bf16(__bf16* c, size_t ldc, int m0,
   constexpr int ROWS_PER_READ = 64 / P::SLP;
   const int g = lane % P::SLP;
   const int gn = n0 + wn * T::WTN + g * 8;
+  __bf16* wave_c = c + (size_t)(m0 + wm * T::WTM) * ldc;   // row offsets inside a wave's rows fit 32 bits
+  const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc((void*)wave_c, 0, 0x7ffffff0, 0x00020000);
 #pragma unroll 8
   for (int it = 0; it < T::WTM / ROWS_PER_READ; ++it) {
     const int row = it * ROWS_PER_READ + lane / P::SLP;
     const u32x4_t v = *(const u32x4_t*)(park + row * P::ROW + ((g ^ P::key(row)) * 16));
     const int gm = m0 + wm * T::WTM + row;
     if (g < P::SL && gm >= m_lo && gm < m_hi && gn < N) {
-      if (STREAM) __builtin_nontemporal_store(v, (u32x4_t*)(c + (size_t)gm * ldc + gn)); else *(u32x4_t*)(c + (size_t)gm * ldc + gn) = v;
+      if constexpr (THROUGH) __builtin_amdgcn_raw_buffer_store_b128(v, rows, (int)((uint32_t)row * (uint32_t)ldc + (uint32_t)gn) * 2, 0, kThrough);
+      else *(u32x4_t*)(c + (size_t)gm * ldc + gn) = v;
     }
   }
 }
 
-template <class T, bool STREAM = false>
+template <class T, bool THROUGH = false>
 __device__ __forceinline__ void store_tile_bf16(const typename T::Acc& acc, __bf16* c, size_t ldc, int m0,
                                                     int n0, int M, int N, char* lds) {
   park_tile_bf16<T>(acc, lds);
-  store_parked_bf16<T, STREAM>(c, ldc, m0, n0, m0, M, N, lds);
+  store_parked_bf16<T, THROUGH>(c, ldc, m0, n0, m0, M, N, lds);
 }
 
 }  // namespace ditron
