@@ -728,9 +728,9 @@ def bench_moe_rs(args):
                    "latency_us": ev_ms * 1e3, "latency_us_quantiles": quant, "tflops": flops / (ev_ms * 1e-3) / 1e12},
         "roofline": {"bound": "hbm", "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": gbs / PEAK_HBM_GBS, "traffic": _traffic("moe_rs"),
                      "traffic_source": _traffic_source("moe_rs"),
-                     "kernel": "moe_rs_prepare_kernel + moe_grouped_gemm_kernel + moe_combine_kernel + reduce_slots_kernel (whole step between events)",
+                     "kernel": "moe_grouped_gemm_kernel + moe_combine_kernel (whole step between events)",
                      "kernel_ms": ev_ms, "bytes": alg_bytes + peer_bytes,
-                     "note": "algorithmic bytes of the four launches plus the emulated peers' copies (read + write of 7 blocks)"},
+                     "note": "algorithmic bytes of the two launches plus the emulated peers' copies (read + write of 7 blocks)"},
         "flags_preset_us": preset,
     }
 

@@ -463,7 +463,7 @@ ditron_status_t ditron_moe_ag_grouped_gemm(const void* const* x_shards, const in
  *  gather_idx, expert_offsets   device, as written by ditron_moe_ag_grouped_gemm
  *  y             device scratch [max_rows, hidden] bf16: the grouped GEMM's output
  *  inverse_idx   device scratch int32[world*tokens_per_rank*top_k]
- *  tile_records  device scratch int32[1 + 5*ditron_moe_max_tiles(max_rows, num_local_experts)]
+ *  tile_records  device scratch int32[1 + 5*ditron_moe_max_tiles(max_rows, num_local_experts)] (not used at present)
  *  combined      device out [world*tokens_per_rank, hidden] bf16: this rank's partial z_rank
  *  peer_partials host array of `world` device pointers; entry s != rank is the [tokens_per_rank, hidden]
  *                bf16 block rank s contributes to this rank (EMULATE_PRODUCER)

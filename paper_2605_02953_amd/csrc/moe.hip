@@ -14,6 +14,7 @@
 // expert's weights.
 #include "gemm_core.h"
 #include "launch.h"
+#include "reduce.h"
 
 namespace ditron {
 
@@ -321,9 +322,10 @@ struct MoeGemmParams {
   __bf16* y;
   const int32_t* expert_offsets;
   const int32_t* gather_idx;
-  const int32_t* tile_records;
+  const int32_t* tile_records;   // null: expert after expert, cut into row tiles from expert_offsets, no arrival stage (every row is local)
   const int32_t* flags;
   int32_t* status;
+  int max_rows;   // without tile_records: what expert_offsets may name at most
   int tokens_per_rank, hidden, inter, top_k, world, max_tiles, npn, num_local, num_xcd;   // hidden: contraction length, inter: output width
   int rows_in_place;   // 1: row p of the left operand is row p of `workspace` (already grouped by expert), no gather
   int32_t* inverse_idx;   // if set: the work-groups of column block 0 also write inverse_idx[gather_idx[p]] = p for their rows
@@ -350,14 +352,25 @@ __global__ __launch_bounds__(NST > 0 ? 2 * T::THREADS : T::THREADS) void moe_gro
   // the chiplets of small experts idle while the large ones run two rounds).  The row tiles of expert j are
   // the positions [first_j, first_j + ceil(n_j / BLOCK_M)) of the tile list, in arrival-stage order.
   const int wg = blockIdx.x;
-  const int ntiles = p.tile_records[0];
-  if (ntiles <= 0) return;   // nothing routed here, or the routing launch reported an error
-  const int per_xcd = cdiv(ntiles * p.npn, p.num_xcd);
-  const int slots_in_grid = WALK ? gridDim.x / p.num_xcd : per_xcd;
+  const bool listed = p.tile_records != nullptr;
+  int ntiles = 0;
+  if (listed) {
+    ntiles = p.tile_records[0];
+    if (ntiles <= 0) return;   // nothing routed here, or the routing launch reported an error
+  } else {
+    const int rows = p.expert_offsets[p.num_local];
+    if (rows > p.max_rows) {
+      if (wg == 0 && threadIdx.x == 0) {
+        p.status[0] = DITRON_ERR_WORKSPACE;
+        p.status[2] = rows;
+      }
+      return;
+    }
+  }
   // lane j of every wave: the row tiles of expert j and of the experts before it (at most 64 local experts)
   const int lane_j = threadIdx.x & 63;
   int nt_j = 0, before_j = 0;
-  if (WALK || p.num_local > kWalkExperts) {
+  if (WALK || !listed || p.num_local > kWalkExperts) {
     nt_j = lane_j < p.num_local ? cdiv(p.expert_offsets[lane_j + 1] - p.expert_offsets[lane_j], T::BM) : 0;
     before_j = nt_j;
 #pragma unroll
@@ -365,17 +378,20 @@ __global__ __launch_bounds__(NST > 0 ? 2 * T::THREADS : T::THREADS) void moe_gro
       const int v = __shfl_up(before_j, d);
       if (lane_j >= d) before_j += v;
     }
+    if (!listed) ntiles = __builtin_amdgcn_readlane(before_j, 63);
     before_j -= nt_j;
   }
+  const int per_xcd = cdiv(ntiles * p.npn, p.num_xcd);
+  const int slots_in_grid = WALK ? gridDim.x / p.num_xcd : per_xcd;
   for (int slot = wg / p.num_xcd; slot < per_xcd; slot += slots_in_grid) {
   const int item = (wg % p.num_xcd) * per_xcd + slot;
   if (item >= ntiles * p.npn) return;
-  int nt, before;
-  if (WALK || p.num_local > kWalkExperts) {
+  int nt, before, owner = 0;
+  if (WALK || !listed || p.num_local > kWalkExperts) {
     // the expert whose items [before_j npn, (before_j + nt_j) npn) hold this one
     const unsigned long long holds = __ballot(item >= before_j * p.npn && item < (before_j + nt_j) * p.npn);
     if (holds == 0) return;
-    const int owner = __ffsll((long long)holds) - 1;
+    owner = __ffsll((long long)holds) - 1;
     // (read into scalar registers: the tile's addresses derive from them and must stay wave-uniform)
     nt = __builtin_amdgcn_readlane(nt_j, owner);
     before = __builtin_amdgcn_readlane(before_j, owner);
@@ -392,9 +408,16 @@ __global__ __launch_bounds__(NST > 0 ? 2 * T::THREADS : T::THREADS) void moe_gro
   }
   const int pid_n = (item - before * p.npn) / nt;
   const int pos = before + (item - before * p.npn) % nt;
-  const int32_t* rec = p.tile_records + 1 + 4 * pos;
-  const int j = rec[0], seg_start = rec[2], seg_end = rec[3];
-  const int p0 = p.tile_records[1 + 4 * p.max_tiles + pos];
+  int j = owner, seg_start = 0, seg_end = 0, p0;
+  if (listed) {
+    const int32_t* rec = p.tile_records + 1 + 4 * pos;
+    j = rec[0];
+    seg_start = rec[2];
+    seg_end = rec[3];
+    p0 = p.tile_records[1 + 4 * p.max_tiles + pos];
+  } else {
+    p0 = p.expert_offsets[owner] + (pos - before) * T::BM;
+  }
   const int p_end = min(p0 + T::BM, p.expert_offsets[j + 1]);
   if (p.wait) flag_wait_block(p.flags, seg_start, seg_end - seg_start + 1, p.epoch, p.spin_limit, p.status);
   if (p.inverse_idx && pid_n == 0) {
@@ -617,60 +640,16 @@ extern "C" ditron_status_t ditron_moe_ag_grouped_gemm(
 // blocks arrive in the scatter buffer, the slots are added in fp32 in slot order.
 namespace ditron {
 
-struct MoeRsPrepareParams {
-  const int32_t* expert_offsets;
-  int32_t* inverse_idx;    // [assignments]
-  int32_t* tile_records;
-  int32_t* status;
-  int num_local, block_m, max_rows, max_tiles, assignments;
-};
-
-// Work-group 0: the tile list (expert after expert, no arrival stage: every row is local).  The others start
-// the inverse index at "not on this rank"; the grouped GEMM that follows fills in the rows that are.
-__global__ __launch_bounds__(1024) void moe_rs_prepare_kernel(const MoeRsPrepareParams p) {
-  if (blockIdx.x > 0) {
-    for (int f = (blockIdx.x - 1) * 1024 + threadIdx.x; f < p.assignments; f += (gridDim.x - 1) * 1024) p.inverse_idx[f] = -1;
-    return;
-  }
-  __shared__ int s_off[kMaxLocalExperts + 1];
-  __shared__ int s_first[kMaxLocalExperts + 1];
-  for (int j = threadIdx.x; j <= p.num_local; j += 1024) s_off[j] = p.expert_offsets[j];
-  __syncthreads();
-  const int R = s_off[p.num_local];
-  if (threadIdx.x == 0) {
-    int tiles = 0;
-    for (int j = 0; j < p.num_local; ++j) {
-      s_first[j] = tiles;
-      tiles += cdiv(s_off[j + 1] - s_off[j], p.block_m);
-    }
-    s_first[p.num_local] = tiles;
-    const bool fits = R <= p.max_rows && tiles <= p.max_tiles;
-    if (!fits) {
-      p.status[0] = DITRON_ERR_WORKSPACE;
-      p.status[2] = R;
-    }
-    p.tile_records[0] = fits ? tiles : 0;
-  }
-  __syncthreads();
-  if (R > p.max_rows || s_first[p.num_local] > p.max_tiles) return;
-  // one thread per tile: its expert by a walk over the (few) firsts
-  for (int t = threadIdx.x; t < s_first[p.num_local]; t += 1024) {
-    int j = 0;
-    while (s_first[j + 1] <= t) ++j;
-    int32_t* rec = p.tile_records + 1 + 4 * t;
-    rec[0] = j; rec[1] = t; rec[2] = 0; rec[3] = 0;
-    p.tile_records[1 + 4 * p.max_tiles + t] = s_off[j] + (t - s_first[j]) * p.block_m;
-  }
-}
-
 struct MoeCombineParams {
   const __bf16* y;             // [rows, hidden] grouped by expert
-  const int32_t* inverse_idx;  // [tokens * top_k]
+  int32_t* inverse_idx;        // [tokens * top_k]: where the grouped GEMM has put an assignment's row, or anything
+  const int32_t* gather_idx;   // the assignment of a row
+  const int32_t* expert_offsets;
   const float* gate;           // [tokens * top_k] or null
   __bf16* combined;            // [tokens, hidden]
-  int tokens, top_k, hidden, combine_wgs;
+  int tokens, tokens_per_rank, rank, top_k, hidden, num_local, max_rows, combine_wgs;
   // own-slot flags and the emulated peers (work-groups behind the combine)
-  int32_t* done;               // work-groups of the combine that have finished
+  int32_t* done;               // work-groups of the combine that have finished the rank's own rows
   int32_t* own_flags;          // [chunks]
   const void* peer[DITRON_MAX_WORLD];
   int order[DITRON_MAX_WORLD];
@@ -680,12 +659,36 @@ struct MoeCombineParams {
   size_t slot_bytes;
   int chunks, n_peers, num_producers, teams;
   int32_t epoch;
+  ReduceParams reduce;         // work-groups behind the peers, if there are any
 };
 
-__global__ __launch_bounds__(1024) void moe_combine_kernel(const MoeCombineParams p) {
+constexpr int kCombineThreads = 512;
+
+// What a wave knows of a token's assignments, one lane each (at most 64 of them): the row, or -1 where the assignment's
+// expert is not on this rank.  inverse_idx holds the row of every assignment that is here, and for the others whatever was there
+// before, so a row counts only if it is the assignment's own (that takes a second load, and no launch that clears the index).
+struct TokenRows {
+  int f, row, owner;
+  float gate;
+};
+
+// One launch, three kinds of work-groups, each waiting only for kinds before it.  (It replaced four launches' last two, and the clearing
+// launch before them: 8192 tokens top-2 of 32 experts, 2048 columns, world 8, 91 -> 70 us for the whole call, 128 tokens of 3000
+// columns 31 -> 21.  Bound by memory: 101 MB for the combine itself take 17.6 us with the peers' blocks resident, 24.3 when every
+// work-group ended with a release; of the others 59 MB are the peers' copies and 38 MB the reduction.)
+//  * the combine: one wave per token and 64 U vectors of 8 columns, the rank's own rows first, U vectors of
+//    each of 8 / U of the token's rows in flight per lane; the last work-group to finish the own rows raises the flags of the own slot;
+//  * the emulated peers;
+//  * the reduction (unless an external producer delivers the peers' blocks: then it is a launch of its own).
+template <int WORLD, int U>
+__global__ __launch_bounds__(kCombineThreads) void moe_combine_kernel(const MoeCombineParams p) {
+  if ((int)blockIdx.x >= p.combine_wgs + p.num_producers) {
+    reduce_slots_work_group<WORLD, kCombineThreads>(p.reduce, blockIdx.x - p.combine_wgs - p.num_producers);
+    return;
+  }
   if ((int)blockIdx.x >= p.combine_wgs) {
     const size_t chunk_bytes = p.slot_bytes / p.chunks;
-    produce_chunks<1024>(
+    produce_chunks<kCombineThreads>(
         p.n_peers * p.chunks, chunk_bytes, blockIdx.x - p.combine_wgs, p.num_producers, p.teams, p.epoch,
         [&](int i) { return (void*)(p.scatter_buf + p.order[i / p.chunks] * p.slot_bytes + (i % p.chunks) * chunk_bytes); },
         [&](int i) { return (const void*)((const char*)p.peer[p.order[i / p.chunks]] + (i % p.chunks) * chunk_bytes); },
@@ -693,58 +696,122 @@ __global__ __launch_bounds__(1024) void moe_combine_kernel(const MoeCombineParam
         [&](int i) { return p.arr_counters + p.order[i / p.chunks] * p.chunks + i % p.chunks; });
     return;
   }
-  // one lane per 8 columns of one token: top_k rows of 16 bytes in, one out
-  const int vpr = p.hidden >> 3;
-  const long total = (long)p.tokens * vpr;
-  for (long v = (long)blockIdx.x * 1024 + threadIdx.x; v < total; v += (long)p.combine_wgs * 1024) {
-    const int t = (int)(v / vpr), c = (int)(v - (long)t * vpr);
-    float acc[8];
+  constexpr int kRows = 8 / U;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int vpr = p.hidden >> 3, blocks = cdiv(vpr, 64 * U);
+  const int total_rows = p.expert_offsets[p.num_local];
+  const int rows = total_rows > p.max_rows ? 0 : total_rows;   // too many: the grouped GEMM has reported it and written none
+  const int stride = p.combine_wgs * (kCombineThreads / 64);
+  const int own = p.tokens_per_rank * blocks, items = p.tokens * blocks;
+  auto token_of = [&](int item) {
+    const int t = p.rank * p.tokens_per_rank + item / blocks;
+    return t >= p.tokens ? t - p.tokens : t;
+  };
+  // assignments j0 .. j0 + 63 of a token: first load and second load
+  auto look_up = [&](int item, int j0) {
+    TokenRows r{-1, -1, -1, 1.f};
+    if (item < items && j0 + lane < p.top_k) {
+      r.f = token_of(item) * p.top_k + j0 + lane;
+      r.row = p.inverse_idx[r.f];
+      if (p.gate) r.gate = p.gate[r.f];
+    }
+    return r;
+  };
+  auto check = [&](TokenRows& r) {
+    if (r.row < 0 || r.row >= rows) r.row = -1;
+    r.owner = r.row >= 0 ? p.gather_idx[r.row] : -1;
+  };
+  // through: the rows are written past the caches (sc0 sc1), so that whoever is told of them needs no write-back
+  auto run = [&](int first, int end, auto through) {
+    TokenRows now = look_up(first, 0), next = look_up(first + stride, 0);
+    check(now);
+    for (int item = first; item < end; item += stride) {
+      TokenRows later = look_up(item + 2 * stride, 0);
+      check(next);
+      const int t = token_of(item), block = item % blocks;
+      float acc[U][8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) acc[q] = 0.f;
-    // the token's assignments eight at a time: positions and gates first, then every row's 16 bytes, then the
-    // sum in the order j = 0, 1, ... (the loads of a batch are in flight together)
-    constexpr int kBatch = 8;
-    for (int j0 = 0; j0 < p.top_k; j0 += kBatch) {
-      int pos[kBatch];
-      float g[kBatch];
-      u32x4_t x[kBatch];
+      for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int b = 0; b < kBatch; ++b) {
-        const bool in = j0 + b < p.top_k;
-        pos[b] = in ? p.inverse_idx[t * p.top_k + j0 + b] : -1;   // -1: the assignment's expert is not on this rank
-        g[b] = (in && p.gate) ? p.gate[t * p.top_k + j0 + b] : 1.f;
-      }
+        for (int q = 0; q < 8; ++q) acc[u][q] = 0.f;
+      for (int j0 = 0; j0 < p.top_k; j0 += 64) {
+        if (j0 > 0) {
+          now = look_up(item, j0);
+          check(now);
+        }
+        if (now.owner != now.f) now.row = -1;
+        if (block == 0 && now.f >= 0 && now.row < 0) p.inverse_idx[now.f] = -1;
+        const int n = min(64, p.top_k - j0);
+        for (int j = 0; j < n; j += kRows) {
+          // kRows rows of the token at a time, all their loads in flight together, then the sum in the order j = 0, 1, ...
+          int row[kRows];
+          float g[kRows];
+          u32x4_t x[kRows][U];
 #pragma unroll
-      for (int b = 0; b < kBatch; ++b)
-        if (pos[b] >= 0) x[b] = __builtin_nontemporal_load((const u32x4_t*)(p.y + (size_t)pos[b] * p.hidden) + c);
+          for (int b = 0; b < kRows; ++b) {
+            row[b] = j + b < n ? __builtin_amdgcn_readlane(now.row, j + b) : -1;
+            g[b] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, now.gate), min(j + b, n - 1)));
+            if (row[b] >= 0) {
 #pragma unroll
-      for (int b = 0; b < kBatch; ++b) {
-        if (pos[b] < 0) continue;
+              for (int u = 0; u < U; ++u) {
+                const int c = (block * U + u) * 64 + lane;
+                if (c < vpr) x[b][u] = __builtin_nontemporal_load((const u32x4_t*)(p.y + (size_t)row[b] * p.hidden) + c);
+              }
+            }
+          }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          acc[2 * q] = __builtin_fmaf(g[b], __builtin_bit_cast(float, x[b][q] << 16), acc[2 * q]);
-          acc[2 * q + 1] = __builtin_fmaf(g[b], __builtin_bit_cast(float, x[b][q] & 0xFFFF0000u), acc[2 * q + 1]);
+          for (int b = 0; b < kRows; ++b) {
+            if (row[b] < 0) continue;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                acc[u][2 * q] = __builtin_fmaf(g[b], __builtin_bit_cast(float, x[b][u][q] << 16), acc[u][2 * q]);
+                acc[u][2 * q + 1] = __builtin_fmaf(g[b], __builtin_bit_cast(float, x[b][u][q] & 0xFFFF0000u), acc[u][2 * q + 1]);
+              }
+          }
         }
       }
-    }
-    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-    u32x4_t r;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      bf16x2_t o = {(__bf16)acc[2 * q], (__bf16)acc[2 * q + 1]};
-      r[q] = __builtin_bit_cast(uint32_t, o);
+      for (int u = 0; u < U; ++u) {
+        const int c = (block * U + u) * 64 + lane;
+        if constexpr (decltype(through)::value) {
+          const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc((void*)(p.combined + (size_t)t * p.hidden), 0, p.hidden * 2, 0x00020000);
+          __builtin_amdgcn_raw_buffer_store_b128(pack_bf16x8(acc[u]), out, c * 16, 0, 17);   // past the row nothing is written
+        } else {
+          if (c < vpr) *((u32x4_t*)(p.combined + (size_t)t * p.hidden) + c) = pack_bf16x8(acc[u]);
+        }
+      }
+      now = next;
+      next = later;
     }
-    *((u32x4_t*)(p.combined + (size_t)t * p.hidden) + c) = r;
+  };
+  const int first = blockIdx.x * (kCombineThreads / 64) + wave;
+  // the last of the work-groups with rows of the rank's own to finish those raises the flags of the own slot
+  const int own_wgs = min(p.combine_wgs, cdiv(own, kCombineThreads / 64));
+  if ((int)blockIdx.x < own_wgs) {
+    run(first, own, std::true_type{});
+    wait_vmcnt0();   // the wave's stores have reached memory
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const int old = __hip_atomic_fetch_add(p.done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (old == own_wgs - 1) {
+        __hip_atomic_store(p.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int c = 0; c < p.chunks; ++c) __hip_atomic_store(p.own_flags + c, p.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
   }
-  // the last work-group of the combine to finish raises the flags of the own slot
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const int old = __hip_atomic_fetch_add(p.done, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    if (old == p.combine_wgs - 1) {
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      __hip_atomic_store(p.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      for (int c = 0; c < p.chunks; ++c) flag_raise(p.own_flags + c, p.epoch);
-    }
+  run(first + cdiv(max(own - first, 0), stride) * stride, items, std::false_type{});
+}
+
+template <int U>
+static void launch_combine(const MoeCombineParams& c, unsigned reducers, hipStream_t s) {
+  const dim3 grid((unsigned)(c.combine_wgs + c.num_producers) + reducers);
+  switch (reducers ? c.reduce.world : 0) {
+    case 8: hipLaunchKernelGGL((moe_combine_kernel<8, U>), grid, dim3(kCombineThreads), 0, s, c); break;
+    case 4: hipLaunchKernelGGL((moe_combine_kernel<4, U>), grid, dim3(kCombineThreads), 0, s, c); break;
+    case 2: hipLaunchKernelGGL((moe_combine_kernel<2, U>), grid, dim3(kCombineThreads), 0, s, c); break;
+    default: hipLaunchKernelGGL((moe_combine_kernel<0, U>), grid, dim3(kCombineThreads), 0, s, c); break;
   }
 }
 
@@ -797,23 +864,11 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
     }
   }
 
-  // 1. tile list; the inverse index starts at "not on this rank"
+  // (tile_records is not needed: the grouped GEMM cuts its row tiles from expert_offsets)
   const long expected_rows = moe_expected_rows((long)world * tokens_per_rank, top_k, num_experts, num_local_experts);
   const MoeTile mt = choose_moe_tile(expected_rows, num_local_experts, hidden);
-  MoeRsPrepareParams pr{};
-  pr.expert_offsets = expert_offsets;
-  pr.inverse_idx = inverse_idx;
-  pr.tile_records = tile_records;
-  pr.status = status;
-  pr.num_local = num_local_experts;
-  pr.block_m = mt.block_m;
-  pr.max_rows = max_rows;
-  pr.max_tiles = max_tiles;
-  pr.assignments = (int)assignments;
-  hipLaunchKernelGGL(moe_rs_prepare_kernel, dim3(1 + (unsigned)std::min<long>(64, (assignments + 1023) / 1024)), dim3(1024), 0, s, pr);
-  if (hipGetLastError() != hipSuccess) return DITRON_ERR_HIP;
 
-  // 2. grouped GEMM y[p, :] = h[p, :] . W2_expert(p): contraction over the intermediate size, hidden columns; its
+  // 1. grouped GEMM y[p, :] = h[p, :] . W2_expert(p): contraction over the intermediate size, hidden columns; its
   //    work-groups of column block 0 also write the inverse index of their rows
   MoeGemmParams g{};
   g.workspace = (const char*)h;
@@ -821,7 +876,8 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
   g.y = (__bf16*)y;
   g.expert_offsets = expert_offsets;
   g.gather_idx = gather_idx;
-  g.tile_records = tile_records;
+  g.tile_records = nullptr;
+  g.max_rows = max_rows;
   g.flags = signals;
   g.status = status;
   g.tokens_per_rank = tokens_per_rank;
@@ -862,20 +918,32 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
   }
   if (st != DITRON_OK) return st;
 
-  // 3. top-k combine into token order; the emulated peers' blocks arrive beside it
+  // 2. top-k combine into token order; the emulated peers' blocks arrive beside it, and behind them the reduction of
+  //    GEMM-ReduceScatter over the `world` slots (own slot: the rank's rows of `combined`)
   const size_t slot_bytes = (size_t)tokens_per_rank * hidden * 2;
   MoeCombineParams c{};
   c.y = (const __bf16*)y;
   c.inverse_idx = inverse_idx;
+  c.gather_idx = gather_idx;
+  c.expert_offsets = expert_offsets;
   c.gate = topk_weights;
   c.combined = (__bf16*)combined;
   c.tokens = world * tokens_per_rank;
+  c.tokens_per_rank = tokens_per_rank;
+  c.rank = rank;
   c.top_k = top_k;
   c.hidden = hidden;
-  // one work-group of 1024 threads per compute unit, so that the emulated peers behind them are resident from the
-  // start (two such work-groups fit a unit); measured at the paper's MoE+RS shape: 256 / 384 / 512 / 2048 combine
-  // work-groups -> 117 / 122 / 124 / 166 us for the whole call
-  c.combine_wgs = (int)std::min<long>(256, ((long)c.tokens * (hidden / 8) + 1023) / 1024);
+  c.num_local = num_local_experts;
+  c.max_rows = max_rows;
+  const int vpr = hidden / 8;
+  auto items_at = [&](int u) { return (long)c.tokens * cdiv(vpr, 64 * u); };
+  // As many vectors per lane as leave a thousand waves; fewer tokens take more of a token's rows at a time instead, over more waves.  us
+  // with 4, 2 and 1, whole calls: 8192 tokens top-2, 2048 columns 70, 73, 81; 1488 top-6, 1456 columns 42.3, 45.9, 50.1; 1200 top-1, 1072 columns
+  // 21.5, 23.3, 24.2; 100 top-4, 1136 columns 22.1, 19.1, 17.5; 68 top-4, 7408 columns 42.0, 36.8, 36.2 (against: 2044 top-6, 2168 columns 64, 59, 54).
+  const int unroll = vpr > 128 && items_at(4) >= 1024 ? 4 : vpr > 64 && items_at(2) >= 1024 ? 2 : 1;
+  const long items = items_at(unroll);
+  // three work-groups to a unit fit; 8192 tokens, 2048 columns, world 8: 256 / 384 / 512 / 768 of them 83 / 75 / 74 / 71 us for the call
+  c.combine_wgs = (int)std::min<long>(768, (items + kCombineThreads / 64 - 1) / (kCombineThreads / 64));
   c.done = signals + world;                                   // the counter word of segment 0 (unused here otherwise)
   c.own_flags = signals + 2 * world + rank * chunks_per_slot;
   for (int i = 0; i < world; ++i) {
@@ -889,18 +957,41 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
   c.chunks = chunks_per_slot;
   c.n_peers = world - 1;
   const ProducerPlan pl = plan_producers((size_t)(world - 1) * slot_bytes, (world - 1) * chunks_per_slot);
-  c.num_producers = (emulate && world > 1) ? std::min(pl.producers, 128) : 0;
+  // twice as many as the plan says: they have half of its threads (at the same sizes 56 / 84 / 112 / 168 of them 78 / 75 / 71 / 73 us)
+  c.num_producers = (emulate && world > 1) ? 2 * pl.producers : 0;
   c.teams = std::min(pl.teams, std::max(1, c.num_producers));
   c.epoch = epoch;
-  hipLaunchKernelGGL(moe_combine_kernel, dim3((unsigned)(c.combine_wgs + c.num_producers)), dim3(1024), 0, s, c);
-  if (hipGetLastError() != hipSuccess) return DITRON_ERR_HIP;
-
-  // 4. the reduction of GEMM-ReduceScatter over the `world` slots (own slot: the rank's rows of `combined`)
   const void* slots[DITRON_MAX_WORLD];
   for (int i = 0; i < world; ++i)
     slots[i] = i == rank ? (const void*)((const char*)combined + (size_t)rank * slot_bytes)
                          : (const void*)((const char*)scatter_buf + (size_t)i * slot_bytes);
-  // flags preset: the peers' blocks are resident and nothing gates the sum but the stream order
-  return ditron_reduce_slots(slots, out, mode == Mode::kPreset ? nullptr : signals + 2 * world, status, tokens_per_rank,
-                             hidden, world, chunks_per_slot, epoch, tuning, stream);
+  unsigned reducers = 0;
+  if (mode != Mode::kExternal) {
+    ReduceParams& r = c.reduce;
+    for (int i = 0; i < world; ++i) {
+      r.slot[i] = slots[i];
+      // flags preset: the peers' blocks are resident
+      r.gate[i] = i == rank || emulate ? c.arr_flags + (size_t)i * chunks_per_slot : nullptr;
+      r.gate_stride[i] = 1;
+    }
+    r.out = (__bf16*)out;
+    r.status = status;
+    r.vec_per_chunk = (size_t)(tokens_per_rank / chunks_per_slot) * hidden / 8;
+    r.chunks = chunks_per_slot;
+    r.world = world;
+    r.epoch = epoch;
+    r.spin_limit = tune.spin_limit;
+    const size_t want = (r.vec_per_chunk + kCombineThreads - 1) / kCombineThreads;
+    r.wgs_per_chunk = (int)std::min<size_t>(want, std::max(1, 256 / chunks_per_slot));
+    reducers = (unsigned)(r.wgs_per_chunk * chunks_per_slot);
+  }
+  if (unroll == 4) launch_combine<4>(c, reducers, s);
+  else if (unroll == 2) launch_combine<2>(c, reducers, s);
+  else launch_combine<1>(c, reducers, s);
+  if (hipGetLastError() != hipSuccess) return DITRON_ERR_HIP;
+  if (reducers) return DITRON_OK;
+
+  // 3. an external producer may need room on the chip while the reduction waits for it: a launch of its own
+  return ditron_reduce_slots(slots, out, signals + 2 * world, status, tokens_per_rank, hidden, world, chunks_per_slot, epoch, tuning,
+                             stream);
 }

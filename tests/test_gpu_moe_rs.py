@@ -38,7 +38,7 @@ def _case(world, t_r, inter_r, hidden, experts, top_k, local, seed, integer):
 
 
 def _run(B, ids, hs, ws, e0s, d, world, t_r, inter_r, hidden, experts, top_k, local, chunks, gate, integer,
-         flags=None, order=None, kn=False):
+         flags=None, order=None, kn=False, stale_rows=False):
     _, offsets, gather = omoe.route(ids, world, experts, e0s[d], local)
     R = int(offsets[-1])
     max_rows = max(R, 1) + 7
@@ -55,6 +55,8 @@ def _run(B, ids, hs, ws, e0s, d, world, t_r, inter_r, hidden, experts, top_k, lo
     i32 = dict(dtype=torch.int32, device="cuda")
     y = torch.full((max_rows, hidden), 0x7FC0, dtype=torch.int16, device="cuda")
     inv = torch.full((tokens * top_k,), 12345, **i32)
+    if stale_rows:   # what an earlier call may have left: rows that exist, of other assignments
+        inv = torch.arange(tokens * top_k, **i32).flip(0) % max(R, 1)
     rec = torch.full((1 + 5 * B.moe_max_tiles(max_rows, local),), -1, **i32)
     combined = torch.full((tokens, hidden), 0x7FC0, dtype=torch.int16, device="cuda")
     scatter = torch.zeros((world, t_r, hidden), dtype=torch.int16, device="cuda")
@@ -120,6 +122,19 @@ def test_moe_rs_end_to_end(B, world, t_r, inter_r, hidden, experts, top_k, local
     for d in sorted({0, world - 1}):
         order = None if d == 0 else [s for s in range(world) if s != d]
         _run(B, ids, hs, ws, e0s, d, world, t_r, inter_r, hidden, experts, top_k, local, chunks, gate, integer, order=order)
+
+
+@pytest.mark.parametrize("world,t_r,hidden,experts,top_k,local", [
+    (2, 520, 1048, 6, 3, 3),      # four vectors per lane: a second, ragged block of columns; two rows at a time and one left over
+    (2, 520, 536, 6, 5, 3),       # two vectors, the second ragged; four rows at a time
+    (2, 24, 520, 12, 9, 6),       # one vector; eight rows at a time
+    (2, 8, 72, 70, 66, 35),       # more assignments than a wave has lanes
+    (4, 3, 2056, 4, 1, 4),        # fewer rows than waves
+])
+def test_moe_rs_combine_forms(B, world, t_r, hidden, experts, top_k, local):
+    ids, hs, ws, e0s = _case(world, t_r, 8, hidden, experts, top_k, local, seed=hidden, integer=True)
+    for stale in (False, True):
+        _run(B, ids, hs, ws, e0s, world - 1, world, t_r, 8, hidden, experts, top_k, local, 1, None, True, stale_rows=stale)
 
 
 def test_moe_rs_weights_kn_and_flags_preset(B):
