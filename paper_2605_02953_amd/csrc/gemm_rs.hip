@@ -283,12 +283,12 @@ static ditron_status_t gemm_rs_impl(const void* a, const void* b, int b_layout, 
   for (int s = 0; s < world; ++s) {
     if (s == rank) {
       r.slot[s] = fuse ? (const char*)scatter_buf + (size_t)rank * slot_bytes : (const char*)gemm_out + (size_t)rank * slot_bytes;
-      r.gate[s] = p.seg_flags + rank;   // the GEMM's flag for the own segment gates every chunk
+      r.gate[s] = mode == Mode::kExternal ? p.seg_flags + rank : nullptr;   // the GEMM's flag for the own segment gates every chunk
       r.gate_stride[s] = 0;
     } else {
       r.slot[s] = (const char*)scatter_buf + (size_t)s * slot_bytes;
-      // flags preset: the peers' blocks are resident, only the GEMM's own segment gates the sum
-      r.gate[s] = mode == Mode::kPreset ? nullptr : p.arr_flags + (size_t)s * chunks_per_slot;
+      // otherwise the peers' blocks are resident, or the launch before this one has delivered them
+      r.gate[s] = mode == Mode::kExternal ? p.arr_flags + (size_t)s * chunks_per_slot : nullptr;
       r.gate_stride[s] = 1;
     }
   }

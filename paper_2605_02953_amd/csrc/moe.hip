@@ -618,7 +618,7 @@ extern "C" ditron_status_t ditron_moe_ag_grouped_gemm(
   g.num_xcd = 8;
   g.epoch = epoch;
   g.spin_limit = tune.spin_limit;
-  g.wait = mode != Mode::kPreset;
+  g.wait = mode == Mode::kExternal;   // the emulated peers were work-groups of the launch before
   if (w_layout == DITRON_B_KN) {   // weights stored [hidden, inter]
     if (mt.block_m == 256)
       return launch_moe_gemm_256_rows_kn(g, moe_block_n_kn_256(expected_rows, num_local_experts, inter, mt.block_n), max_tiles, s);
