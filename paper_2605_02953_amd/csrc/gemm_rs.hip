@@ -257,12 +257,6 @@ static ditron_status_t gemm_rs_impl(const void* a, const void* b, int b_layout, 
   // 7680, 83.1, 79.6; 240 + 16, 2048 x 1920, K 3584 49.4, 56.1.
   const int tiles = cdiv(m, 128) * cdiv(n, 128);
   const bool paired = tiles + p.num_producers > 256;
-  // [n, k] weights, up to eight K tiles and 64 tiles or more, up to sixteen and 144 tiles: the staged tile.  us with it and with TileSmall: 96 tiles, 288 x 4088, K 256
-  // 24.6, 24.9; 512 24.4, 24.9; 768 25.0, 24.9 (2 ranks 19.6, 19.6; 18.3, 19.5; 19.8, 18.6); 120, 992 x 1872, 29.1, 29.5; 29.1, 29.5; 29.4, 29.8
-  // (21.2, 21.8; 21.5, 21.3; 21.3, 22.0); 40, 520 x 1024, K 512 16.6, 17.8 (13.6, 12.9), 768 18.0, 16.6; against the calls as they were
-  // with it, 128 x 128 tiles on the ring took 21.3 -> 21.7 (512 x 4096 over 2 ranks, K 512), 28.8 -> 29.6 (992 x 1872 fused, K 456).
-  // 168 tiles, 460 x 5336 over 2 ranks, K 568 27.0 -> 27.9; 200, 1160 x 2560, K 1024 30.6, 31.4 (28.6, 28.5); 224, 904 x 3584, 768 32.9, 34.0.
-  const bool staged = tiles >= 64 && k_local <= (tiles >= 144 ? 1024 : 512);
   ditron_status_t st;
   if (b_layout == DITRON_B_KN) {
     st = tc.big               ? launch_rs<TileBigKN>(p, (hipStream_t)stream)
@@ -272,7 +266,6 @@ static ditron_status_t gemm_rs_impl(const void* a, const void* b, int b_layout, 
   } else {
     st = tc.big               ? launch_rs<TileBigDirect>(p, (hipStream_t)stream)
          : tc.block_n == 64 ? launch_rs<TileSmall64>(p, (hipStream_t)stream)
-         : staged           ? launch_rs<TileSmallStaged>(p, (hipStream_t)stream)
          : paired           ? launch_rs<TileSmallPaired>(p, (hipStream_t)stream)
                             : launch_rs<TileSmall>(p, (hipStream_t)stream);
   }

@@ -35,8 +35,8 @@ typedef GemmTile4W<256, 256, true, true, true> TileBigKN;
 typedef GemmTile4W<256, 224, true, true, true> TileBigKN224;
 typedef GemmTile4W<256, 192, true, true, true> TileBigKN192;
 typedef GemmTile4W<128, 128, true, true, true> TileSmallKN;
-// The first form of that tile: register-staged, two LDS stages (64 KiB), 32 x 32 x 16 MFMA.  Left where a few K tiles are all there is
-// (gemm_rs_impl, the MoE down-projection), by 0 to 3 % there.
+// The first form of that tile: register-staged, two LDS stages (64 KiB), 32 x 32 x 16 MFMA.  Left for the MoE down-projection of a few K
+// tiles.
 typedef GemmTile4W<128, 128> TileSmallStaged;
 // The same two with two K tiles in flight (80 KiB): two work-groups share a unit.  For launches whose work-groups need several
 // rounds all the same and are bound by more than their K loops (GEMM-ReduceScatter with the peers' copies, short MoE contractions).
@@ -191,12 +191,12 @@ inline TileChoice choose_tile(int m, int n, int k, Narrow narrow) {
   // Half as wide where that many tiles still fit the chip in one round and the K loop is what the call spends its time on.
   // us with 128 and with 64 columns.  AllGather-GEMM, B stored [K, N] ([N, K]: the decode kernel): 64 x 3584, K 512 12.5, 11.4; 8192
   // 56.4, 42.2; 1024 x 2048 (256 of these tiles) K 512 14.1, 14.2; 1024 19.4, 18.8; 4096 44.2, 39.5.
-  // GEMM-ReduceScatter needs units for the peers' copies and the reduction beside the tiles, so only up to 128 of them, and long
-  // contractions: 128 x 8192 (128 of them) K 512 18.3, 20.7; 1024 18.8, 19.3; 1536 21.0, 21.9 ([K, N]: 22.2, 21.7); 2048 23.2, 22.8; 2560
-  // 28.2, 27.0; 4096 33.4, 30.5; 128 x 4096 512 15.2, 15.6; 1024 17.0, 16.7; 1536 19.2, 18.2; 256 tiles: 128 x 16384, K 1024 30.3, 37.5,
-  // 512 x 4096, K 2048 28.8, 40.4.
+  // GEMM-ReduceScatter: where the tiles and the peers' copying work-groups (8 to 32) still fit the units together; beyond 64 tiles of 128
+  // columns the contraction has to be longer for it to pay.  128 / 64 columns, us for the call (tiles of 128 columns): K 424 (119)
+  // 16.7, 17.2; 544 (28) 12.1, 12.2; 552 (27) 13.2, 12.5; 728 (24) 14.5, 13.2; 968 (56) 17.2, 15.3; 1144 (60) 20.1, 17.4; 816 (80) 16.8, 17.6; 800 (106)
+  // 15.9, 15.4; 1064 (114) 20.1, 19.4; 1568 (78) 20.3, 17.7; 2976 (94) 26.5, 22.7; 3192 (110) 38.2, 31.8; 848 (124, no units left) 17.5, 24.2.
   const long tiles_small = (long)cdiv(m, 128) * cdiv(n, 128);
-  const bool fits = narrow == Narrow::kNever ? tiles_small <= 64 && k >= 1536 : tiles_small <= 128 && k >= 512;
+  const bool fits = narrow == Narrow::kNever ? tiles_small <= (k >= 1024 ? 112 : 64) && k >= 512 : tiles_small <= 128 && k >= 512;
   if (fits && narrow != Narrow::kAllReduce) t.block_n = 64;
   if (t.big && (narrow == Narrow::kNK || narrow == Narrow::kF8 || (narrow == Narrow::kKN && tiles_big <= 192))) {
     double best = 0.98 * tiling_cost(tiles_big, 256);

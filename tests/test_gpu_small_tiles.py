@@ -112,6 +112,23 @@ def test_64_column_tiles_reduce_bit_exact(B, m_per_rank, n, k, kn):
         assert np.array_equal(bits(dsts[r][d]), parts[d][r * m_per_rank:(r + 1) * m_per_rank])
 
 
+# the shortest contractions that take 64 columns beside few and beside many tiles of 128, and the ones just below
+@pytest.mark.parametrize("n,k,block_n", [(1000, 504, 128), (1000, 512, 64), (1000, 520, 64), (14272, 1016, 128), (14272, 1024, 64)])
+@pytest.mark.parametrize("kn", [False, True], ids=["b_nk", "b_kn"])
+def test_64_column_tiles_from_short_contractions_on(B, n, k, block_n, kn):
+    world, d, m_r = 4, 2, 5
+    st, tc = B.tile_config(1, world * m_r, n, k)
+    assert (st, tc["block_m"], tc["block_n"]) == (B.OK, 128, block_n)
+    cfg = synth.CONFIGS[3].scaled(world=world, m_per_rank=m_r, n=n, k=k)
+    a_list, b_list = synth.gemm_rs_inputs(cfg, integer=True)
+    parts = [oar.partial_bits(a, b) for a, b in zip(a_list, b_list)]
+    mine = slice(d * m_r, (d + 1) * m_r)
+    blocks = [None if s == d else to_dev(parts[s][mine]) for s in range(world)]
+    rs = GemmRsRun(B, world, cfg.m, n, k, 5)
+    _ok(B, rs(to_dev(a_list[d]), to_dev(b_list[d] if kn else nk(b_list[d])), blocks, d, b_layout=B.B_KN if kn else B.B_NK), rs)
+    assert np.array_equal(bits(rs.gemm_out), parts[d]) and np.array_equal(bits(rs.out), oar.allreduce_partials_f32_ordered(parts)[mine])
+
+
 # 255 tiles of 128 x 128 beside the peers' copies: [k, n] weights, and [n, k] ones beyond 1024, on tiles that share a unit (a ring of
 # two K tiles in five pieces); [n, k] up to 1024 on the register-staged tile; from less than a K tile on, whole and ragged last ones
 @pytest.mark.parametrize("k", [8, 72, 128, 192, 200, 328, 512, 584, 1024, 1032, 1096])

@@ -89,6 +89,14 @@ def test_reduce_scatter_tiles_by_contraction(B):
     assert rows(2048, 2048, 512) == 256 and rows(2048, 2048, 2048) == 128
 
 
+def test_reduce_scatter_64_columns(B):
+    """GEMM-ReduceScatter: 64 columns up to 64 tiles of 128 from K 512 on, up to 112 from K 1024 on.  Both sides of every line."""
+    def cols(tiles, k):
+        return B.tile_config(1, 120, tiles * 128, k)[1]["block_n"]
+    assert [cols(64, 504), cols(64, 512), cols(65, 512), cols(65, 1016), cols(65, 1024)] == [128, 64, 128, 128, 64]
+    assert [cols(112, 1024), cols(113, 1024), cols(113, 8192)] == [64, 128, 128]
+
+
 def test_operand_staging_choice(B):
     """256 x 256 tiles of [n, k] operands take the direct-to-LDS staging, whatever the contraction length."""
     assert B.tile_config(0, 8192, 3584, 8192)[1]["direct_staging"] == 1      # cfg 2
