@@ -617,11 +617,20 @@ extern "C" ditron_status_t ditron_ag_gemm_decode(const void* const* a_shards, co
   p.kt_per_split = plan.kt_per_split;
   p.partials = (char*)workspace + align256(a_bytes);
   const hipStream_t s = (hipStream_t)stream;
-  switch (plan.variant) {
-    case 2: return bf16 ? launch_splitk<true, SplitKTile<128, 128>>(p, s) : launch_splitk<false, SplitKTile<128, 128>>(p, s);
-    case 3: return bf16 ? launch_splitk<true, SplitKTile<128, 64>>(p, s) : launch_splitk<false, SplitKTile<128, 64>>(p, s);
-    case 4: return bf16 ? launch_splitk<true, SplitKTile<16, 128>>(p, s) : launch_splitk<false, SplitKTile<16, 128>>(p, s);
-    default: break;
+  if (plan.variant != 1) {
+    auto launch = [&](auto tile) {
+      typedef decltype(tile) T;
+      return bf16 ? launch_splitk<true, T>(p, s) : launch_splitk<false, T>(p, s);
+    };
+    switch (plan.block_m * 1000 + plan.block_n) {
+      case 128128: return launch(SplitKTile<128, 128>{});
+      case 128064: return launch(SplitKTile<128, 64>{});
+      case 64064: return launch(SplitKTile<64, 64>{});
+      case 32064: return launch(SplitKTile<32, 64>{});
+      case 16064: return launch(SplitKTile<16, 64>{});
+      case 16128: return launch(SplitKTile<16, 128>{});
+      default: return DITRON_ERR_UNSUPPORTED;
+    }
   }
   if (p.epoch_word) return DITRON_ERR_UNSUPPORTED;   // the 128 x 32 kernel takes its epoch as an argument only
   if (!(bf16 ? set_dynamic_lds<ag_gemm_decode_kernel<true>>(DecodeTile::LDS_BYTES)

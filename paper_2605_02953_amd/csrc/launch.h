@@ -246,6 +246,12 @@ inline TileChoice choose_tile_decode(int /*m*/, int /*n*/, int /*k*/) {
 // per-shard form, 16-row tiles (one shard's rows at the decode shape: a tile waits for that shard only).
 // S doubles while the grid stays within one work-group per compute unit, at most 8, and every split keeps at
 // least four 128-byte K tiles.
+// Variant 0 is variant 2 with the tile cut to the rows there are (16, 32 or 64 of them) and to 64 columns: a unit loads and exchanges no
+// rows that do not exist, and half as many splits meet in a tile.  us for the call, 128 x 128, the narrower tile of 128 columns and this one,
+// 8 ranks: bf16 64 x 3584, K 8192 33.6, 26.6, 25.9; 32 rows 32.7, 22.5, 20.4; 16 rows 32.1, 20.7, 18.6; 64 x 8192 57.2, 51.3, 46.4; 64 x 512, K 1024
+// 12.5, 10.2, 9.8; e4m3 64 x 3584 26.9, 21.5, 18.5; 64 x 13056, K 4096 26.8, 21.1, 20.8; 8 x 6656, K 2048 20.0, 12.3, 11.0.  More than 64
+// rows take 64 columns where eight splits would meet otherwise: 128 x 3584, K 8192 e4m3 28.8 -> 22.9, bf16 35.8 -> 34.5 (with four it is
+// 0 to 5 %, 128 x 8192 32.7 -> 31.0, and the answer of ditron_tile_config stays).
 struct DecodePlan {
   int variant, block_m, block_n, splits, kt_per_split, ntiles;
   size_t partial_bytes;   // partial tiles (8 bytes per element: fp32 value + epoch), behind the gathered operand in the workspace
@@ -255,11 +261,19 @@ inline DecodePlan plan_decode(int m, int n, int k_bytes, int variant) {
   d.variant = variant == 0 ? 2 : variant;
   d.block_m = d.variant == 4 ? 16 : 128;
   d.block_n = d.variant == 1 ? 32 : (d.variant == 3 ? 64 : 128);
-  d.ntiles = cdiv(m, d.block_m) * cdiv(n, d.block_n);
   const int kt = cdiv(k_bytes, 128);
-  d.splits = 1;
-  if (d.variant != 1)
-    while ((long)d.ntiles * d.splits * 2 <= 256 && d.splits * 2 <= 8 && kt / (d.splits * 2) >= 4) d.splits *= 2;
+  auto split = [&] {
+    d.ntiles = cdiv(m, d.block_m) * cdiv(n, d.block_n);
+    d.splits = 1;
+    if (d.variant != 1)
+      while ((long)d.ntiles * d.splits * 2 <= 256 && d.splits * 2 <= 8 && kt / (d.splits * 2) >= 4) d.splits *= 2;
+  };
+  split();
+  if (variant == 0 && (m <= 64 || d.splits == 8)) {
+    d.block_m = m <= 16 ? 16 : m <= 32 ? 32 : m <= 64 ? 64 : 128;
+    d.block_n = 64;
+    split();
+  }
   d.kt_per_split = cdiv(kt, d.splits);
   d.partial_bytes = d.splits > 1 ? (size_t)d.ntiles * d.splits * d.block_m * d.block_n * 2 * sizeof(float) : 0;
   return d;
