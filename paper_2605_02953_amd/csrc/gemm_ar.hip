@@ -199,14 +199,15 @@ __global__ __launch_bounds__(T::THREADS) void gemm_ar_kernel(const GemmArParams 
         ar_tile_at(p, q, ntiles, pid_m, pid_n);
         ar_copy_tile<T>(p, p.reduced[s], pid_m * T::BM, pid_n * T::BN);
       }
+      // (no release: nothing of this launch reads the output, its end publishes it)
+      stores_done();
       __syncthreads();
       if (threadIdx.x == 0) {
-        const int old = __hip_atomic_fetch_add(p.prod_count, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        const int old = __hip_atomic_fetch_add(p.prod_count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (old == p.num_producers - 1) {
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
           __hip_atomic_store(p.prod_count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           for (int r = 0; r < p.world; ++r)
-            if (r != p.rank) flag_raise(p.peer_done + r, p.epoch);
+            if (r != p.rank) flag_raise_stored(p.peer_done + r, p.epoch);
         }
       }
     }
@@ -260,7 +261,8 @@ __global__ __launch_bounds__(T::THREADS) void gemm_ar_kernel(const GemmArParams 
   }
   // the last consumer to leave puts the queue back to zero for the next call
   if (threadIdx.x == 0) {
-    const int old = __hip_atomic_fetch_add(p.done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    // (relaxed: the count guards nothing but the two words below, and every consumer's last ticket has been drawn before it counts itself)
+    const int old = __hip_atomic_fetch_add(p.done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (old == p.early + p.late - 1) {
       if constexpr (TWO) {
         // the output is complete when the call returns: the peers' broadcasts must have landed too
