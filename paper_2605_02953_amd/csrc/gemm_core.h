@@ -865,15 +865,19 @@ __device__ __forceinline__ void store_parked_bf16(__bf16* c, size_t ldc, int m0,
   constexpr int ROWS_PER_READ = 64 / P::SLP;
   const int g = lane % P::SLP;
   const int gn = n0 + wn * T::WTN + g * 8;
-  __bf16* wave_c = c + (size_t)(m0 + wm * T::WTM) * ldc;   // row offsets inside a wave's rows fit 32 bits
-  const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc((void*)wave_c, 0, 0x7ffffff0, 0x00020000);
+  __bf16* wave_c = c + (size_t)(m0 + wm * T::WTM) * ldc;
 #pragma unroll 8
   for (int it = 0; it < T::WTM / ROWS_PER_READ; ++it) {
     const int row = it * ROWS_PER_READ + lane / P::SLP;
     const u32x4_t v = *(const u32x4_t*)(park + row * P::ROW + ((g ^ P::key(row)) * 16));
     const int gm = m0 + wm * T::WTM + row;
     if (g < P::SL && gm >= m_lo && gm < m_hi && gn < N) {
-      if constexpr (THROUGH) __builtin_amdgcn_raw_buffer_store_b128(v, rows, (int)((uint32_t)row * (uint32_t)ldc + (uint32_t)gn) * 2, 0, kThrough);
+      if constexpr (THROUGH) {
+        // (a base for every few rows: the widest outputs there are, 2^27 columns, exceed 32 bits over all rows of the wave)
+        const __amdgpu_buffer_rsrc_t rows =
+            __builtin_amdgcn_make_buffer_rsrc((void*)(wave_c + (size_t)(it * ROWS_PER_READ) * ldc), 0, -1, 0x00020000);
+        __builtin_amdgcn_raw_buffer_store_b128(v, rows, (int)(((uint32_t)(lane / P::SLP) * (uint32_t)ldc + (uint32_t)gn) * 2u), 0, kThrough);
+      }
       else *(u32x4_t*)(c + (size_t)gm * ldc + gn) = v;
     }
   }

@@ -980,7 +980,7 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
     r.chunks = chunks_per_slot;
     r.world = world;
     r.epoch = epoch;
-    r.spin_limit = tune.spin_limit;
+    r.spin_limit = std::max(tune.spin_limit, 1u << 20);   // (it waits for work-groups of its own launch only: the limit is for peers)
     const size_t want = (r.vec_per_chunk + kCombineThreads - 1) / kCombineThreads;
     r.wgs_per_chunk = (int)std::min<size_t>(want, std::max(1, 256 / chunks_per_slot));
     reducers = (unsigned)(r.wgs_per_chunk * chunks_per_slot);

@@ -259,3 +259,21 @@ def test_llama_405b_share_sampled(B):
     assert compare.max_row_rel_error(formats.decode_bf16(gemm_out[rows]), pref) <= TOL_BF16
     slots = [gemm_out[d * m_r:(d + 1) * m_r] if s == d else peers_np[s] for s in range(cfg.world)]
     assert np.array_equal(bits(run.out), ors.reduce_slots_f32_ordered(slots))
+
+
+def test_rows_beyond_32_bit_offsets(B):
+    """An output so wide that the rows of one wave are more than 2 GiB apart (the tile is stored with 32-bit offsets from a base
+    that moves with the rows).  One rank, eight products of small integers per element: the bits are exact."""
+    m, n, k = 128, 8_912_896, 8
+    g = torch.Generator(device="cuda").manual_seed(3)
+    a = torch.randint(-3, 4, (m, k), device="cuda", generator=g).to(torch.bfloat16)
+    b = torch.randint(-3, 4, (n, k), device="cuda", generator=g).to(torch.bfloat16)
+    run = GemmRsRun(B, 1, m, n, k)
+    st = run(a.view(torch.int16), b.view(torch.int16), None, 0)
+    assert st == B.OK, B.status_string(st)
+    torch.cuda.synchronize()
+    assert run.status.cpu().tolist()[0] == 0
+    for lo in range(0, m, 32):
+        want = (a[lo:lo + 32].float() @ b.float().t()).to(torch.bfloat16).view(torch.int16)
+        assert torch.equal(run.gemm_out[lo:lo + 32], want)
+        assert torch.equal(run.out[lo:lo + 32], want)
