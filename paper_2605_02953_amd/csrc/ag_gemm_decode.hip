@@ -255,7 +255,7 @@ struct SplitKTile {
   static_assert(MB >= 1 && NB >= 1 && PENDING_B <= 63 && PENDING_A <= 63, "tile shape");
 };
 
-template <bool BF16, class T>
+template <bool BF16, class T, bool ROTATE>
 __device__ __forceinline__ void splitk_work_group(const AgGemmDecodeParams& p, const int32_t epoch, char* lds) {
   const int K = p.k * (BF16 ? 2 : 1);   // bytes per row of A and of B
   if ((int)blockIdx.x < p.num_producers) {
@@ -315,8 +315,17 @@ __device__ __forceinline__ void splitk_work_group(const AgGemmDecodeParams& p, c
   // K tile i of this split (requests past its end fetch 16 constant bytes into a free stage: the number of
   // loads per iteration stays fixed, which the in-order wait counts rely on, and nothing more is asked of
   // memory: re-reading real tiles there kept 5 stale tiles per unit in the queues the partial exchange needs)
-  auto issue_a = [&](int i) {
+  // ROTATE (rows a multiple of 8 KiB apart): the chiplets begin in eight places of the split, for the reason given at chiplet_k_tile.  us with one
+  // beginning and with eight: bf16 64 x 3584, K 4096 18.7, 18.3; 8192 25.7, 25.1; 128 x 3584 34.3, 34.0; e4m3 128 x 8192, K 8192 31.5, 31.2; 256 x
+  // 2048, 16384 34.8, 34.3; not so at other distances, 64 x 3584, K 2000 15.4, 15.8.
+  const int k_first = ROTATE ? (int)((unsigned)kt_n * (unsigned)(wg % p.num_xcd) / (unsigned)p.num_xcd) : 0;
+  auto tile_at = [&](int i) {
     const int kt = min(i, kt_n - 1);
+    if constexpr (!ROTATE) return kt;
+    return kt + k_first >= kt_n ? kt + k_first - kt_n : kt + k_first;
+  };
+  auto issue_a = [&](int i) {
+    const int kt = tile_at(i);
     char* stage = lds_a + (i % T::NA) * T::A_STAGE;
 #pragma unroll
     for (int j = 0; j < T::A_LOADS; ++j) {
@@ -328,7 +337,7 @@ __device__ __forceinline__ void splitk_work_group(const AgGemmDecodeParams& p, c
     }
   };
   auto issue_b = [&](int i) {
-    const int kt = min(i, kt_n - 1);
+    const int kt = tile_at(i);
     char* stage = lds_b + (i % T::NBR) * T::B_STAGE;
 #pragma unroll
     for (int j = 0; j < T::B_LOADS; ++j) {
@@ -537,11 +546,11 @@ __device__ __forceinline__ void splitk_work_group(const AgGemmDecodeParams& p, c
   }
 }
 
-template <bool BF16, class T>
+template <bool BF16, class T, bool ROTATE>
 __global__ __launch_bounds__(T::THREADS) void ag_gemm_splitk_kernel(const AgGemmDecodeParams p) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int32_t epoch = call_epoch(p.epoch, p.epoch_word);
-  splitk_work_group<BF16, T>(p, epoch, lds);
+  splitk_work_group<BF16, T, ROTATE>(p, epoch, lds);
   advance_epoch(epoch, p.epoch_word, p.finished);
 }
 
@@ -549,12 +558,12 @@ __global__ __launch_bounds__(T::THREADS) void ag_gemm_splitk_kernel(const AgGemm
 
 using namespace ditron;
 
-template <bool BF16, class T>
+template <bool BF16, class T, bool ROTATE>
 static ditron_status_t launch_splitk(AgGemmDecodeParams& p, hipStream_t stream) {
-  if (!set_dynamic_lds<ag_gemm_splitk_kernel<BF16, T>>(T::LDS_BYTES)) return DITRON_ERR_HIP;
+  if (!set_dynamic_lds<ag_gemm_splitk_kernel<BF16, T, ROTATE>>(T::LDS_BYTES)) return DITRON_ERR_HIP;
   const int per_xcd = cdiv(p.npm * p.npn, p.num_xcd) * p.splits;   // work-groups of one chiplet
   const unsigned grid = (unsigned)(p.num_producers + per_xcd * p.num_xcd);
-  hipLaunchKernelGGL((ag_gemm_splitk_kernel<BF16, T>), dim3(grid), dim3(T::THREADS), T::LDS_BYTES, stream, p);
+  hipLaunchKernelGGL((ag_gemm_splitk_kernel<BF16, T, ROTATE>), dim3(grid), dim3(T::THREADS), T::LDS_BYTES, stream, p);
   return hipGetLastError() == hipSuccess ? DITRON_OK : DITRON_ERR_HIP;
 }
 
@@ -620,7 +629,9 @@ extern "C" ditron_status_t ditron_ag_gemm_decode(const void* const* a_shards, co
   if (plan.variant != 1) {
     auto launch = [&](auto tile) {
       typedef decltype(tile) T;
-      return bf16 ? launch_splitk<true, T>(p, s) : launch_splitk<false, T>(p, s);
+      const bool rotate = k * (bf16 ? 2 : 1) % 8192 == 0;
+      if (bf16) return rotate ? launch_splitk<true, T, true>(p, s) : launch_splitk<true, T, false>(p, s);
+      return rotate ? launch_splitk<false, T, true>(p, s) : launch_splitk<false, T, false>(p, s);
     };
     switch (plan.block_m * 1000 + plan.block_n) {
       case 128128: return launch(SplitKTile<128, 128>{});

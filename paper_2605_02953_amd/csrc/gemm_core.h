@@ -289,6 +289,20 @@ struct Stager4W {
   }
 };
 
+// The K tile that a work-group of this chiplet begins with where rows are a multiple of 16 KiB apart (rows_share_channels): an eighth of
+// the contraction after the chiplet before it.  A K tile takes 128 bytes of every row; at such distances the same 128 bytes of all rows
+// share few memory channels, and work-groups that walk the contraction in step ask those few all at once.  Inside a chiplet they
+// stay in step and share its L2.  (The order in which products are added changes with it, not their number or their format.)  128-row
+// tiles of [n, k] operands, us with one beginning and with eight: AllGather-GEMM 1024 x 3696, K 8192 81.3, 74.7 (on another card, where
+// the allocation fell better, 72.4, 70.9); 1024 x 2560, K 16384 152, 135; rows 8 KiB or less apart, K 4096, 512 x 6656 36.6, 36.8, 1024 x 3696 41.8, 42.1;
+// [k, n] operands 64 x 3584, K 8192 40.0, 40.9; 256-row tiles, 8192 x 3584, 365, 367.  A beginning per column block instead of per chiplet
+// costs the L2's sharing: 1024 x 3696 80 -> 81, 8192 x 3584 365 -> 395.  MoE, hidden 8192: 1024 tokens, 32 experts, 512 columns 102, 97;
+// 4096 tokens top-2, 8 of 64 experts, 768 columns 112, 111; 256 tokens top-2, 8 experts, 1024 columns 85, 82.
+__device__ __forceinline__ int chiplet_k_tile(int K) {
+  return (int)((unsigned)(K / 64) * (blockIdx.x & 7u) >> 3);
+}
+__host__ __device__ inline bool rows_share_channels(int K) { return K % 8192 == 0; }
+
 // ------------------------------------------------------------------ 16 x 16 x 32 form
 // The transposing read beside direct-to-LDS loads.  A bare builtin call carries no alias information, and the compiler then
 // waits for every load in flight (vmcnt(0)) before it, as if it might read what they write: the loop below took three times
@@ -371,10 +385,11 @@ __device__ __forceinline__ void loads_of_slot(F&& load) {
 // go behind different MFMAs, each MFMA fenced so that the compiler keeps them there (measured: with both behind
 // the slot's last MFMA the loads cost ~300 and the reads ~150 cycles of a K tile's 2048; spread like this the
 // cfg 2 GEMM takes 4 % less time).
-// On entry the LDS must be idle; on exit no load is in flight.
-template <class T, bool WHOLE, class ARow, class BRow>
+// On entry the LDS must be idle; on exit no load is in flight.  ROTATE: the K tiles are taken from k_first
+// round to the one before it (see chiplet_k_tile; an instance of its own, since the counter costs the others 0.5 %).
+template <class T, bool WHOLE, bool ROTATE, class ARow, class BRow>
 __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const char* a_base, ARow a_row,
-                                                     const char* b_base, BRow b_row, int K, char* lds) {
+                                                     const char* b_base, BRow b_row, int K, char* lds, int k_first) {
   constexpr int MB = T::MB, NB = T::NB, READS = MB + T::B_READS * NB, AL = T::A_LOADS, BL = T::B_LOADS;
   constexpr int SLOTS = MB * NB / 4;   // per step
   constexpr int PIECE = T::PIECE_BYTES, D = T::DEPTH;
@@ -414,10 +429,14 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
   // load I of K tile kt into the piece at `piece` (the stager puts B loads T::A_BYTES behind the address it is given)
   auto load_a = [&](auto i, int kt, char* piece) { st.template issue_one<decltype(i)::value, WHOLE>(kt, K, piece); };
   auto load_b = [&](auto i, int kt, char* piece) { st.template issue_one<AL + decltype(i)::value, WHOLE>(kt, K, piece - T::A_BYTES); };
+  int rotated = k_first;   // ROTATE: the K tile requested next
+  auto next_rotated = [&] { rotated = rotated == kt_last ? 0 : rotated + 1; };
   static_for<0, D>([&](auto j) {
     constexpr int J = decltype(j)::value;
-    static_for<0, AL>([&](auto i) { load_a(i, min(J, kt_last), lds + J * NEXT_A); });
-    static_for<0, BL>([&](auto i) { load_b(i, min(J, kt_last), ring_b + J * NEXT_B); });
+    const int kf = ROTATE ? rotated : min(J, kt_last);
+    static_for<0, AL>([&](auto i) { load_a(i, kf, lds + J * NEXT_A); });
+    static_for<0, BL>([&](auto i) { load_b(i, kf, ring_b + J * NEXT_B); });
+    if constexpr (ROTATE) next_rotated();
   });
   wait_vmcnt<(D - 1) * (AL + BL)>();
   barrier_no_drain();
@@ -445,7 +464,7 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
       free_a = lds + wrap(ia + 2 * D) * PIECE;   // held B(kt-1): nobody has read it since the last barrier
       free_b = lds + ia * PIECE;             // A(kt): free after this iteration's barrier
     }
-    const int kf = min(kt + D, kt_last);   // past the end the last K tile is requested again, into pieces nobody reads
+    const int kf = ROTATE ? rotated : min(kt + D, kt_last);   // past the end some K tile is requested again, into pieces nobody reads
     static_for<0, SLOTS>([&](auto sl) {
       constexpr int S = decltype(sl)::value;
       mma_one16<T, S, 0>(acc, f0);
@@ -482,8 +501,9 @@ __device__ __forceinline__ void gemm_mainloop_x16(typename T::Acc16& acc, const 
       __builtin_amdgcn_sched_barrier(0);
     });
     if constexpr (!T::TWO_RINGS) ia = wrap(ia + 2);
+    if constexpr (ROTATE) next_rotated();
   }
-  wait_vmcnt0();   // the last iteration's requests (the last K tile once more) are not left in flight
+  wait_vmcnt0();   // the last iteration's requests are not left in flight
 }
 
 // ------------------------------------------------------------------ fp8 form
@@ -641,17 +661,17 @@ __device__ __forceinline__ void gemm_mainloop_f8(typename T::Acc16& acc, const c
 // On entry the LDS stages must be idle (every wave of the work-group past its last access to them): they are written
 // from the first instruction on.  On exit none of the wave's loads
 // is in flight; other waves may still be reading fragments, so a barrier precedes any reuse of the stages.
-template <class T, class ARow, class BRow>
+template <class T, bool ROTATE = false, class ARow, class BRow>
 __device__ __forceinline__ void gemm_mainloop(typename T::Acc& acc, const char* a_base, ARow a_row,
-                                                 const char* b_base, BRow b_row, int K, char* lds) {
+                                                 const char* b_base, BRow b_row, int K, char* lds, int k_first = 0) {
   if constexpr (T::F8) {
     if (K % 64 == 0) gemm_mainloop_f8<T, true>(acc, a_base, a_row, b_base, b_row, K, lds);
     else gemm_mainloop_f8<T, false>(acc, a_base, a_row, b_base, b_row, K, lds);
     return;
   } else if constexpr (T::X16) {
     // two copies of the loop: the per-load range test of a ragged last K tile costs the others 0.8 %
-    if (K % 64 == 0) gemm_mainloop_x16<T, true>(acc, a_base, a_row, b_base, b_row, K, lds);
-    else gemm_mainloop_x16<T, false>(acc, a_base, a_row, b_base, b_row, K, lds);
+    if (K % 64 == 0) gemm_mainloop_x16<T, true, ROTATE>(acc, a_base, a_row, b_base, b_row, K, lds, k_first);
+    else gemm_mainloop_x16<T, false, ROTATE>(acc, a_base, a_row, b_base, b_row, K, lds, k_first);
     return;
   } else {
   constexpr int PAIRS = T::PAIRS, SLOTS = T::SLOTS, READS = T::READS, LOADS = T::LOADS;
@@ -866,6 +886,9 @@ __device__ __forceinline__ void store_parked_bf16(__bf16* c, size_t ldc, int m0,
   const int g = lane % P::SLP;
   const int gn = n0 + wn * T::WTN + g * 8;
   __bf16* wave_c = c + (size_t)(m0 + wm * T::WTM) * ldc;
+  // 32-bit offsets reach over all rows of the wave up to 2^22 columns; beyond, the base moves with the rows
+  const bool wide = ldc > (1u << 22);
+  const __amdgpu_buffer_rsrc_t all_rows = __builtin_amdgcn_make_buffer_rsrc((void*)wave_c, 0, -1, 0x00020000);
 #pragma unroll 8
   for (int it = 0; it < T::WTM / ROWS_PER_READ; ++it) {
     const int row = it * ROWS_PER_READ + lane / P::SLP;
@@ -873,10 +896,13 @@ __device__ __forceinline__ void store_parked_bf16(__bf16* c, size_t ldc, int m0,
     const int gm = m0 + wm * T::WTM + row;
     if (g < P::SL && gm >= m_lo && gm < m_hi && gn < N) {
       if constexpr (THROUGH) {
-        // (a base for every few rows: the widest outputs there are, 2^27 columns, exceed 32 bits over all rows of the wave)
-        const __amdgpu_buffer_rsrc_t rows =
-            __builtin_amdgcn_make_buffer_rsrc((void*)(wave_c + (size_t)(it * ROWS_PER_READ) * ldc), 0, -1, 0x00020000);
-        __builtin_amdgcn_raw_buffer_store_b128(v, rows, (int)(((uint32_t)(lane / P::SLP) * (uint32_t)ldc + (uint32_t)gn) * 2u), 0, kThrough);
+        if (wide) {
+          const __amdgpu_buffer_rsrc_t rows =
+              __builtin_amdgcn_make_buffer_rsrc((void*)(wave_c + (size_t)(it * ROWS_PER_READ) * ldc), 0, -1, 0x00020000);
+          __builtin_amdgcn_raw_buffer_store_b128(v, rows, (int)(((uint32_t)(lane / P::SLP) * (uint32_t)ldc + (uint32_t)gn) * 2u), 0, kThrough);
+        } else {
+          __builtin_amdgcn_raw_buffer_store_b128(v, all_rows, (int)(((uint32_t)row * (uint32_t)ldc + (uint32_t)gn) * 2u), 0, kThrough);
+        }
       }
       else *(u32x4_t*)(c + (size_t)gm * ldc + gn) = v;
     }

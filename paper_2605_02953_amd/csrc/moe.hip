@@ -450,7 +450,9 @@ __global__ __launch_bounds__(NST > 0 ? 2 * T::THREADS : T::THREADS) void moe_gro
         return;
       }
     } else {
-      gemm_mainloop<T>(acc, p.workspace, a_row, wj, b_row, p.hidden, lds);
+      constexpr bool kRotates = T::X16 && T::BM == 128;
+      if (kRotates && rows_share_channels(p.hidden)) gemm_mainloop<T, kRotates>(acc, p.workspace, a_row, wj, b_row, p.hidden, lds, chiplet_k_tile(p.hidden));
+      else gemm_mainloop<T>(acc, p.workspace, a_row, wj, b_row, p.hidden, lds);
     }
   }
   store_tile_bf16<T>(acc, p.y, (size_t)p.inter, p0, n0, p_end, N, lds);
