@@ -1,22 +1,32 @@
 // GEMM + AllReduce in one-shot form, one rank's share (paper, Appendix "GEMM All-Reduce").
 //
-// One launch holds three kinds of work-groups.
+// One launch holds up to three kinds of work-groups.
 //  * GEMM tiles: one work-group per tile of P = A . B, taken in the grouped tile order; it stores
 //    the tile as bf16 into the buffer the peers would read and raises the tile's flag in this
 //    rank's flag array.
 //  * The emulated peers (lowest indices): every other rank's partial is resident in this GPU's
 //    memory, so a peer is reduced to what the consumer sees of it, its tile flags, raised in the
 //    order a peer's own GEMM finishes tiles.
-//  * The all-reduce consumer: work-groups that draw tickets; ticket q is the tile at position q
+//  * The sum.  One-shot with one tile per unit at most, or with two whole rounds of them: the tile's
+//    own work-group waits for the tile's flag of every peer and adds the peers' copies to its own, which it
+//    still has in LDS.  It has published its tile before it waits, and every rank takes the tiles in the
+//    same order, so the first tile that some rank has not published is always one that runs: no rank can block another.
+//    Otherwise consumers: work-groups that draw tickets; ticket q is the tile at position q
 //    of the tile order, so tiles are reduced in the order they are finished.  The holder waits
-//    for the tile's flag of every rank (one lane per rank), adds the `world` published copies in
-//    fp32 in rank order with 128-bit loads, rounds once to bf16 and writes the output tile.
+//    for the tile's flag of every rank (one lane per rank).  Either way the `world` published copies
+//    are added in fp32 in rank order with 128-bit loads, rounded once to bf16 and written to the output tile.
+// us with consumers and with the tiles' own sums, 8 ranks: 128 x 2048, K 512 (16 tiles) 16.6, 12.8; 64 x 4096, K 1024 15.2, 13.8; 16 x 8192, K 2048
+// 17.7, 16.8; 512 x 8192, K 3584 (256 tiles) 45.6, 41.6; 4096 x 4096, K 2048 (256 large ones) 105.6, 103.2; 200 x 4096, K 1000, 2 ranks 16.3, 14.9;
+// two rounds, 1024 x 8192, K 3584 88, 81 to 88; 4096 x 8192, K 512 148, 135, 3584 259, 257, 2 ranks, 2048 144, 128.  Units that a last round
+// leaves empty are better consumers: 272 tiles, 2000 x 2056, K 2048 53.5, 58.1; 480, 2048 x 3840, 48.2, 52.8; 304 large ones 179, 203; and with more
+// rounds the sums of a round coincide: 768 large ones, 8192 x 6144, K 2048 269, 296; 1024, K 512 267, 258 to 265, 3584 478, 483 to 499.  (Consumers for all rounds but the last, own
+// sums in that: 4096 x 8192, K 3584 258, 286; 8192 x 8192 473, 488.)
 // Where the consumers sit in the grid decides when they run.  When the GEMM needs more than one
 // chip-wide round of tiles, X consumers follow the first round of tiles: they take X compute
 // units as the first tiles retire and keep them to the end, reducing finished tiles while the
 // other units compute the next ones.  Behind the last tile sit as many consumers again as the
 // chip has units; they pick up compute units as the last tiles retire and the whole chip
-// finishes the queue.  A tile never waits, and a consumer only waits (bounded) for tiles that
+// finishes the queue.  A tile never waits for its own launch, and a consumer only waits (bounded) for tiles that
 // are ahead of it in the grid, so the launch cannot deadlock.
 //
 // Sizing X: one work-group streams about 50 GB/s on its compute unit whatever it keeps in
@@ -55,9 +65,12 @@ struct GemmArParams {
   int num_producers;
   int head_tiles;        // tiles ahead of the early consumers
   int early, late;       // consumers behind the first round of tiles / behind the last tile
+  int own_sums;          // a tile's work-group adds the peers' copies itself, there are no consumers (one-shot)
   int peers_resident;    // flags preset: the peers' partials are complete, only the own tile flags are waited for
   int group_m, num_xcd, per_xcd, npm, npn;
 };
+
+constexpr int kOwnSumColumns = 1 << 22;   // the most columns with which a tile's rows lie within 32-bit offsets
 
 __device__ __forceinline__ void ar_tile_at(const GemmArParams& p, int position, int ntiles, int& pid_m, int& pid_n) {
   const int id = xcd_remap(position, ntiles, p.num_xcd, p.per_xcd);
@@ -138,6 +151,70 @@ __device__ __forceinline__ void ar_reduce_tile(const GemmArParams& p, int m0, in
         }
       }
     }
+  }
+}
+
+// One-shot in a tile's own work-group: the parked tile (this rank's partial, rounded as the peers read it) plus the peers' partials
+// of it, in rank order.  U vectors of 16 bytes per lane and peer are in flight; they are dealt over the rows and columns that exist.
+template <class T, int WORLD, int U>
+__device__ __forceinline__ void ar_sum_parked(const GemmArParams& p, int m0, int n0, const char* lds) {
+  typedef ParkedTile<T> P;
+  constexpr uint32_t kOut = 0xF0000000;   // end of every buffer: kOwnSumColumns keeps a tile's rows below it
+  const int world = WORLD > 0 ? WORLD : p.world;
+  const int tile_m = min(T::BM, p.m - m0), tile_n = min(T::BN, p.n - n0);
+  const int vpr = tile_n >> 3;                 // 16-byte vectors per tile row
+  const int nvec = tile_m * vpr;
+  const size_t first = (size_t)m0 * p.n + n0;
+  // (the own partial's buffer is empty: its loads cost nothing)
+  auto rows_of = [&](int s) {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)((const __bf16*)p.part[s] + first), 0, s == p.rank ? 0 : (int)kOut, 0x00020000);
+  };
+  const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc((void*)(p.out + first), 0, (int)kOut, 0x00020000);
+#pragma unroll 1
+  for (int v0 = threadIdx.x; v0 < nvec; v0 += T::THREADS * U) {
+    uint32_t off[U];
+    const char* own[U];
+    u32x4_t x[WORLD > 0 ? WORLD : 1][U];
+    float acc[U][8];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int v = v0 + u * T::THREADS;
+      const int row = tile_n == T::BN ? v / (T::BN / 8) : v / vpr;
+      const int col = v - row * vpr;
+      off[u] = v < nvec ? ((uint32_t)row * (uint32_t)p.n + (uint32_t)col * 8u) * 2u : kOut;
+      // the wave that parked it, its row and slot there (a vector past the tile reads some parked one and is not stored)
+      const int r = row % T::WTM, g = col % P::SL;
+      own[u] = lds + ((row / T::WTM % T::WAVES_M * T::WAVES_N + col / P::SL) * T::WTM + r) * P::ROW + (g ^ P::key(r)) * 16;
+    }
+    if constexpr (WORLD > 0) {
+#pragma unroll
+      for (int s = 0; s < WORLD; ++s) {
+        const __amdgpu_buffer_rsrc_t rows = rows_of(s);
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[s][u] = __builtin_amdgcn_raw_buffer_load_b128(rows, (int)off[u], 0, kStreaming);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const u32x4_t mine = *(const u32x4_t*)own[u];
+        ar_set(acc[u], p.rank == 0 ? mine : x[0][u]);
+#pragma unroll
+        for (int s = 1; s < WORLD; ++s) ar_add(acc[u], s == p.rank ? mine : x[s][u]);
+      }
+    } else {
+      for (int s = 0; s < world; ++s) {
+        const __amdgpu_buffer_rsrc_t rows = rows_of(s);
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[0][u] = __builtin_amdgcn_raw_buffer_load_b128(rows, (int)off[u], 0, kStreaming);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const u32x4_t term = s == p.rank ? *(const u32x4_t*)own[u] : x[0][u];
+          if (s == 0) ar_set(acc[u], term);
+          else ar_add(acc[u], term);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) __builtin_amdgcn_raw_buffer_store_b128(ar_pack(acc[u]), out, (int)off[u], 0, kStreaming);
   }
 }
 
@@ -238,9 +315,26 @@ __global__ __launch_bounds__(T::THREADS) void gemm_ar_kernel(const GemmArParams 
       gemm_mainloop<T>(acc, p.a, a_row, p.b, b_row, p.k, lds);
     }
     store_tile_bf16<T, true>(acc, p.gemm_out, (size_t)p.n, m0, n0, M, N, lds);
+    // Summed here: every wave looks at the peers' flags once while its stores are on their way (it waits for them only after this
+    // rank's own flag is up, so that ranks which wait for each other cannot block).
+    const bool sums = !TWO && p.own_sums;
+    const int lane = threadIdx.x & 63;
+    const bool gate = sums && !p.peers_resident && lane < p.world && lane != p.rank;
+    const int32_t* flag = p.tile_flags + (size_t)(gate ? lane : 0) * ntiles + pid_m * p.npn + pid_n;
+    const bool up = !gate || __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == p.epoch;
     stores_done();
     __syncthreads();   // every wave's part of the tile is in memory: notify
     if (threadIdx.x == 0) flag_raise_stored(p.tile_flags + (size_t)p.rank * ntiles + pid_m * p.npn + pid_n, p.epoch);
+    if constexpr (!TWO) {
+      if (sums) {
+        if (!up) flag_wait_lane(p.tile_flags + (size_t)lane * ntiles, pid_m * p.npn + pid_n, 1, p.epoch, p.spin_limit, p.status);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        const int nvec = min(T::BM, p.m - m0) * (min(T::BN, p.n - n0) >> 3);
+        if (nvec <= 2 * T::THREADS) ar_sum_parked<T, WORLD, 2>(p, m0, n0, lds);
+        else if (T::BM == 256 || nvec <= 4 * T::THREADS) ar_sum_parked<T, WORLD, 4>(p, m0, n0, lds);
+        else ar_sum_parked<T, WORLD, 8>(p, m0, n0, lds);
+      }
+    }
     return;
   }
 
@@ -286,7 +380,8 @@ static ditron_status_t launch_ar(GemmArParams& p, int units, bool two_shot, hipS
   units = units / 8 * 8;
   p.head_tiles = std::min(ntiles, units);
   p.early = 0;
-  if (ntiles > units) {
+  p.own_sums = !two_shot && p.n <= kOwnSumColumns && (ntiles <= units || ntiles == 2 * units);   // (measured: see the top of the file)
+  if (!p.own_sums && ntiles > units) {
     // X units reduce while units - X compute the tiles at the per-unit MFMA rate of a full-chip GEMM:
     // balance the two.  Per GEMM tile the consumer moves (world + 1) tile-sized streams in the one-shot
     // form and 2 in the two-shot form (world reads and world writes for one tile in `world`), at ~40 GB/s
@@ -298,7 +393,7 @@ static ditron_status_t launch_ar(GemmArParams& p, int units, bool two_shot, hipS
     const int x = (int)(units * t_reduce / (t_reduce + t_gemm) / 8 + 0.5) * 8;
     p.early = std::max(0, std::min(x, units / 2));
   }
-  p.late = std::min(units, ntiles);
+  p.late = p.own_sums ? 0 : std::min(units, ntiles);
   const unsigned grid = (unsigned)(p.num_producers + ntiles + p.early + p.late);
   auto launch = [&](auto instance) {
     constexpr auto kern = decltype(instance)::value;

@@ -334,3 +334,24 @@ def test_all_reduce_consumer_by_rank_count(B, world, rows, n, k):
         for t in range(world):
             if t != d:
                 assert np.array_equal(bits(outs[t]), want), (layout, t)
+
+
+# Sums by the tiles' own work-groups: one vector per lane and less, two, four and eight of them, the last batch partly empty, a
+# last tile of one vector; two whole rounds of tiles (512 of them), and the queue on both sides of that (272, 549)
+@pytest.mark.parametrize("world,m,n,d", [
+    (2, 2, 8, 1), (3, 3, 136, 0), (8, 16, 264, 7), (8, 32, 128, 0), (4, 64, 392, 2), (5, 100, 256, 4), (8, 128, 1024, 5),
+    (2, 1024, 8192, 0), (2, 2000, 2056, 1), (2, 1056, 7808, 1),
+])
+def test_all_reduce_sums_bit_exact(B, world, m, n, d):
+    k = 72
+    cfg = synth.CONFIGS[3].scaled(world=world, m_per_rank=m // world, n=n, k=k)
+    a_list, b_list = synth.gemm_rs_inputs(cfg, integer=True)
+    parts = [oar.partial_bits(a, b) for a, b in zip(a_list, b_list)]
+    full = oar.allreduce_partials_f32_ordered(parts)
+    peers = [None if s == d else to_dev(parts[s]) for s in range(world)]
+    a_dev, b_dev = to_dev(a_list[d]), to_dev(nk(b_list[d]))
+    ar = GemmArRun(B, world, cfg.m, n, k)
+    for flags in (None, B.FLAGS_PRESET):
+        ar.out.fill_(0x7FC0)
+        _ok(B, ar(a_dev, b_dev, peers, d, flags=flags), ar)
+        assert np.array_equal(bits(ar.gemm_out), parts[d]) and np.array_equal(bits(ar.out), full)
