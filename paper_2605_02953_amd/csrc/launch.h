@@ -145,8 +145,8 @@ inline double tiling_cost(long tiles, int block_n) {
 // every world-th tile, reduces it and broadcasts it, so the tiling is part of what the ranks agree on and what a call returns.
 enum class Narrow { kNever, kNK, kKN, kF8, kAllReduce };   // kF8: as kNK, e4m3 operands
 
-// The most 128 x 128 tiles with which GEMM-ReduceScatter stays on them.  Every tile ends with a release (the segment counter),
-// which a short contraction does not hide, and 256-row tiles have a quarter as many; in a long one a second round of small
+// The most 128 x 128 tiles with which GEMM-ReduceScatter stays on them.  Every tile ends by waiting for its stores and counting itself,
+// which a short contraction does not hide, and 256-row tiles have a quarter as many (the figures are from tiles that ended with a release, which costs more); in a long one a second round of small
 // tiles is partly empty and its units take the peers' copies, while the large tiles leave half of the chip to nobody.  So the
 // line depends on K.  us with 128 x 128 tiles (as gemm_rs_impl runs them) and with 256-row ones, 8 ranks, weights not in the caches:
 //   240 tiles, 2048 x 1920: K 1024 35.2, 33.2; 1536 37.1, 41.7; 3584 50.5, 75.0
