@@ -355,3 +355,16 @@ def test_all_reduce_sums_bit_exact(B, world, m, n, d):
         ar.out.fill_(0x7FC0)
         _ok(B, ar(a_dev, b_dev, peers, d, flags=flags), ar)
         assert np.array_equal(bits(ar.gemm_out), parts[d]) and np.array_equal(bits(ar.out), full)
+
+
+# Rows 16 KiB apart (the tile engine) and 8 KiB (the decode kernel): the chiplets begin the contraction in eight places.  132 tiles
+# of 128 x 128; decode tiles of 64 and of 16 rows, split and not.  Integer inputs: any order of the sum gives the same bits
+@pytest.mark.parametrize("m_per_rank,n,k", [(64, 4224, 8192), (8, 200, 4096), (2, 72, 12288), (16, 8200, 4096)])
+def test_contractions_begun_in_eight_places_are_bit_exact(B, m_per_rank, n, k):
+    cfg = synth.CONFIGS[2].scaled(world=8, m_per_rank=m_per_rank, n=n, k=k, rank=3)
+    shards, b = synth.ag_gemm_inputs(cfg, integer=True)
+    run = AgGemmRun(B, 8, m_per_rank, n, k)
+    st = run([to_dev(s) for s in shards], to_dev(nk(b)), cfg.rank)
+    _ok(B, st, run)
+    assert np.array_equal(bits(run.workspace), oag.gather(shards))
+    assert np.array_equal(bits(run.c), formats.encode_bf16_rne(oag.ag_gemm(shards, b).astype(np.float32)))
