@@ -661,7 +661,6 @@ struct MoeCombineParams {
   size_t slot_bytes;
   int chunks, n_peers, num_producers, teams;
   int32_t epoch;
-  ReduceParams reduce;         // work-groups behind the peers, if there are any
 };
 
 constexpr int kCombineThreads = 512;
@@ -674,20 +673,12 @@ struct TokenRows {
   float gate;
 };
 
-// One launch, three kinds of work-groups, each waiting only for kinds before it.  (It replaced four launches' last two, and the clearing
-// launch before them: 8192 tokens top-2 of 32 experts, 2048 columns, world 8, 91 -> 70 us for the whole call, 128 tokens of 3000
-// columns 31 -> 21.  Bound by memory: 101 MB for the combine itself take 17.6 us with the peers' blocks resident, 24.3 when every
-// work-group ended with a release; of the others 59 MB are the peers' copies and 38 MB the reduction.)
-//  * the combine: one wave per token and 64 U vectors of 8 columns, the rank's own rows first, U vectors of
-//    each of 8 / U of the token's rows in flight per lane; the last work-group to finish the own rows raises the flags of the own slot;
-//  * the emulated peers;
-//  * the reduction (unless an external producer delivers the peers' blocks: then it is a launch of its own).
-template <int WORLD, int U>
+// The combine and, behind it, the emulated peers; neither waits for anything.  (8192 tokens top-2 of 32 experts, 2048 columns, world
+// 8: bound by memory, 101 MB for the combine itself, which take 17.6 us with the peers' blocks resident, and 59 MB for the peers' copies.)
+// One wave per token and 64 U vectors of 8 columns, the rank's own rows first, U vectors of each of 8 / U of the token's rows in flight per
+// lane; the last work-group to finish the own rows raises the flags of the own slot, for whoever waits on another stream.
+template <int U>
 __global__ __launch_bounds__(kCombineThreads) void moe_combine_kernel(const MoeCombineParams p) {
-  if ((int)blockIdx.x >= p.combine_wgs + p.num_producers) {
-    reduce_slots_work_group<WORLD, kCombineThreads>(p.reduce, blockIdx.x - p.combine_wgs - p.num_producers);
-    return;
-  }
   if ((int)blockIdx.x >= p.combine_wgs) {
     const size_t chunk_bytes = p.slot_bytes / p.chunks;
     produce_chunks<kCombineThreads>(
@@ -806,17 +797,6 @@ __global__ __launch_bounds__(kCombineThreads) void moe_combine_kernel(const MoeC
   run(first + cdiv(max(own - first, 0), stride) * stride, items, std::false_type{});
 }
 
-template <int U>
-static void launch_combine(const MoeCombineParams& c, unsigned reducers, hipStream_t s) {
-  const dim3 grid((unsigned)(c.combine_wgs + c.num_producers) + reducers);
-  switch (reducers ? c.reduce.world : 0) {
-    case 8: hipLaunchKernelGGL((moe_combine_kernel<8, U>), grid, dim3(kCombineThreads), 0, s, c); break;
-    case 4: hipLaunchKernelGGL((moe_combine_kernel<4, U>), grid, dim3(kCombineThreads), 0, s, c); break;
-    case 2: hipLaunchKernelGGL((moe_combine_kernel<2, U>), grid, dim3(kCombineThreads), 0, s, c); break;
-    default: hipLaunchKernelGGL((moe_combine_kernel<0, U>), grid, dim3(kCombineThreads), 0, s, c); break;
-  }
-}
-
 }  // namespace ditron
 
 extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
@@ -920,8 +900,7 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
   }
   if (st != DITRON_OK) return st;
 
-  // 2. top-k combine into token order; the emulated peers' blocks arrive beside it, and behind them the reduction of
-  //    GEMM-ReduceScatter over the `world` slots (own slot: the rank's rows of `combined`)
+  // 2. top-k combine into token order; the emulated peers' blocks arrive beside it
   const size_t slot_bytes = (size_t)tokens_per_rank * hidden * 2;
   MoeCombineParams c{};
   c.y = (const __bf16*)y;
@@ -940,11 +919,12 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
   const int vpr = hidden / 8;
   auto items_at = [&](int u) { return (long)c.tokens * cdiv(vpr, 64 * u); };
   // As many vectors per lane as leave a thousand waves; fewer tokens take more of a token's rows at a time instead, over more waves.  us
-  // with 4, 2 and 1, whole calls: 8192 tokens top-2, 2048 columns 70, 73, 81; 1488 top-6, 1456 columns 42.3, 45.9, 50.1; 1200 top-1, 1072 columns
+  // with 4, 2 and 1, whole calls (the reduction was part of the launch then): 8192 tokens top-2, 2048 columns 70, 73, 81; 1488 top-6, 1456 columns 42.3, 45.9, 50.1; 1200 top-1, 1072 columns
   // 21.5, 23.3, 24.2; 100 top-4, 1136 columns 22.1, 19.1, 17.5; 68 top-4, 7408 columns 42.0, 36.8, 36.2 (against: 2044 top-6, 2168 columns 64, 59, 54).
   const int unroll = vpr > 128 && items_at(4) >= 1024 ? 4 : vpr > 64 && items_at(2) >= 1024 ? 2 : 1;
   const long items = items_at(unroll);
-  // three work-groups to a unit fit; 8192 tokens, 2048 columns, world 8: 256 / 384 / 512 / 768 of them 83 / 75 / 74 / 71 us for the call
+  // three work-groups to a unit fit; 8192 tokens, 2048 columns, world 8: 256 / 512 / 768 of them 83 / 78 / 77 us for the call beside 56 copying
+  // work-groups; 768 / 1024 68 / 73 beside 112
   c.combine_wgs = (int)std::min<long>(768, (items + kCombineThreads / 64 - 1) / (kCombineThreads / 64));
   c.done = signals + world;                                   // the counter word of segment 0 (unused here otherwise)
   c.own_flags = signals + 2 * world + rank * chunks_per_slot;
@@ -959,7 +939,7 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
   c.chunks = chunks_per_slot;
   c.n_peers = world - 1;
   const ProducerPlan pl = plan_producers((size_t)(world - 1) * slot_bytes, (world - 1) * chunks_per_slot);
-  // twice as many as the plan says: they have half of its threads (at the same sizes 56 / 84 / 112 / 168 of them 78 / 75 / 71 / 73 us)
+  // twice as many as the plan says: they have half of its threads (at the same sizes 56 / 84 / 112 / 168 of them 77 / 72 / 68 / 68 us)
   c.num_producers = (emulate && world > 1) ? 2 * pl.producers : 0;
   c.teams = std::min(pl.teams, std::max(1, c.num_producers));
   c.epoch = epoch;
@@ -967,33 +947,17 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
   for (int i = 0; i < world; ++i)
     slots[i] = i == rank ? (const void*)((const char*)combined + (size_t)rank * slot_bytes)
                          : (const void*)((const char*)scatter_buf + (size_t)i * slot_bytes);
-  unsigned reducers = 0;
-  if (mode != Mode::kExternal) {
-    ReduceParams& r = c.reduce;
-    for (int i = 0; i < world; ++i) {
-      r.slot[i] = slots[i];
-      // flags preset: the peers' blocks are resident
-      r.gate[i] = i == rank || emulate ? c.arr_flags + (size_t)i * chunks_per_slot : nullptr;
-      r.gate_stride[i] = 1;
-    }
-    r.out = (__bf16*)out;
-    r.status = status;
-    r.vec_per_chunk = (size_t)(tokens_per_rank / chunks_per_slot) * hidden / 8;
-    r.chunks = chunks_per_slot;
-    r.world = world;
-    r.epoch = epoch;
-    r.spin_limit = std::max(tune.spin_limit, 1u << 20);   // (it waits for work-groups of its own launch only: the limit is for peers)
-    const size_t want = (r.vec_per_chunk + kCombineThreads - 1) / kCombineThreads;
-    r.wgs_per_chunk = (int)std::min<size_t>(want, std::max(1, 256 / chunks_per_slot));
-    reducers = (unsigned)(r.wgs_per_chunk * chunks_per_slot);
-  }
-  if (unroll == 4) launch_combine<4>(c, reducers, s);
-  else if (unroll == 2) launch_combine<2>(c, reducers, s);
-  else launch_combine<1>(c, reducers, s);
+  const dim3 grid((unsigned)(c.combine_wgs + c.num_producers));
+  if (unroll == 4) hipLaunchKernelGGL(moe_combine_kernel<4>, grid, dim3(kCombineThreads), 0, s, c);
+  else if (unroll == 2) hipLaunchKernelGGL(moe_combine_kernel<2>, grid, dim3(kCombineThreads), 0, s, c);
+  else hipLaunchKernelGGL(moe_combine_kernel<1>, grid, dim3(kCombineThreads), 0, s, c);
   if (hipGetLastError() != hipSuccess) return DITRON_ERR_HIP;
-  if (reducers) return DITRON_OK;
 
-  // 3. an external producer may need room on the chip while the reduction waits for it: a launch of its own
-  return ditron_reduce_slots(slots, out, signals + 2 * world, status, tokens_per_rank, hidden, world, chunks_per_slot, epoch, tuning,
-                             stream);
+  // 3. the reduction of GEMM-ReduceScatter over the `world` slots (own slot: the rank's rows of `combined`).  A launch of its own, so that
+  //    the stream orders it and only an external producer's blocks are waited for.  As work-groups of the launch before, it held units while
+  //    it polled for the combine, and preset flags told it nothing.  us in that launch and in its own: 8192 tokens, 2048 columns, world 8
+  //    71.7, 67.5; 2044 tokens top-6, 2168 columns, 4 ranks 82.1, 68.5; 1024 tokens, 4096 columns, 2 ranks 68.9, 57.4; 128 tokens of 3000
+  //    columns 20.6, 20.9; 1488 top-6, 1456 columns 33.9, 34.9; 1200 top-1, 1072 columns 19.8, 20.2.
+  return ditron_reduce_slots(slots, out, mode == Mode::kExternal ? signals + 2 * world : nullptr, status, tokens_per_rank, hidden, world,
+                             chunks_per_slot, epoch, tuning, stream);
 }

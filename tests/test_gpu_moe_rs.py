@@ -38,7 +38,7 @@ def _case(world, t_r, inter_r, hidden, experts, top_k, local, seed, integer):
 
 
 def _run(B, ids, hs, ws, e0s, d, world, t_r, inter_r, hidden, experts, top_k, local, chunks, gate, integer,
-         flags=None, order=None, kn=False, stale_rows=False):
+         flags=None, order=None, kn=False, stale_rows=False, flags_up=False, tuning=None):
     _, offsets, gather = omoe.route(ids, world, experts, e0s[d], local)
     R = int(offsets[-1])
     max_rows = max(R, 1) + 7
@@ -63,6 +63,8 @@ def _run(B, ids, hs, ws, e0s, d, world, t_r, inter_r, hidden, experts, top_k, lo
     out = torch.full((t_r, hidden), 0x7FC0, dtype=torch.int16, device="cuda")
     signals = torch.zeros(B.signal_words(world, chunks), **i32)
     status = torch.zeros(B.STATUS_WORDS, **i32)
+    if flags_up:
+        signals[2 * world:2 * world + world * chunks] = 3
     if flags == B.FLAGS_PRESET:
         for s in range(world):
             if s != d:
@@ -73,7 +75,7 @@ def _run(B, ids, hs, ws, e0s, d, world, t_r, inter_r, hidden, experts, top_k, lo
                                to_dev(gather.astype(np.int32)) if R else torch.zeros(1, **i32), to_dev(offsets.astype(np.int32)),
                                y, inv, rec, combined, None if flags == B.FLAGS_PRESET else peers, scatter, out, signals, status,
                                order, t_r, hidden, inter_r, experts, top_k, local, max_rows, world, d, chunks, 3,
-                               B.EMULATE_PRODUCER if flags is None else flags)
+                               B.EMULATE_PRODUCER if flags is None else flags, tuning=tuning)
     assert st == B.OK, B.status_string(st)
     torch.cuda.synchronize()
     assert status.cpu().tolist()[0] == 0
@@ -142,6 +144,17 @@ def test_moe_rs_weights_kn_and_flags_preset(B):
     ids, hs, ws, e0s = _case(world, t_r, inter_r, hidden, experts, top_k, experts, seed=5, integer=True)
     _run(B, ids, hs, ws, e0s, 1, world, t_r, inter_r, hidden, experts, top_k, experts, 2, None, True, kn=True)
     _run(B, ids, hs, ws, e0s, 2, world, t_r, inter_r, hidden, experts, top_k, experts, 2, None, True, flags=B.FLAGS_PRESET)
+
+
+# `combined` holds NaN before the call: a sum that starts before the combine has stored the rank's own rows shows
+@pytest.mark.parametrize("world,t_r,hidden,experts,top_k,chunks", [(2, 8, 72, 4, 2, 1), (2, 520, 1048, 6, 3, 4), (8, 512, 1032, 16, 2, 2)])
+def test_moe_rs_reduction_follows_the_combine(B, world, t_r, hidden, experts, top_k, chunks):
+    ids, hs, ws, e0s = _case(world, t_r, 8, hidden, experts, top_k, experts, seed=t_r, integer=True)
+    shape = (world, t_r, 8, hidden, experts, top_k, experts, chunks, None, True)
+    # flags preset, as the mode's name has it: every arrival word, the own slot's too, holds the epoch before the call
+    _run(B, ids, hs, ws, e0s, world - 1, *shape, flags=B.FLAGS_PRESET, flags_up=True)
+    # emulated peers: nothing is left to wait for when the reduction starts, so one poll is enough
+    _run(B, ids, hs, ws, e0s, 0, *shape, tuning=B.tuning(spin_limit=1))
 
 
 # [k, n] weights: contractions up to 512 take a ring of two K tiles (its five pieces: less than one K tile up to two turns, whole
