@@ -7,7 +7,7 @@
 //  * The emulated peers (lowest indices): every other rank's partial is resident in this GPU's
 //    memory, so a peer is reduced to what the consumer sees of it, its tile flags, raised in the
 //    order a peer's own GEMM finishes tiles.
-//  * The sum.  One-shot with one tile per unit at most, or with two whole rounds of them: the tile's
+//  * The sum.  One-shot with one tile per unit at most, or with nearly two (see launch_ar): the tile's
 //    own work-group waits for the tile's flag of every peer and adds the peers' copies to its own, which it
 //    still has in LDS.  It has published its tile before it waits, and every rank takes the tiles in the
 //    same order, so the first tile that some rank has not published is always one that runs: no rank can block another.
@@ -16,11 +16,19 @@
 //    for the tile's flag of every rank (one lane per rank).  Either way the `world` published copies
 //    are added in fp32 in rank order with 128-bit loads, rounded once to bf16 and written to the output tile.
 // us with consumers and with the tiles' own sums, 8 ranks: 128 x 2048, K 512 (16 tiles) 16.6, 12.8; 64 x 4096, K 1024 15.2, 13.8; 16 x 8192, K 2048
-// 17.7, 16.8; 512 x 8192, K 3584 (256 tiles) 45.6, 41.6; 4096 x 4096, K 2048 (256 large ones) 105.6, 103.2; 200 x 4096, K 1000, 2 ranks 16.3, 14.9;
-// two rounds, 1024 x 8192, K 3584 88, 81 to 88; 4096 x 8192, K 512 148, 135, 3584 259, 257, 2 ranks, 2048 144, 128.  Units that a last round
-// leaves empty are better consumers: 272 tiles, 2000 x 2056, K 2048 53.5, 58.1; 480, 2048 x 3840, 48.2, 52.8; 304 large ones 179, 203; and with more
-// rounds the sums of a round coincide: 768 large ones, 8192 x 6144, K 2048 269, 296; 1024, K 512 267, 258 to 265, 3584 478, 483 to 499.  (Consumers for all rounds but the last, own
-// sums in that: 4096 x 8192, K 3584 258, 286; 8192 x 8192 473, 488.)
+// 17.7, 16.8; 512 x 8192, K 3584 (256 tiles) 45.6, 41.6; 4096 x 4096, K 2048 (256 large ones) 105.6, 103.2; 200 x 4096, K 1000, 2 ranks 16.3, 14.9.
+// Two rounds (X as below; w: ranks):
+//  * fewer than X units are left empty and t_gemm >= 3 t_reduce (large tiles: 3.5): 1024 x 8064 (504 tiles), K 3584 w2 84.0, 74.1; w4 87.1, 78.6; w8 93.1,
+//    89.3; 512 w8 92.5, 92.2; 464 tiles, K 1536 w2 47.8, 43.8; K 2560 w4 71.2, 61.9; 512, K 1536 w2 45.9, 46.5; K 4096 w4 90.6, 90.0; 4608 x 7168
+//    (504 large ones), K 3584 w2 239, 205; 512 large ones, K 2560 w4 187, 179;
+//  * the same, t_gemm between that and 0.5 t_reduce: 512 tiles, K 2048 w8 65.5, 72.0; K 1024 w4 41.1, 43.7; 512 large ones, K 2048
+//    w8 192, 206; w4 161, 163; K 3584 w8 266, 271; 504, K 2048 w8 186, 207;
+//  * t_gemm below half of t_reduce: 512 tiles, K 512 w8 45.9, 52.6; K 256 w4 34.5, 34.5; 512 large ones, K 512 w8 152, 142; K 256 w8 140, 135, w4 86.7, 86.5;
+//    464, K 256 w8 131, 128, w4 85, 79; 448, K 512 w8 132, 134;
+//  * X units or more are left empty: 272 tiles, K 2048 w8 50.9, 55.9, w2 41.3, 42.7; 448, K 3584 w4 67, 74; 488, K 4096 w2 71, 80; 464 large ones, K 3072
+//    w2 154, 168.
+// With more rounds the sums of a round coincide: 768 large ones, 8192 x 6144, K 2048 269, 296; 1024, K 512 267, 258 to 265, 3584 478, 483 to 499.  (Consumers
+// for all rounds but the last, own sums in that: 4096 x 8192, K 3584 258, 286; 8192 x 8192 473, 488.)
 // Where the consumers sit in the grid decides when they run.  When the GEMM needs more than one
 // chip-wide round of tiles, X consumers follow the first round of tiles: they take X compute
 // units as the first tiles retire and keep them to the end, reducing finished tiles while the
@@ -379,20 +387,24 @@ static ditron_status_t launch_ar(GemmArParams& p, int units, bool two_shot, hipS
   const int ntiles = p.npm * p.npn;
   units = units / 8 * 8;
   p.head_tiles = std::min(ntiles, units);
-  p.early = 0;
-  p.own_sums = !two_shot && p.n <= kOwnSumColumns && (ntiles <= units || ntiles == 2 * units);   // (measured: see the top of the file)
-  if (!p.own_sums && ntiles > units) {
-    // X units reduce while units - X compute the tiles at the per-unit MFMA rate of a full-chip GEMM:
-    // balance the two.  Per GEMM tile the consumer moves (world + 1) tile-sized streams in the one-shot
-    // form and 2 in the two-shot form (world reads and world writes for one tile in `world`), at ~40 GB/s
-    // per unit (50 while streaming, less the waits).
-    constexpr double kUnitBytes = 40e9, kUnitFlops = 5.3e12;   // (measured at table shape 3: X = 40 / 56 / 64 / 72 / 80 -> 555 / 534 / 528 / 540 / 545 us)
-    const double streams = two_shot ? 2.0 : p.world + 1.0;
-    const double t_reduce = streams * T::BM * T::BN * 2 / kUnitBytes;   // unit-seconds per tile
-    const double t_gemm = 2.0 * T::BM * T::BN * p.k / kUnitFlops;
-    const int x = (int)(units * t_reduce / (t_reduce + t_gemm) / 8 + 0.5) * 8;
-    p.early = std::max(0, std::min(x, units / 2));
-  }
+  // X units reduce while units - X compute the tiles at the per-unit MFMA rate of a full-chip GEMM:
+  // balance the two.  Per GEMM tile the consumer moves (world + 1) tile-sized streams in the one-shot
+  // form and 2 in the two-shot form (world reads and world writes for one tile in `world`), at ~40 GB/s
+  // per unit (50 while streaming, less the waits).
+  constexpr double kUnitBytes = 40e9, kUnitFlops = 5.3e12;   // (measured at table shape 3: X = 40 / 56 / 64 / 72 / 80 -> 555 / 534 / 528 / 540 / 545 us)
+  const double streams = two_shot ? 2.0 : p.world + 1.0;
+  const double t_reduce = streams * T::BM * T::BN * 2 / kUnitBytes;   // unit-seconds per tile
+  const double t_gemm = 2.0 * T::BM * T::BN * p.k / kUnitFlops;
+  const int x = std::min((int)(units * t_reduce / (t_reduce + t_gemm) / 8 + 0.5) * 8, units / 2);
+  // One round of tiles: the tiles sum.  Two rounds that leave fewer than X units empty: the X consumers would push a part of the tiles into a
+  // third round, which costs about a t_gemm; the tiles' own sums coincide in both rounds instead, which costs more the shorter the
+  // contraction is against the number of ranks (figures of both sides at the top of the file).  So the tiles sum if t_gemm is three
+  // times t_reduce or more (256-row tiles: three and a half); and, 256-row tiles, if it is half of it or less: memory is then the bound, and
+  // a tile's sum reads one copy less of it.
+  const bool third_round = ntiles > 2 * units - x && ntiles <= 2 * units;
+  const bool memory_bound = T::BM == 256 && t_reduce >= 2 * t_gemm && ntiles > 2 * units - units / 4;
+  p.own_sums = !two_shot && p.n <= kOwnSumColumns && (ntiles <= units || (third_round && (t_gemm >= (T::BM == 256 ? 3.5 : 3.0) * t_reduce || memory_bound)));
+  p.early = !p.own_sums && ntiles > units ? x : 0;
   p.late = p.own_sums ? 0 : std::min(units, ntiles);
   const unsigned grid = (unsigned)(p.num_producers + ntiles + p.early + p.late);
   auto launch = [&](auto instance) {

@@ -337,7 +337,7 @@ def test_all_reduce_consumer_by_rank_count(B, world, rows, n, k):
 
 
 # Sums by the tiles' own work-groups: one vector per lane and less, two, four and eight of them, the last batch partly empty, a
-# last tile of one vector; two whole rounds of tiles (512 of them), and the queue on both sides of that (272, 549)
+# last tile of one vector; the queue with 512 tiles, with 272 and with 549
 @pytest.mark.parametrize("world,m,n,d", [
     (2, 2, 8, 1), (3, 3, 136, 0), (8, 16, 264, 7), (8, 32, 128, 0), (4, 64, 392, 2), (5, 100, 256, 4), (8, 128, 1024, 5),
     (2, 1024, 8192, 0), (2, 2000, 2056, 1), (2, 1056, 7808, 1),
@@ -355,6 +355,35 @@ def test_all_reduce_sums_bit_exact(B, world, m, n, d):
         ar.out.fill_(0x7FC0)
         _ok(B, ar(a_dev, b_dev, peers, d, flags=flags), ar)
         assert np.array_equal(bits(ar.gemm_out), parts[d]) and np.array_equal(bits(ar.out), full)
+
+
+# Two rounds of tiles, both sides of each line of the choice between the tiles' own sums and consumers.  2 ranks, K 1200 (t_gemm = 3.02
+# t_reduce, X = 64): 448 tiles leave room for the consumers, 456 do not, 513 are three rounds; K 1184 (2.98) is too short.  256-row tiles:
+# K 1400 (3.52, X = 56) and 1384; 8 ranks, K 72 (memory-bound), 448 and 464 tiles
+@pytest.mark.parametrize("world,m,n,k,block_m,own", [
+    (2, 1024, 7168, 1200, 128, False), (2, 1024, 7176, 1200, 128, True), (2, 1032, 7296, 1200, 128, False), (2, 1024, 7176, 1184, 128, False),
+    (2, 264, 59272, 1400, 256, True), (2, 264, 59272, 1384, 256, False),
+    (8, 264, 57344, 72, 256, False), (8, 264, 59272, 72, 256, True),
+])
+def test_all_reduce_two_rounds(B, world, m, n, k, block_m, own):
+    g = torch.Generator(device="cuda").manual_seed(n + k)
+    d = world - 1
+    # products and sums of small integers are exact in fp32; every rank's partial is rounded once, and so is their sum in rank order
+    a = torch.randint(-3, 4, (m, k), device="cuda", generator=g).to(torch.bfloat16)
+    b = torch.randint(-1, 2, (n, k), device="cuda", generator=g).to(torch.bfloat16)
+    parts = [torch.randint(-200, 201, (m, n), device="cuda", generator=g).to(torch.bfloat16) for _ in range(world)]
+    parts[d] = (a.float() @ b.float().t()).to(torch.bfloat16)
+    want = parts[0].float()
+    for part in parts[1:]:
+        want = want + part.float()
+    run = GemmArRun(B, world, m, n, k)
+    assert run.tc["block_m"] == block_m
+    sched = torch.full((4 * run.ntiles,), -1, dtype=torch.int32, device="cuda")
+    peers = [None if s == d else parts[s].view(torch.int16) for s in range(world)]
+    _ok(B, run(a.view(torch.int16), b.view(torch.int16), peers, d, schedule=sched), run)
+    assert torch.equal(run.gemm_out.view(torch.bfloat16), parts[d]) and torch.equal(run.out.view(torch.bfloat16), want.to(torch.bfloat16))
+    # consumers sit behind the first round of tiles; without them the tiles are numbered through
+    assert (sched.view(-1, 4)[:, 2].cpu().tolist() == list(range(run.ntiles))) == own
 
 
 # Rows 16 KiB apart (the tile engine) and 8 KiB (the decode kernel): the chiplets begin the contraction in eight places.  132 tiles
