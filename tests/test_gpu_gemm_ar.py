@@ -229,3 +229,76 @@ def test_flags_preset_waits_for_own_tiles_only(B):
     flags = run.signals.cpu().numpy()[2 * world:2 * world + world * run.ntiles].reshape(world, run.ntiles)
     for s in range(world):
         assert flags[s].tolist() == [run.epoch if s == d else 0] * run.ntiles
+
+
+# More tiles than units and a short contraction: consumers sum (the last tile row and column ragged).  Every number of ranks that
+# has a loop of its own, and the loop over any number of them
+@pytest.mark.parametrize("world,m,n,kn", [(2, 1000, 4360, True), (3, 999, 4360, False), (4, 1000, 4360, False), (5, 1000, 5512, False), (8, 1000, 4360, True)])
+def test_one_shot_consumers(B, world, m, n, kn):
+    cfg = synth.CONFIGS[3].scaled(world=world, m_per_rank=m // world, n=n, k=72)
+    a_list, b_list = synth.gemm_rs_inputs(cfg, integer=True)
+    parts = [oar.partial_bits(a, b) for a, b in zip(a_list, b_list)]
+    full = oar.allreduce_partials_f32_ordered(parts)
+    d = world // 2
+    peers = [None if s == d else to_dev(parts[s]) for s in range(world)]
+    a_dev, b_dev = to_dev(a_list[d]), to_dev(b_list[d] if kn else nk(b_list[d]))
+    run = GemmArRun(B, world, cfg.m, n, 72)
+    assert 256 < run.ntiles < 512
+    for flags in (None, B.FLAGS_PRESET):
+        run.out.fill_(0x7FC0)
+        sched = torch.full((4 * run.ntiles,), -1, dtype=torch.int32, device="cuda")
+        _ok(B, run(a_dev, b_dev, peers, d, flags=flags, schedule=sched, b_layout=B.B_KN if kn else B.B_NK), run)
+        assert np.array_equal(bits(run.gemm_out), parts[d]) and np.array_equal(bits(run.out), full)
+        rec = sched.cpu().numpy().reshape(-1, 4)
+        _check_schedule(run, cfg, rec)
+        assert rec[-1, 2] > run.ntiles                                   # consumers between the tiles
+        assert run.signals[:2 * world].tolist() == [0] * (2 * world)     # their queue is back at zero
+
+
+def test_one_shot_consumers_external_producer_and_timeout(B):
+    """What test_external_producer_and_timeout looks at, with consumers: 272 tiles."""
+    world, m, n, k, d = 4, 2048, 2056, 72, 1
+    cfg = synth.CONFIGS[3].scaled(world=world, m_per_rank=m // world, n=n, k=k)
+    a_list, b_list = synth.gemm_rs_inputs(cfg, integer=True)
+    parts = [oar.partial_bits(a, b) for a, b in zip(a_list, b_list)]
+    want = oar.allreduce_partials_f32_ordered(parts)
+    run = GemmArRun(B, world, m, n, k)
+    bm, npn, nt = run.tc["block_m"], run.npn, run.ntiles
+    assert (bm, npn, nt) == (128, 17, 272)
+    src = [to_dev(p) for p in parts]
+    a_dev, b_dev = to_dev(a_list[d]), to_dev(nk(b_list[d]))
+    # the last, the first and a middle tile row of one peer each arrive late, from one publisher, 20 us per tile; everything else is in place
+    late = [(0, 15), (2, 0), (3, 7)]
+    landing = [t.clone() for t in src]
+    flags = run.signals[2 * world:2 * world + world * nt].view(world, nt)
+    flags.fill_(run.epoch + 1)
+    flags[d].zero_()
+    dst, srcs, nbytes, fidx = [], [], [], []
+    for s, pm in late:
+        rows = slice(pm * bm, (pm + 1) * bm)
+        landing[s][rows] = 0x7FC0
+        flags[s, pm * npn:(pm + 1) * npn] = 0
+        for pn in range(npn):                     # the row's other tiles ride on the first one's copy
+            dst.append(landing[s][rows] if pn == 0 else None)
+            srcs.append(src[s][rows] if pn == 0 else None)
+            nbytes.append(bm * n * 2 if pn == 0 else 0)
+            fidx.append(run.flag_index(s, pm, pn))
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    assert B.publish_chunks(dst, srcs, nbytes, fidx, run.signals, run.epoch + 1, delay_cycles=2000, stream=side) == B.OK
+    polls = 0
+    while polls < 10000 and run.signals[fidx[0]].item() != run.epoch + 1:   # the publisher has its place before the call fills the chip
+        polls += 1
+    peers = [None if s == d else landing[s] for s in range(world)]
+    _ok(B, run(a_dev, b_dev, peers, d, flags=B.EXTERNAL_PRODUCER), run)
+    assert np.array_equal(bits(run.out), want)
+    assert run.signals[:2].tolist() == [0, 0]
+    # nobody raises the peers' flags: every wait gives up, and the queue counters are left at zero
+    assert run(a_dev, b_dev, peers, d, flags=B.EXTERNAL_PRODUCER, tuning=B.tuning(spin_limit=64)) == B.OK
+    torch.cuda.synchronize()
+    st = run.status.cpu().tolist()
+    assert st[0] == B.ERR_TIMEOUT and 0 <= st[1] < nt
+    assert run.signals[:2].tolist() == [0, 0]
+    run.status.zero_()
+    _ok(B, run(a_dev, b_dev, peers, d), run)
+    assert np.array_equal(bits(run.out), want)
