@@ -450,6 +450,8 @@ __global__ __launch_bounds__(NST > 0 ? 2 * T::THREADS : T::THREADS) void moe_gro
         return;
       }
     } else {
+      // (both loops in one kernel, unlike ag_gemm_kernel: the plain one takes the same time with the other one beside it, 8192 tokens, hidden
+      // 4096, 8 of 64 experts 86.8, 86.9 us; 1024 tokens, 32 experts 65.3, 65.4; 256 tokens, hidden 7168, 8 experts 77.2, 77.3)
       constexpr bool kRotates = T::X16 && T::BM == 128;
       if (kRotates && rows_share_channels(p.hidden)) gemm_mainloop<T, kRotates>(acc, p.workspace, a_row, wj, b_row, p.hidden, lds, chiplet_k_tile(p.hidden));
       else gemm_mainloop<T>(acc, p.workspace, a_row, wj, b_row, p.hidden, lds);

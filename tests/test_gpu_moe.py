@@ -100,6 +100,21 @@ def test_moe_table_shapes_tensor_parallel_placement(B, hidden, inter, experts, t
     _run_and_check(B, cfg, xs, ids, w, 8 * 128 * top_k, integer=False)
 
 
+# Rows a multiple of 16 KiB apart: the chiplets begin the contraction of a 128 x 128 tile in eight places.  Two row tiles per
+# expert, the second ragged, and one; a ragged last column block; more experts than the scalar walk takes (17).  Exact: any order of the sum gives the same bits
+@pytest.mark.parametrize("world,t_r,hidden,inter,experts,top_k,local,rank", [
+    (4, 100, 8192, 264, 4, 2, 2, 1),
+    (2, 68, 16384, 136, 17, 17, 17, 0),
+    (2, 40, 8192, 1000, 3, 1, 3, 1),
+])
+def test_moe_contractions_begun_in_eight_places(B, world, t_r, hidden, inter, experts, top_k, local, rank):
+    cfg = synth.CONFIGS[4].scaled(world=world, tokens_per_rank=t_r, k=hidden, n=inter, num_experts=experts,
+                                  top_k=top_k, num_local_experts=local, rank=rank)
+    assert B.moe_tile_choice(world * t_r, top_k, experts, local, inter)[1:] == (128, 128)
+    xs, ids, w = synth.moe_inputs(cfg, integer=True)
+    _run_and_check(B, cfg, xs, ids, w, world * t_r * top_k, integer=True)
+
+
 def test_moe_large_experts_use_the_256_row_tile(B):
     """2048 rows per expert (the Mixtral-8x22B shape at half its tokens): the schedule is cut in 256-row tiles."""
     cfg = synth.CONFIGS[4].scaled(world=8, tokens_per_rank=512, k=2048, n=776, num_experts=8, top_k=2,

@@ -172,6 +172,15 @@ def test_moe_rs_weights_kn_by_contraction(B, inter_r, hidden):
     _run(B, ids, hs, ws, e0s, 3, world, t_r, inter_r, hidden, experts, top_k, experts, 2, None, True, kn=True)
 
 
+def test_moe_rs_contraction_begun_in_eight_places(B):
+    """Rows 16 KiB apart, 128 x 128 tiles of [n, k] weights: the grouped GEMM's rows are exact in any order of the sum."""
+    world, t_r, inter_r, hidden, experts, top_k = 2, 150, 8192, 264, 2, 1
+    ids, hs, ws, e0s = _case(world, t_r, inter_r, hidden, experts, top_k, experts, seed=8, integer=True)
+    assert B.moe_tile_choice(world * t_r, top_k, experts, experts, hidden)[1:] == (128, 128)
+    gate = np.ones(ids.shape, dtype=np.float32)   # (with a gate the whole is compared within the tolerance: partials beyond 256 are rounded)
+    _run(B, ids, hs, ws, e0s, 1, world, t_r, inter_r, hidden, experts, top_k, experts, 1, gate, True)
+
+
 def test_moe_rs_large_experts_and_row_overflow(B):
     # 2048 rows per expert: the 256-row tile
     world, t_r, inter_r, hidden, experts, top_k = 8, 512, 128, 264, 4, 2
