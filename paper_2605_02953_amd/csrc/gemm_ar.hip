@@ -48,6 +48,7 @@
 // slower than with one work-group per tile, which the dispatcher also load-balances).
 #include "gemm_core.h"
 #include "launch.h"
+#include "reduce.h"
 
 namespace ditron {
 
@@ -85,31 +86,6 @@ __device__ __forceinline__ void ar_tile_at(const GemmArParams& p, int position, 
   grouped_order(id, p.npm, p.npn, p.group_m, pid_m, pid_n);
 }
 
-__device__ __forceinline__ void ar_set(float (&acc)[8], const u32x4_t v) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    acc[2 * j] = __builtin_bit_cast(float, v[j] << 16);
-    acc[2 * j + 1] = __builtin_bit_cast(float, v[j] & 0xFFFF0000u);
-  }
-}
-__device__ __forceinline__ void ar_add(float (&acc)[8], const u32x4_t v) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    acc[2 * j] += __builtin_bit_cast(float, v[j] << 16);
-    acc[2 * j + 1] += __builtin_bit_cast(float, v[j] & 0xFFFF0000u);
-  }
-}
-__device__ __forceinline__ u32x4_t ar_pack(const float (&acc)[8]) {
-  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-  u32x4_t r;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    bf16x2_t v = {(__bf16)acc[2 * j], (__bf16)acc[2 * j + 1]};
-    r[j] = __builtin_bit_cast(uint32_t, v);
-  }
-  return r;
-}
-
 // Sum of the `world` published copies of one output tile.  U vectors of 16 bytes per lane and
 // rank are in flight at once (a single work-group owns its compute unit, so the loads in
 // flight per lane are what fills the memory pipe).
@@ -137,8 +113,8 @@ __device__ __forceinline__ void ar_reduce_tile(const GemmArParams& p, int m0, in
 #pragma unroll
           for (int s = 0; s < WORLD; ++s) x[u][s] = __builtin_nontemporal_load((const u32x4_t*)p.part[s] + off[u]);
         } else {
-          ar_set(acc[u], __builtin_nontemporal_load((const u32x4_t*)p.part[0] + off[u]));
-          for (int s = 1; s < world; ++s) ar_add(acc[u], __builtin_nontemporal_load((const u32x4_t*)p.part[s] + off[u]));
+          set_bf16x8(acc[u], __builtin_nontemporal_load((const u32x4_t*)p.part[0] + off[u]));
+          for (int s = 1; s < world; ++s) add_bf16x8(acc[u], __builtin_nontemporal_load((const u32x4_t*)p.part[s] + off[u]));
         }
       }
     }
@@ -147,11 +123,11 @@ __device__ __forceinline__ void ar_reduce_tile(const GemmArParams& p, int m0, in
       const int v = v0 + u * T::THREADS;
       if (v < nvec) {
         if constexpr (WORLD > 0) {
-          ar_set(acc[u], x[u][0]);
+          set_bf16x8(acc[u], x[u][0]);
 #pragma unroll
-          for (int s = 1; s < WORLD; ++s) ar_add(acc[u], x[u][s]);
+          for (int s = 1; s < WORLD; ++s) add_bf16x8(acc[u], x[u][s]);
         }
-        const u32x4_t r = ar_pack(acc[u]);
+        const u32x4_t r = pack_bf16x8(acc[u]);
         if constexpr (TWO) {   // the broadcast: the reduced tile goes to every rank's output
           for (int d = 0; d < world; ++d) __builtin_nontemporal_store(r, (u32x4_t*)p.out_dst[d] + off[u]);
         } else {
@@ -204,9 +180,9 @@ __device__ __forceinline__ void ar_sum_parked(const GemmArParams& p, int m0, int
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const u32x4_t mine = *(const u32x4_t*)own[u];
-        ar_set(acc[u], p.rank == 0 ? mine : x[0][u]);
+        set_bf16x8(acc[u], p.rank == 0 ? mine : x[0][u]);
 #pragma unroll
-        for (int s = 1; s < WORLD; ++s) ar_add(acc[u], s == p.rank ? mine : x[s][u]);
+        for (int s = 1; s < WORLD; ++s) add_bf16x8(acc[u], s == p.rank ? mine : x[s][u]);
       }
     } else {
       for (int s = 0; s < world; ++s) {
@@ -216,13 +192,13 @@ __device__ __forceinline__ void ar_sum_parked(const GemmArParams& p, int m0, int
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const u32x4_t term = s == p.rank ? *(const u32x4_t*)own[u] : x[0][u];
-          if (s == 0) ar_set(acc[u], term);
-          else ar_add(acc[u], term);
+          if (s == 0) set_bf16x8(acc[u], term);
+          else add_bf16x8(acc[u], term);
         }
       }
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) __builtin_amdgcn_raw_buffer_store_b128(ar_pack(acc[u]), out, (int)off[u], 0, kStreaming);
+    for (int u = 0; u < U; ++u) __builtin_amdgcn_raw_buffer_store_b128(pack_bf16x8(acc[u]), out, (int)off[u], 0, kStreaming);
   }
 }
 

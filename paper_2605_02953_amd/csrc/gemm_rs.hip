@@ -172,9 +172,7 @@ static ditron_status_t launch_reduce(ReduceParams& p, bool flags_pending, hipStr
   // enough work-groups to cover the chip several times over, at least one per row chunk
   const size_t per_wg = (size_t)kReduceThreads * kReduceUnroll;
   size_t want = (p.vec_per_chunk + per_wg - 1) / per_wg;
-  bool gated = false;
-  for (int s = 0; s < p.world; ++s) gated = gated || p.gate[s] != nullptr;
-  const int max_wgs = (gated && flags_pending) ? 256 : kReduceMaxWgs;
+  const int max_wgs = flags_pending ? 256 : kReduceMaxWgs;
   const size_t cap = (size_t)(max_wgs / p.chunks > 0 ? max_wgs / p.chunks : 1);
   if (want > cap) want = cap;
   if (want < 1) want = 1;

@@ -716,7 +716,7 @@ __global__ __launch_bounds__(kCombineThreads) void moe_combine_kernel(const MoeC
     if (r.row < 0 || r.row >= rows) r.row = -1;
     r.owner = r.row >= 0 ? p.gather_idx[r.row] : -1;
   };
-  // through: the rows are written past the caches (sc0 sc1), so that whoever is told of them needs no write-back
+  // through: the rows are written through (see stores_done), so that whoever is told of them needs no write-back
   auto run = [&](int first, int end, auto through) {
     TokenRows now = look_up(first, 0), next = look_up(first + stride, 0);
     check(now);
@@ -772,7 +772,7 @@ __global__ __launch_bounds__(kCombineThreads) void moe_combine_kernel(const MoeC
         const int c = (block * U + u) * 64 + lane;
         if constexpr (decltype(through)::value) {
           const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc((void*)(p.combined + (size_t)t * p.hidden), 0, p.hidden * 2, 0x00020000);
-          __builtin_amdgcn_raw_buffer_store_b128(pack_bf16x8(acc[u]), out, c * 16, 0, 17);   // past the row nothing is written
+          __builtin_amdgcn_raw_buffer_store_b128(pack_bf16x8(acc[u]), out, c * 16, 0, kThrough);   // past the row nothing is written
         } else {
           if (c < vpr) *((u32x4_t*)(p.combined + (size_t)t * p.hidden) + c) = pack_bf16x8(acc[u]);
         }
@@ -786,13 +786,13 @@ __global__ __launch_bounds__(kCombineThreads) void moe_combine_kernel(const MoeC
   const int own_wgs = min(p.combine_wgs, cdiv(own, kCombineThreads / 64));
   if ((int)blockIdx.x < own_wgs) {
     run(first, own, std::true_type{});
-    wait_vmcnt0();   // the wave's stores have reached memory
+    stores_done();
     __syncthreads();
     if (threadIdx.x == 0) {
       const int old = __hip_atomic_fetch_add(p.done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (old == own_wgs - 1) {
         __hip_atomic_store(p.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (int c = 0; c < p.chunks; ++c) __hip_atomic_store(p.own_flags + c, p.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int c = 0; c < p.chunks; ++c) flag_raise_stored(p.own_flags + c, p.epoch);
       }
     }
   }
