@@ -119,10 +119,10 @@ struct ReduceParams {
 };
 
 constexpr int kReduceThreads = 1024;
-constexpr int kReduceUnroll = 1;     // 16-byte vectors per lane per slot in flight
 constexpr int kReduceMaxWgs = 1024;
 
-// WORLD > 0 fixes the number of slots at compile time (fully unrolled slot loop).
+// WORLD > 0 fixes the number of slots at compile time: a vector of every slot is in flight per lane before the first is added.  (One after
+// another, as the compiler places loads that stand between the additions: GEMM-ReduceScatter 128 x 8192, K 3584, 8 ranks 23.5 -> 24.6 us.)
 template <int WORLD>
 __global__ __launch_bounds__(kReduceThreads) void reduce_slots_kernel(const ReduceParams p) {
   const int chunk = blockIdx.x / p.wgs_per_chunk;
@@ -135,34 +135,20 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_slots_kernel(const Redu
   const size_t base = (size_t)chunk * p.vec_per_chunk;
   const size_t step = (size_t)p.wgs_per_chunk * kReduceThreads;
   u32x4_t* out = (u32x4_t*)p.out + base;
-  size_t i = (size_t)part * kReduceThreads + threadIdx.x;
-  for (; i + (kReduceUnroll - 1) * step < p.vec_per_chunk; i += kReduceUnroll * step) {
-    float acc[kReduceUnroll][8];
-    {
-      u32x4_t v[kReduceUnroll];
-#pragma unroll
-      for (int u = 0; u < kReduceUnroll; ++u)
-        v[u] = __builtin_nontemporal_load((const u32x4_t*)p.slot[0] + base + i + u * step);
-#pragma unroll
-      for (int u = 0; u < kReduceUnroll; ++u) set_bf16x8(acc[u], v[u]);
-    }
-#pragma unroll
-    for (int s = 1; s < world; ++s) {
-      u32x4_t v[kReduceUnroll];
-#pragma unroll
-      for (int u = 0; u < kReduceUnroll; ++u)
-        v[u] = __builtin_nontemporal_load((const u32x4_t*)p.slot[s] + base + i + u * step);
-#pragma unroll
-      for (int u = 0; u < kReduceUnroll; ++u) add_bf16x8(acc[u], v[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < kReduceUnroll; ++u) __builtin_nontemporal_store(pack_bf16x8(acc[u]), out + i + u * step);
-  }
-  for (; i < p.vec_per_chunk; i += step) {
+  for (size_t i = (size_t)part * kReduceThreads + threadIdx.x; i < p.vec_per_chunk; i += step) {
     float acc[8];
-    set_bf16x8(acc, ((const u32x4_t*)p.slot[0])[base + i]);
-    for (int s = 1; s < world; ++s) add_bf16x8(acc, ((const u32x4_t*)p.slot[s])[base + i]);
-    out[i] = pack_bf16x8(acc);
+    if constexpr (WORLD > 0) {
+      u32x4_t v[WORLD];
+#pragma unroll
+      for (int s = 0; s < WORLD; ++s) v[s] = __builtin_nontemporal_load((const u32x4_t*)p.slot[s] + base + i);
+      set_bf16x8(acc, v[0]);
+#pragma unroll
+      for (int s = 1; s < WORLD; ++s) add_bf16x8(acc, v[s]);
+    } else {
+      set_bf16x8(acc, __builtin_nontemporal_load((const u32x4_t*)p.slot[0] + base + i));
+      for (int s = 1; s < world; ++s) add_bf16x8(acc, __builtin_nontemporal_load((const u32x4_t*)p.slot[s] + base + i));
+    }
+    __builtin_nontemporal_store(pack_bf16x8(acc), out + i);
   }
 }
 
@@ -170,8 +156,7 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_slots_kernel(const Redu
 // that needs room on the chip to run); the waiting work-groups are then kept to half the chip.
 static ditron_status_t launch_reduce(ReduceParams& p, bool flags_pending, hipStream_t stream) {
   // enough work-groups to cover the chip several times over, at least one per row chunk
-  const size_t per_wg = (size_t)kReduceThreads * kReduceUnroll;
-  size_t want = (p.vec_per_chunk + per_wg - 1) / per_wg;
+  size_t want = (p.vec_per_chunk + kReduceThreads - 1) / kReduceThreads;
   const int max_wgs = flags_pending ? 256 : kReduceMaxWgs;
   const size_t cap = (size_t)(max_wgs / p.chunks > 0 ? max_wgs / p.chunks : 1);
   if (want > cap) want = cap;
