@@ -121,9 +121,12 @@ struct ReduceParams {
 constexpr int kReduceThreads = 1024;
 constexpr int kReduceMaxWgs = 1024;
 
-// WORLD > 0 fixes the number of slots at compile time: a vector of every slot is in flight per lane before the first is added.  (One after
-// another, as the compiler places loads that stand between the additions: GEMM-ReduceScatter 128 x 8192, K 3584, 8 ranks 23.5 -> 24.6 us.)
-template <int WORLD>
+// WORLD > 0 fixes the number of slots at compile time.  TOGETHER: a lane has a vector of every slot in flight before the first is added;
+// otherwise one after another, and the other waves of the unit cover the wait: the chip's loads then walk the slots roughly in step, which
+// the memory likes better.  us one after another and together, buffers not in the caches, 8 slots of 0.26 MB 6.9, 5.1; 2.1 MB 7.5, 6.1; 4.2 MB
+// (256 work-groups) 8.8, 8.2; 6.3 MB 11.3, 11.3; 8.4 MB 13.1, 14.0; 16.8 MB 24.5, 26.9; 134 MB 198, 228; 4 slots of 4.2 MB 6.3, 6.0; 8.4 MB 8.2, 8.7;
+// 134 MB 107, 118; 2 slots of 4.2 MB 5.1, 4.7; 134 MB 64.5, 67.3.
+template <int WORLD, bool TOGETHER>
 __global__ __launch_bounds__(kReduceThreads) void reduce_slots_kernel(const ReduceParams p) {
   const int chunk = blockIdx.x / p.wgs_per_chunk;
   const int part = blockIdx.x % p.wgs_per_chunk;
@@ -137,7 +140,7 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_slots_kernel(const Redu
   u32x4_t* out = (u32x4_t*)p.out + base;
   for (size_t i = (size_t)part * kReduceThreads + threadIdx.x; i < p.vec_per_chunk; i += step) {
     float acc[8];
-    if constexpr (WORLD > 0) {
+    if constexpr (WORLD > 0 && TOGETHER) {
       u32x4_t v[WORLD];
 #pragma unroll
       for (int s = 0; s < WORLD; ++s) v[s] = __builtin_nontemporal_load((const u32x4_t*)p.slot[s] + base + i);
@@ -146,7 +149,11 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_slots_kernel(const Redu
       for (int s = 1; s < WORLD; ++s) add_bf16x8(acc, v[s]);
     } else {
       set_bf16x8(acc, __builtin_nontemporal_load((const u32x4_t*)p.slot[0] + base + i));
-      for (int s = 1; s < world; ++s) add_bf16x8(acc, __builtin_nontemporal_load((const u32x4_t*)p.slot[s] + base + i));
+#pragma unroll
+      for (int s = 1; s < world; ++s) {
+        __builtin_amdgcn_sched_barrier(0);   // (the compiler would put the loads together where it sees all of them)
+        add_bf16x8(acc, __builtin_nontemporal_load((const u32x4_t*)p.slot[s] + base + i));
+      }
     }
     __builtin_nontemporal_store(pack_bf16x8(acc), out + i);
   }
@@ -163,10 +170,19 @@ static ditron_status_t launch_reduce(ReduceParams& p, bool flags_pending, hipStr
   if (want < 1) want = 1;
   p.wgs_per_chunk = (int)want;
   const dim3 grid((unsigned)(p.wgs_per_chunk * p.chunks));
-  if (p.world == 8) hipLaunchKernelGGL(reduce_slots_kernel<8>, grid, dim3(kReduceThreads), 0, stream, p);
-  else if (p.world == 4) hipLaunchKernelGGL(reduce_slots_kernel<4>, grid, dim3(kReduceThreads), 0, stream, p);
-  else if (p.world == 2) hipLaunchKernelGGL(reduce_slots_kernel<2>, grid, dim3(kReduceThreads), 0, stream, p);
-  else hipLaunchKernelGGL(reduce_slots_kernel<0>, grid, dim3(kReduceThreads), 0, stream, p);
+  // up to a work-group per unit: 16 waves a unit are too few to cover a load of each slot in turn
+  const bool together = grid.x <= 256;
+  auto launch = [&](auto world) {
+    constexpr int W = decltype(world)::value;
+    if (together) hipLaunchKernelGGL((reduce_slots_kernel<W, true>), grid, dim3(kReduceThreads), 0, stream, p);
+    else hipLaunchKernelGGL((reduce_slots_kernel<W, false>), grid, dim3(kReduceThreads), 0, stream, p);
+  };
+  switch (p.world) {
+    case 8: launch(std::integral_constant<int, 8>{}); break;
+    case 4: launch(std::integral_constant<int, 4>{}); break;
+    case 2: launch(std::integral_constant<int, 2>{}); break;
+    default: hipLaunchKernelGGL((reduce_slots_kernel<0, false>), grid, dim3(kReduceThreads), 0, stream, p); break;
+  }
   return hipGetLastError() == hipSuccess ? DITRON_OK : DITRON_ERR_HIP;
 }
 

@@ -277,3 +277,21 @@ def test_rows_beyond_32_bit_offsets(B):
         want = (a[lo:lo + 32].float() @ b.float().t()).to(torch.bfloat16).view(torch.int16)
         assert torch.equal(run.gemm_out[lo:lo + 32], want)
         assert torch.equal(run.out[lo:lo + 32], want)
+
+
+# Up to 256 work-groups of 1024 vectors the loads of all slots go out together, beyond that one after another: the largest of the one,
+# the smallest of the other, a ragged last round, and 3 ranks (the loop over any number of them)
+@pytest.mark.parametrize("world", [2, 3, 4, 8])
+@pytest.mark.parametrize("rows,n,chunks", [(1, 8, 1), (3, 2048 * 8 + 8, 3), (1, 256 * 1024 * 8, 1), (1, 256 * 1024 * 8 + 8, 1), (5, 1024 * 1024 * 8 + 24, 1)])
+def test_reduce_slots_forms(B, world, rows, n, chunks):
+    g = torch.Generator(device="cuda").manual_seed(n + world)
+    slots = [torch.randn((rows, n), device="cuda", generator=g).to(torch.bfloat16) for _ in range(world)]
+    out = torch.full((rows * n + 8,), 7, dtype=torch.int16, device="cuda")
+    status = torch.zeros(B.STATUS_WORDS, dtype=torch.int32, device="cuda")
+    assert B.reduce_slots([t.view(torch.int16) for t in slots], out, None, status, rows, n, world, chunks, 1) == B.OK
+    torch.cuda.synchronize()
+    want = slots[0].float()
+    for t in slots[1:]:
+        want = want + t.float()          # fp32, slot after slot
+    assert torch.equal(out[:rows * n].view(torch.bfloat16).view(rows, n), want.to(torch.bfloat16))
+    assert (out[rows * n:] == 7).all()
