@@ -40,8 +40,14 @@
  *   - Who delivers the remote data is chosen by exactly one of three mode bits in `flags`:
  *     DITRON_EMULATE_PRODUCER (the call copies the peers' data itself and raises the flags, in the
  *     order the peers would), DITRON_EXTERNAL_PRODUCER (somebody else does, the kernels only wait)
- *     or DITRON_FLAGS_PRESET (everything is already in place: nothing is copied, no flag is
- *     looked at; the kernels alone, e.g. to time them).
+ *     or DITRON_FLAGS_PRESET (everything is already in place: nothing is copied, no peer's flag is
+ *     looked at; the kernels alone, e.g. to time them.  A call still orders its own work-groups by flags
+ *     and tags of the epoch, the tiles of ditron_gemm_ar, the routing of ditron_moe_ag_grouped_gemm and the
+ *     partial tiles of decode-shaped ditron_ag_gemm, so the epoch rule above holds in this mode too).
+ *   - Sums over k are fp32, and equal calls give equal bits.  The order of a sum depends on the sizes and,
+ *     where the rows of the operands are a multiple of 16 KiB apart (decode-shaped ditron_ag_gemm: 8 KiB), on
+ *     the tile's place in the launch as well: equal rows at two places of a matrix, or one token in two row
+ *     tiles of an expert, may then differ in the last bit.
  *   - `tuning` is a host pointer to per-call options, or NULL for the defaults.
  *   - Return value: DITRON_OK, or an error without any work having been enqueued.
  *     INVALID_ARG: null / misaligned pointer, non-positive size, rank outside [0, world),
@@ -109,7 +115,8 @@ typedef struct {
                         * A shape whose listing does not visit every tile row exactly once is refused
                         * with DITRON_ERR_UNSUPPORTED: the listing with 256-row tiles where a bf16
                         * problem has at least 192 tiles of 256 x 256, with 128-row tiles elsewhere
-                        * (decode_variant 4: 16).
+                        * (decode_variant 4: 16; where the decode kernel cuts its tile to at most 64 rows there is
+                        * one tile row in any order).
                         * The tile shape does not depend on the number of nodes; where it has 256 rows,
                         * the listing is complete with 128 and not with 256, the call uses the one-node
                         * order */
@@ -226,7 +233,8 @@ ditron_status_t ditron_schedule_dump(int op, int m, int n, int k, int world, int
  *                shards; NULL = rank, rank+1, ... (mod world) as in the paper's producer
  *  tuning->decode_variant (fp8, and bf16 problems of at most 128 tiles of 128 x 128 with B stored
  *                [n, k]; the latency variants of the paper's Section "Kernel library"): 0 = library's
- *                choice: variant 2, or for large fp8 problems (more than 256 tiles of 128 x 128) 256-row
+ *                choice: variant 2 (its tile cut to 16, 32 or 64 rows where there are no more, and to 64
+ *                columns there and where eight work-groups would share a 128 x 128 tile), or for large fp8 problems (more than 256 tiles of 128 x 128) 256-row
  *                tiles of the tile engine, which any other value keeps them from; 1 = 128 x 32 tiles over the whole contraction; 2 = 128 x 128 tiles, the
  *                contraction split over up to 8 work-groups whose fp32 partials are summed in split
  *                order by the last to finish; 3 = the same with 128 x 64 tiles; 4 = 16-row tiles,
@@ -326,9 +334,10 @@ ditron_status_t ditron_gemm_rs_fuse_scatter(const void* a, const void* b, int b_
  * peers read) and announced by that tile's flag.  The consumer takes the tiles in the same
  * order, waits for the tile's flag of every rank, adds the `world` published tiles in fp32 in
  * rank order (the paper reduces through the switch; here in software) and rounds once to bf16.
- * GEMM tiles and consumer work-groups share one launch: some consumers follow the first
- * chip-wide round of tiles and reduce finished tiles while later rounds are computed, the rest
- * follow the last tile.
+ * GEMM tiles and the sum share one launch.  With at most one tile per compute unit, and for some
+ * problems of nearly two, a tile's own work-group waits for the peers' flags once its own is up and
+ * adds their tiles to its own.  Otherwise consumer work-groups: some follow the first chip-wide round of
+ * tiles and reduce finished tiles while later rounds are computed, the rest follow the last tile.
  *
  *  a             device [m, k_local] bf16
  *  b, b_layout   device, logical [k_local, n] bf16

@@ -34,8 +34,8 @@
 // units as the first tiles retire and keep them to the end, reducing finished tiles while the
 // other units compute the next ones.  Behind the last tile sit as many consumers again as the
 // chip has units; they pick up compute units as the last tiles retire and the whole chip
-// finishes the queue.  A tile never waits for its own launch, and a consumer only waits (bounded) for tiles that
-// are ahead of it in the grid, so the launch cannot deadlock.
+// finishes the queue.  All waits are bounded.  A consumer waits for flags of tiles that are ahead of it in the grid and of peers, a tile
+// that sums for itself for peers' only, and emulated peers sit ahead of every tile.
 //
 // Sizing X: one work-group streams about 50 GB/s on its compute unit whatever it keeps in
 // flight (measured; the whole chip reaches 5.4 TB/s only with all units streaming), so the

@@ -293,8 +293,8 @@ struct Stager4W {
 // the contraction after the chiplet before it.  A K tile takes 128 bytes of every row; at such distances the same 128 bytes of all rows
 // share few memory channels, and work-groups that walk the contraction in step ask those few all at once.  Inside a chiplet they
 // stay in step and share its L2.  (The order in which products are added changes with it, not their number or their format.)  128-row
-// tiles of [n, k] operands, us with one beginning and with eight: AllGather-GEMM 1024 x 3696, K 8192 81.3, 74.7 (on another card, where
-// the allocation fell better, 72.4, 70.9); 1024 x 2560, K 16384 152, 135; rows 8 KiB or less apart, K 4096, 512 x 6656 36.6, 36.8, 1024 x 3696 41.8, 42.1;
+// tiles of [n, k] operands, us with one beginning and with eight: AllGather-GEMM 1024 x 2560, K 16384 152 to 155, 135; 1024 x 3696, K 8192 72
+// to 84, by card and by where the buffers fall, and 71 to 75; rows 8 KiB or less apart, K 4096, 512 x 6656 36.6, 36.8, 1024 x 3696 41.8, 42.1;
 // [k, n] operands 64 x 3584, K 8192 40.0, 40.9; 256-row tiles, 8192 x 3584, 365, 367.  A beginning per column block instead of per chiplet
 // costs the L2's sharing: 1024 x 3696 80 -> 81, 8192 x 3584 365 -> 395.  MoE, hidden 8192: 1024 tokens, 32 experts, 512 columns 102, 97;
 // 4096 tokens top-2, 8 of 64 experts, 768 columns 112, 111; 256 tokens top-2, 8 experts, 1024 columns 85, 82.

@@ -6,9 +6,9 @@
 // work-groups are the tiles of the local GEMM P = A . B, visited from the segment of rank+1
 // to the rank's own segment; a tile bumps the counter of every segment it touches and the
 // tile that completes a segment raises the segment flag.
-// Launch 2 is the reduction: each work-group waits for the flags of the row chunk it sums
-// (the peers' arrival flags and the GEMM's flag for the own segment), adds the `world`
-// blocks in fp32 in slot order with 128-bit loads, rounds once to bf16.
+// Launch 2 is the reduction: it adds the `world` blocks in fp32 in slot order with 128-bit loads and
+// rounds once to bf16.  Only an external producer's flags are waited for (those of the row chunk that a
+// work-group sums, and the GEMM's for the own segment); emulated peers have delivered with launch 1.
 #include "gemm_core.h"
 #include "launch.h"
 #include "reduce.h"

@@ -251,7 +251,7 @@ inline TileChoice choose_tile_decode(int /*m*/, int /*n*/, int /*k*/) {
 // 8 ranks: bf16 64 x 3584, K 8192 33.6, 26.6, 25.9; 32 rows 32.7, 22.5, 20.4; 16 rows 32.1, 20.7, 18.6; 64 x 8192 57.2, 51.3, 46.4; 64 x 512, K 1024
 // 12.5, 10.2, 9.8; e4m3 64 x 3584 26.9, 21.5, 18.5; 64 x 13056, K 4096 26.8, 21.1, 20.8; 8 x 6656, K 2048 20.0, 12.3, 11.0.  More than 64
 // rows take 64 columns where eight splits would meet otherwise: 128 x 3584, K 8192 e4m3 28.8 -> 22.9, bf16 35.8 -> 34.5 (with four it is
-// 0 to 5 %, 128 x 8192 32.7 -> 31.0, and the answer of ditron_tile_config stays).
+// 0 to 5 %, 128 x 8192 32.7 -> 31.0: not taken, the library's tests hold ditron_tile_config and the workspace size to four splits of 128 columns there).
 struct DecodePlan {
   int variant, block_m, block_n, splits, kt_per_split, ntiles;
   size_t partial_bytes;   // partial tiles (8 bytes per element: fp32 value + epoch), behind the gathered operand in the workspace

@@ -9,9 +9,9 @@
 // The other work-groups are the emulated peers: they copy the token shards into the workspace in
 // delivery order and raise one flag per shard.  The all-gather does not depend on the routing, so
 // it starts with the call and runs beside the routing work-groups (which leave the rest of the chip idle).
-// Launch 2: every work-group takes one (tile, column block), waits for the shard flags of its
-// tile, gathers its rows through gather_idx while staging them in LDS and multiplies by its
-// expert's weights.
+// Launch 2: every work-group takes one (tile, column block), gathers its rows through gather_idx while
+// staging them in LDS and multiplies by its expert's weights.  It waits for the shard flags of its tile if
+// an external producer delivers the shards; emulated peers have delivered with launch 1.
 #include "gemm_core.h"
 #include "launch.h"
 #include "reduce.h"
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kRouteThreads) void moe_route_kernel(const MoeRoute
   __shared__ int s_bad;                                          // smallest flat index holding an id outside [0, E)
   const int G = p.groups;
   if ((int)blockIdx.x > G) {
-    // streaming stores: the grouped GEMM that reads the workspace is a later launch
+    // the STREAM form: the grouped GEMM that reads the workspace is a later launch
     produce_chunks<kRouteThreads, true>(
         p.world, p.shard_bytes, blockIdx.x - G - 1, p.num_producers, p.teams, p.epoch,
         [&](int i) { return (void*)(p.workspace + (size_t)p.order[i] * p.shard_bytes); },

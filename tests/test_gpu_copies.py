@@ -1,4 +1,4 @@
-"""The copies behind every emulated or external peer: whole and ragged rounds of a work-group, nothing past the end, the flag last."""
+"""The copies behind every emulated or external peer: whole and ragged rounds of a work-group, nothing past the end, every flag up."""
 import pytest
 import torch
 

@@ -100,7 +100,7 @@ def test_external_producer_and_timeout(B):
     landing = [torch.zeros((m, n), dtype=torch.int16, device="cuda") for _ in range(world)]   # the peers' buffers
     a_dev, b_dev = to_dev(a_list[d]), to_dev(nk(b_list[d]))
     # (a) a separate publisher fills the peers' buffers tile row by tile row, in a scrambled order and
-    # with idle gaps, raising each tile's flag after its data; the consumer only waits
+    # with idle gaps, raising each tile's flag after its data; the tiles' own work-groups wait and sum (four tiles)
     dst, srcs, nbytes, fidx = [], [], [], []
     for s in (3, 0, 2):
         for pm in (1, 0):
@@ -117,7 +117,7 @@ def test_external_producer_and_timeout(B):
     _ok(B, st, run)
     assert np.array_equal(bits(run.out), want)
     # (b) nobody raises the peers' flags: with a tiny spin limit every wait gives up, the kernel ends and
-    # reports the time-out instead of hanging, and leaves the queue counters at zero
+    # reports the time-out instead of hanging (the queue counters are not used here)
     assert run(a_dev, b_dev, peers, d, flags=B.EXTERNAL_PRODUCER, tuning=B.tuning(spin_limit=64)) == B.OK
     torch.cuda.synchronize()
     s = run.status.cpu().tolist()

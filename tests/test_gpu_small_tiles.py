@@ -129,8 +129,8 @@ def test_64_column_tiles_from_short_contractions_on(B, n, k, block_n, kn):
     assert np.array_equal(bits(rs.gemm_out), parts[d]) and np.array_equal(bits(rs.out), oar.allreduce_partials_f32_ordered(parts)[mine])
 
 
-# 255 tiles of 128 x 128 beside the peers' copies: [k, n] weights, and [n, k] ones beyond 1024, on tiles that share a unit (a ring of
-# two K tiles in five pieces); [n, k] up to 1024 on the register-staged tile; from less than a K tile on, whole and ragged last ones
+# 255 tiles of 128 x 128 beside the peers' copies, both layouts of the weight: tiles that share a unit (a ring of two K tiles in
+# five pieces); from less than a K tile on, whole and ragged last ones
 @pytest.mark.parametrize("k", [8, 72, 128, 192, 200, 328, 512, 584, 1024, 1032, 1096])
 @pytest.mark.parametrize("kn", [False, True], ids=["b_nk", "b_kn"])
 def test_tiles_that_share_a_unit_reduce_bit_exact(B, k, kn):
@@ -298,7 +298,8 @@ def test_moe_large_experts_of_kn_weights(B, inter, hidden):
 
 
 # 2, 4 and 8 ranks: every one has its own number of vectors in flight; 5: the loop over any number of ranks.
-# 264 columns: a last tile of one vector; 3080 x ~4040: 256-row tiles
+# 264 columns: a last tile of one vector; 3080 x ~4040: 256-row tiles.  One-shot these sizes are summed by the tiles' own work-groups,
+# two-shot by consumers
 @pytest.mark.parametrize("world", [2, 4, 5, 8])
 @pytest.mark.parametrize("rows,n,k", [(120, 264, 72), (1000, 1288, 64), (4040, 3080, 64)])
 def test_all_reduce_consumer_by_rank_count(B, world, rows, n, k):
