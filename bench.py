@@ -33,12 +33,12 @@ PEAK_HBM_GBS = 8000.0
 # profiler), so every entry says which build it was measured on; re-measure after changing the kernel.
 MEASURED_TRAFFIC = {
     # workload: (bytes read + bytes written, profile, kernels as of commit)
-    "cfg2": (873.0e6 + 193.0e6, "profiles/ag_gemm_kernel_cfg2.md", "6445342"),   # fused launch; GEMM-only launch 739.8e6 + 58.8e6; algorithmic 251.7e6 (+ 268.4e6 emulated gather)
-    "cfg3": (822.4e6 + 251.8e6, "profiles/gemm_rs_kernel_reduce_slots_kernel_cfg3.md", "6a80893"),   # gemm_rs_kernel fused; reduce_slots_kernel 134.3e6 + 16.8e6 = its algorithmic 151.0e6
-    "cfg4": (147.5e6 + 6.2e6, "profiles/moe_kernels_cfg4.md", "e21fbd9"),   # moe_grouped_gemm_kernel (algorithmic 123.2e6); the gather in the routing launch: 67.5e6 + 67.2e6
-    "gemm_ar": (1956.3e6 + 269.8e6, "profiles/gemm_ar_kernel_table_shape3.md", "6a80893"),   # fused launch: operand panels ~0.9e9 + eight partials 1.07e9 read; partial + output written
-    "moe_rs": (33.1e6 + 67.7e6 + 97.1e6 + 62.9e6 + 33.6e6 + 4.2e6 + 0.1e6, "profiles/moe_rs_kernels_table_shape.md", "04f4682"),   # grouped GEMM + combine (with the peers' copies) + reduction + preparation
-    "cfg5": (102.1e6 + 28.5e6, "profiles/ag_gemm_splitk_kernel_cfg5.md", "431892f"),   # ag_gemm_splitk_kernel (fp8) with emulated peers: B 67.1e6 + A + three quarters of the partial tiles out and back; algorithmic 70.3e6
+    "cfg2": (873.0e6 + 193.1e6, "profiles/ag_gemm_kernel_cfg2.md", "b2eba1d"),   # fused launch; GEMM-only launch 746.4e6 + 58.8e6; algorithmic 251.7e6 (+ 268.4e6 emulated gather)
+    "cfg3": (822.4e6 + 251.7e6, "profiles/gemm_rs_kernel_reduce_slots_kernel_cfg3.md", "b2eba1d"),   # gemm_rs_kernel fused; reduce_slots_kernel 134.3e6 + 16.8e6 = its algorithmic 151.0e6
+    "cfg4": (136.8e6 + 6.2e6, "profiles/moe_kernels_cfg4.md", "b2eba1d"),   # moe_grouped_gemm_kernel (algorithmic 123.2e6); the gather in the routing launch: 67.4e6 + 67.1e6
+    "gemm_ar": (1955.6e6 + 268.8e6, "profiles/gemm_ar_kernel_table_shape3.md", "b2eba1d"),   # fused launch: operand panels ~0.9e9 + eight partials 1.07e9 read; partial + output written
+    "moe_rs": (33.1e6 + 67.7e6 + 97.9e6 + 62.9e6 + 33.6e6 + 4.2e6, "profiles/moe_rs_kernels_table_shape.md", "b2eba1d"),   # grouped GEMM + combine (with the peers' copies) + reduction
+    "cfg5": (102.1e6 + 28.5e6, "profiles/ag_gemm_splitk_kernel_cfg5.md", "b2eba1d"),   # ag_gemm_splitk_kernel (fp8) with emulated peers: B 67.1e6 + A + three quarters of the partial tiles out and back; algorithmic 70.3e6
 }
 
 
@@ -344,7 +344,7 @@ def bench_gemm_rs(args):
         "flags_preset": {"ms": preset_ms, "us_quantiles": _quantiles_us(pe), "achieved": flops / (preset_ms * 1e-3) / 1e12,
                          "frac": flops / (preset_ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS,
                          "note": "same entry point, peer blocks resident and arrival flags preset: gemm_rs_kernel without "
-                                 "emulated-peer work-groups + the gated reduce_slots_kernel"},
+                                 "emulated-peer work-groups + reduce_slots_kernel"},
         "reduction": {"bound": "hbm", "achieved": red_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                       "frac": red_gbs / PEAK_HBM_GBS, "us": red_ms * 1e3, "bytes": red_bytes,
                       "note": "reduce_slots_kernel alone, 4 rotating buffer sets (604 MB) so the 256 MB cache cannot hold them"},
@@ -728,9 +728,9 @@ def bench_moe_rs(args):
                    "latency_us": ev_ms * 1e3, "latency_us_quantiles": quant, "tflops": flops / (ev_ms * 1e-3) / 1e12},
         "roofline": {"bound": "hbm", "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": gbs / PEAK_HBM_GBS, "traffic": _traffic("moe_rs"),
                      "traffic_source": _traffic_source("moe_rs"),
-                     "kernel": "moe_grouped_gemm_kernel + moe_combine_kernel (whole step between events)",
+                     "kernel": "moe_grouped_gemm_kernel + moe_combine_kernel + reduce_slots_kernel (whole step between events)",
                      "kernel_ms": ev_ms, "bytes": alg_bytes + peer_bytes,
-                     "note": "algorithmic bytes of the two launches plus the emulated peers' copies (read + write of 7 blocks)"},
+                     "note": "algorithmic bytes of the three launches plus the emulated peers' copies (read + write of 7 blocks)"},
         "flags_preset_us": preset,
     }
 
