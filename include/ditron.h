@@ -480,7 +480,9 @@ ditron_status_t ditron_moe_ag_grouped_gemm(const void* const* x_shards, const in
  *  out           device out [tokens_per_rank, hidden] bf16
  *  signals       device int32[ditron_signal_words(world, chunks_per_slot)], laid out as for ditron_gemm_rs:
  *                the arrival flag of (slot s, row chunk c) is word 2*world + s*chunks_per_slot + c; the
- *                own slot's flags are raised by the combine
+ *                own slot's flags are raised by the combine; where rows are narrow (hidden <= 512) or tokens few (fewer than
+ *                1024 rows of up to 1024 columns in all, wider rows counted in pieces) the emulated peers' too, all of them
+ *                together once it has delivered and summed their blocks
  *  If R exceeds max_rows: status[0] = DITRON_ERR_WORKSPACE, status[2] = R, and `out` is undefined.
  */
 ditron_status_t ditron_moe_grouped_gemm_rs(const void* h, const void* w, int w_layout, const float* topk_weights,

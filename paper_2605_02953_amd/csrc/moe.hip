@@ -651,7 +651,8 @@ struct MoeCombineParams {
   const int32_t* expert_offsets;
   const float* gate;           // [tokens * top_k] or null
   __bf16* combined;            // [tokens, hidden]
-  int tokens, tokens_per_rank, rank, top_k, hidden, num_local, max_rows, combine_wgs;
+  __bf16* out;                 // [tokens_per_rank, hidden] (moe_combine_sum_kernel)
+  int tokens, tokens_per_rank, rank, world, top_k, hidden, num_local, max_rows, combine_wgs;
   // own-slot flags and the emulated peers (work-groups behind the combine)
   int32_t* done;               // work-groups of the combine that have finished the rank's own rows
   int32_t* own_flags;          // [chunks]
@@ -673,6 +674,21 @@ constexpr int kCombineThreads = 512;
 struct TokenRows {
   int f, row, owner;
   float gate;
+  // assignments j0 .. j0 + 63 of token t (none if t < 0): first load and second load.  rows: how many there are
+  __device__ __forceinline__ static TokenRows look_up(const MoeCombineParams& p, int t, int j0) {
+    const int lane = threadIdx.x & 63;
+    TokenRows r{-1, -1, -1, 1.f};
+    if (t >= 0 && j0 + lane < p.top_k) {
+      r.f = t * p.top_k + j0 + lane;
+      r.row = p.inverse_idx[r.f];
+      if (p.gate) r.gate = p.gate[r.f];
+    }
+    return r;
+  }
+  __device__ __forceinline__ void check(const MoeCombineParams& p, int rows) {
+    if (row < 0 || row >= rows) row = -1;
+    owner = row >= 0 ? p.gather_idx[row] : -1;
+  }
 };
 
 // The combine and, behind it, the emulated peers; neither waits for anything.  (8192 tokens top-2 of 32 experts, 2048 columns, world
@@ -702,27 +718,14 @@ __global__ __launch_bounds__(kCombineThreads) void moe_combine_kernel(const MoeC
     const int t = p.rank * p.tokens_per_rank + item / blocks;
     return t >= p.tokens ? t - p.tokens : t;
   };
-  // assignments j0 .. j0 + 63 of a token: first load and second load
-  auto look_up = [&](int item, int j0) {
-    TokenRows r{-1, -1, -1, 1.f};
-    if (item < items && j0 + lane < p.top_k) {
-      r.f = token_of(item) * p.top_k + j0 + lane;
-      r.row = p.inverse_idx[r.f];
-      if (p.gate) r.gate = p.gate[r.f];
-    }
-    return r;
-  };
-  auto check = [&](TokenRows& r) {
-    if (r.row < 0 || r.row >= rows) r.row = -1;
-    r.owner = r.row >= 0 ? p.gather_idx[r.row] : -1;
-  };
+  auto look_up = [&](int item, int j0) { return TokenRows::look_up(p, item < items ? token_of(item) : -1, j0); };
   // through: the rows are written through (see stores_done), so that whoever is told of them needs no write-back
   auto run = [&](int first, int end, auto through) {
     TokenRows now = look_up(first, 0), next = look_up(first + stride, 0);
-    check(now);
+    now.check(p, rows);
     for (int item = first; item < end; item += stride) {
       TokenRows later = look_up(item + 2 * stride, 0);
-      check(next);
+      next.check(p, rows);
       const int t = token_of(item), block = item % blocks;
       float acc[U][8];
 #pragma unroll
@@ -732,7 +735,7 @@ __global__ __launch_bounds__(kCombineThreads) void moe_combine_kernel(const MoeC
       for (int j0 = 0; j0 < p.top_k; j0 += 64) {
         if (j0 > 0) {
           now = look_up(item, j0);
-          check(now);
+          now.check(p, rows);
         }
         if (now.owner != now.f) now.row = -1;
         if (block == 0 && now.f >= 0 && now.row < 0) p.inverse_idx[now.f] = -1;
@@ -797,6 +800,107 @@ __global__ __launch_bounds__(kCombineThreads) void moe_combine_kernel(const MoeC
     }
   }
   run(first + cdiv(max(own - first, 0), stride) * stride, items, std::false_type{});
+}
+
+// The same where a wave takes 64 vectors of a token (few tokens or narrow rows), with the rest of the call in it: the lane that has combined
+// a vector of the rank's own rows also delivers the peers' (unless they are resident) and adds the slots in their order.  A lane adds
+// what it holds itself: nothing is waited for, neither flags nor other work-groups, and the launch of the reduction falls away.  The
+// work-group that finishes own rows last raises the flags of the slots, for whoever waits on another stream.
+// Such calls are bound by launches and round trips to memory: the peers' vectors are asked for before the token's rows are known, and the code is
+// kept short (6.2 KB; with branches around loads 9 KB and 1 us more a call, with a second loop for the others' rows and the next item's vectors asked
+// for ahead 18 KB and 2 to 3 us more).  us with the reduction behind the combine and with this kernel, top-2: 8 ranks, 7 tokens each of 1408 columns
+// 14.1, 11.6; 16 of 3000 21.2, 19.7; 127 of 1024 19.0, 14.2; 1024 of 512 29.7, 23.4; 2 ranks, 33 of 2032 14.9, 12.3; 4096 of 512 36.0, 25.8;
+// 8 ranks, top-6, 7 of 1392 20.9, 15.8; 512 of 128 20.2, 16.3.
+__global__ __launch_bounds__(kCombineThreads) void moe_combine_sum_kernel(const MoeCombineParams p) {
+  constexpr int kSlots = 8;   // slots in flight
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int blocks = cdiv(p.hidden >> 3, 64);
+  const int total_rows = p.expert_offsets[p.num_local];
+  const int rows = total_rows > p.max_rows ? 0 : total_rows;   // too many: the grouped GEMM has reported it and written none
+  const int own = p.tokens_per_rank * blocks, items = p.tokens * blocks, stride = p.combine_wgs * (kCombineThreads / 64);
+  // one row of a block of rows, or nothing (no loads, no stores) where `exists` is false
+  auto row_of = [&](const void* base, bool exists, int row) {
+    return __builtin_amdgcn_make_buffer_rsrc((char*)base + (size_t)row * p.hidden * 2, 0, exists ? p.hidden * 2 : 0, 0x00020000);
+  };
+  for (int item = blockIdx.x * (kCombineThreads / 64) + wave; item < items; item += stride) {
+    const int r = item / blocks, block = item % blocks, vec = (block * 64 + lane) * 16;
+    const int t = p.rank * p.tokens_per_rank + r < p.tokens ? p.rank * p.tokens_per_rank + r : p.rank * p.tokens_per_rank + r - p.tokens;
+    const bool is_own = item < own;
+    TokenRows now = TokenRows::look_up(p, t, 0);
+    float sum[8];
+    u32x4_t mine;
+    for (int s0 = 0; s0 < (is_own ? p.world : 1); s0 += kSlots) {
+      u32x4_t x[kSlots];
+      if (is_own) {
+#pragma unroll
+        for (int b = 0; b < kSlots; ++b) {
+          const int s = min(s0 + b, p.world - 1);
+          const char* slot = p.peer[s] ? (const char*)p.peer[s] : p.scatter_buf + s * p.slot_bytes;
+          x[b] = __builtin_amdgcn_raw_buffer_load_b128(row_of(slot, s0 + b < p.world && s != p.rank, r), vec, 0, kStreaming);
+        }
+      }
+      if (s0 == 0) {
+        now.check(p, rows);
+        float acc[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc[q] = 0.f;
+        for (int j0 = 0; j0 < p.top_k; j0 += 64) {
+          if (j0 > 0) {
+            now = TokenRows::look_up(p, t, j0);
+            now.check(p, rows);
+          }
+          if (now.owner != now.f) now.row = -1;
+          if (block == 0 && now.f >= 0 && now.row < 0) p.inverse_idx[now.f] = -1;
+          const int n = min(64, p.top_k - j0);
+          for (int j = 0; j < n; j += kSlots) {
+            // as in moe_combine_kernel; the loads of rows that are not there are of an empty buffer
+            u32x4_t y[kSlots];
+#pragma unroll
+            for (int b = 0; b < kSlots; ++b) {
+              const int row = j + b < n ? __builtin_amdgcn_readlane(now.row, min(j + b, 63)) : -1;
+              y[b] = __builtin_amdgcn_raw_buffer_load_b128(row_of(p.y, row >= 0, max(row, 0)), vec, 0, kStreaming);
+            }
+#pragma unroll
+            for (int b = 0; b < kSlots; ++b) {
+              if (j + b >= n || __builtin_amdgcn_readlane(now.row, min(j + b, 63)) < 0) continue;
+              const float g = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, now.gate), min(j + b, 63)));
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                acc[2 * q] = __builtin_fmaf(g, __builtin_bit_cast(float, y[b][q] << 16), acc[2 * q]);
+                acc[2 * q + 1] = __builtin_fmaf(g, __builtin_bit_cast(float, y[b][q] & 0xFFFF0000u), acc[2 * q + 1]);
+              }
+            }
+          }
+        }
+        mine = pack_bf16x8(acc);
+        __builtin_amdgcn_raw_buffer_store_b128(mine, row_of(p.combined, true, t), vec, 0, kThrough);   // past the row nothing is written
+      }
+      if (is_own) {
+#pragma unroll
+        for (int b = 0; b < kSlots; ++b) {
+          const int s = s0 + b;
+          if (s < p.world) {
+            __builtin_amdgcn_raw_buffer_store_b128(x[b], row_of(p.scatter_buf + s * p.slot_bytes, p.peer[s] != nullptr, r), vec, 0, kThrough);
+            const u32x4_t term = s == p.rank ? mine : x[b];
+            if (s == 0) set_bf16x8(sum, term);
+            else add_bf16x8(sum, term);
+          }
+        }
+      }
+    }
+    if (is_own) __builtin_amdgcn_raw_buffer_store_b128(pack_bf16x8(sum), row_of(p.out, true, r), vec, 0, kStreaming);
+  }
+  const int own_wgs = min(p.combine_wgs, cdiv(own, kCombineThreads / 64));
+  if ((int)blockIdx.x >= own_wgs) return;
+  stores_done();
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  int old = 0;
+  if (lane == 0) old = __hip_atomic_fetch_add(p.done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (__builtin_amdgcn_readfirstlane(old) != own_wgs - 1) return;
+  if (lane == 0) __hip_atomic_store(p.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int i = lane; i < p.world * p.chunks; i += 64)
+    if (i / p.chunks == p.rank || p.peer[i / p.chunks]) flag_raise_stored(p.arr_flags + i, p.epoch);
 }
 
 }  // namespace ditron
@@ -902,7 +1006,7 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
   }
   if (st != DITRON_OK) return st;
 
-  // 2. top-k combine into token order; the emulated peers' blocks arrive beside it
+  // 2. top-k combine into token order; the emulated peers' blocks arrive beside it, and where few items are all there is it sums as well
   const size_t slot_bytes = (size_t)tokens_per_rank * hidden * 2;
   MoeCombineParams c{};
   c.y = (const __bf16*)y;
@@ -911,9 +1015,11 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
   c.expert_offsets = expert_offsets;
   c.gate = topk_weights;
   c.combined = (__bf16*)combined;
+  c.out = (__bf16*)out;
   c.tokens = world * tokens_per_rank;
   c.tokens_per_rank = tokens_per_rank;
   c.rank = rank;
+  c.world = world;
   c.top_k = top_k;
   c.hidden = hidden;
   c.num_local = num_local_experts;
@@ -945,6 +1051,10 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
   c.num_producers = (emulate && world > 1) ? 2 * pl.producers : 0;
   c.teams = std::min(pl.teams, std::max(1, c.num_producers));
   c.epoch = epoch;
+  if (unroll == 1 && mode != Mode::kExternal) {   // (an external producer's blocks are waited for by the reduction below)
+    hipLaunchKernelGGL(moe_combine_sum_kernel, dim3((unsigned)c.combine_wgs), dim3(kCombineThreads), 0, s, c);
+    return hipGetLastError() == hipSuccess ? DITRON_OK : DITRON_ERR_HIP;
+  }
   const void* slots[DITRON_MAX_WORLD];
   for (int i = 0; i < world; ++i)
     slots[i] = i == rank ? (const void*)((const char*)combined + (size_t)rank * slot_bytes)
@@ -958,8 +1068,8 @@ extern "C" ditron_status_t ditron_moe_grouped_gemm_rs(
   // 3. the reduction of GEMM-ReduceScatter over the `world` slots (own slot: the rank's rows of `combined`).  A launch of its own, so that
   //    the stream orders it and only an external producer's blocks are waited for.  As work-groups of the launch before, it held units while
   //    it polled for the combine, and preset flags told it nothing.  us in that launch and in its own: 8192 tokens, 2048 columns, world 8
-  //    71.7, 67.5; 2044 tokens top-6, 2168 columns, 4 ranks 82.1, 68.5; 1024 tokens, 4096 columns, 2 ranks 68.9, 57.4; 128 tokens of 3000
-  //    columns 20.6, 20.9; 1488 top-6, 1456 columns 33.9, 34.9; 1200 top-1, 1072 columns 19.8, 20.2.
+  //    71.7, 67.5; 2044 tokens top-6, 2168 columns, 4 ranks 82.1, 68.5; 1024 tokens, 4096 columns, 2 ranks 68.9, 57.4; 1488 top-6,
+  //    1456 columns 33.9, 34.9; 1200 top-1, 1072 columns 19.8, 20.2.
   return ditron_reduce_slots(slots, out, mode == Mode::kExternal ? signals + 2 * world : nullptr, status, tokens_per_rank, hidden, world,
                              chunks_per_slot, epoch, tuning, stream);
 }

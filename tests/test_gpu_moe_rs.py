@@ -69,11 +69,18 @@ def _run(B, ids, hs, ws, e0s, d, world, t_r, inter_r, hidden, experts, top_k, lo
         for s in range(world):
             if s != d:
                 scatter[s].copy_(peers[s])
+    if flags == B.EXTERNAL_PRODUCER:   # one publisher on another stream, 200 us a chunk, the last rank's last chunk first
+        side, rows = torch.cuda.Stream(), t_r // chunks
+        torch.cuda.synchronize()
+        late = [(s, c) for s in reversed(range(world)) if s != d for c in reversed(range(chunks))]
+        st = B.publish_chunks([scatter[s, c * rows:(c + 1) * rows] for s, c in late], [peers[s][c * rows:(c + 1) * rows] for s, c in late],
+                              [rows * hidden * 2] * len(late), [2 * world + s * chunks + c for s, c in late], signals, 3, 20000, side)
+        assert st == B.OK, B.status_string(st)
     w = ws[d] if kn else np.ascontiguousarray(np.transpose(ws[d], (0, 2, 1)))      # [E, hidden, inter] when B_NK
     st = B.moe_grouped_gemm_rs(to_dev(hs[d]) if R else torch.zeros((1, inter_r), dtype=torch.int16, device="cuda"),
                                to_dev(w), B.B_KN if kn else B.B_NK, None if gate is None else to_dev(gate.reshape(-1)),
                                to_dev(gather.astype(np.int32)) if R else torch.zeros(1, **i32), to_dev(offsets.astype(np.int32)),
-                               y, inv, rec, combined, None if flags == B.FLAGS_PRESET else peers, scatter, out, signals, status,
+                               y, inv, rec, combined, peers if flags is None else None, scatter, out, signals, status,
                                order, t_r, hidden, inter_r, experts, top_k, local, max_rows, world, d, chunks, 3,
                                B.EMULATE_PRODUCER if flags is None else flags, tuning=tuning)
     assert st == B.OK, B.status_string(st)
@@ -155,6 +162,27 @@ def test_moe_rs_reduction_follows_the_combine(B, world, t_r, hidden, experts, to
     _run(B, ids, hs, ws, e0s, world - 1, *shape, flags=B.FLAGS_PRESET, flags_up=True)
     # emulated peers: nothing is left to wait for when the reduction starts, so one poll is enough
     _run(B, ids, hs, ws, e0s, 0, *shape, tuning=B.tuning(spin_limit=1))
+
+
+# Few tokens or narrow rows: the combine delivers and sums as well.  Slots in flight: one, eight and a batch more, three batches; one vector to a
+# row, a second block of one; more assignments than a wave has lanes; waves with a second item, of others' rows and of the rank's own; the most
+# tokens of 1024 columns that take this kernel, and one more, which take the reduction behind it
+@pytest.mark.parametrize("world,t_r,hidden,experts,top_k,chunks", [
+    (1, 5, 8, 3, 2, 1), (8, 7, 520, 16, 2, 7), (9, 3, 1032, 9, 3, 1), (20, 1, 72, 20, 2, 1), (2, 4, 2056, 70, 66, 2), (8, 800, 64, 8, 1, 4),
+    (1, 6200, 16, 4, 1, 2), (3, 341, 1024, 6, 2, 1), (4, 256, 1024, 6, 2, 1),
+])
+def test_moe_rs_combine_that_sums(B, world, t_r, hidden, experts, top_k, chunks):
+    local = experts if experts <= 64 else experts // 2
+    ids, hs, ws, e0s = _case(world, t_r, 8, hidden, experts, top_k, local, seed=hidden + t_r, integer=True)
+    shape = (world, t_r, 8, hidden, experts, top_k, local, chunks, None, True)
+    _run(B, ids, hs, ws, e0s, 0, *shape, stale_rows=True)
+    _run(B, ids, hs, ws, e0s, world - 1, *shape, flags=B.FLAGS_PRESET, flags_up=True)
+
+
+@pytest.mark.parametrize("world,t_r,hidden,chunks", [(4, 6, 264, 3), (2, 520, 1048, 2)])
+def test_moe_rs_external_producer(B, world, t_r, hidden, chunks):
+    ids, hs, ws, e0s = _case(world, t_r, 8, hidden, 6, 2, 6, seed=t_r, integer=True)
+    _run(B, ids, hs, ws, e0s, 1, world, t_r, 8, hidden, 6, 2, 6, chunks, None, True, flags=B.EXTERNAL_PRODUCER)
 
 
 # [k, n] weights: contractions up to 512 take a ring of two K tiles (its five pieces: less than one K tile up to two turns, whole
